@@ -787,8 +787,10 @@ struct Elem8<float> {
 // columns per step, so that every global instruction covers two full 256-column row segments
 // (512 B of bf16, 1 KB of fp32, contiguous) instead of 64-column pieces.  That matters most when
 // ld is odd and no 16-byte access is aligned: the number of partially covered 128-byte lines per
-// instruction drops four-fold.  The G (and W) values of the second slab are requested while the
-// first one is consumed.
+// instruction drops four-fold.  DEPTH passes of G (and W) values are in flight: a pass is requested that
+// many passes before it is consumed, across the change of slab.
+// (The norm pass, MODE 0, over 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256: 271 us = 0.57 PFLOP/s; 628 us
+// while it had no loads in flight and spilled 72 registers.)
 #define FIRA_EPI_STRIDE 260   // floats per staged row: 256 + 4 (keeps 16-byte alignment, shifts banks)
 #define FIRA_EPI_SLAB (2 * 32 * FIRA_EPI_STRIDE * 4)
 #define FIRA_EPI_LDS (FIRA_EPI_SLAB + FIRA_BB * 4)   // the slabs, then one factor per tile row (matrices with m > n)
@@ -797,8 +799,8 @@ template <int MODE, typename T, bool INTERIOR>
 __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[4][2], char* lds, const FiraMat& mt,
                                                       const FiraEnt& ent, int i0, int j0, float c, float lr_alpha, bool unitk) {
   typedef typename Elem8<T>::Raw Raw;
-  // fp32 tiles would need 128 more registers: no prefetch; neither in the norm pass, which spills with it
-  constexpr bool PIPE = sizeof(T) == 2 && MODE == 1;
+  // passes in flight: 64 registers of G and W values beside the accumulators
+  constexpr int DEPTH = sizeof(T) == 2 ? 8 : 4;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave & 1, wn = wave >> 1;
   float* buf = reinterpret_cast<float*>(lds) + wn * (32 * FIRA_EPI_STRIDE);
@@ -814,7 +816,8 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[4][2], cha
   const long long wave_row0 = (long long)i0 + wn * 64 + 16 * wm;
   const long long lane_off = (unsigned)(ih * (int)mt.ld + jl);
   auto slab_row = [&](int p) { return 16 * wm + 2 * p + ih; };
-  auto fetch = [&](int tn, int p, Raw& gr, Raw& wr) {
+  auto fetch = [&](int q, Raw& gr, Raw& wr) {   // pass q = 8 * slab + pass of the slab
+    const int tn = q >> 3, p = q & 7;
     if (INTERIOR) {
       const long long base = (wave_row0 + 32 * tn + 2 * p) * mt.ld + j0;
       gr = Elem8<T>::template load_raw<true>(G + base, lane_off, 0);
@@ -826,11 +829,9 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[4][2], cha
       if (MODE == 1) wr = ok ? Elem8<T>::template load_raw<false>(W + i * mt.ld, j, mt.n) : Elem8<T>::zero();
     }
   };
-  Raw gbuf[PIPE ? 8 : 1], wbuf[PIPE ? 8 : 1];
-  if (PIPE) {
+  Raw gbuf[DEPTH], wbuf[MODE == 1 ? DEPTH : 1];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) fetch(0, p, gbuf[p], wbuf[p]);
-  }
+  for (int q = 0; q < DEPTH; ++q) fetch(q, gbuf[q], wbuf[MODE == 1 ? q : 0]);
   float cphi[8];
   if (mt.left) {
 #pragma unroll
@@ -860,9 +861,9 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[4][2], cha
     for (int p = 0; p < 8; ++p) {
       const int il = slab_row(p);
       const long long i = (long long)i0 + wn * 64 + 32 * tn + il;
-      if (!PIPE) fetch(tn, p, gbuf[0], wbuf[0]);
-      Raw& gr = gbuf[PIPE ? p : 0];
-      Raw& wr = wbuf[PIPE ? p : 0];
+      const int q = 8 * tn + p;
+      Raw& gr = gbuf[q % DEPTH];
+      Raw& wr = wbuf[MODE == 1 ? q % DEPTH : 0];
       if (INTERIOR || (i < mt.m && j < mt.n)) {
         const f32x4 u0 = *reinterpret_cast<const f32x4*>(buf + il * FIRA_EPI_STRIDE + jl);
         const f32x4 u1 = *reinterpret_cast<const f32x4*>(buf + il * FIRA_EPI_STRIDE + jl + 4);
@@ -889,7 +890,10 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[4][2], cha
           else Elem8<T>::template store<false>(w, W + i * mt.ld, j, mt.n);
         }
       }
-      if (PIPE && tn == 0) fetch(1, p, gr, wr);
+      if (q + DEPTH < 16) fetch(q + DEPTH, gr, wr);
+      // Nothing is stored in the norm pass, so nothing but this keeps the compiler from gathering every pass's loads at
+      // the top and the whole chain of additions at the end, with all values spilled in between.
+      if (MODE == 0) asm volatile("" : "+v"(sum) :: "memory");
     }
   }
   return sum;
