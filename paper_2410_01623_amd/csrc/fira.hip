@@ -270,7 +270,7 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
     }                                                                                                \
   } while (0)
   // the contraction kernels use more dynamic LDS than the 64 KB default (gfx950 has 160 KB per CU)
-  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_PROJ_LDS));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_PROJ_LDS_MAX));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<0, bf16_raw>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<1, bf16_raw>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<0, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
@@ -466,17 +466,6 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   auto mark = [&](int k) { if (pe) (void)hipEventRecord(pe[k], q); };
   mark(0);
 
-  // fp32 matrices: split the gradient into bf16 planes first (one launch for all of them)
-  {
-    long long most = 0;
-    for (int e = 0; e < count; ++e) {
-      const HostMat& h = ctx->plan.mats[idx[e]];
-      if (h.dev.kx > 1) most = std::max(most, (long long)h.dev.m * h.dev.n);
-    }
-    if (most > 0)
-      hipLaunchKernelGGL(fira_split_gradients_kernel, dim3((unsigned)std::min<long long>((most + 255) / 256, 4096), count), dim3(256), 0, q,
-                         ctx->d_mats, s->d_ents);
-  }
   auto grid8 = [](int n) { return dim3((unsigned)(((n + 7) / 8) * 8)); };
   const dim3 blk(FIRA_PROJ_THREADS);
   // R = P^T G (long-side major) for both orientations in one launch
@@ -484,7 +473,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     int nl = s->ntiles[kTilesProjBigLeft], nr = s->ntiles[kTilesProjBigRight];
     int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
     if (nl + nr)
-      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), blk, FIRA_PROJ_LDS, q, ctx->d_mats, s->d_ents,
+      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), blk, FIRA_PROJ_LDS_MAX, q, ctx->d_mats, s->d_ents,
                          s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, (const FiraScal*)ctx->d_scal, hp);
     nl = s->ntiles[kTilesProjSmallLeft]; nr = s->ntiles[kTilesProjSmallRight];
     bl = (nl + 7) / 8 * 8; br = (nr + 7) / 8 * 8;
@@ -492,12 +481,8 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       hipLaunchKernelGGL(fira_project_small_kernel, dim3(bl + br), blk, FIRA_PROJ_SMALL_LDS, q, ctx->d_mats, s->d_ents,
                          s->d_tiles[kTilesProjSmallLeft], nl, bl, s->d_tiles[kTilesProjSmallRight], nr, norm_arg, (const FiraScal*)ctx->d_scal, hp);
   };
-  // 0. Gram route, fp32 matrices only: ||G_i||^2 for every factor (bf16 matrices get it from step 1)
   const bool only_scaling = ctx->variant == FIRA_VARIANT_ONLY_SCALING;
   const int want_g2 = (ctx->norm_mode == FIRA_NORM_GRAM || only_scaling) ? 1 : 0;   // ||G_i||^2 per factor
-  if (want_g2 && s->ntiles[kTilesBackF32] > 0)
-    hipLaunchKernelGGL(fira_gradnorm_kernel, dim3(s->g2blocks), dim3(256), 0, q, ctx->d_mats, ctx->d_scal, s->d_ents, count,
-                       s->g2blocks, hp);
   // Which listed matrices take the Gram route to ||S|| (the kernels apply the same test per matrix: both
   // gate values of FiraScal within FiraHp's tolerances).  A matrix whose second gate value is still to be
   // measured takes the residual route in this step, and the limiter measures it.
@@ -881,8 +866,8 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     // of the same gradient: long side L' = S, contraction over S' = L, operand "PT" = Top, output "Rt" = Y.
     FiraMat& v = vmats[e];
     std::memset(&v, 0, sizeof(v));
-    // fp32 matrices: the way back reads a bf16 rounding of the gradient made below (the way there runs on the
-    // matrix's own split planes, as in a step)
+    // fp32 matrices: the way back reads a bf16 rounding of the gradient made below (the way there reads the
+    // gradient itself, as in a step)
     const bool f32 = m.kx != 1;
     v.m = m.m; v.n = m.n; v.r = m.r; v.left = !m.left; v.ld = f32 ? refresh_gb_ld(m.n) : m.ld;
     v.L = m.S; v.S = m.L; v.rp = m.rp; v.Sp = re.Lp; v.kx = 1; v.dtype = FIRA_BF16;
@@ -910,12 +895,11 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     if (n16) hipLaunchKernelGGL(fira_zero_fill_kernel, dim3(grid), dim3(256), 0, q, reinterpret_cast<u32x4*>(ws + rp.top_begin), n16);
   }
 
-  for (int e = 0; e < count; ++e) {   // fp32 matrices: split planes for the way there, a bf16 rounding for the way back
+  for (int e = 0; e < count; ++e) {   // fp32 matrices: a bf16 rounding for the way back
     const FiraMat& m = ctx->plan.mats[idx[e]].dev;
     if (m.kx == 1) continue;
     const long long total = (long long)m.m * m.n;
     const int grid = (int)std::min<long long>((total + 255) / 256, 65535);
-    hipLaunchKernelGGL(fira_split_gradient_kernel, dim3(grid), dim3(256), 0, q, m, (const float*)dev_G[e]);
     hipLaunchKernelGGL(fira_round_gradient_kernel, dim3(grid), dim3(256), 0, q, (const float*)dev_G[e],
                        (bf16_raw*)(ws + rp.off_gb[e]), m.m, m.n, (long long)m.ld, (long long)refresh_gb_ld(m.n));
   }
@@ -955,7 +939,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   auto launch_project = [&](const FiraMat* mats, const FiraEnt* ents_d, const FiraTile* tl, int nl, const FiraTile* tr, int nr) {
     const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
     if (nl + nr)
-      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_PROJ_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0,
+      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_PROJ_LDS_MAX, q, mats, ents_d, tl, nl, bl, tr, nr, 0,
                          (const FiraScal*)ctx->d_scal, refresh_hp);
   };
   for (int it = 0; it < iters; ++it) {

@@ -35,7 +35,7 @@ struct FiraMat {
   int L, S;            // long side max(m,n) (number of factors), short side min(m,n)
   int rp, Sp;          // rank and short side rounded up to 64 (zero padded operand rows)
   int kx, dtype;       // K-expansion (1: bf16, 6: fp32 split); dtype of W and G (0 f32, 1 bf16)
-  long long gx_ld;     // leading dimension of the split copy of G (fp32 matrices only)
+  long long gx_ld;     // leading dimension of Gx
   // The library's own bf16 operand arrays are stored K-blocked, [K/32][rows][32]: the 32 k of one
   // row are 64 contiguous bytes and consecutive rows follow each other, so the 16 rows x 32 k that
   // one LDS-direct load instruction moves are 1 KB of contiguous memory (see kblk_index).  Row
@@ -59,7 +59,8 @@ struct FiraMat {
   bf16_raw* Rb;        // [kx*rp/32][Lq][32] R of this step as MFMA operand (residual route)
   bf16_raw* Pn;        // [kx*rp/32][Sq][32] projector, rank along K (operand of the back-projection)
   bf16_raw* PT;        // [kx*Sp/32][rq][32] projector transposed, short side along K (operand of R)
-  bf16_raw* Gx;        // fp32 matrices: split copy of G ([kx*Sp][gx_ld] if left, [m][gx_ld] else)
+  bf16_raw* Gx;        // fp32 matrices: room for a split copy of G ([kx*Sp][gx_ld] if left, [m][gx_ld] else); no kernel uses it,
+                       // the projection splits the gradient on its way through registers
 };
 
 // Element (row, k) of a K-blocked operand with `rows` (padded) rows.

@@ -607,35 +607,6 @@ __device__ __forceinline__ void prep_projector_body(const FiraMat& mt, const TP*
 template <typename TP>
 __global__ void fira_prep_projector_kernel(FiraMat mt, const TP* __restrict__ P) { prep_projector_body<TP>(mt, P); }
 
-// fp32 gradient -> split bf16 planes (sequence A), stacked along the contraction axis.
-__device__ __forceinline__ void split_gradient_body(const FiraMat& mt, const float* __restrict__ G) {
-  const long long total = (long long)mt.m * mt.n;
-  gptr<bf16_raw> Gx = as_global(mt.Gx);
-  for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (long long)gridDim.x * blockDim.x) {
-    const long long i = idx / mt.n;
-    const long long j = idx - i * mt.n;
-    bf16_raw h, m, l;
-    split3(G[i * mt.ld + j], h, m, l);
-    const bf16_raw seq[6] = {h, h, m, h, l, m};
-    if (mt.left) {   // contraction over rows i: plane p occupies rows [p*Sp, p*Sp + m)
-#pragma unroll
-      for (int p = 0; p < 6; ++p) Gx[((long long)p * mt.Sp + i) * mt.gx_ld + j] = seq[p];
-    } else {         // contraction over columns j: plane p occupies columns [p*Sp, p*Sp + n)
-#pragma unroll
-      for (int p = 0; p < 6; ++p) Gx[i * mt.gx_ld + (long long)p * mt.Sp + j] = seq[p];
-    }
-  }
-}
-__global__ void fira_split_gradient_kernel(FiraMat mt, const float* __restrict__ G) { split_gradient_body(mt, G); }
-// ... for every fp32 matrix of a step's work list in one launch (blockIdx.y = list entry; bf16 entries exit)
-__global__ void fira_split_gradients_kernel(const FiraMat* __restrict__ mats, const FiraEnt* __restrict__ ents) {
-  const FiraEnt ent = ents[blockIdx.y];
-  const FiraMat mt = mats[ent.mat];
-  if (mt.kx == 1) return;
-  split_gradient_body(mt, reinterpret_cast<const float*>(ent.G));
-}
-
 // One float in device memory (the step size lr * alpha), written in stream order.
 __global__ void fira_store_float_kernel(float* __restrict__ dst, float value) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *as_global(dst) = value;
@@ -652,105 +623,6 @@ __global__ void fira_round_gradient_kernel(const float* __restrict__ G, bf16_raw
     const long long j = idx - i * n;
     out[i * ldb + j] = f32_to_bf16(G[i * ld + j]);
   }
-}
-
-// ------------------------------------------------------------------------------------------------
-// Gram route to ||S||: g2[i] = sum over the short axis of G(s, i)^2 for every long index i.
-//   left  (m <= n): column sums of squares; one workgroup per 256 columns walks all m rows with
-//                   row-contiguous 16-byte loads (32 lanes = 512 B of one row), 8 row lanes.
-//   right (m >  n): row sums of squares; one wavefront per row.
-// Fixed summation order: deterministic.
-// ------------------------------------------------------------------------------------------------
-
-__device__ __forceinline__ int find_g2_entry(const FiraEnt* __restrict__ ents, int count, int blk) {
-  int lo = 0, hi = count - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (ents[mid].g2b0 <= blk) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
-template <typename T>
-__device__ __forceinline__ void g2_load8(float (&x)[8], gptr<const T> row, long long idx, long long limit);
-template <>
-__device__ __forceinline__ void g2_load8<bf16_raw>(float (&x)[8], gptr<const bf16_raw> row, long long idx, long long limit) {
-  unsigned w[4] = {0u, 0u, 0u, 0u};
-  if (idx + 8 <= limit) {
-    const u32x4 v = *reinterpret_cast<gptr<const u32x4_a2>>(row + idx);
-    w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (idx + e < limit) w[e >> 1] |= ((unsigned)row[idx + e]) << ((e & 1) * 16);
-  }
-#pragma unroll
-  for (int d = 0; d < 4; ++d) { x[2 * d] = __uint_as_float(w[d] << 16); x[2 * d + 1] = __uint_as_float(w[d] & 0xffff0000u); }
-}
-template <>
-__device__ __forceinline__ void g2_load8<float>(float (&x)[8], gptr<const float> row, long long idx, long long limit) {
-#pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = (idx + e < limit) ? row[idx + e] : 0.0f;
-}
-
-template <typename T>
-__device__ __forceinline__ void g2_block(const FiraMat& mt, const FiraEnt& ent, int blk, float* red) {
-  gptr<const T> G = as_global(reinterpret_cast<const T*>(ent.G));
-  gptr<float> g2 = as_global(mt.g2);
-  const int t = threadIdx.x;
-  if (mt.left) {
-    const int cc = t & 31, rl = t >> 5;                 // 32 column chunks x 8 row lanes
-    const long long j = (long long)blk * 256 + 8 * cc;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (j < mt.n) {
-      for (int i = rl; i < mt.m; i += 8) {
-        float x[8];
-        g2_load8<T>(x, G + (long long)i * mt.ld, j, mt.n);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += x[e] * x[e];
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) red[(rl * 32 + cc) * 8 + e] = acc[e];
-    __syncthreads();
-    // thread t sums column t of the block over the 8 row lanes, in order
-    const int c = t >> 3, e = t & 7;
-    float s = 0.0f;
-#pragma unroll
-    for (int r8 = 0; r8 < 8; ++r8) s += red[(r8 * 32 + c) * 8 + e];
-    const long long col = (long long)blk * 256 + t;
-    if (col < mt.n) g2[col] = s;
-  } else {
-    const int lane = t & 63, wave = t >> 6;
-    for (int rr = 0; rr < 8; ++rr) {
-      const long long i = (long long)blk * FIRA_G2_ROWS_PER_WG + wave * 8 + rr;
-      if (i >= mt.m) break;
-      float s = 0.0f;
-      for (long long j = 8 * lane; j < mt.n; j += 512) {
-        float x[8];
-        g2_load8<T>(x, G + i * mt.ld, j, mt.n);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s += x[e] * x[e];
-      }
-      s = wave_sum(s);
-      if (lane == 0) g2[i] = s;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void fira_gradnorm_kernel(const FiraMat* __restrict__ mats,
-                                                            const FiraScal* __restrict__ scal,
-                                                            const FiraEnt* __restrict__ ents, int count,
-                                                            int total_blocks, FiraHp hp) {
-  __shared__ float red[256 * 8];
-  const int b = blockIdx.x;
-  if (b >= total_blocks) return;
-  const int e = find_g2_entry(ents, count, b);
-  const FiraEnt ent = ents[e];
-  if (!have_g2(hp)) return;
-  const FiraMat mt = mats[ent.mat];
-  if (mt.dtype == 1) return;   // bf16 matrices: the projection kernel accumulates ||G_i||^2 itself
-  g2_block<float>(mt, ent, b - ent.g2b0, red);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -460,6 +460,291 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[4][2], char* lds, 
   stage(std::true_type{}, SS - 1);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Kernel 1 for fp32 matrices.  The gradient is read once, in fp32: a thread holds a 4 x 4 block of it in
+// registers, splits every value into its three bf16 planes (x = h + m + l, split3) and writes them to
+// three LDS tiles; the six plane products hh, mh, lh, hm, mm, hl of a block of 32 k run from there, so
+// that a gradient plane is read from LDS and a projector plane from memory once instead of two or three
+// times.  ||G_i||^2 is summed in fp32 from the unsplit values on the way.  What bounds it is the matrix
+// pipe (six products per element) and the additions beside it.  Over the 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256 it takes
+// 930 us; the split of G through memory (six planes written and read back), its projection and a pass of
+// its own for ||G_i||^2 took 1361 + 1123 + 918 us.  One 256 x 688 matrix at r = 64: 15 us against 5 + 60 + 30.
+//
+// Tile: 128 factors x 64 TM rank components; wave w holds 32 TM factors x 64 rank components, TM = 4, 2
+// or 1 (the smallest that covers r, so that no wavefront multiplies padding only).  A block of 32 k:
+//   registers -> three LDS tiles [128][32 k], 80 bytes per row (conflict-free for the 8-byte writes of
+//   four rows and the 16-byte fragment reads of sixteen); then the products with the projector's plane h, then
+//   those with its planes m and l (K blocks 0, Sp/32 and 3 Sp/32 of sequence B).  The planes m, l arrive while
+//   the tiles are written and h is multiplied; h and A of the next block while the rest is.
+// Loads never leave the matrix: a group of four that would is moved back and shifted in registers, rows
+// past the end read the last row; values past the contraction length are set to zero.
+// ------------------------------------------------------------------------------------------------
+#define FIRA_SPLIT_PITCH 80
+#define FIRA_SPLIT_PLANE (FIRA_PA * FIRA_SPLIT_PITCH)
+#define FIRA_SPLIT_LDS (3 * FIRA_SPLIT_PLANE + FIRA_RING_STAGES * FIRA_PROJ_RING_STAGE)
+#define FIRA_PROJ_LDS_MAX (FIRA_SPLIT_LDS > FIRA_PROJ_LDS ? FIRA_SPLIT_LDS : FIRA_PROJ_LDS)
+
+// Thread t holds rows 4 b .. 4 b + 3 and k = 4 kq .. 4 kq + 3 of the tile; 32 consecutive threads write
+// four rows' whole 64 bytes.
+__device__ __forceinline__ int split_b(int t) { return (t & 3) | ((t >> 5) << 2); }
+__device__ __forceinline__ int split_kq(int t) { return (t >> 2) & 7; }
+
+// The lane number, formed anew at each call: the multiply loops leave no registers for addresses that would be
+// kept from one block to the next, and one reloaded from scratch would wait for every load in flight.
+__device__ __forceinline__ int fresh_lane() {
+  unsigned zero = 0;
+  asm volatile("" : "+s"(zero));
+  return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+__device__ __forceinline__ int fresh_thread() { return fresh_lane() + 64 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// ASYNC: 16-byte inline-assembly loads (at least four elements along the contiguous axis); otherwise
+// element by element (matrices with fewer).
+template <bool LEFT, bool ASYNC>
+struct SplitALoader {
+  gptr<const float> G;
+  long long ld;
+  int row0, L, S;
+  // request q (of 4) of the block of 32 k that starts at k0; t: the thread
+  __device__ __forceinline__ void load_one(u32x4 (&ra)[4], int k0, int q, int t) {
+    const int b = split_b(t), kq = split_kq(t);
+    if (ASYNC) {
+      if (LEFT) {
+        const int c0 = min(row0, L - 4);
+        gload16_async(ra[q], reinterpret_cast<const char*>((const float*)G + (long long)k0 * ld + c0),
+                      (unsigned)(min(row0 + 4 * b, L - 4) - c0) * 4u + (unsigned)min(4 * kq + q, S - 1 - k0) * (unsigned)(ld * 4));
+      } else {
+        gload16_async(ra[q], reinterpret_cast<const char*>((const float*)G + (long long)row0 * ld),
+                      (unsigned)(min(row0 + 4 * b + q, L - 1) - row0) * (unsigned)(ld * 4) + (unsigned)min(k0 + 4 * kq, S - 4) * 4u);
+      }
+    } else {
+      unsigned w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = k0 + 4 * kq + (LEFT ? q : e), row = row0 + 4 * b + (LEFT ? e : q);
+        w[e] = (k < S && row < L) ? __float_as_uint(LEFT ? G[(long long)k * ld + row] : G[(long long)row * ld + k]) : 0u;
+      }
+      ra[q] = u32x4{w[0], w[1], w[2], w[3]};
+    }
+  }
+  static __device__ __forceinline__ u32x4 shifted(u32x4 v, int d) {
+    if (d & 1) v = u32x4{v.y, v.z, v.w, 0u};
+    if (d & 2) v = u32x4{v.z, v.w, 0u, 0u};
+    return d < 4 ? v : u32x4{0u, 0u, 0u, 0u};
+  }
+  // after the wait: the loaded groups as x[e][j] = element (row 4 b + e, k = k0 + 4 kq + j), zeros past S
+  __device__ __forceinline__ void unpack(u32x4 (&ra)[4], int k0, float (&x)[4][4], int t) {
+    const int kq = split_kq(t);
+    if (ASYNC) {
+      if (LEFT) {
+        if (row0 + FIRA_PA > L) {            // a group of four columns that was moved back
+          const int c = row0 + 4 * split_b(t), shift = c - min(c, L - 4);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) ra[q] = shifted(ra[q], shift);
+        }
+        if (k0 + 32 > S) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (k0 + 4 * kq + q >= S) ra[q] = u32x4{0u, 0u, 0u, 0u};
+        }
+      } else if (k0 + 32 > S) {
+        const int k = k0 + 4 * kq, d = k - min(k, S - 4);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ra[q] = shifted(ra[q], d);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const unsigned w[4] = {ra[q].x, ra[q].y, ra[q].z, ra[q].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) (LEFT ? x[e][q] : x[q][e]) = __uint_as_float(w[e]);
+    }
+  }
+};
+
+// Registers -> the three plane tiles; sq[e] += the row's share of ||G_i||^2.
+__device__ __forceinline__ void split_store_a(char* la, const float (&x)[4][4], float (&sq)[4], int t) {
+  char* dst = la + 4 * split_b(t) * FIRA_SPLIT_PITCH + 8 * split_kq(t);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const u32x2 h = u32x2{pack_bf16x2(x[e][0], x[e][1]), pack_bf16x2(x[e][2], x[e][3])};
+    float d[4];
+    d[0] = x[e][0] - __uint_as_float(h.x << 16); d[1] = x[e][1] - __uint_as_float(h.x & 0xffff0000u);
+    d[2] = x[e][2] - __uint_as_float(h.y << 16); d[3] = x[e][3] - __uint_as_float(h.y & 0xffff0000u);
+    const u32x2 m = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
+    d[0] -= __uint_as_float(m.x << 16); d[1] -= __uint_as_float(m.x & 0xffff0000u);
+    d[2] -= __uint_as_float(m.y << 16); d[3] -= __uint_as_float(m.y & 0xffff0000u);
+    const u32x2 l = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
+    *reinterpret_cast<u32x2*>(dst + e * FIRA_SPLIT_PITCH) = h;
+    *reinterpret_cast<u32x2*>(dst + e * FIRA_SPLIT_PITCH + FIRA_SPLIT_PLANE) = m;
+    *reinterpret_cast<u32x2*>(dst + e * FIRA_SPLIT_PITCH + 2 * FIRA_SPLIT_PLANE) = l;
+    sq[e] += (x[e][0] * x[e][0] + x[e][1] * x[e][1]) + (x[e][2] * x[e][2] + x[e][3] * x[e][3]);
+  }
+}
+
+// Half of a block of 32 k: three plane products (two slices of 16 k each) into a fresh accumulator per 32 x 32
+// block, which is then added to acc on the vector unit.  Six products in a row on acc itself would round the
+// running sum twelve times per block, against twice when the small products are kept apart (their own size is
+// 2^-8 and less of it); this way it is rounded twice as well, and to nearest.
+//   H: projector plane h against the gradient's h, m, l;    else: planes m, l as h m, h l, m m.
+// `piece(j)`, j = 0..3, is called, and the next row block's fragments and the previous block's additions run,
+// between the multiplies.
+template <int TM, bool H, typename Piece>
+__device__ __forceinline__ void split_compute(f32x16_t (&acc)[TM][2], const char* la, const char* lb, int a0, int b0, Piece piece) {
+  const int lane = fresh_lane();
+  // product i uses gradient fragment FA(i) = 2 * plane + slice and projector fragment FB(i) = 2 * (plane of lb) +
+  // slice, the smallest products first (the error of R against 64 bits is a quarter smaller than with the largest first)
+  constexpr int NA = H ? 6 : 4, NB = H ? 2 : 4, BSTRIDE = TM * 4096;
+  constexpr int FA[6] = {H ? 4 : 2, H ? 5 : 3, H ? 2 : 0, H ? 3 : 1, 0, 1};
+  constexpr int FB[6] = {0, 1, H ? 0 : 2, H ? 1 : 3, 0, 1};
+  bf16x8_t fa[NA], fb[2][NB];
+  auto read_a = [&](int f, int t) {
+    fa[f] = *reinterpret_cast<const bf16x8_t*>(la + (f >> 1) * FIRA_SPLIT_PLANE + (a0 + 32 * t + (lane & 31)) * FIRA_SPLIT_PITCH +
+                                               (2 * (f & 1) + (lane >> 5)) * 16);
+  };
+#pragma unroll
+  for (int f = 0; f < NA; ++f) read_a(f, 0);
+  auto read_b = [&](int f, int t) {
+    fb[t][f] = *reinterpret_cast<const bf16x8_t*>(lb + (f >> 1) * BSTRIDE + ring_tile_off(b0 + 32 * t + (lane & 31), 2 * (f & 1) + (lane >> 5)));
+  };
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int f = 0; f < NB; ++f) read_b(f, t);
+  __builtin_amdgcn_sched_barrier(0);
+  f32x16_t part[2];
+#pragma unroll
+  for (int blk = 0; blk < 2 * TM; ++blk) {
+    const int tm = blk >> 1, tn = blk & 1;
+    f32x16_t& p = part[blk & 1];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) p[v] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[FA[i]], fb[tn][FB[i]], p, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (tn == 1 && tm + 1 < TM && (H || i < 2 || i > 3)) read_a(FA[i], tm + 1);   // after this fragment's last use
+      if (blk == 0 && i < 4) piece(i);
+      if (blk > 0 && i >= 2) {
+        f32x16_t& d = acc[(blk - 1) >> 1][(blk - 1) & 1];
+#pragma unroll
+        for (int v = 4 * (i - 2); v < 4 * (i - 1); ++v) d[v] += part[(blk - 1) & 1][v];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  acc[TM - 1][1] += part[1];
+}
+
+// acc and sq (rows 4 b + e, this thread's k) must be zero on entry.  B: the projector's planes (sequence B).
+template <bool LEFT, int TM, bool ASYNC>
+__device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds, const FiraMat& mt, const float* G, int a_row0, int b_row0,
+                                               int a0, int b0, float (&sq)[4]) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char* la = lds;
+  // The projector's planes h, m, l of a block, 64 TM rows each.  With TM <= 2 there is room for two blocks, and a
+  // block's operands are requested a whole block ahead.
+  constexpr bool TWO = TM <= 2;
+  constexpr int PLANE = TM * 4096;
+  char* lb = lds + 3 * FIRA_SPLIT_PLANE;
+  const unsigned lb0 = (unsigned)(size_t)(lds_ptr)lb;
+  const int nblocks = (mt.S + 31) / 32, planes = mt.Sp / 32;
+  const char* pb = reinterpret_cast<const char*>(mt.PT) + ((long long)b_row0 + 16 * TM * wave) * 64;
+  // this wave's share (TM requests) of plane pl of block kb
+  auto request_b = [&](int kb, int pl) {
+    const int lane = fresh_lane(), lrow = lane >> 2;
+    const unsigned offb = (unsigned)(lrow * 64 + ((lane & 3) ^ ring_swz(lrow)) * 16);
+    const int kofs = (pl == 2 ? 3 : pl) * planes + kb, slot = (TWO ? 3 * (kb & 1) : 0) + pl;
+#pragma unroll
+    for (int q = 0; q < TM; ++q)
+      lds_dma16(pb + ((long long)kofs * mt.rq) * 64 + q * 1024, offb,
+                (unsigned)__builtin_amdgcn_readfirstlane((int)(lb0 + (unsigned)(slot * PLANE + (TM * wave + q) * 1024))));
+  };
+  SplitALoader<LEFT, ASYNC> al{as_global(G), mt.ld, a_row0, mt.L, mt.S};
+  u32x4 ra[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) al.load_one(ra, 0, q, fresh_thread());
+  request_b(0, 0);
+  if (TWO) {
+    request_b(0, 1);
+    request_b(0, 2);
+  }
+  // The last block is written out separately so that on every path a request is followed by its wait.
+  auto block = [&](auto last, int kb) {
+    constexpr bool LAST = decltype(last)::value;
+    wait_loads<0>(ra);                           // A(kb) and plane h (TWO: every plane) have landed
+    float x[4][4];
+    const int t = fresh_thread();
+    al.unpack(ra, 32 * kb, x, t);
+    asm volatile("s_barrier" ::: "memory");      // everybody is done with the previous block's tiles and planes
+    if (!TWO) {
+      request_b(kb, 1);
+      request_b(kb, 2);
+    } else if (!LAST) {
+      request_b(kb + 1, 0);
+      request_b(kb + 1, 1);
+      request_b(kb + 1, 2);
+    }
+    split_store_a(la, x, sq, t);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const char* lk = lb + (TWO ? 3 * (kb & 1) * PLANE : 0);
+    split_compute<TM, true>(acc, la, lk, a0, b0, [&](int j) {
+      if (!LAST) al.load_one(ra, 32 * (kb + 1), j, fresh_thread());
+    });
+    if (!TWO) {
+      // planes m and l have landed; A(kb+1) may be in flight (its element-wise form is not counted)
+      if (!LAST && ASYNC) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+      if (!LAST) request_b(kb + 1, 0);           // plane h's place is free
+    }
+    split_compute<TM, false>(acc, la, lk + PLANE, a0, b0, [](int) {});
+  };
+  for (int kb = 0; kb + 1 < nblocks; ++kb) block(std::false_type{}, kb);
+  block(std::true_type{}, nblocks - 1);
+}
+
+template <bool LEFT, int TM>
+__device__ __forceinline__ void project_split_tile(char* lds, const FiraMat& mt, const FiraEnt& ent, const FiraTile& tile, int norm_mode) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int a_row0 = tile.ta * FIRA_PA, b_row0 = tile.tb * FIRA_PB;
+  const int a0 = 32 * TM * (wave % (4 / TM)), b0 = 64 * (wave / (4 / TM));
+  const float* G = reinterpret_cast<const float*>(ent.G);
+  f32x16_t acc[TM][2];
+  float sq[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.0f;
+  if ((LEFT ? mt.L : mt.S) >= 4) split_pipeline<LEFT, TM, true>(acc, lds, mt, G, a_row0, b_row0, a0, b0, sq);
+  else split_pipeline<LEFT, TM, false>(acc, lds, mt, G, a_row0, b_row0, a0, b0, sq);
+  if (norm_mode == 1 && tile.tb == 0) {
+    gptr<float> g2 = as_global(mt.g2);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {          // the eight threads that share a row
+      float s = sq[e];
+      s += __shfl_xor(s, 4, 64);
+      s += __shfl_xor(s, 8, 64);
+      s += __shfl_xor(s, 16, 64);
+      const int row = a_row0 + 4 * split_b(threadIdx.x) + e;
+      if (split_kq(threadIdx.x) == 0 && row < mt.L) g2[row] = s;
+    }
+  }
+  gptr<float> Rt = as_global(mt.Rt);
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < 2; ++tn) {
+      const int col = b_row0 + b0 + 32 * tn + (lane & 31);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = a_row0 + a0 + 32 * tm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        if (row < mt.L && col < mt.r) Rt[(long long)row * mt.r + col] = acc[tm][tn][v];
+      }
+    }
+}
+
 template <bool LEFT>
 __device__ __forceinline__ void project_tile(char* lds, const FiraMat* __restrict__ mats, const FiraEnt* __restrict__ ents,
                                              const FiraTile& tile, int norm_mode, const FiraScal* __restrict__ scal, const FiraHp& hp) {
@@ -467,6 +752,12 @@ __device__ __forceinline__ void project_tile(char* lds, const FiraMat* __restric
   if (hp.mixed && use_gram(hp, scal[ent.mat])) return;   // the fused kernel serves this matrix
   const FiraMat mt = mats[ent.mat];
 
+  if (mt.kx != 1) {
+    if (mt.r <= 64) project_split_tile<LEFT, 1>(lds, mt, ent, tile, norm_mode);
+    else if (mt.r <= 128) project_split_tile<LEFT, 2>(lds, mt, ent, tile, norm_mode);
+    else project_split_tile<LEFT, 4>(lds, mt, ent, tile, norm_mode);
+    return;
+  }
   GemmOperands g;
   g.a_row0 = tile.ta * FIRA_PA;
   g.a_rows = mt.L;
@@ -474,16 +765,10 @@ __device__ __forceinline__ void project_tile(char* lds, const FiraMat* __restric
   g.b_rows = mt.r;
   g.B = as_global<const bf16_raw>(mt.PT);
   g.ldb = mt.rq;
-  g.KB = mt.kx * mt.Sp;
-  if (mt.kx == 1) {
-    g.A = as_global(reinterpret_cast<const bf16_raw*>(ent.G));
-    g.lda = mt.ld;
-    g.KA = mt.S;
-  } else {
-    g.A = as_global<const bf16_raw>(mt.Gx);
-    g.lda = mt.gx_ld;
-    g.KA = mt.kx * mt.Sp;
-  }
+  g.KB = mt.Sp;
+  g.A = as_global(reinterpret_cast<const bf16_raw*>(ent.G));
+  g.lda = mt.ld;
+  g.KA = mt.S;
   f32x16_t acc[4][2];
   float sq[4];
 #pragma unroll
@@ -496,9 +781,8 @@ __device__ __forceinline__ void project_tile(char* lds, const FiraMat* __restric
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // Gram route: ||G_i||^2 of the tile's 128 factors falls out of the A fragments of wave 0 in the
-  // first rank tile of each panel.  (fp32 matrices feed split planes through here; their norms
-  // come from fira_gradnorm_kernel.)
-  const bool sumsq = norm_mode == 1 && mt.kx == 1 && tile.tb == 0 && wave == 0;
+  // first rank tile of each panel.
+  const bool sumsq = norm_mode == 1 && tile.tb == 0 && wave == 0;
   // LEFT: the k rows of G are whole rows of the matrix (any ld); RIGHT: a row of G holds KA values
   const bool interior = g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB;
   if (interior) {
@@ -542,7 +826,7 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_project_kernel(cons
                                                                             int blocks_left,
                                                                             const FiraTile* __restrict__ tiles_right, int ntiles_right,
                                                                             int norm_mode, const FiraScal* __restrict__ scal, FiraHp hp) {
-  extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_PROJ_LDS bytes
+  extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_PROJ_LDS_MAX bytes
   if ((int)blockIdx.x < blocks_left) {
     const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
     if (ti < 0) return;

@@ -1,0 +1,46 @@
+"""fp32 matrices at the sizes where their kernels can go wrong: tile edges and remainders along the long side
+(128 factors, groups of four), the short side (blocks of 32 k, groups of four) and the rank (64, 128, 256 and the
+next one), leading dimensions, and matrices too small for a 16-byte load.  Against the CPU oracle, with the bounds
+of the fp32 stages (sums of products that are exact to 2^-24, 1e-5 of the largest entry)."""
+import numpy as np
+import pytest
+
+from oracle import fira_oracle as orc
+from paper_2410_01623_amd import fira, synth
+
+import fira_harness as H
+
+pytestmark = pytest.mark.gpu
+
+# m, n, r, ld
+CASES = [
+    (128, 256, 64, 256), (256, 128, 64, 128),        # whole tiles, smallest rank tile
+    (127, 129, 65, 129), (130, 127, 65, 131),        # one past and one short of a tile, ragged k, middle rank tile
+    (96, 131, 96, 131), (131, 99, 99, 102),          # full rank; a last group of three along either side
+    (161, 385, 129, 388), (385, 162, 128, 163),      # large rank tile by one; r on the edge of the middle one
+    (300, 333, 257, 333), (333, 301, 300, 301),      # two rank tiles
+    (31, 40, 5, 40), (33, 32, 7, 35),                # a single block of k; one and a remainder of one
+    (5, 6, 2, 9), (4, 4, 3, 4), (3, 3, 1, 3), (2, 70, 2, 71), (70, 3, 2, 3), (1, 130, 1, 130),
+]
+
+
+@pytest.mark.parametrize("norm", [fira.FIRA_NORM_GRAM, fira.FIRA_NORM_RESIDUAL], ids=["gram", "residual"])
+@pytest.mark.parametrize("m,n,r,ld", CASES, ids=[f"{m}x{n}r{r}ld{ld}" for m, n, r, ld in CASES])
+def test_fp32_step_at_the_edges(m, n, r, ld, norm):
+    rng = np.random.default_rng(1000 * m + n)
+    W0 = (0.02 * rng.standard_normal((m, n))).astype(np.float32)
+    Gs = [(1e-2 * rng.standard_normal((m, n))).astype(np.float32) for _ in range(4)]
+    S = min(m, n)
+    P = synth.store_projector(np.linalg.qr(rng.standard_normal((S, r)))[0], "f32")
+    if r < S:                       # the third step is limited: its part outside the subspace is eight times larger
+        g, p = Gs[2].astype(np.float64), P.astype(np.float64)
+        Gs[2] = (8.0 * g - 7.0 * (p @ (p.T @ g) if m <= n else (g @ p) @ p.T)).astype(np.float32)
+    res = H.run_case([(m, n)], r, fira.FIRA_F32, 4, lambda i: W0, lambda i, s: Gs[s], lambda i, s: P if s == 0 else None,
+                     orc.OracleHparams(), lds=[ld], norm_mode=norm)
+    print(H.fmt(res), flush=True)
+    assert max(res.w_err) <= 1e-4
+    # k_i of a factor whose R_i is a single small entry carries that entry's own relative error
+    assert res.worst["R"] <= 1e-5 and res.worst["M"] <= 1e-5 and res.worst["V"] <= 1e-5
+    assert res.worst["k"] <= (1e-5 if r >= 32 else 1e-4)
+    if r < S:                       # at full rank S is what rounding leaves of it
+        assert res.c_min < 1.0 and res.worst["s_pre"] <= 1e-4 and res.worst["c"] <= 1e-4
