@@ -277,7 +277,7 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<1, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_chol_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_CHOL_PAN_ROWS * (FIRA_CHOL_NB + 1) * 8));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_solve_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_SOLVE_LDS));
-  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(1)));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(2)));
   FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_stage_all, p.slot_bytes * kSlots, hipHostMallocDefault));
@@ -533,8 +533,12 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     launch_project(want_g2);
     mark(1);
     // 2. Adam on R, factor norms
-    hipLaunchKernelGGL(fira_adam_kernel, dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds * (ctx->zsplit ? 2 : 1), q, ctx->d_mats, ctx->d_scal,
-                       s->d_ents, count, s->rowblocks, hp);
+    if (s->ntiles[kTilesBackBf16])
+      hipLaunchKernelGGL(fira_adam_kernel<1>, dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds * (ctx->zsplit ? 2 : 1), q, ctx->d_mats, ctx->d_scal,
+                         s->d_ents, count, s->rowblocks, hp);
+    if (s->ntiles[kTilesBackF32])
+      hipLaunchKernelGGL(fira_adam_kernel<FIRA_KX_SPLIT>, dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds_f32, q, ctx->d_mats, ctx->d_scal,
+                         s->d_ents, count, s->rowblocks, hp);
     mark(2);
   } else {
     mark(1);

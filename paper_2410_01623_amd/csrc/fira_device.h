@@ -27,6 +27,7 @@ typedef f32x4 __attribute__((aligned(4))) f32x4_a4;
 //   A: h h m h l m        B: h m h l h m
 #define FIRA_KX_SPLIT 6
 #define FIRA_ZREADY_MAX_R 1024
+#define FIRA_ZREADY_MAX_R_F32 512   // fp32 rows have three planes: 48 KB of LDS for sixteen of them
 
 // Immutable description of one weight matrix (device array, one element per matrix).
 struct FiraMat {
@@ -43,8 +44,8 @@ struct FiraMat {
   int Lq;              // rows of Nb and Rb: L rounded up to 256
   int Sq;              // rows of Pn: S rounded up to 256
   int rq;              // rows of PT: r rounded up to 256
-  // 1: the Adam kernel keeps a factor's row in registers and writes Z for c = 1 directly (bf16
-  // matrices with r a multiple of 4, up to FIRA_ZREADY_MAX_R); the Z kernel then only corrects
+  // 1: the Adam kernel keeps a factor's row in registers and writes Z for c = 1 directly (r a multiple of 4,
+  // up to FIRA_ZREADY_MAX_R, or FIRA_ZREADY_MAX_R_F32 for fp32 matrices); the Z kernel then only corrects
   // the matrices whose limiter factor came out below 1.
   int zready;
   // low-rank arrays, all "long-side major": row i holds the r values of factor i
@@ -54,6 +55,7 @@ struct FiraMat {
   float* phi;          // [L]      scaling factors k_i of this step
   float* g2;           // [L]      ||G_i||^2 (Gram mode)
   float* q;            // [L]      k_i^2 (||G_i||^2 - ||R_i||^2), the terms of ||S||^2 (Gram mode)
+  // fp32 matrices store the three planes h, m, l of Nb and Rb; the contraction runs over them in sequence A
   bf16_raw* Nb;        // [kx*rp/32][Lq][32] Z = N - c k_i R_i of this step (MFMA operand); bf16 matrices have room for a
                        // second plane of K blocks, Z's rounding remainder, used when FiraHp::zsplit is set
   bf16_raw* Rb;        // [kx*rp/32][Lq][32] R of this step as MFMA operand (residual route)

@@ -39,7 +39,7 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
-// store one low-rank value as an MFMA operand element (plain bf16, or the 6-plane split, sequence A)
+// store one low-rank value as an MFMA operand element (plain bf16, or the three planes of the split)
 // (`op` is a K-blocked array with `rows` padded rows; plane p of the split occupies k = p*rp + a.)
 template <int KX>
 __device__ __forceinline__ void store_operand(gptr<bf16_raw> op, int rows, long long row, int rp, int a, float x) {
@@ -48,16 +48,16 @@ __device__ __forceinline__ void store_operand(gptr<bf16_raw> op, int rows, long 
   } else {
     bf16_raw h, m, l;
     split3(x, h, m, l);
-    const bf16_raw seq[6] = {h, h, m, h, l, m};
-#pragma unroll
-    for (int p = 0; p < 6; ++p) op[kblk_index(rows, row, p * rp + a)] = seq[p];
+    op[kblk_index(rows, row, a)] = h;
+    op[kblk_index(rows, row, rp + a)] = m;
+    op[kblk_index(rows, row, 2 * rp + a)] = l;
   }
 }
 template <int KX>
 __device__ __forceinline__ float load_operand(gptr<const bf16_raw> op, int rows, long long row, int rp, int a) {
   if (KX == 1) return bf16_to_f32(op[kblk_index(rows, row, a)]);
-  return (bf16_to_f32(op[kblk_index(rows, row, a)]) + bf16_to_f32(op[kblk_index(rows, row, 2 * rp + a)])) +
-         bf16_to_f32(op[kblk_index(rows, row, 4 * rp + a)]);
+  return (bf16_to_f32(op[kblk_index(rows, row, a)]) + bf16_to_f32(op[kblk_index(rows, row, rp + a)])) +
+         bf16_to_f32(op[kblk_index(rows, row, 2 * rp + a)]);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -128,21 +128,38 @@ __device__ __forceinline__ void adam_row(const FiraMat& mt, const FiraHp& hp, fl
   }
 }
 
+// What is left of four values when their nearest-even bf16 `hi` is taken off (exact).
+__device__ __forceinline__ f32x4 bf16_remainder(const f32x4& z, const u32x2& hi) {
+  return f32x4{z[0] - __uint_as_float(hi.x << 16), z[1] - __uint_as_float(hi.x & 0xffff0000u),
+               z[2] - __uint_as_float(hi.y << 16), z[3] - __uint_as_float(hi.y & 0xffff0000u)};
+}
+__device__ __forceinline__ u32x2 pack_bf16x4(const f32x4& z) { return u32x2{pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3])}; }
 // Second bf16 plane of four values whose first plane (nearest-even bf16) is `hi`: bf16(z - hi), so that
 // hi + lo carries 16 mantissa bits of z.
-__device__ __forceinline__ u32x2 split_remainder(const f32x4& z, const u32x2& hi) {
-  const float h0 = __uint_as_float(hi.x << 16), h1 = __uint_as_float(hi.x & 0xffff0000u);
-  const float h2 = __uint_as_float(hi.y << 16), h3 = __uint_as_float(hi.y & 0xffff0000u);
-  return u32x2{pack_bf16x2(z[0] - h0, z[1] - h1), pack_bf16x2(z[2] - h2, z[3] - h3)};
+__device__ __forceinline__ u32x2 split_remainder(const f32x4& z, const u32x2& hi) { return pack_bf16x4(bf16_remainder(z, hi)); }
+
+// Planes of an operand row element: 1, 2 (Z of a bf16 matrix with hp.zsplit) or 3 (fp32 matrices).
+template <int KX>
+__device__ __forceinline__ int z_planes(const FiraHp& hp) { return KX == 1 ? (hp.zsplit ? 2 : 1) : 3; }
+// Four consecutive values as that many planes (each the rounding of what the ones before leave).
+template <int KX>
+__device__ __forceinline__ void bf16_planes(const f32x4& z, int planes, u32x2 (&pl)[3]) {
+  pl[0] = pack_bf16x4(z);
+  if (KX != 1 || planes == 2) {
+    const f32x4 d = bf16_remainder(z, pl[0]);
+    pl[1] = pack_bf16x4(d);
+    if (KX != 1) pl[2] = pack_bf16x4(bf16_remainder(d, pl[1]));
+  }
 }
 
-// Same update for bf16 matrices with r % 4 == 0 and r <= FIRA_ZREADY_MAX_R: the factor's N and R stay
-// in registers until k_i is known, and the row is written once as the back-projection operand for
+// Same update for matrices with r % 4 == 0 and r <= FIRA_ZREADY_MAX_R (fp32: FIRA_ZREADY_MAX_R_F32): the factor's N
+// and R stay in registers until k_i is known, and the row is written once as the back-projection operand for
 // an inactive limiter, Z_i = N_i - k_i R_i, rounded from fp32 a single time.  R is written as an
 // operand only when the residual contraction will need it.  Z is K-blocked, 64 B per row and K
 // block, so the workgroup's 16 rows are collected in LDS ([K block][16 rows][32]) and leave as
-// 1 KB contiguous pieces (fira_adam_kernel).
-template <int NIT>   // 256 * NIT >= r
+// 1 KB contiguous pieces (fira_adam_kernel).  fp32 matrices move 26 bytes per element here; with N and R written
+// as planes and turned into Z by a pass of their own it was 92 (350M shapes at r = 256: 916 + 602 -> 364 us).
+template <int KX, int NIT>   // 256 * NIT >= r
 __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp& hp, float bias, long long row, bool gram,
                                                 bf16_raw* zl, int rowlocal) {
   const int lane = threadIdx.x & 63;
@@ -175,23 +192,27 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
   nn = wave_sum(nn);
   rr = wave_sum(rr);
   const float k = (hp.scaling == 2) ? 1.0f : sqrtf(nn) / (sqrtf(rr) + hp.epsf);
-  const int lo_off = (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32);   // second plane of the LDS image (hp.zsplit)
+  const int planes = z_planes<KX>(hp), plane_off = (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32);   // planes of the LDS image
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int a = lane * 4 + 256 * it;
     if (a < mt.rp) {
-      u32x2 zv = u32x2{0u, 0u}, zlo = u32x2{0u, 0u};
+      u32x2 zp[3];
+      zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};
       if (a < r) {
-        const f32x4 z = nv[it] - k * rv[it];
-        zv = u32x2{pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3])};
-        if (hp.zsplit) zlo = split_remainder(z, zv);
-        if (!gram)
-          *reinterpret_cast<gptr<u32x2>>(Rb + kblk_index(mt.Lq, row, a)) =
-              u32x2{pack_bf16x2(rv[it][0], rv[it][1]), pack_bf16x2(rv[it][2], rv[it][3])};
+        bf16_planes<KX>(nv[it] - k * rv[it], planes, zp);
+        if (!gram) {
+          u32x2 rb[3];
+          bf16_planes<KX>(rv[it], KX == 1 ? 1 : 3, rb);
+#pragma unroll
+          for (int p = 0; p < (KX == 1 ? 1 : 3); ++p)
+            *reinterpret_cast<gptr<u32x2>>(Rb + kblk_index(mt.Lq, row, p * mt.rp + a)) = rb[p];
+        }
       }
       bf16_raw* dst = zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + rowlocal * 32 + (a & 31);
-      *reinterpret_cast<u32x2*>(dst) = zv;
-      if (hp.zsplit) *reinterpret_cast<u32x2*>(dst + lo_off) = zlo;
+#pragma unroll
+      for (int p = 0; p < (KX == 1 ? 2 : 3); ++p)
+        if (p < planes) *reinterpret_cast<u32x2*>(dst + p * plane_off) = zp[p];
     }
   }
   if (lane == 0) {
@@ -202,6 +223,7 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
 
 // Small ranks (r <= 64, e.g. the fine-tuning setting's r = 32): a factor's row is at most 256 bytes, so
 // a wavefront takes its four rows at once, 16 lanes per row, instead of one after the other.
+template <int KX>
 __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp& hp, float bias, long long row_base,
                                                  bool gram, bf16_raw* zl, int wave) {
   const int lane = threadIdx.x & 63;
@@ -236,18 +258,23 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
   }
   const float k = (hp.scaling == 2) ? 1.0f : sqrtf(nn) / (sqrtf(rr) + hp.epsf);
   if (a < mt.rp) {
-    u32x2 zv = u32x2{0u, 0u}, zlo = u32x2{0u, 0u};   // rows beyond L and columns beyond r: the operand's zero padding
+    const int planes = z_planes<KX>(hp);
+    u32x2 zp[3];
+    zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};   // rows beyond L and columns beyond r: the operand's zero padding
     if (live) {
-      const f32x4 z = nv - k * rv;
-      zv = u32x2{pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3])};
-      if (hp.zsplit) zlo = split_remainder(z, zv);
-      if (!gram)
-        *reinterpret_cast<gptr<u32x2>>(as_global(mt.Rb) + kblk_index(mt.Lq, row, a)) =
-            u32x2{pack_bf16x2(rv[0], rv[1]), pack_bf16x2(rv[2], rv[3])};
+      bf16_planes<KX>(nv - k * rv, planes, zp);
+      if (!gram) {
+        u32x2 rb[3];
+        bf16_planes<KX>(rv, KX == 1 ? 1 : 3, rb);
+#pragma unroll
+        for (int p = 0; p < (KX == 1 ? 1 : 3); ++p)
+          *reinterpret_cast<gptr<u32x2>>(as_global(mt.Rb) + kblk_index(mt.Lq, row, p * mt.rp + a)) = rb[p];
+      }
     }
     bf16_raw* dst = zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + g) * 32 + (a & 31);
-    *reinterpret_cast<u32x2*>(dst) = zv;
-    if (hp.zsplit) *reinterpret_cast<u32x2*>(dst + (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32)) = zlo;
+#pragma unroll
+    for (int p = 0; p < (KX == 1 ? 2 : 3); ++p)
+      if (p < planes) *reinterpret_cast<u32x2*>(dst + p * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32)) = zp[p];
   }
   if ((lane & 15) == 0 && row < mt.L) {
     as_global(mt.phi)[row] = k;
@@ -255,16 +282,20 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
   }
 }
 
+// KX: the matrices that this launch serves, bf16 (1) or fp32 (FIRA_KX_SPLIT); the row-blocks of the others leave.
+// (One kernel for both took ten registers too many for four wavefronts per SIMD, and 2 % of the bf16 time.)
+template <int KX>
 __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __restrict__ mats,
                                                         const FiraScal* __restrict__ scal,
                                                         const FiraEnt* __restrict__ ents, int count,
                                                         int total_rowblocks, FiraHp hp) {
-  extern __shared__ __attribute__((aligned(16))) char adam_lds[];   // zready matrices: 16 rows x rp bf16
+  extern __shared__ __attribute__((aligned(16))) char adam_lds[];   // zready matrices: 16 rows x planes x rp bf16
   const int rb = blockIdx.x;
   if (rb >= total_rowblocks) return;
   const int e = find_entry(ents, count, rb);
   const FiraEnt ent = ents[e];
   const FiraMat mt = mats[ent.mat];
+  if ((mt.kx == 1) != (KX == 1)) return;
   bf16_raw* zl = reinterpret_cast<bf16_raw*>(adam_lds);
   const bool zready = mt.zready && hp.scaling != 1;   // the matrix-level factor is not known in this kernel
   // bias correction with the 1-based step count (Eq. 4), in double: 1 - beta2^t loses all
@@ -276,20 +307,22 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const float bias = (float)(sqrt(1.0 - pow(hp.beta2, (double)t)) / (1.0 - pow(hp.beta1, (double)t)));
   const int wave = threadIdx.x >> 6;
   const long long row_base = (long long)(rb - ent.row0) * FIRA_ROWS_PER_WG + wave * 4;
-  if (zready && mt.r <= 64) adam_rows4_small(mt, hp, bias, row_base, gram, zl, wave);
+  const int planes = z_planes<KX>(hp);
+  if (zready && mt.r <= 64) adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, wave);
   else for (int i = 0; i < 4; ++i) {
     const long long row = row_base + i;
     if (row >= mt.L) {
       if (zready)   // rows of the padding: zeros
-        for (int a = (threadIdx.x & 63) * 4; a < (hp.zsplit ? 2 : 1) * mt.rp; a += 256)
+        for (int a = (threadIdx.x & 63) * 4; a < planes * mt.rp; a += 256)
           *reinterpret_cast<u32x2*>(zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + i) * 32 + (a & 31)) = u32x2{0u, 0u};
       continue;
     }
     if (zready) {
-      if (mt.r <= 256) adam_row_zready<1>(mt, hp, bias, row, gram, zl, wave * 4 + i);
-      else if (mt.r <= 512) adam_row_zready<2>(mt, hp, bias, row, gram, zl, wave * 4 + i);
-      else adam_row_zready<FIRA_ZREADY_MAX_R / 256>(mt, hp, bias, row, gram, zl, wave * 4 + i);
-    } else if (mt.kx == 1) {
+      constexpr int max_nit = (KX == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32) / 256;
+      if (mt.r <= 256) adam_row_zready<KX, 1>(mt, hp, bias, row, gram, zl, wave * 4 + i);
+      else if (mt.r <= 512) adam_row_zready<KX, 2>(mt, hp, bias, row, gram, zl, wave * 4 + i);
+      else if (max_nit > 2) adam_row_zready<KX, max_nit>(mt, hp, bias, row, gram, zl, wave * 4 + i);
+    } else if (KX == 1) {
       if ((mt.r & 3) == 0) adam_row<1, 4>(mt, hp, bias, row, gram); else adam_row<1, 1>(mt, hp, bias, row, gram);
     } else {
       adam_row<FIRA_KX_SPLIT, 1>(mt, hp, bias, row, gram);
@@ -300,7 +333,7 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
     // the 16 rows of one K block are 1 KB of contiguous memory
     gptr<char> nb = reinterpret_cast<gptr<char>>(as_global(mt.Nb));
     const long long row0 = (long long)(rb - ent.row0) * FIRA_ROWS_PER_WG;
-    const int nbytes = (hp.zsplit ? 2 : 1) * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 64);   // K blocks [rp/32, 2 rp/32): the lo plane
+    const int nbytes = planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 64);   // plane p: K blocks from p rp/32
     for (int o = threadIdx.x * 16; o < nbytes; o += 256 * 16) {
       const int kb = o / (FIRA_ROWS_PER_WG * 64), w = o % (FIRA_ROWS_PER_WG * 64);
       *reinterpret_cast<gptr<u32x4>>(nb + ((long long)kb * mt.Lq + row0) * 64 + w) =
@@ -474,6 +507,27 @@ __device__ __forceinline__ void fixz_row_from_moments(const FiraMat& mt, const F
   }
 }
 
+// fp32 rows that hold Z for c = 1: Z = N - c k R formed again from the updated M and V and from R.
+__device__ __forceinline__ void fixz_row_split(const FiraMat& mt, const FiraHp& hp, float f, float bias, long long row) {
+  const int lane = threadIdx.x & 63;
+  gptr<bf16_raw> Nb = as_global(mt.Nb);
+  gptr<const float> R = as_global<const float>(mt.Rt) + row * mt.r;
+  gptr<const float> M = as_global<const float>(mt.M) + row * mt.r;
+  gptr<const float> V = as_global<const float>(mt.V) + row * mt.r;
+  for (int a = lane * 4; a < mt.r; a += 256) {
+    const f32x4 rv = *reinterpret_cast<gptr<const f32x4>>(R + a);
+    const f32x4 mv = *reinterpret_cast<gptr<const f32x4>>(M + a);
+    const f32x4 vv = *reinterpret_cast<gptr<const f32x4>>(V + a);
+    f32x4 z;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z[e] = adam_direction(mv[e], vv[e], bias, hp.epsf) - f * rv[e];
+    u32x2 zp[3];
+    bf16_planes<FIRA_KX_SPLIT>(z, 3, zp);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<gptr<u32x2>>(Nb + kblk_index(mt.Lq, row, p * mt.rp + a)) = zp[p];
+  }
+}
+
 #define FIRA_MAKEZ_PARTS 32   // workgroups per listed matrix
 // One workgroup per (listed matrix, part): it reads the matrix's c once and, in the common case, exits;
 // otherwise it takes every FIRA_MAKEZ_PARTS-th block of 16 rows.
@@ -492,14 +546,15 @@ __global__ __launch_bounds__(256) void fira_makez_kernel(const FiraMat* __restri
   const int rowblocks = (mt.L + FIRA_ROWS_PER_WG - 1) / FIRA_ROWS_PER_WG;
   // the limiter has already advanced t: the bias correction of this step uses the count as it stands now
   const int t = scal[ent.mat].t;
-  const float bias = fused_here ? (float)(sqrt(1.0 - pow(hp.beta2, (double)t)) / (1.0 - pow(hp.beta1, (double)t))) : 0.0f;
+  const float bias = fused_here || mt.kx != 1 ? (float)(sqrt(1.0 - pow(hp.beta2, (double)t)) / (1.0 - pow(hp.beta1, (double)t))) : 0.0f;
   for (int rb = part; rb < rowblocks; rb += FIRA_MAKEZ_PARTS) {
     const long long row_base = (long long)rb * FIRA_ROWS_PER_WG + wave * 4;
     for (int i = 0; i < 4; ++i) {
       const long long row = row_base + i;
       if (row >= mt.L) break;
       const float k = as_global<const float>(mt.phi)[row];
-      if (zready && fused_here) fixz_row_from_moments(mt, hp, c, bias, row);
+      if (zready && mt.kx != 1) fixz_row_split(mt, hp, c * k, bias, row);
+      else if (zready && fused_here) fixz_row_from_moments(mt, hp, c, bias, row);
       else if (zready) fixz_row(mt, (1.0f - c) * k, row, hp.zsplit != 0);
       else if (mt.kx == 1) makez_row<1>(mt, c * k, row);
       else makez_row<FIRA_KX_SPLIT>(mt, c * k, row);

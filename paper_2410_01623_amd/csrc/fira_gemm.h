@@ -69,6 +69,9 @@ struct GemmOperands {
   long long ldb;      // padded row count of B
   int b_row0, b_rows;
   int KB;             // stored contraction length of B (>= KA, a multiple of 64)
+  // ring core only: K blocks of 32 per plane of an operand stored as the planes h, m, l that is contracted in the order
+  // h h m h l m (sequence A); 0 = plain
+  int planesA = 0, planesB = 0;
   int wrapA = 0, wrapB = 0;   // ring core only: K blocks of 32 after which the operand repeats (Z in two planes meets P twice); 0 = never
 };
 
@@ -181,9 +184,16 @@ __device__ __forceinline__ void ring_mainloop(f32x16_t (&acc)[4][2], char* lds, 
   // this wave's first group of each operand in K block 0; a K block is rows * 64 bytes further
   const char* pa = reinterpret_cast<const char*>((const bf16_raw*)g.A) + ((long long)g.a_row0 + 64 * wave) * 64;
   const char* pb = reinterpret_cast<const char*>((const bf16_raw*)g.B) + ((long long)g.b_row0 + 32 * wave) * 64;
+  int kb = 0, pos = 0;                         // K block inside the plane, position in sequence A, of the next stage to issue
   auto issue = [&](int s) {
     const unsigned dst = lds0 + (unsigned)((s % FIRA_RING_STAGES) * FIRA_RING_STAGE);
-    const int sa = (g.wrapA && s >= g.wrapA) ? s - g.wrapA : s, sb = (g.wrapB && s >= g.wrapB) ? s - g.wrapB : s;
+    int sa = (g.wrapA && s >= g.wrapA) ? s - g.wrapA : s, sb = (g.wrapB && s >= g.wrapB) ? s - g.wrapB : s;
+    const int np = g.planesA | g.planesB;
+    if (np) {
+      const int plane = (0x610 >> (2 * pos)) & 3;   // 0 0 1 0 2 1
+      if (g.planesA) sa = plane * np + kb; else sb = plane * np + kb;
+      if (++kb == np) { kb = 0; ++pos; }
+    }
     const char* ka = pa + (long long)sa * g.lda * 64;
     const char* kb = pb + (long long)sb * g.ldb * 64;
 #pragma unroll
@@ -1210,10 +1220,12 @@ __global__ __launch_bounds__(FIRA_BACK_THREADS, 2) void fira_backproject_kernel(
   g.b_row0 = tile.tb * FIRA_BB;
   g.b_rows = mt.m;
   // Z in two planes (hi + lo): the contraction runs over 2 rp, and the projector's K blocks are used twice
-  const bool split = MODE == 1 && hp.zsplit && mt.zready && hp.scaling != 1;
+  const bool split = MODE == 1 && hp.zsplit && mt.zready && mt.kx == 1 && hp.scaling != 1;
   g.KA = g.KB = (split ? 2 : mt.kx) * mt.rp;
   g.wrapA = (split && !mt.left) ? mt.rp / FIRA_RK : 0;
   g.wrapB = (split && mt.left) ? mt.rp / FIRA_RK : 0;
+  g.planesA = (mt.kx != 1 && mt.left) ? mt.rp / FIRA_RK : 0;
+  g.planesB = (mt.kx != 1 && !mt.left) ? mt.rp / FIRA_RK : 0;
   g.A = mt.left ? lowrank : proj;
   g.B = mt.left ? proj : lowrank;
   g.lda = mt.left ? mt.Lq : mt.Sq;

@@ -56,7 +56,7 @@ struct Plan {
   size_t off_slots = 0, slot_bytes = 0, slot_off_tiles[kNumTileLists] = {};
   std::vector<HostMat> mats;
   int max_tiles[kNumTileLists] = {};
-  int adam_lds = 0;          // dynamic LDS of the Adam kernel: 16 rows of the widest register-resident matrix
+  int adam_lds = 0, adam_lds_f32 = 0;   // dynamic LDS of the Adam kernel: 16 rows of the widest register-resident matrix
 };
 
 bool valid_desc(const fira_matrix_desc& d, std::string* why) {
@@ -88,8 +88,9 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     m.dtype = d[i].wg_dtype;
     m.kx = (m.dtype == FIRA_F32) ? FIRA_KX_SPLIT : 1;
     m.Lq = round_up_int(m.L, 256); m.Sq = round_up_int(m.S, 256); m.rq = round_up_int(m.r, 256);
-    m.zready = (m.kx == 1 && (m.r & 3) == 0 && m.r <= FIRA_ZREADY_MAX_R) ? 1 : 0;
-    if (m.zready) plan->adam_lds = std::max(plan->adam_lds, FIRA_ROWS_PER_WG * m.rp * 2);   // (twice that with Z in two planes)
+    m.zready = ((m.r & 3) == 0 && m.r <= (m.kx == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32)) ? 1 : 0;
+    if (m.zready && m.kx != 1) plan->adam_lds_f32 = std::max(plan->adam_lds_f32, FIRA_ROWS_PER_WG * m.rp * 6);
+    if (m.zready && m.kx == 1) plan->adam_lds = std::max(plan->adam_lds, FIRA_ROWS_PER_WG * m.rp * 2);   // (twice that with Z in two planes)
     m.gx_ld = m.left ? round_up_int(m.n, 8) : operand_pitch((long long)m.kx * m.Sp);
     const size_t Lr = (size_t)m.L * m.r;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
@@ -117,7 +118,7 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     h.small_proj = m.kx == 1 && m.r <= FIRA_PS;
     total_tiles[(h.small_proj ? kTilesProjSmallLeft : kTilesProjBigLeft) + (m.left ? 0 : 1)] += h.tiles_project;
     total_tiles[m.dtype == FIRA_BF16 ? kTilesBackBf16 : kTilesBackF32] += h.tiles_back;
-    if (m.zready && m.r >= FIRA_FUSE_MIN_R && m.r <= FIRA_FUSE_MAX_R) {
+    if (m.zready && m.kx == 1 && m.r >= FIRA_FUSE_MIN_R && m.r <= FIRA_FUSE_MAX_R) {
       h.fuse_list = kTilesFuse + 2 * (m.r > 256 ? 1 : 0) + (m.left ? 0 : 1);
       total_tiles[h.fuse_list] += h.ta_project;
     }
