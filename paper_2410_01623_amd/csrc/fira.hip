@@ -353,8 +353,7 @@ fira_status fira_set_projector(fira_ctx* ctx, int idx, const void* dev_P, fira_d
   if (!dev_P) return fail(ctx, FIRA_ERR_INVALID_ARG, "dev_P is null");
   if (p_dtype != FIRA_F32 && p_dtype != FIRA_BF16) return fail(ctx, FIRA_ERR_DTYPE, "p_dtype must be FIRA_F32 or FIRA_BF16");
   HostMat& h = ctx->plan.mats[idx];
-  const long long total = (long long)h.dev.S * h.dev.r;
-  const int grid = (int)std::min<long long>((total + 255) / 256, 65535);
+  const int grid = prep_tiles(h.dev.S, h.dev.r);
   if (p_dtype == FIRA_F32)
     hipLaunchKernelGGL(fira_prep_projector_kernel<float>, dim3(grid), dim3(256), 0, ctx->stream, h.dev, (const float*)dev_P);
   else
@@ -418,7 +417,7 @@ fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* idx, const 
       max_S = std::max(max_S, ctx->h_install[e].S);
       max_r = std::max(max_r, ctx->h_install[e].r);
     }
-    const int prep_blocks = (int)std::min<long long>(((long long)max_S * max_r + 255) / 256, 4096);
+    const int prep_blocks = prep_tiles(max_S, max_r);
     hipLaunchKernelGGL(fira_refresh_prep_kernel, dim3(prep_blocks, nb), dim3(256), 0, q, ctx->d_mats, d_table + e0);
     hipLaunchKernelGGL(fira_refresh_ortho_y_kernel, dim3((max_S + 3) / 4, nb), dim3(256), 0, q, ctx->d_mats, d_table + e0);
     hipLaunchKernelGGL(fira_refresh_ortho_z_kernel, dim3(FIRA_ORTHO_SPLITS, nb), dim3(256), 0, q, ctx->d_mats, d_table + e0);
@@ -926,7 +925,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
                        d_ents, (unsigned long long)seed);
   }
   const int nt64 = (max_r + 63) / 64;
-  const int prep_blocks = (int)std::min<long long>(((long long)max_S * max_r + 255) / 256, 4096);
+  const int prep_blocks = prep_tiles(max_S, max_r);
   auto orthonormalise = [&](const FiraRefreshEnt* de) {
     hipLaunchKernelGGL(fira_refresh_gram_kernel, dim3(nt64 * (nt64 + 1) / 2, count), dim3(256), 0, q, de);
     hipLaunchKernelGGL(fira_refresh_orthocheck_kernel, dim3(count), dim3(256), 0, q, de);   // (second pass only; else it leaves at once)

@@ -29,6 +29,9 @@ inline int operand_pitch(long long k) {
   return (int)(lines * 128);
 }
 
+// Workgroups of the kernel that makes a projector's operand copies: tiles of 32 (short side) x 64 (rank).
+inline int prep_tiles(int S, int r) { return ((S + 31) / 32) * ((r + 63) / 64); }
+
 struct HostMat {
   fira_matrix_desc d;
   FiraMat dev;          // copy of the device description (pointers are device pointers)
