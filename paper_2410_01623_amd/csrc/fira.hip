@@ -934,7 +934,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
       hipLaunchKernelGGL(fira_refresh_chol_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), (size_t)pan_rows * (FIRA_CHOL_NB + 1) * 8, q, de, pan_rows);
     }
     const int nj = (max_r + FIRA_SOLVE_JB - 1) / FIRA_SOLVE_JB;
-    hipLaunchKernelGGL(fira_refresh_diaginv_kernel, dim3(nj, count), dim3(64), 0, q, de);
+    hipLaunchKernelGGL(fira_refresh_diaginv_kernel, dim3(nj, count), dim3(256), 0, q, de);
     for (int J = 0; J < nj; ++J)
       hipLaunchKernelGGL(fira_refresh_solve_kernel, dim3((max_S + 63) / 64, count), dim3(256), FIRA_SOLVE_LDS, q, de, J);
   };

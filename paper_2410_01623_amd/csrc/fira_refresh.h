@@ -194,120 +194,164 @@ __global__ __launch_bounds__(256) void fira_refresh_orthocheck_kernel(const Fira
 }
 __device__ __forceinline__ bool refresh_pass_done(const FiraRefreshEnt& e) { return e.done && *as_global<const int>(e.done) != 0; }
 
-// In-place Cholesky factorisation of the lower triangle of C (fp64), one workgroup per matrix,
-// blocked by 32 columns: factor the diagonal block in LDS, solve the panel below it one row per
-// thread, update the trailing triangle from the panel.  A pivot that is not safely positive (Y
-// numerically rank deficient) is replaced by a small multiple of the largest diagonal entry, which
-// keeps the factor finite; the directions it affects carry no energy of G.
+// In-place Cholesky factorisation of the lower triangle of C (fp64), one workgroup per matrix, blocked by 32
+// columns: factor the diagonal block, solve the panel below it one row per thread, update the trailing triangle from
+// the panel.  A pivot that is not safely positive (Y numerically rank deficient) is replaced by a small multiple of
+// the largest diagonal entry, which keeps the factor finite; the directions it affects carry no energy of G.
+//
+// What bounds it is the chain of dependent steps of one panel, not its arithmetic, so both triangular parts work in
+// registers: the diagonal block with one row per lane and the column's entries handed round by lane reads, the panel
+// with one row per thread and independent multiply-adds per column; the triangle's old values are requested before
+// the products that are taken off them.  168 matrices of r = 512: 870 us; 56 of r = 128: 88 us (1890 and 255 us
+// while both parts went through LDS element by element and the largest diagonal entry was looked for by one thread).
 #define FIRA_CHOL_THREADS 512
 #define FIRA_CHOL_NB 32
 #define FIRA_CHOL_PAN_ROWS 544   // panel rows kept in LDS: 544 x 33 doubles = 140 KB (every panel of a matrix with r <= 576)
+
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+// sqrt(x) and 1 / sqrt(x) for a normal x > 0: two rounds of Goldschmidt's coupled iteration from the hardware's estimate
+// and a last Newton correction of each (within one ulp), a third of the instructions of a square root and a division.
+__device__ __forceinline__ void sqrt_and_inverse(double x, double& root, double& inv) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+  }
+  root = fma(fma(-g, g, x), h, g);
+  inv = 2.0 * h;
+  inv = fma(inv, fma(-inv, root, 1.0), inv);
+}
+
 __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(const FiraRefreshEnt* __restrict__ ents, int pan_rows) {
-  __shared__ double D[FIRA_CHOL_NB][FIRA_CHOL_NB + 1];
-  __shared__ double rinv_s[FIRA_CHOL_NB];
-  __shared__ double dmax_s;
-  // the panel below the diagonal block, [rows][FIRA_CHOL_NB + 1], while it fits (pan_rows rows of dynamic LDS):
+  constexpr int NB = FIRA_CHOL_NB, PP = NB + 1, DP = NB + 2;
+  __shared__ __attribute__((aligned(16))) double DT[NB * DP];   // the diagonal block's factor, by columns: L[i][k] at k * DP + i
+  __shared__ double rinv_s[NB];
+  __shared__ double dmax_s[FIRA_CHOL_THREADS / 64];
+  // the panel below the diagonal block, [rows][PP], while it fits (pan_rows rows of dynamic LDS):
   // the panel solve and the trailing update then read it from LDS instead of walking through memory
   extern __shared__ __attribute__((aligned(16))) double chol_pan[];
-  constexpr int PP = FIRA_CHOL_NB + 1;
   const FiraRefreshEnt e = ents[blockIdx.x];
   if (refresh_pass_done(e)) return;
-  const int r = e.r, t = threadIdx.x;
+  const int r = e.r, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   gptr<double> C = as_global(e.C);
-  if (t == 0) {
+  {
     double mx = 0.0;
-    for (int i = 0; i < r; ++i) mx = fmax(mx, C[(long long)i * r + i]);
-    dmax_s = mx;
+    for (int i = t; i < r; i += FIRA_CHOL_THREADS) mx = fmax(mx, C[(long long)i * r + i]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) dmax_s[wave] = mx;
   }
   __syncthreads();
-  const double floor_piv = dmax_s * 1e-24 + 1e-300;
-  for (int jb = 0; jb < r; jb += FIRA_CHOL_NB) {
-    const int nb = min(FIRA_CHOL_NB, r - jb);
-    // (1) diagonal block -> LDS, factor with the first 32 threads (column by column)
-    for (int x = t; x < nb * nb; x += FIRA_CHOL_THREADS) {
-      const int i = x / nb, k = x % nb;
-      D[i][k] = (k <= i) ? C[(long long)(jb + i) * r + jb + k] : 0.0;
+  double dmax = 0.0;
+#pragma unroll
+  for (int w = 0; w < FIRA_CHOL_THREADS / 64; ++w) dmax = fmax(dmax, dmax_s[w]);
+  const double floor_piv = dmax * 1e-24 + 1e-300;
+  for (int jb = 0; jb < r; jb += NB) {
+    const int nb = min(NB, r - jb);
+    // (1) diagonal block -> LDS -> registers of the first wavefront (lane i: row i; identity past the end)
+    for (int x = t; x < NB * NB; x += FIRA_CHOL_THREADS) {
+      const int i = x / NB, k = x % NB;
+      DT[k * DP + i] = (i < nb && k <= i) ? C[(long long)(jb + i) * r + jb + k] : (i == k ? 1.0 : 0.0);
     }
     __syncthreads();
-    if (t < 64) {
-      for (int j = 0; j < nb; ++j) {
-        // every lane computes the same pivot from LDS
-        const double piv = sqrt(fmax(D[j][j], floor_piv));
-        const double inv = 1.0 / piv;
-        __builtin_amdgcn_wave_barrier();
-        if (t == j) D[j][j] = piv;
-        if (t > j && t < nb) D[t][j] *= inv;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // trailing update inside the block: row t, columns j+1..t
-        if (t > j && t < nb) {
-          const double lt = D[t][j];
-          for (int k = j + 1; k <= t; ++k) D[t][k] -= lt * D[k][j];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (wave == 0) {
+      const int row = lane & (NB - 1);
+      double d[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) d[k] = DT[k * DP + row];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        double piv, inv;
+        sqrt_and_inverse(fmax(lane_value(d[j], j), floor_piv), piv, inv);
+        const double lj = d[j] * inv;          // (rows above j hold what nobody reads)
+        d[j] = row == j ? piv : lj;
+        if (lane == j) rinv_s[j] = inv;
+#pragma unroll
+        for (int k = j + 1; k < NB; ++k) d[k] = fma(-lj, lane_value(lj, k), d[k]);
+        __builtin_amdgcn_sched_barrier(0);     // (else the lane reads of many columns are gathered, and spill)
+      }
+      if (lane < NB) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) DT[k * DP + row] = k <= row ? d[k] : 0.0;
       }
     }
     __syncthreads();
-    for (int x = t; x < nb * nb; x += FIRA_CHOL_THREADS) {
-      const int i = x / nb, k = x % nb;
-      if (k <= i) C[(long long)(jb + i) * r + jb + k] = D[i][k];
+    for (int x = t; x < NB * NB; x += FIRA_CHOL_THREADS) {
+      const int i = x / NB, k = x % NB;
+      if (i < nb && k <= i) C[(long long)(jb + i) * r + jb + k] = DT[k * DP + i];
     }
-    if (t < nb) rinv_s[t] = 1.0 / D[t][t];
-    // (2) panel: rows below the block, X D^T = C_panel  (forward substitution along the block's columns)
+    // (2) panel: rows below the block (which is then a whole one), X D^T = C_panel, forward substitution along its columns
     const int below = r - (jb + nb);
     const bool in_lds = below <= pan_rows;
     if (in_lds) {
-      for (int x = t; x < below * nb; x += FIRA_CHOL_THREADS) {
-        const int i = x / nb, k = x % nb;
-        chol_pan[i * PP + k] = C[(long long)(jb + nb + i) * r + jb + k];
+      for (int x = t; x < below * NB; x += FIRA_CHOL_THREADS) {
+        const int i = x / NB, k = x % NB;
+        chol_pan[i * PP + k] = C[(long long)(jb + NB + i) * r + jb + k];
       }
       __syncthreads();
-      for (int i = t; i < below; i += FIRA_CHOL_THREADS) {
-        double* row = chol_pan + i * PP;
-        for (int k = 0; k < nb; ++k) {
-          double sacc = row[k];
-          for (int p = 0; p < k; ++p) sacc -= row[p] * D[k][p];
-          row[k] = sacc * rinv_s[k];
-        }
-      }
-      __syncthreads();
-      for (int x = t; x < below * nb; x += FIRA_CHOL_THREADS) {
-        const int i = x / nb, k = x % nb;
-        C[(long long)(jb + nb + i) * r + jb + k] = chol_pan[i * PP + k];
-      }
-    } else
+    }
     for (int i = t; i < below; i += FIRA_CHOL_THREADS) {
-      gptr<double> row = C + (long long)(jb + nb + i) * r + jb;
-      // the row's own earlier results are read back from memory (a thread sees its own stores)
-      for (int k = 0; k < nb; ++k) {
-        double sacc = row[k];
-        for (int p = 0; p < k; ++p) sacc -= row[p] * D[k][p];
-        row[k] = sacc / D[k][k];
+      gptr<double> grow = C + (long long)(jb + NB + i) * r + jb;
+      double x[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) x[k] = in_lds ? chol_pan[i * PP + k] : grow[k];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {
+        int col = k * DP;      // known only when x[k] is: the factor is read column by column (gathered at the top, it spills)
+        asm volatile("" : "+s"(col) : "v"(x[k]));
+        x[k] *= rinv_s[k];
+#pragma unroll
+        for (int j = k + 1; j < NB; ++j) x[j] = fma(-x[k], DT[col + j], x[j]);
+      }
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {
+        if (in_lds) chol_pan[i * PP + k] = x[k];
+        else grow[k] = x[k];
       }
     }
     __syncthreads();   // (HIP's barrier also waits for this wave's global stores)
-    // (3) trailing triangle: C[i][k] -= sum_p P[i][p] P[k][p],  jb+nb <= k <= i < r,  P = the panel
-    if (in_lds && below > 0) {
-      // on the matrix pipe: 32 x 32 blocks of the triangle dealt out to the wavefronts, operands from the panel in
+    if (in_lds) {
+      for (int x = t; x < below * NB; x += FIRA_CHOL_THREADS) {
+        const int i = x / NB, k = x % NB;
+        C[(long long)(jb + NB + i) * r + jb + k] = chol_pan[i * PP + k];
+      }
+      // (3) trailing triangle: C[i][k] -= sum_p P[i][p] P[k][p],  jb+NB <= k <= i < r,  P = the panel, on the matrix
+      // pipe: 32 x 32 blocks of the triangle dealt out to the wavefronts, operands from the panel in
       // LDS (rows past the end are clamped to the last row; what they produce is not stored)
-      const int lane = t & 63, wave = t >> 6, nb32 = (below + 31) / 32;
+      const int nb32 = (below + 31) / 32;
       int cnt = 0;
       for (int bi = 0; bi < nb32; ++bi)
         for (int bk = 0; bk <= bi; ++bk, ++cnt) {
           if (cnt % (FIRA_CHOL_THREADS / 64) != wave) continue;
+          double old[2][2][4];
+          gptr<double> Cb = C + (long long)(jb + NB + 32 * bi) * r + jb + NB + 32 * bk;
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                const int ri = 16 * i + (lane >> 4) + 4 * v, ck = 16 * j + (lane & 15);
+                const bool in = 32 * bi + ri < below && 32 * bk + ck <= 32 * bi + ri;
+                old[i][j][v] = in ? Cb[(long long)ri * r + ck] : 0.0;
+              }
           const int m0 = min(32 * bi + (lane & 15), below - 1), m1 = min(32 * bi + 16 + (lane & 15), below - 1);
           const int n0 = min(32 * bk + (lane & 15), below - 1), n1 = min(32 * bk + 16 + (lane & 15), below - 1);
           RefreshAcc acc;
           refresh_acc_zero(acc);
 #pragma unroll
-          for (int k4 = 0; k4 < FIRA_CHOL_NB; k4 += 4) {
+          for (int k4 = 0; k4 < NB; k4 += 4) {
             const int k = k4 + (lane >> 4);
-            const bool kin = k < nb;
-            const double a0 = kin ? chol_pan[m0 * PP + k] : 0.0, a1 = kin ? chol_pan[m1 * PP + k] : 0.0;
-            const double b0 = kin ? chol_pan[n0 * PP + k] : 0.0, b1 = kin ? chol_pan[n1 * PP + k] : 0.0;
+            const double a0 = chol_pan[m0 * PP + k], a1 = chol_pan[m1 * PP + k];
+            const double b0 = chol_pan[n0 * PP + k], b1 = chol_pan[n1 * PP + k];
             acc.v[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc.v[0][0], 0, 0, 0);
             acc.v[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc.v[0][1], 0, 0, 0);
             acc.v[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc.v[1][0], 0, 0, 0);
@@ -319,8 +363,8 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
             for (int j = 0; j < 2; ++j)
 #pragma unroll
               for (int v = 0; v < 4; ++v) {
-                const int ri = 32 * bi + 16 * i + (lane >> 4) + 4 * v, ck = 32 * bk + 16 * j + (lane & 15);
-                if (ri < below && ck <= ri) C[(long long)(jb + nb + ri) * r + jb + nb + ck] -= acc.v[i][j][v];
+                const int ri = 16 * i + (lane >> 4) + 4 * v, ck = 16 * j + (lane & 15);
+                if (32 * bi + ri < below && 32 * bk + ck <= 32 * bi + ri) Cb[(long long)ri * r + ck] = old[i][j][v] - acc.v[i][j][v];
               }
         }
     } else {
@@ -370,32 +414,65 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
 #define FIRA_SOLVE_LDS (16 * 80 * 4 + 16 * 64 * 8 + 64 * 65 * 8 + 64 * 64 * 8)   // staged Q (rows of FIRA_STAGE_LD floats), staged L, T, inverse
 
 // inv(L_JJ) for every diagonal block J of a matrix: inv[J][k][c], k >= c (zero above the diagonal).
-// Rows and columns beyond r act as an identity.
-__global__ __launch_bounds__(64) void fira_refresh_diaginv_kernel(const FiraRefreshEnt* __restrict__ ents) {
-  __shared__ double Ld[64][65];
+// Rows and columns beyond r act as an identity.  By halves: the inverses of the two 32 x 32 triangles A and B, one
+// column per lane in registers (independent multiply-adds per row of the substitution), then the lower left quarter
+// -inv(B) C inv(A).  (48 us for 168 matrices of r = 512; 390 us as one chain of 64 dependent rows per lane.)
+__global__ __launch_bounds__(256) void fira_refresh_diaginv_kernel(const FiraRefreshEnt* __restrict__ ents) {
+  constexpr int H = 32, DP = H + 2;
+  __shared__ __attribute__((aligned(16))) double LT[2][H * DP];   // the triangles by columns: L[i][k] at k * DP + i
+  __shared__ double Cq[H][H + 1], W[H][H + 1], rinv[2][H];
+  __shared__ double X[2][H][H + 1];
   const FiraRefreshEnt e = ents[blockIdx.y];
-  const int r = e.r, j0 = blockIdx.x * FIRA_SOLVE_JB, c = threadIdx.x;
+  const int r = e.r, j0 = blockIdx.x * FIRA_SOLVE_JB, t = threadIdx.x;
   if (j0 >= r || refresh_pass_done(e)) return;
   gptr<const double> Lm = as_global<const double>(e.C);
-  for (int x = c; x < 64 * 64; x += 64) {
-    const int i = x >> 6, k = x & 63;
-    const bool in = j0 + i < r && j0 + k < r;
-    Ld[i][k] = (in && k <= i) ? Lm[(long long)(j0 + i) * r + j0 + k] : (i == k ? 1.0 : 0.0);
+#pragma unroll
+  for (int p = 0; p < 16; ++p) {
+    const int x = t + 256 * p, i = x >> 6, k = x & 63;
+    const bool in = j0 + i < r && k <= i;
+    const double v = in ? Lm[(long long)(j0 + i) * r + j0 + k] : (i == k ? 1.0 : 0.0);
+    if (i >= H && k < H) Cq[i - H][k] = v;
+    else if (i < H && k < H) LT[0][k * DP + i] = v;
+    else if (i >= H) LT[1][(k - H) * DP + i - H] = v;
+    if (i == k) rinv[i / H][i % H] = 1.0 / v;
   }
   __syncthreads();
-  // column c of the inverse: L x = e_c
-  double x[64];
+  if (t < 2 * H) {
+    const int half = t / H, c = t % H;      // column c of the inverse of a triangle: L x = e_c
+    double x[H];
 #pragma unroll
-  for (int i = 0; i < 64; ++i) {
-    double v = (i == c) ? 1.0 : 0.0;
+    for (int i = 0; i < H; ++i) x[i] = i == c ? 1.0 : 0.0;
 #pragma unroll
-    for (int p = 0; p < 64; ++p)
-      if (p < i) v -= Ld[i][p] * x[p];
-    x[i] = (i < c) ? 0.0 : v / Ld[i][i];
+    for (int p = 0; p < H; ++p) {
+      x[p] *= rinv[half][p];
+#pragma unroll
+      for (int i = p + 1; i < H; ++i) x[i] = fma(-LT[half][p * DP + i], x[p], x[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < H; ++i) X[half][i][c] = x[i];
   }
+  __syncthreads();
+  const int row = t >> 3, c4 = (t & 7) * 4;
+  double q[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int k = 0; k < H; ++k)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) q[c] = fma(Cq[row][k], X[0][k][c4 + c], q[c]);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) W[row][c4 + c] = q[c];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 4; ++c) q[c] = 0.0;
+  for (int k = 0; k < H; ++k)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) q[c] = fma(X[1][row][k], W[k][c4 + c], q[c]);
   gptr<double> inv = reinterpret_cast<gptr<double>>(as_global(e.inst)) + (size_t)blockIdx.x * 64 * 64;
 #pragma unroll
-  for (int i = 0; i < 64; ++i) inv[i * 64 + c] = x[i];
+  for (int c = 0; c < 4; ++c) {
+    inv[row * 64 + c4 + c] = X[0][row][c4 + c];
+    inv[row * 64 + H + c4 + c] = 0.0;
+    inv[(H + row) * 64 + c4 + c] = -q[c];
+    inv[(H + row) * 64 + H + c4 + c] = X[1][row][c4 + c];
+  }
 }
 
 // Column block J of Q for 64 rows.
