@@ -84,17 +84,15 @@ __device__ __forceinline__ void gemm_mfma_slice(f32x16_t (&acc)[4][2], const Fra
 // Sum of squares of the A fragments (v_dot2c_f32_bf16: two bf16 products per instruction): with the
 // gradient on the A side this accumulates ||G_i||^2 for the wave's A rows at no extra memory traffic.
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void gemm_sumsq_slice(float (&sq)[4], const Frags& f) {
+__device__ __forceinline__ float frag_sumsq(const bf16x8_t& f, float sq) {
+  const u32x4 w = __builtin_bit_cast(u32x4, f);
+  const unsigned d[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-  for (int tm = 0; tm < 4; ++tm) {
-    const u32x4 w = __builtin_bit_cast(u32x4, f.a[tm]);
-    const unsigned d[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bf16x2_t v = __builtin_bit_cast(bf16x2_t, d[e]);
-      sq[tm] = __builtin_amdgcn_fdot2_f32_bf16(v, v, sq[tm], false);
-    }
+  for (int e = 0; e < 4; ++e) {
+    const bf16x2_t v = __builtin_bit_cast(bf16x2_t, d[e]);
+    sq = __builtin_amdgcn_fdot2_f32_bf16(v, v, sq, false);
   }
+  return sq;
 }
 // ------------------------------------------------------------------------------------------------
 // Ring core for the rank-axis contractions (K = r is short, the epilogue is long): 256 threads,
@@ -238,8 +236,9 @@ __device__ __forceinline__ void gload16_async(u32x4& dst, const void* base, unsi
 }
 template <int N>
 __device__ __forceinline__ void wait_loads(u32x4 (&r)[4]) {
-  static_assert(N == 4 || N == 1 || N == 0, "queue depths used by the projection pipelines");
+  static_assert(N == 4 || N == 2 || N == 1 || N == 0, "queue depths used by the projection pipelines");
   if (N == 4) asm volatile("s_waitcnt vmcnt(4) ; %0 %1 %2 %3" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) :: "memory");
+  else if (N == 2) asm volatile("s_waitcnt vmcnt(2) ; %0 %1 %2 %3" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) :: "memory");
   else if (N == 1) asm volatile("s_waitcnt vmcnt(1) ; %0 %1 %2 %3" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) :: "memory");
   else asm volatile("s_waitcnt vmcnt(0) ; %0 %1 %2 %3" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) :: "memory");
 }
@@ -354,35 +353,45 @@ __device__ __forceinline__ void proj_store_a(char* la, const u32x4 (&ra)[4], int
 // and gradient tile) then runs with the matrix pipe idle.  So that work is dealt out between the
 // multiplies of the first slice: `piece(j)`, j = 0..7, is called after the j-th of them, and scheduling
 // barriers keep the compiler from gathering the multiplies again.
-template <bool SUMSQ, typename Piece>
-__device__ __forceinline__ void proj_compute(f32x16_t (&acc)[4][2], const char* la, const char* lb, int kk4,
-                                             float (&sq)[4], Piece piece) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  Frags f[2];
+// TM: row blocks of 32 that the wave owns, from row a0; its 64 B rows start at b0.
+template <int TM, bool SUMSQ, typename Piece>
+__device__ __forceinline__ void proj_compute(f32x16_t (&acc)[TM][2], const char* la, const char* lb, int a0, int b0, int kk4,
+                                             float (&sq)[TM], Piece piece) {
+  const int lane = threadIdx.x & 63;
+  bf16x8_t fa[2][TM], fb[2][2];
   auto read_a = [&](int kk, int t) {
-    f[kk].a[t] = *reinterpret_cast<const bf16x8_t*>(la + lds_tile_off(32 * t + (lane & 31), 2 * (kk4 + kk) + (lane >> 5)));
+    fa[kk][t] = *reinterpret_cast<const bf16x8_t*>(la + lds_tile_off(a0 + 32 * t + (lane & 31), 2 * (kk4 + kk) + (lane >> 5)));
   };
   auto read_b = [&](int kk, int t) {
-    f[kk].b[t] = *reinterpret_cast<const bf16x8_t*>(lb + ring_tile_off(wave * 64 + 32 * t + (lane & 31), 2 * kk + (lane >> 5)));
+    fb[kk][t] = *reinterpret_cast<const bf16x8_t*>(lb + ring_tile_off(b0 + 32 * t + (lane & 31), 2 * kk + (lane >> 5)));
+  };
+  auto sumsq = [&](int kk) {
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) sq[tm] = frag_sumsq(fa[kk][tm], sq[tm]);
   };
 #pragma unroll
-  for (int t = 0; t < 4; ++t) read_a(0, t);
+  for (int t = 0; t < TM; ++t) read_a(0, t);
 #pragma unroll
   for (int t = 0; t < 2; ++t) read_b(0, t);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
+  for (int j = 0; j < 2 * TM; ++j) {
     const int tm = j >> 1, tn = j & 1;
-    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[0].a[tm], f[0].b[tn], acc[tm][tn], 0, 0, 0);
+    acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][tm], fb[0][tn], acc[tm][tn], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    if (j < 4) read_a(1, j);
-    else if (j < 6) read_b(1, j - 4);
-    piece(j);
+    if (j < TM) read_a(1, j);
+    else if (j < TM + 2) read_b(1, j - TM);
+#pragma unroll
+    for (int c = 0; c < 4 / TM; ++c) piece(j * (4 / TM) + c);
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (SUMSQ) gemm_sumsq_slice(sq, f[0]);
-  gemm_mfma_slice(acc, f[1]);
-  if (SUMSQ) gemm_sumsq_slice(sq, f[1]);
+  if (SUMSQ) sumsq(0);
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < 2; ++tn)
+      acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1][tm], fb[1][tn], acc[tm][tn], 0, 0, 0);
+  if (SUMSQ) sumsq(1);
 }
 
 // RT = rank tiles of 256 that one workgroup covers (256*RT threads, wave w owns rank rows 64 w ..).
@@ -391,10 +400,13 @@ __device__ __forceinline__ void proj_compute(f32x16_t (&acc)[4][2], const char* 
 // loading wavefront's is vmcnt(8).
 // (LOADER is a template parameter rather than a test inside, so that each kind of wavefront runs
 // straight-line code in which every request is followed by its own wait.)
-template <bool LEFT, bool FAST, bool SUMSQ, int RT = 1, bool LOADER = true>
-__device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[4][2], char* lds, const GemmOperands& g, float (&sq)[4]) {
+// TM = 2: half a rank tile (r <= 128), two wavefronts along the factors (64 each) and two along the rank; a ring
+// stage is 128 rows, two requests per wave, and the queue depths are TM where four requests make them 4 above.
+template <bool LEFT, bool FAST, bool SUMSQ, int RT = 1, bool LOADER = true, int TM = 4>
+__device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds, const GemmOperands& g, float (&sq)[TM]) {
   static_assert(LOADER || RT == 2, "only the second rank tile's wavefronts go without the gradient");
-  constexpr int STAGE = RT * FIRA_PROJ_RING_STAGE;
+  static_assert(TM == 4 || RT == 1, "half a rank tile, or whole ones");
+  constexpr int STAGE = RT * TM * 4096;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   constexpr bool loader = LOADER;
   char* la = lds;
@@ -404,18 +416,17 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[4][2], char* lds, 
   const int lrow = lane >> 2;
   const int chunk = (lane & 3) ^ ring_swz(lrow);
   const unsigned offb = (unsigned)(lrow * 64 + chunk * 16);
-  const char* pb = reinterpret_cast<const char*>((const bf16_raw*)g.B) + ((long long)g.b_row0 + 64 * wave) * 64;
-  auto request_b = [&](int s) {
-    const unsigned dst = ring0 + (unsigned)((s % FIRA_RING_STAGES) * STAGE);
-    const char* kb = pb + (long long)s * g.ldb * 64;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) lds_dma16(kb + q * 1024, offb, dst + (unsigned)((4 * wave + q) * 1024));
-  };
-  // request q (of 4) of ring stage s
+  const int a0 = TM == 2 ? 64 * (wave >> 1) : 0, b0 = TM == 2 ? 64 * (wave & 1) : 64 * wave;
+  const char* pb = reinterpret_cast<const char*>((const bf16_raw*)g.B) + ((long long)g.b_row0 + 16 * TM * wave) * 64;
+  // request q (of TM) of ring stage s
   auto request_b1 = [&](int s, int q) {
     const unsigned dst = ring0 + (unsigned)((s % FIRA_RING_STAGES) * STAGE);
     const char* kb = pb + (long long)s * g.ldb * 64;
-    lds_dma16(kb + q * 1024, offb, dst + (unsigned)((4 * wave + q) * 1024));
+    lds_dma16(kb + q * 1024, offb, dst + (unsigned)((TM * wave + q) * 1024));
+  };
+  auto request_b = [&](int s) {
+#pragma unroll
+    for (int q = 0; q < TM; ++q) request_b1(s, q);
   };
   ProjALoader<LEFT, FAST> al(g);
   u32x4 ra[4];
@@ -427,17 +438,17 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[4][2], char* lds, 
   auto stage = [&](auto last, int S) {
     constexpr bool LAST = decltype(last)::value;
     // E half
-    if (loader) wait_loads<4>(ra);             // A(S) and D(2S) have landed; D(2S+1) may be in flight
+    if (loader) wait_loads<TM>(ra);            // A(S) and D(2S) have landed; D(2S+1) may be in flight
     else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");    // everybody is done with the previous stage's A tile and ring slot
     if (loader) proj_store_a<LEFT>(la, ra);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     // the requests of D(2S+2) (into the slot of D(2S-1), free since the first barrier) and of A(S+1)
     // (whose registers proj_store_a has just released) go out between the multiplies
-    proj_compute<SUMSQ>(acc, la, ring + ((2 * S) % FIRA_RING_STAGES) * STAGE, 0, sq, [&](int j) {
+    proj_compute<TM, SUMSQ>(acc, la, ring + ((2 * S) % FIRA_RING_STAGES) * STAGE, a0, b0, 0, sq, [&](int j) {
       if (LAST) return;
-      if (j < 4) request_b1(2 * S + 2, j);
-      else if (loader) {
+      if (j < TM) request_b1(2 * S + 2, j);
+      else if (j >= 4 && loader) {
         if (FAST) {
           al.load_one(ra, j - 4);
           if (j == 7) al.advance();
@@ -448,12 +459,17 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[4][2], char* lds, 
     });
     // O half
     // D(2S+1) has landed.  Guarded A loads are the compiler's and may be fewer than 4 instructions,
-    // so the edge path only lets D(2S+2)'s four stay in flight.
+    // so the edge path only lets D(2S+2)'s stay in flight.
     if (LAST) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    else if (FAST && loader) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
-    proj_compute<SUMSQ>(acc, la, ring + ((2 * S + 1) % FIRA_RING_STAGES) * STAGE, 2, sq, [&](int j) {
-      if (!LAST && j < 4) request_b1(2 * S + 3, j);
+    else if (FAST && loader) {
+      if (TM == 4) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");
+    } else {
+      if (TM == 4) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(2)\n\ts_barrier" ::: "memory");
+    }
+    proj_compute<TM, SUMSQ>(acc, la, ring + ((2 * S + 1) % FIRA_RING_STAGES) * STAGE, a0, b0, 2, sq, [&](int j) {
+      if (!LAST && j < TM) request_b1(2 * S + 3, j);
     });
   };
   for (int S = 0; S + 1 < SS; ++S) stage(std::false_type{}, S);
@@ -865,15 +881,7 @@ __device__ __forceinline__ void proj_compute_small(f32x16_t (&acc)[2], const cha
   for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk], fb[kk][t], acc[t], 0, 0, 0);
-    if (SUMSQ) {
-      const u32x4 w = __builtin_bit_cast(u32x4, fa[kk]);
-      const unsigned d[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bf16x2_t v = __builtin_bit_cast(bf16x2_t, d[e]);
-        sq = __builtin_amdgcn_fdot2_f32_bf16(v, v, sq, false);
-      }
-    }
+    if (SUMSQ) sq = frag_sumsq(fa[kk], sq);
   }
 }
 
