@@ -270,7 +270,8 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
     }                                                                                                \
   } while (0)
   // the contraction kernels use more dynamic LDS than the 64 KB default (gfx950 has 160 KB per CU)
-  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_PROJ_LDS_MAX));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_PROJ_LDS));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_fp32_project_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_SPLIT_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<0, bf16_raw>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<1, bf16_raw>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<0, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
@@ -471,9 +472,12 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   auto launch_project = [&](int norm_arg) {
     int nl = s->ntiles[kTilesProjBigLeft], nr = s->ntiles[kTilesProjBigRight];
     int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
-    if (nl + nr)
-      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), blk, FIRA_PROJ_LDS_MAX, q, ctx->d_mats, s->d_ents,
+    if (nl + nr && s->ntiles[kTilesBackBf16])
+      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), blk, FIRA_PROJ_LDS, q, ctx->d_mats, s->d_ents,
                          s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, (const FiraScal*)ctx->d_scal, hp);
+    if (nl + nr && s->ntiles[kTilesBackF32])
+      hipLaunchKernelGGL(fira_fp32_project_kernel, dim3(bl + br), blk, FIRA_SPLIT_LDS, q, ctx->d_mats, s->d_ents,
+                         s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg);
     nl = s->ntiles[kTilesProjSmallLeft]; nr = s->ntiles[kTilesProjSmallRight];
     bl = (nl + 7) / 8 * 8; br = (nr + 7) / 8 * 8;
     if (nl + nr)
@@ -939,23 +943,25 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
       hipLaunchKernelGGL(fira_refresh_solve_kernel, dim3((max_S + 63) / 64, count), dim3(256), FIRA_SOLVE_LDS, q, de, J);
   };
   const FiraHp refresh_hp = make_hp(ctx);   // (mixed = 0: the projection kernel serves every listed matrix)
-  auto launch_project = [&](const FiraMat* mats, const FiraEnt* ents_d, const FiraTile* tl, int nl, const FiraTile* tr, int nr) {
+  auto launch_project = [&](const FiraMat* mats, const FiraEnt* ents_d, const FiraTile* tl, int nl, const FiraTile* tr, int nr, bool bf16, bool fp32) {
     const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
-    if (nl + nr)
-      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_PROJ_LDS_MAX, q, mats, ents_d, tl, nl, bl, tr, nr, 0,
+    if (nl + nr && bf16)
+      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_PROJ_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0,
                          (const FiraScal*)ctx->d_scal, refresh_hp);
+    if (nl + nr && fp32)
+      hipLaunchKernelGGL(fira_fp32_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_SPLIT_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0);
   };
   for (int it = 0; it < iters; ++it) {
     // operands of Q (the fp32 Q becomes the matrix's projector copies; no gate estimate needed here)
     hipLaunchKernelGGL(fira_refresh_prep_kernel, dim3(prep_blocks, count), dim3(256), 0, q, ctx->d_mats, d_ents);
     // T = G^T Q (or G Q): the projection kernel, norm route off
     launch_project(ctx->d_mats, s->d_ents, s->d_tiles[kTilesProjectLeft], s->ntiles[kTilesProjectLeft],
-                   s->d_tiles[kTilesProjectRight], s->ntiles[kTilesProjectRight]);
+                   s->d_tiles[kTilesProjectRight], s->ntiles[kTilesProjectRight], s->ntiles[kTilesBackBf16] > 0, s->ntiles[kTilesBackF32] > 0);
     // pack T as the K-blocked operand of the way back
     hipLaunchKernelGGL(fira_refresh_pack_kernel, dim3((max_Lp / 32) * nt64, count), dim3(256), 0, q, d_ents);
     // Y = G T (or G^T T): the projection kernel on the other orientation (list [1] is the K-slow one)
     launch_project(d_vmats, d_vents, (const FiraTile*)(ws + rp.off_vtiles[1]), rp.ntiles[1],
-                   (const FiraTile*)(ws + rp.off_vtiles[0]), rp.ntiles[0]);
+                   (const FiraTile*)(ws + rp.off_vtiles[0]), rp.ntiles[0], true, false);
     // Q = orth(Y): CholeskyQR in fp64
     orthonormalise(d_ents);
   }

@@ -498,7 +498,6 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 #define FIRA_SPLIT_PITCH 80
 #define FIRA_SPLIT_PLANE (FIRA_PA * FIRA_SPLIT_PITCH)
 #define FIRA_SPLIT_LDS (3 * FIRA_SPLIT_PLANE + FIRA_RING_STAGES * FIRA_PROJ_RING_STAGE)
-#define FIRA_PROJ_LDS_MAX (FIRA_SPLIT_LDS > FIRA_PROJ_LDS ? FIRA_SPLIT_LDS : FIRA_PROJ_LDS)
 
 // Thread t holds rows 4 b .. 4 b + 3 and k = 4 kq .. 4 kq + 3 of the tile; 32 consecutive threads write
 // four rows' whole 64 bytes.
@@ -761,19 +760,10 @@ __device__ __forceinline__ void project_split_tile(char* lds, const FiraMat& mt,
     }
 }
 
-template <bool LEFT>
-__device__ __forceinline__ void project_tile(char* lds, const FiraMat* __restrict__ mats, const FiraEnt* __restrict__ ents,
-                                             const FiraTile& tile, int norm_mode, const FiraScal* __restrict__ scal, const FiraHp& hp) {
-  const FiraEnt ent = ents[tile.ent];
-  if (hp.mixed && use_gram(hp, scal[ent.mat])) return;   // the fused kernel serves this matrix
-  const FiraMat mt = mats[ent.mat];
-
-  if (mt.kx != 1) {
-    if (mt.r <= 64) project_split_tile<LEFT, 1>(lds, mt, ent, tile, norm_mode);
-    else if (mt.r <= 128) project_split_tile<LEFT, 2>(lds, mt, ent, tile, norm_mode);
-    else project_split_tile<LEFT, 4>(lds, mt, ent, tile, norm_mode);
-    return;
-  }
+// bf16 matrices: TM = 2 where the rank fits half a rank tile (64 < r <= 128 in a step; a refresh also brings smaller
+// ones), else 4.  (Both orientations of 56 matrices of 512 x 512 and 512 x 1376 at r = 128: 31 us; 38 us with TM = 4.)
+template <bool LEFT, int TM>
+__device__ __forceinline__ void project_tile_as(char* lds, const FiraMat& mt, const FiraEnt& ent, const FiraTile& tile, int norm_mode) {
   GemmOperands g;
   g.a_row0 = tile.ta * FIRA_PA;
   g.a_rows = mt.L;
@@ -785,10 +775,10 @@ __device__ __forceinline__ void project_tile(char* lds, const FiraMat* __restric
   g.A = as_global(reinterpret_cast<const bf16_raw*>(ent.G));
   g.lda = mt.ld;
   g.KA = mt.S;
-  f32x16_t acc[4][2];
-  float sq[4];
+  f32x16_t acc[TM][2];
+  float sq[TM];
 #pragma unroll
-  for (int tm = 0; tm < 4; ++tm) {
+  for (int tm = 0; tm < TM; ++tm) {
     sq[tm] = 0.0f;
 #pragma unroll
     for (int tn = 0; tn < 2; ++tn)
@@ -796,39 +786,52 @@ __device__ __forceinline__ void project_tile(char* lds, const FiraMat* __restric
       for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.0f;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // Gram route: ||G_i||^2 of the tile's 128 factors falls out of the A fragments of wave 0 in the
-  // first rank tile of each panel.
-  const bool sumsq = norm_mode == 1 && tile.tb == 0 && wave == 0;
+  const int a0 = TM == 2 ? 64 * (wave >> 1) : 0, b0 = TM == 2 ? 64 * (wave & 1) : 64 * wave;   // this wave's part of the tile
+  // Gram route: ||G_i||^2 of the tile's 128 factors falls out of the A fragments of the waves with the
+  // first 64 columns of each panel's first rank tile.
+  const bool sumsq = norm_mode == 1 && tile.tb == 0 && b0 == 0;
   // LEFT: the k rows of G are whole rows of the matrix (any ld); RIGHT: a row of G holds KA values
   const bool interior = g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB;
   if (interior) {
-    if (sumsq) proj_pipeline<LEFT, true, true>(acc, lds, g, sq);
-    else proj_pipeline<LEFT, true, false>(acc, lds, g, sq);
+    if (sumsq) proj_pipeline<LEFT, true, true, 1, true, TM>(acc, lds, g, sq);
+    else proj_pipeline<LEFT, true, false, 1, true, TM>(acc, lds, g, sq);
   } else {
-    if (sumsq) proj_pipeline<LEFT, false, true>(acc, lds, g, sq);
-    else proj_pipeline<LEFT, false, false>(acc, lds, g, sq);
+    if (sumsq) proj_pipeline<LEFT, false, true, 1, true, TM>(acc, lds, g, sq);
+    else proj_pipeline<LEFT, false, false, 1, true, TM>(acc, lds, g, sq);
   }
   if (sumsq) {
     gptr<float> g2 = as_global(mt.g2);
 #pragma unroll
-    for (int tm = 0; tm < 4; ++tm) {
+    for (int tm = 0; tm < TM; ++tm) {
       const float tot = sq[tm] + __shfl_xor(sq[tm], 32, 64);
-      const int row = g.a_row0 + 32 * tm + (lane & 31);
+      const int row = g.a_row0 + a0 + 32 * tm + (lane & 31);
       if (lane < 32 && row < mt.L) g2[row] = tot;
     }
   }
   gptr<float> Rt = as_global(mt.Rt);
 #pragma unroll
-  for (int tm = 0; tm < 4; ++tm)
+  for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
     for (int tn = 0; tn < 2; ++tn) {
-      const int col = g.b_row0 + wave * 64 + 32 * tn + (lane & 31);
+      const int col = g.b_row0 + b0 + 32 * tn + (lane & 31);
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int row = g.a_row0 + 32 * tm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        const int row = g.a_row0 + a0 + 32 * tm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
         if (row < mt.L && col < mt.r) Rt[(long long)row * mt.r + col] = acc[tm][tn][v];
       }
     }
+}
+
+template <bool LEFT>
+__device__ __forceinline__ void project_tile(char* lds, const FiraMat* __restrict__ mats, const FiraEnt* __restrict__ ents,
+                                             const FiraTile& tile, int norm_mode, const FiraScal* __restrict__ scal, const FiraHp& hp) {
+  const FiraEnt ent = ents[tile.ent];
+  if (hp.mixed && use_gram(hp, scal[ent.mat])) return;   // the fused kernel serves this matrix
+  const FiraMat mt = mats[ent.mat];
+
+  if (mt.kx != 1) return;                                // fira_fp32_project_kernel's
+  if (mt.r <= 128) project_tile_as<LEFT, 2>(lds, mt, ent, tile, norm_mode);
+  else project_tile_as<LEFT, 4>(lds, mt, ent, tile, norm_mode);
 }
 
 // One grid for both orientations: workgroups [0, blocks_left) take the tiles of the matrices with
@@ -842,7 +845,7 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_project_kernel(cons
                                                                             int blocks_left,
                                                                             const FiraTile* __restrict__ tiles_right, int ntiles_right,
                                                                             int norm_mode, const FiraScal* __restrict__ scal, FiraHp hp) {
-  extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_PROJ_LDS_MAX bytes
+  extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_PROJ_LDS bytes
   if ((int)blockIdx.x < blocks_left) {
     const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
     if (ti < 0) return;
@@ -851,6 +854,36 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_project_kernel(cons
     const int ti = xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
     if (ti < 0) return;
     project_tile<false>(lds, mats, ents, tiles_right[ti], norm_mode, scal, hp);
+  }
+}
+
+// The fp32 matrices of the same tile lists (the tiles of bf16 matrices leave at once, as those of fp32 ones do above; in
+// one kernel for both the two forms together took more registers than either).
+template <bool LEFT>
+__device__ __forceinline__ void project_fp32_tile(char* lds, const FiraMat* __restrict__ mats, const FiraEnt* __restrict__ ents,
+                                                  const FiraTile& tile, int norm_mode) {
+  const FiraEnt ent = ents[tile.ent];
+  const FiraMat mt = mats[ent.mat];
+  if (mt.kx == 1) return;
+  if (mt.r <= 64) project_split_tile<LEFT, 1>(lds, mt, ent, tile, norm_mode);
+  else if (mt.r <= 128) project_split_tile<LEFT, 2>(lds, mt, ent, tile, norm_mode);
+  else project_split_tile<LEFT, 4>(lds, mt, ent, tile, norm_mode);
+}
+__global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_fp32_project_kernel(const FiraMat* __restrict__ mats,
+                                                                                 const FiraEnt* __restrict__ ents,
+                                                                                 const FiraTile* __restrict__ tiles_left, int ntiles_left,
+                                                                                 int blocks_left,
+                                                                                 const FiraTile* __restrict__ tiles_right, int ntiles_right,
+                                                                                 int norm_mode) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_SPLIT_LDS bytes
+  if ((int)blockIdx.x < blocks_left) {
+    const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
+    if (ti < 0) return;
+    project_fp32_tile<true>(lds, mats, ents, tiles_left[ti], norm_mode);
+  } else {
+    const int ti = xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
+    if (ti < 0) return;
+    project_fp32_tile<false>(lds, mats, ents, tiles_right[ti], norm_mode);
   }
 }
 
