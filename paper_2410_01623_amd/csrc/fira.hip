@@ -926,13 +926,12 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   {
     const long long mx = (long long)max_S * max_r;
     hipLaunchKernelGGL(fira_refresh_init_kernel, dim3((unsigned)std::min<long long>((mx + 255) / 256, 4096), count), dim3(256), 0, q,
-                       d_ents, (unsigned long long)seed);
+                       d_ents, (unsigned long long)seed, (int*)(ws + rp.off_done));
   }
   const int nt64 = (max_r + 63) / 64;
   const int prep_blocks = prep_tiles(max_S, max_r);
   auto orthonormalise = [&](const FiraRefreshEnt* de) {
     hipLaunchKernelGGL(fira_refresh_gram_kernel, dim3(nt64 * (nt64 + 1) / 2, count), dim3(256), 0, q, de);
-    hipLaunchKernelGGL(fira_refresh_orthocheck_kernel, dim3(count), dim3(256), 0, q, de);   // (second pass only; else it leaves at once)
     {
       const int pan_rows = std::min(FIRA_CHOL_PAN_ROWS, std::max(max_r - FIRA_CHOL_NB, 0));
       hipLaunchKernelGGL(fira_refresh_chol_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), (size_t)pan_rows * (FIRA_CHOL_NB + 1) * 8, q, de, pan_rows);

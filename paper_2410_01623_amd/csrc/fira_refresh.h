@@ -25,8 +25,11 @@ __device__ __forceinline__ unsigned long long refresh_mix64(unsigned long long z
 }
 
 // Q0: uniform(-1, 1) entries, a function of (seed, matrix, element) only.
-__global__ __launch_bounds__(256) void fira_refresh_init_kernel(const FiraRefreshEnt* __restrict__ ents, unsigned long long seed) {
+// Also clears the flags of the second orthonormalisation pass.
+__global__ __launch_bounds__(256) void fira_refresh_init_kernel(const FiraRefreshEnt* __restrict__ ents, unsigned long long seed,
+                                                                int* __restrict__ done) {
   const FiraRefreshEnt e = ents[blockIdx.y];
+  if (blockIdx.x == 0 && threadIdx.x == 0) as_global(done)[blockIdx.y] = 0;
   const long long total = (long long)e.S * e.r;
   gptr<float> Q = as_global(e.Q);
   const unsigned long long key = refresh_mix64(seed ^ ((unsigned long long)(unsigned)e.mat << 32));
@@ -157,42 +160,21 @@ __global__ __launch_bounds__(256) void fira_refresh_gram_kernel(const FiraRefres
     __syncthreads();
   }
   gptr<double> C = as_global(e.C);
+  bool off = false;
   refresh_acc_foreach(acc, [&](int row, int col, double v) {
     const int ra_ = ta * 64 + row, cb = tb * 64 + col;
-    if (ra_ < e.r && cb < e.r && cb <= ra_) C[(long long)ra_ * e.r + cb] = v;
+    if (ra_ < e.r && cb < e.r && cb <= ra_) {
+      C[(long long)ra_ * e.r + cb] = v;
+      off = off || !(fabs(v - (ra_ == cb ? 1.0 : 0.0)) <= (double)e.done_tol);   // (true for a NaN)
+    }
   });
+  // Second pass only: is the basis that the pass was given orthonormal already, max |C - I| within the entry's tolerance?
+  // (Every tile that finds it is not stores the same value.)
+  if (e.done && off) *as_global(e.done) = 1;
 }
 
-// Second pass only: is the basis that the pass was given orthonormal already?  max |C - I| over the lower triangle
-// of its Gram matrix (just computed) against the entry's tolerance; one workgroup per matrix.
-__global__ __launch_bounds__(256) void fira_refresh_orthocheck_kernel(const FiraRefreshEnt* __restrict__ ents) {
-  __shared__ double red[4];
-  const FiraRefreshEnt e = ents[blockIdx.x];
-  if (!e.done) return;
-  gptr<const double> C = as_global<const double>(e.C);
-  const int r = e.r, t = threadIdx.x;
-  double worst = 0.0;
-  for (long long x = t; x < (long long)r * r; x += 256) {
-    const int i = (int)(x / r), k = (int)(x - (long long)i * r);
-    if (k <= i) {
-      const double d = fabs(C[x] - (i == k ? 1.0 : 0.0));
-      worst = (d > worst || d != d) ? d : worst;      // a NaN stays
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const double other = __shfl_xor(worst, o, 64);
-    worst = (other > worst || other != other) ? other : worst;
-  }
-  if ((t & 63) == 0) red[t >> 6] = worst;
-  __syncthreads();
-  if (t == 0) {
-    double w = red[0];
-    for (int i = 1; i < 4; ++i) w = (red[i] > w || red[i] != red[i]) ? red[i] : w;
-    *as_global(e.done) = (w <= (double)e.done_tol) ? 1 : 0;     // false for a NaN
-  }
-}
-__device__ __forceinline__ bool refresh_pass_done(const FiraRefreshEnt& e) { return e.done && *as_global<const int>(e.done) != 0; }
+// (*done counts against the pass: 0 until a tile of the Gram matrix shows that the basis is not orthonormal yet)
+__device__ __forceinline__ bool refresh_pass_done(const FiraRefreshEnt& e) { return e.done && *as_global<const int>(e.done) == 0; }
 
 // In-place Cholesky factorisation of the lower triangle of C (fp64), one workgroup per matrix, blocked by 32
 // columns: factor the diagonal block, solve the panel below it one row per thread, update the trailing triangle from
@@ -411,7 +393,10 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
 // which is idle until the solves are done.  (Forms that kept a workgroup's rows in LDS and walked along
 // the columns, one row per lane with L read from memory or staged in LDS, ran at a tenth of the fp64
 // rate: bound by the latency, or the LDS bandwidth, of the operand every lane shares.)
-#define FIRA_SOLVE_LDS (16 * 80 * 4 + 16 * 64 * 8 + 64 * 65 * 8 + 64 * 64 * 8)   // staged Q (rows of FIRA_STAGE_LD floats), staged L, T, inverse
+// The staged operands and, after them, Y_J - update share the LDS (33 KB, four workgroups per CU: the stages of 16 k
+// are short, and what hides their barriers is other workgroups); the inverse is read from L2 as it is multiplied.
+// 168 matrices of 2048 rows at r = 512, the eight launches: 2.4 ms; 3.2 ms with 79 KB and two workgroups per CU.
+#define FIRA_SOLVE_LDS (64 * 65 * 8)   // [64][65] Y_J - update; before that staged Q (rows of FIRA_STAGE_LD floats) and L
 
 // inv(L_JJ) for every diagonal block J of a matrix: inv[J][k][c], k >= c (zero above the diagonal).
 // Rows and columns beyond r act as an identity.  By halves: the inverses of the two 32 x 32 triangles A and B, one
@@ -480,8 +465,7 @@ __global__ __launch_bounds__(256) void fira_refresh_solve_kernel(const FiraRefre
   extern __shared__ __attribute__((aligned(16))) char solve_lds[];
   float* sa = reinterpret_cast<float*>(solve_lds);                                   // [16][FIRA_STAGE_LD]  Q[s0 + i][k0 + kk]
   double* sb = reinterpret_cast<double*>(solve_lds + 16 * FIRA_STAGE_LD * 4);        // [16][64]  L[j0 + j][k0 + kk]
-  double (*st)[65] = reinterpret_cast<double (*)[65]>(solve_lds + 16 * FIRA_STAGE_LD * 4 + 16 * 64 * 8);   // [64][65] Y_J - update
-  double* invT = reinterpret_cast<double*>(solve_lds + 16 * FIRA_STAGE_LD * 4 + 16 * 64 * 8 + 64 * 65 * 8);   // [c][k]
+  double (*st)[65] = reinterpret_cast<double (*)[65]>(solve_lds);                    // [64][65] Y_J - update
   const FiraRefreshEnt e = ents[blockIdx.y];
   const int r = e.r, s0 = blockIdx.x * 64, j0 = J * FIRA_SOLVE_JB;
   if (s0 >= e.S || j0 >= r || refresh_pass_done(e)) return;
@@ -527,19 +511,29 @@ __global__ __launch_bounds__(256) void fira_refresh_solve_kernel(const FiraRefre
     refresh_acc_steps<16>(acc, sa, FIRA_STAGE_LD, 1, sb, 64, 1);   // sum_k Q[row][k] L[j0 + col][k]
     __syncthreads();
   }
-  // T = Y_J - update, and the inverse of the diagonal block (transposed: invT[c][k] = inv[k][c])
+  // T = Y_J - update  (the last stage's barrier has freed the staged operands)
   refresh_acc_foreach(acc, [&](int row, int col, double v) {
     const double y = (s0 + row < e.S && j0 + col < r) ? (double)Y[(long long)(s0 + row) * r + j0 + col] : 0.0;
     st[row][col] = y - v;
   });
-  for (int x = t; x < 64 * 64; x += 256) {
-    const int k = x >> 6, c = x & 63;
-    invT[c * 64 + k] = inv[x];
-  }
   __syncthreads();
   // Q_J = T inv^T:  q[row][k] = sum_{c <= k} T[row][c] inv[k][c]
   refresh_acc_zero(acc);
-  refresh_acc_steps<64>(acc, &st[0][0], 1, 65, invT, 64, 1);
+  {
+    const int lane = t & 63, wave = t >> 6;
+    const int m0 = 32 * (wave >> 1) + (lane & 15), n0 = 32 * (wave & 1) + (lane & 15), kq = lane >> 4;
+    const int kn = 32 * ((wave & 1) + 1);          // (inv is zero above its diagonal)
+#pragma unroll 4
+    for (int k4 = 0; k4 < kn; k4 += 4) {
+      const int k = k4 + kq;
+      const double b0 = inv[n0 * 64 + k], b1 = inv[(n0 + 16) * 64 + k];
+      const double a0 = st[m0][k], a1 = st[m0 + 16][k];
+      acc.v[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc.v[0][0], 0, 0, 0);
+      acc.v[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc.v[0][1], 0, 0, 0);
+      acc.v[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc.v[1][0], 0, 0, 0);
+      acc.v[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc.v[1][1], 0, 0, 0);
+    }
+  }
   refresh_acc_foreach(acc, [&](int row, int k, double v) {
     if (s0 + row < e.S && j0 + k < r) Q[(long long)(s0 + row) * r + j0 + k] = (float)v;
   });
