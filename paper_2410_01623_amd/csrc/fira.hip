@@ -108,6 +108,14 @@ struct fira_ctx {
   FiraRefreshEnt* h_install = nullptr;
   hipEvent_t install_event = nullptr;
   bool install_pending = false;
+  // fira_refresh_projectors: host image (pinned, room for every matrix) of the tables at the start of its workspace, and
+  // the event after its upload
+  char* h_refresh = nullptr;
+  hipEvent_t refresh_event = nullptr;
+  bool refresh_pending = false;
+  // Matrices whose projector was installed after the last step that could measure their second gate value: that value
+  // is +inf, which is all a step has to know to take the residual route for them, so it need not wait for the read-back.
+  std::vector<char> unmeasured;
   uint64_t use_counter = 0;
   int device = -1;               // HIP device that was current at fira_init_state
   void* static_scratch = nullptr;   // that device's copy of the library's static scratch array
@@ -256,6 +264,8 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
     if (ctx->h_stage_all) (void)hipHostFree(ctx->h_stage_all);
     if (ctx->h_gate) (void)hipHostFree(ctx->h_gate);
     if (ctx->h_install) (void)hipHostFree(ctx->h_install);
+    if (ctx->h_refresh) (void)hipHostFree(ctx->h_refresh);
+    if (ctx->refresh_event) (void)hipEventDestroy(ctx->refresh_event);
     if (ctx->ortho_event) (void)hipEventDestroy(ctx->ortho_event);
     if (ctx->install_event) (void)hipEventDestroy(ctx->install_event);
     delete ctx;
@@ -287,6 +297,15 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   FIRA_INIT_HIP(hipEventCreateWithFlags(&ctx->ortho_event, hipEventDisableTiming));
   FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_install, sizeof(FiraRefreshEnt) * count, hipHostMallocDefault));
   FIRA_INIT_HIP(hipEventCreateWithFlags(&ctx->install_event, hipEventDisableTiming));
+  {
+    RefreshPlan rp;
+    std::vector<int> all(count);
+    for (int i = 0; i < count; ++i) all[i] = i;
+    make_refresh_plan(p, count, all.data(), &rp);
+    FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_refresh, rp.top_begin, hipHostMallocDefault));
+    FIRA_INIT_HIP(hipEventCreateWithFlags(&ctx->refresh_event, hipEventDisableTiming));
+  }
+  ctx->unmeasured.assign(count, 0);
   for (int i = 0; i < kSlots; ++i) {
     ListSlot& s = ctx->slots[i];
     s.h_stage = ctx->h_stage_all + p.slot_bytes * i;
@@ -373,6 +392,7 @@ fira_status fira_set_projector(fira_ctx* ctx, int idx, const void* dev_P, fira_d
   FIRA_HIP(ctx, hipEventRecord(ctx->ortho_event, ctx->stream));
   ctx->ortho_pending = true;
   h.has_projector = true;
+  ctx->unmeasured[idx] = 1;
   return FIRA_OK;
 }
 
@@ -437,6 +457,7 @@ fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* idx, const 
   for (int e = 0; e < count; ++e) {
     ctx->h_gate[idx[e]] = fira_ctx::Gate{INFINITY, INFINITY};
     ctx->plan.mats[idx[e]].has_projector = true;
+    ctx->unmeasured[idx[e]] = 1;
   }
   return read_back_gates(ctx);
 }
@@ -491,7 +512,11 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   // measured takes the residual route in this step, and the limiter measures it.
   bool need_residual = !only_scaling;
   bool any_gram = false, measures = false;
-  if (need_residual && ctx->norm_mode == FIRA_NORM_GRAM) {
+  bool all_unmeasured = true;
+  for (int e = 0; e < count; ++e) all_unmeasured = all_unmeasured && ctx->unmeasured[idx[e]];
+  if (need_residual && ctx->norm_mode == FIRA_NORM_GRAM && all_unmeasured) {
+    measures = true;            // (whatever the first gate value will turn out to be)
+  } else if (need_residual && ctx->norm_mode == FIRA_NORM_GRAM) {
     if (ctx->ortho_pending) {   // gate values are on their way back (a projector was installed, or a step measured one)
       FIRA_HIP(ctx, hipEventSynchronize(ctx->ortho_event));
       ctx->ortho_pending = false;
@@ -584,6 +609,8 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   }
   mark(6);
   FIRA_HIP(ctx, hipGetLastError());
+  if (!only_scaling && ctx->norm_mode == FIRA_NORM_GRAM)
+    for (int e = 0; e < count; ++e) ctx->unmeasured[idx[e]] = 0;
   if (measures) return read_back_gates(ctx);   // the limiter has measured a second gate value: the next step needs it
   return FIRA_OK;
 }
@@ -720,6 +747,7 @@ fira_status fira_set_gate(fira_ctx* ctx, int idx, float ortho_err, float gram_er
   const fira_ctx::Gate gt{ortho_err, gram_err};
   FIRA_HIP(ctx, hipMemcpy(reinterpret_cast<char*>(ctx->d_scal + idx) + offsetof(FiraScal, ortho_err), &gt, sizeof(gt), hipMemcpyHostToDevice));
   ctx->h_gate[idx] = gt;
+  ctx->unmeasured[idx] = 0;
   return FIRA_OK;
 }
 
@@ -846,11 +874,18 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   const int nmat = (int)ctx->plan.mats.size();
   hipStream_t q = ctx->stream;
 
-  // host images of the small tables
-  std::vector<FiraRefreshEnt> ents(count), ents2(count);
-  std::vector<FiraMat> vmats(count);
-  std::vector<FiraEnt> vents(count);
-  std::vector<FiraTile> vtiles[2];
+  // Host image of the small tables: everything in front of the packed operands, in one upload from pinned memory, so that
+  // nothing here waits for the stream.
+  if (ctx->refresh_pending) {   // the previous call's image may still be on its way to the device
+    FIRA_HIP(ctx, hipEventSynchronize(ctx->refresh_event));
+    ctx->refresh_pending = false;
+  }
+  std::memset(ctx->h_refresh, 0, rp.top_begin);
+  FiraRefreshEnt* ents = (FiraRefreshEnt*)(ctx->h_refresh + rp.off_ents);
+  FiraRefreshEnt* ents2 = (FiraRefreshEnt*)(ctx->h_refresh + rp.off_ents2);
+  FiraMat* vmats = (FiraMat*)(ctx->h_refresh + rp.off_vmats);
+  FiraEnt* vents = (FiraEnt*)(ctx->h_refresh + rp.off_vents);
+  FiraTile* vtiles[2] = {(FiraTile*)(ctx->h_refresh + rp.off_vtiles[0]), (FiraTile*)(ctx->h_refresh + rp.off_vtiles[1])};
   int max_S = 0, max_r = 0, max_Lp = 0;
   for (int e = 0; e < count; ++e) {
     const FiraMat& m = ctx->plan.mats[idx[e]].dev;
@@ -885,17 +920,11 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     ve.mat = e; ve.W = nullptr; ve.G = f32 ? (const void*)(ws + rp.off_gb[e]) : dev_G[e];
     const int ta_n = (m.S + FIRA_PA - 1) / FIRA_PA, tb_n = (m.r + FIRA_PB - 1) / FIRA_PB;
     for (int ta = 0; ta < ta_n; ++ta)
-      for (int tb = 0; tb < tb_n; ++tb) vtiles[m.left ? 0 : 1].push_back(FiraTile{e, ta, tb, 0});
+      for (int tb = 0; tb < tb_n; ++tb) *vtiles[m.left ? 0 : 1]++ = FiraTile{e, ta, tb, 0};
   }
-  FIRA_HIP(ctx, hipMemcpyAsync(ws + rp.off_ents, ents.data(), sizeof(FiraRefreshEnt) * count, hipMemcpyHostToDevice, q));
-  FIRA_HIP(ctx, hipMemcpyAsync(ws + rp.off_ents2, ents2.data(), sizeof(FiraRefreshEnt) * count, hipMemcpyHostToDevice, q));
-  FIRA_HIP(ctx, hipMemcpyAsync(ws + rp.off_vmats, vmats.data(), sizeof(FiraMat) * count, hipMemcpyHostToDevice, q));
-  FIRA_HIP(ctx, hipMemcpyAsync(ws + rp.off_vents, vents.data(), sizeof(FiraEnt) * count, hipMemcpyHostToDevice, q));
-  for (int l = 0; l < 2; ++l)
-    if (!vtiles[l].empty())
-      FIRA_HIP(ctx, hipMemcpyAsync(ws + rp.off_vtiles[l], vtiles[l].data(), sizeof(FiraTile) * vtiles[l].size(), hipMemcpyHostToDevice, q));
-  // the host vectors go away when this function returns: the copies above must have been made
-  FIRA_HIP(ctx, hipStreamSynchronize(q));
+  FIRA_HIP(ctx, hipMemcpyAsync(ws, ctx->h_refresh, rp.top_begin, hipMemcpyHostToDevice, q));
+  FIRA_HIP(ctx, hipEventRecord(ctx->refresh_event, q));
+  ctx->refresh_pending = true;
   {   // padding rows of the packed operand must read as zero (the workspace keeps whatever it held before)
     const size_t n16 = (rp.top_end - rp.top_begin) / 16;
     const unsigned grid = (unsigned)std::min<size_t>((n16 + 255) / 256, 8192);
@@ -992,6 +1021,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   for (int e = 0; e < count; ++e) {
     ctx->h_gate[idx[e]] = fira_ctx::Gate{INFINITY, INFINITY};
     ctx->plan.mats[idx[e]].has_projector = true;
+    ctx->unmeasured[idx[e]] = 1;
   }
   return read_back_gates(ctx);
 }
@@ -1009,6 +1039,8 @@ void fira_destroy(fira_ctx* ctx) {
   if (ctx->h_stage_all) (void)hipHostFree(ctx->h_stage_all);
   if (ctx->h_gate) (void)hipHostFree(ctx->h_gate);
   if (ctx->h_install) (void)hipHostFree(ctx->h_install);
+  if (ctx->h_refresh) (void)hipHostFree(ctx->h_refresh);
+  if (ctx->refresh_event) (void)hipEventDestroy(ctx->refresh_event);
   if (ctx->ortho_event) (void)hipEventDestroy(ctx->ortho_event);
   if (ctx->install_event) (void)hipEventDestroy(ctx->install_event);
   delete ctx;
