@@ -477,27 +477,30 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 }
 
 // ------------------------------------------------------------------------------------------------
-// Kernel 1 for fp32 matrices.  The gradient is read once, in fp32: a thread holds a 4 x 4 block of it in
-// registers, splits every value into its three bf16 planes (x = h + m + l, split3) and writes them to
-// three LDS tiles; the six plane products hh, mh, lh, hm, mm, hl of a block of 32 k run from there, so
-// that a gradient plane is read from LDS and a projector plane from memory once instead of two or three
-// times.  ||G_i||^2 is summed in fp32 from the unsplit values on the way.  What bounds it is the matrix
-// pipe (six products per element) and the additions beside it.  Over the 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256 it takes
-// 930 us; the split of G through memory (six planes written and read back), its projection and a pass of
-// its own for ||G_i||^2 took 1361 + 1123 + 918 us.  One 256 x 688 matrix at r = 64: 15 us against 5 + 60 + 30.
+// Kernel 1 for fp32 matrices.  The gradient is read in fp32: a thread holds a 4 x 4 block of it in
+// registers, splits the values into bf16 planes (x = h + m + l, split3) and writes the plane in turn to an
+// LDS tile.  The six plane products run one after the other over the whole contraction, the largest first (sequences A
+// and B): what the small ones add meets a sum that is already whole, and is rounded at the size of the result, where
+// all six taken together per block of k round six times as often at the size of the running sum (twice the error of R
+// where it cancels).  So G is read six times, from the memory-side cache as far as it holds it; that and the
+// latency of a stage bound the kernel, and it still takes about half of what the way through memory took (six
+// planes written, read back, and a pass of its own for ||G_i||^2, which falls out of the first product here): 1808 us over
+// the 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256, against 1361 + 1123 + 918; one 256 x 688 matrix at r = 64:
+// 45 us against 5 + 60 + 30.  (Sums of all six products per block of 32 k, apart from the running sum: 930 us and a quarter
+// of the error of R, but single weights then differ from the former results by more than rounding explains locally:
+// an element whose R is tiny in every step hands its relative error on to N.)
 //
 // Tile: 128 factors x 64 TM rank components; wave w holds 32 TM factors x 64 rank components, TM = 4, 2
-// or 1 (the smallest that covers r, so that no wavefront multiplies padding only).  A block of 32 k:
-//   registers -> three LDS tiles [128][32 k], 80 bytes per row (conflict-free for the 8-byte writes of
-//   four rows and the 16-byte fragment reads of sixteen); then the products with the projector's plane h, then
-//   those with its planes m and l (K blocks 0, Sp/32 and 3 Sp/32 of sequence B).  The planes m, l arrive while
-//   the tiles are written and h is multiplied; h and A of the next block while the rest is.
+// or 1 (the smallest that covers r, so that no wavefront multiplies padding only).  A stage is one product over 32 k:
+//   registers -> LDS tile [128][32 k], 80 bytes per row (conflict-free for the 8-byte writes of
+//   four rows and the 16-byte fragment reads of sixteen), the projector's plane beside it; both doubled, one barrier
+//   per stage; the next stage's operands are requested between the multiplies.
 // Loads never leave the matrix: a group of four that would is moved back and shifted in registers, rows
 // past the end read the last row; values past the contraction length are set to zero.
 // ------------------------------------------------------------------------------------------------
 #define FIRA_SPLIT_PITCH 80
 #define FIRA_SPLIT_PLANE (FIRA_PA * FIRA_SPLIT_PITCH)
-#define FIRA_SPLIT_LDS (3 * FIRA_SPLIT_PLANE + FIRA_RING_STAGES * FIRA_PROJ_RING_STAGE)
+#define FIRA_SPLIT_LDS (2 * FIRA_SPLIT_PLANE + 2 * FIRA_PROJ_RING_STAGE)
 
 // Thread t holds rows 4 b .. 4 b + 3 and k = 4 kq .. 4 kq + 3 of the tile; 32 consecutive threads write
 // four rows' whole 64 bytes.
@@ -577,78 +580,58 @@ struct SplitALoader {
   }
 };
 
-// Registers -> the three plane tiles; sq[e] += the row's share of ||G_i||^2.
-__device__ __forceinline__ void split_store_a(char* la, const float (&x)[4][4], float (&sq)[4], int t) {
+// Plane pl (0, 1, 2: h, m, l) of the block -> its tile.
+__device__ __forceinline__ void split_store_a(char* la, const float (&x)[4][4], int pl, int t) {
   char* dst = la + 4 * split_b(t) * FIRA_SPLIT_PITCH + 8 * split_kq(t);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const u32x2 h = u32x2{pack_bf16x2(x[e][0], x[e][1]), pack_bf16x2(x[e][2], x[e][3])};
-    float d[4];
-    d[0] = x[e][0] - __uint_as_float(h.x << 16); d[1] = x[e][1] - __uint_as_float(h.x & 0xffff0000u);
-    d[2] = x[e][2] - __uint_as_float(h.y << 16); d[3] = x[e][3] - __uint_as_float(h.y & 0xffff0000u);
-    const u32x2 m = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
-    d[0] -= __uint_as_float(m.x << 16); d[1] -= __uint_as_float(m.x & 0xffff0000u);
-    d[2] -= __uint_as_float(m.y << 16); d[3] -= __uint_as_float(m.y & 0xffff0000u);
-    const u32x2 l = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
-    *reinterpret_cast<u32x2*>(dst + e * FIRA_SPLIT_PITCH) = h;
-    *reinterpret_cast<u32x2*>(dst + e * FIRA_SPLIT_PITCH + FIRA_SPLIT_PLANE) = m;
-    *reinterpret_cast<u32x2*>(dst + e * FIRA_SPLIT_PITCH + 2 * FIRA_SPLIT_PLANE) = l;
-    sq[e] += (x[e][0] * x[e][0] + x[e][1] * x[e][1]) + (x[e][2] * x[e][2] + x[e][3] * x[e][3]);
+    u32x2 v = u32x2{pack_bf16x2(x[e][0], x[e][1]), pack_bf16x2(x[e][2], x[e][3])};
+    if (pl != 0) {
+      float d[4];
+      d[0] = x[e][0] - __uint_as_float(v.x << 16); d[1] = x[e][1] - __uint_as_float(v.x & 0xffff0000u);
+      d[2] = x[e][2] - __uint_as_float(v.y << 16); d[3] = x[e][3] - __uint_as_float(v.y & 0xffff0000u);
+      v = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
+      if (pl == 2) {
+        d[0] -= __uint_as_float(v.x << 16); d[1] -= __uint_as_float(v.x & 0xffff0000u);
+        d[2] -= __uint_as_float(v.y << 16); d[3] -= __uint_as_float(v.y & 0xffff0000u);
+        v = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
+      }
+    }
+    *reinterpret_cast<u32x2*>(dst + e * FIRA_SPLIT_PITCH) = v;
   }
 }
 
-// Half of a block of 32 k: three plane products (two slices of 16 k each) into a fresh accumulator per 32 x 32
-// block, which is then added to acc on the vector unit.  Six products in a row on acc itself would round the
-// running sum twelve times per block, against twice when the small products are kept apart (their own size is
-// 2^-8 and less of it); this way it is rounded twice as well, and to nearest.
-//   H: projector plane h against the gradient's h, m, l;    else: planes m, l as h m, h l, m m.
-// `piece(j)`, j = 0..3, is called, and the next row block's fragments and the previous block's additions run,
-// between the multiplies.
-template <int TM, bool H, typename Piece>
+// One stage: 32 k of a plane product, `piece(j)`, j = 0..7, between its first multiplies (see proj_compute).
+template <int TM, typename Piece>
 __device__ __forceinline__ void split_compute(f32x16_t (&acc)[TM][2], const char* la, const char* lb, int a0, int b0, Piece piece) {
   const int lane = fresh_lane();
-  // product i uses gradient fragment FA(i) = 2 * plane + slice and projector fragment FB(i) = 2 * (plane of lb) +
-  // slice, the smallest products first (the error of R against 64 bits is a quarter smaller than with the largest first)
-  constexpr int NA = H ? 6 : 4, NB = H ? 2 : 4, BSTRIDE = TM * 4096;
-  constexpr int FA[6] = {H ? 4 : 2, H ? 5 : 3, H ? 2 : 0, H ? 3 : 1, 0, 1};
-  constexpr int FB[6] = {0, 1, H ? 0 : 2, H ? 1 : 3, 0, 1};
-  bf16x8_t fa[NA], fb[2][NB];
-  auto read_a = [&](int f, int t) {
-    fa[f] = *reinterpret_cast<const bf16x8_t*>(la + (f >> 1) * FIRA_SPLIT_PLANE + (a0 + 32 * t + (lane & 31)) * FIRA_SPLIT_PITCH +
-                                               (2 * (f & 1) + (lane >> 5)) * 16);
+  bf16x8_t fa[2][TM], fb[2][2];
+  auto read_a = [&](int kk, int t) {
+    fa[kk][t] = *reinterpret_cast<const bf16x8_t*>(la + (a0 + 32 * t + (lane & 31)) * FIRA_SPLIT_PITCH + (2 * kk + (lane >> 5)) * 16);
+  };
+  auto read_b = [&](int kk, int t) {
+    fb[kk][t] = *reinterpret_cast<const bf16x8_t*>(lb + ring_tile_off(b0 + 32 * t + (lane & 31), 2 * kk + (lane >> 5)));
   };
 #pragma unroll
-  for (int f = 0; f < NA; ++f) read_a(f, 0);
-  auto read_b = [&](int f, int t) {
-    fb[t][f] = *reinterpret_cast<const bf16x8_t*>(lb + (f >> 1) * BSTRIDE + ring_tile_off(b0 + 32 * t + (lane & 31), 2 * (f & 1) + (lane >> 5)));
-  };
+  for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int f = 0; f < NB; ++f) read_b(f, t);
-  __builtin_amdgcn_sched_barrier(0);
-  f32x16_t part[2];
-#pragma unroll
-  for (int blk = 0; blk < 2 * TM; ++blk) {
-    const int tm = blk >> 1, tn = blk & 1;
-    f32x16_t& p = part[blk & 1];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) p[v] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[FA[i]], fb[tn][FB[i]], p, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (tn == 1 && tm + 1 < TM && (H || i < 2 || i > 3)) read_a(FA[i], tm + 1);   // after this fragment's last use
-      if (blk == 0 && i < 4) piece(i);
-      if (blk > 0 && i >= 2) {
-        f32x16_t& d = acc[(blk - 1) >> 1][(blk - 1) & 1];
-#pragma unroll
-        for (int v = 4 * (i - 2); v < 4 * (i - 1); ++v) d[v] += part[(blk - 1) & 1][v];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int t = 0; t < TM; ++t) read_a(kk, t);
+    read_b(kk, 0);
+    read_b(kk, 1);
   }
-  acc[TM - 1][1] += part[1];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int j = 0; j < 2 * TM; ++j) {
+      acc[j >> 1][j & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][j >> 1], fb[kk][j & 1], acc[j >> 1][j & 1], 0, 0, 0);
+      if (kk == 0) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < 4 / TM; ++c) piece(j * (4 / TM) + c);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
 }
 
 // acc and sq (rows 4 b + e, this thread's k) must be zero on entry.  B: the projector's planes (sequence B).
@@ -656,66 +639,53 @@ template <bool LEFT, int TM, bool ASYNC>
 __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds, const FiraMat& mt, const float* G, int a_row0, int b_row0,
                                                int a0, int b0, float (&sq)[4]) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  char* la = lds;
-  // The projector's planes h, m, l of a block, 64 TM rows each.  With TM <= 2 there is room for two blocks, and a
-  // block's operands are requested a whole block ahead.
-  constexpr bool TWO = TM <= 2;
-  constexpr int PLANE = TM * 4096;
-  char* lb = lds + 3 * FIRA_SPLIT_PLANE;
+  constexpr int SLOT = TM * 4096;
+  char* lb = lds + 2 * FIRA_SPLIT_PLANE;
   const unsigned lb0 = (unsigned)(size_t)(lds_ptr)lb;
   const int nblocks = (mt.S + 31) / 32, planes = mt.Sp / 32;
   const char* pb = reinterpret_cast<const char*>(mt.PT) + ((long long)b_row0 + 16 * TM * wave) * 64;
-  // this wave's share (TM requests) of plane pl of block kb
-  auto request_b = [&](int kb, int pl) {
+  // request q (of TM) of this wave's share of the projector's plane `pos` of sequence B, block kb
+  auto request_b = [&](int pos, int kb, int slot, int q) {
     const int lane = fresh_lane(), lrow = lane >> 2;
     const unsigned offb = (unsigned)(lrow * 64 + ((lane & 3) ^ ring_swz(lrow)) * 16);
-    const int kofs = (pl == 2 ? 3 : pl) * planes + kb, slot = (TWO ? 3 * (kb & 1) : 0) + pl;
-#pragma unroll
-    for (int q = 0; q < TM; ++q)
-      lds_dma16(pb + ((long long)kofs * mt.rq) * 64 + q * 1024, offb,
-                (unsigned)__builtin_amdgcn_readfirstlane((int)(lb0 + (unsigned)(slot * PLANE + (TM * wave + q) * 1024))));
+    lds_dma16(pb + ((long long)(pos * planes + kb) * mt.rq) * 64 + q * 1024, offb,
+              (unsigned)__builtin_amdgcn_readfirstlane((int)(lb0 + (unsigned)(slot * SLOT + (TM * wave + q) * 1024))));
   };
   SplitALoader<LEFT, ASYNC> al{as_global(G), mt.ld, a_row0, mt.L, mt.S};
   u32x4 ra[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) al.load_one(ra, 0, q, fresh_thread());
-  request_b(0, 0);
-  if (TWO) {
-    request_b(0, 1);
-    request_b(0, 2);
-  }
-  // The last block is written out separately so that on every path a request is followed by its wait.
-  auto block = [&](auto last, int kb) {
+#pragma unroll
+  for (int q = 0; q < TM; ++q) request_b(0, 0, 0, q);
+  // The last stage is written out separately so that on every path a request is followed by its wait.
+  auto stage = [&](auto last, int pos, int kb, int slot) {
     constexpr bool LAST = decltype(last)::value;
-    wait_loads<0>(ra);                           // A(kb) and plane h (TWO: every plane) have landed
+    wait_loads<0>(ra);                           // this stage's operands have landed
     float x[4][4];
     const int t = fresh_thread();
     al.unpack(ra, 32 * kb, x, t);
-    asm volatile("s_barrier" ::: "memory");      // everybody is done with the previous block's tiles and planes
-    if (!TWO) {
-      request_b(kb, 1);
-      request_b(kb, 2);
-    } else if (!LAST) {
-      request_b(kb + 1, 0);
-      request_b(kb + 1, 1);
-      request_b(kb + 1, 2);
+    if (pos == 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sq[e] += (x[e][0] * x[e][0] + x[e][1] * x[e][1]) + (x[e][2] * x[e][2] + x[e][3] * x[e][3]);
     }
-    split_store_a(la, x, sq, t);
+    split_store_a(lds + slot * FIRA_SPLIT_PLANE, x, (0x610 >> (2 * pos)) & 3, t);   // sequence A: planes 0 0 1 0 2 1
+    // everybody's share is there, and everybody is done with the other slot's stage
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    const char* lk = lb + (TWO ? 3 * (kb & 1) * PLANE : 0);
-    split_compute<TM, true>(acc, la, lk, a0, b0, [&](int j) {
-      if (!LAST) al.load_one(ra, 32 * (kb + 1), j, fresh_thread());
+    const bool wrap = kb + 1 == nblocks;
+    const int npos = wrap ? pos + 1 : pos, nkb = wrap ? 0 : kb + 1;
+    split_compute<TM>(acc, lds + slot * FIRA_SPLIT_PLANE, lb + slot * SLOT, a0, b0, [&](int j) {
+      if (LAST) return;
+      if (j < TM) request_b(npos, nkb, slot ^ 1, j);
+      else if (j >= 4) al.load_one(ra, 32 * nkb, j - 4, fresh_thread());
     });
-    if (!TWO) {
-      // planes m and l have landed; A(kb+1) may be in flight (its element-wise form is not counted)
-      if (!LAST && ASYNC) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-      if (!LAST) request_b(kb + 1, 0);           // plane h's place is free
-    }
-    split_compute<TM, false>(acc, la, lk + PLANE, a0, b0, [](int) {});
   };
-  for (int kb = 0; kb + 1 < nblocks; ++kb) block(std::false_type{}, kb);
-  block(std::true_type{}, nblocks - 1);
+  int pos = 0, kb = 0, slot = 0;
+  for (int s = 0; s + 1 < 6 * nblocks; ++s) {
+    stage(std::false_type{}, pos, kb, slot);
+    slot ^= 1;
+    if (++kb == nblocks) { kb = 0; ++pos; }
+  }
+  stage(std::true_type{}, pos, kb, slot);
 }
 
 template <bool LEFT, int TM>
@@ -1032,7 +1002,8 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 4) void fira_project_small_kerne
 // ------------------------------------------------------------------------------------------------
 // The rank-axis contraction of fp32 matrices: every block of 32 k holds the planes h, m, l of both operands in LDS
 // (72 KB, single-buffered, two workgroups per CU) and runs the six plane products from there, so that a plane is
-// brought in once instead of two or three times, summed apart from the running sum (see split_compute).  First B's
+// brought in once instead of two or three times, summed per block apart from the running sum, which is then rounded to
+// nearest once per three products.  First B's
 // plane h against A's l, m, h, while B's m and l arrive; then those against A's h and m, while the next
 // block's A l and B h arrive in the places that are free by then.  350M shapes at r = 256, update: 1240 us, against
 // 1293 us with the six products one after the other through the ring.
