@@ -248,8 +248,8 @@ FIRA_API fira_status fira_get_projector(fira_ctx* ctx, int idx, float* host_P);
  *   dev_G[e]       gradient of matrix idx[e], same layout as in fira_step; read only
  *   dev_workspace  device scratch of fira_refresh_workspace_bytes(ctx, count, idx) bytes, 256-byte
  *                  aligned, owned by the caller, free to reuse once the stream has passed this call
- * Enqueues on the context's stream and returns; the small work lists are uploaded with blocking
- * copies, so the call is not meant for the step's inner loop.  Uses the listed matrices' step
+ * Enqueues on the context's stream and returns; the small work lists go up in one copy from pinned
+ * memory (a call waits for the previous call's upload before it rewrites them).  Uses the listed matrices' step
  * scratch (not their state).  The rounds of the iteration work in the matrices' own operand copies of
  * P: if a launch fails on the way (FIRA_ERR_HIP), the listed matrices are left WITHOUT a projector
  * (fira_step reports FIRA_ERR_NO_PROJECTOR for them until one is installed again); M, V, t and the
