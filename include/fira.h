@@ -149,7 +149,8 @@ FIRA_API fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* id
  * fira_set_options, fira_set_variant, fira_set_fusion, and fira_set_projector(s) or
  * fira_refresh_projectors calls (which may change a matrix's route) do not reach it, and it must be
  * captured again after any of them.  Capture only from the second step after a projector was
- * installed on (the first one measures the Gram route's gate and reads it back).  While a captured
+ * installed on: in the FIRA_NORM_GRAM mode the first one measures the Gram route's gate and reads it back, and
+ * is refused while the stream is being captured (FIRA_ERR_HIP, nothing enqueued).  While a captured
  * step may still be replayed, do not step more than three other distinct (idx, W, G) lists on the
  * same context: the fifth distinct list reuses the oldest slot and would rewrite the captured one's
  * work list. */
@@ -249,7 +250,9 @@ FIRA_API fira_status fira_get_projector(fira_ctx* ctx, int idx, float* host_P);
  *   dev_workspace  device scratch of fira_refresh_workspace_bytes(ctx, count, idx) bytes, 256-byte
  *                  aligned, owned by the caller, free to reuse once the stream has passed this call
  * Enqueues on the context's stream and returns; the small work lists go up in one copy from pinned
- * memory (a call waits for the previous call's upload before it rewrites them).  Uses the listed matrices' step
+ * memory (a call waits for the previous call's upload before it rewrites them).  A HIP graph cannot hold
+ * that upload: while the stream is being captured the call is refused (FIRA_ERR_HIP, nothing enqueued,
+ * every projector as it was).  Uses the listed matrices' step
  * scratch (not their state).  The rounds of the iteration work in the matrices' own operand copies of
  * P: if a launch fails on the way (FIRA_ERR_HIP), the listed matrices are left WITHOUT a projector
  * (fira_step reports FIRA_ERR_NO_PROJECTOR for them until one is installed again); M, V, t and the
@@ -258,9 +261,9 @@ FIRA_API size_t fira_refresh_workspace_bytes(const fira_ctx* ctx, int count, con
 FIRA_API fira_status fira_refresh_projectors(fira_ctx* ctx, int count, const int* idx, const void* const* dev_G,
                                              int iters, uint64_t seed, void* dev_workspace, size_t workspace_bytes);
 
-/* fira_refresh_projectors for callers that cannot allocate device memory (code that runs under a HIP
- * graph capture, tight serving or training loops, harnesses that forbid hipMalloc): the same computation
- * with the same kernels and the same result, but the workspace is a static device array of
+/* fira_refresh_projectors for callers that cannot allocate device memory (tight serving or training
+ * loops, harnesses that forbid hipMalloc): the same computation with the same kernels and the same
+ * result, refused under a graph capture like the other one, but the workspace is a static device array of
  * FIRA_STATIC_SCRATCH_BYTES that is part of the library's code object, so the call performs no device
  * allocation and takes no workspace argument.  FIRA_ERR_WORKSPACE (nothing enqueued) when the listed
  * matrices need more than that (fira_refresh_workspace_bytes tells how much: about 16 MB for a

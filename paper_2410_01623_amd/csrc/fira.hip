@@ -139,6 +139,15 @@ fira_status fail(fira_ctx* ctx, fira_status st, const std::string& msg) {
       return fail(ctx, FIRA_ERR_HIP, std::string(#call) + ": " + hipGetErrorString(e_));        \
   } while (0)
 
+// Refuses a call that cannot be recorded into a HIP graph while the context's stream is being captured (the capture goes
+// on without it).  Asked before the call enqueues or changes anything.
+fira_status refuse_capture(fira_ctx* ctx, const char* what) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  FIRA_HIP(ctx, hipStreamIsCapturing(ctx->stream, &cs));
+  if (cs == hipStreamCaptureStatusNone) return FIRA_OK;
+  return fail(ctx, FIRA_ERR_HIP, std::string(what) + " cannot be captured in a HIP graph");
+}
+
 // lr * alpha lives in device memory and is rewritten in stream order: the value travels as a kernel argument,
 // so no host buffer has to outlive the call.
 hipError_t store_step_size(fira_ctx* ctx) {
@@ -477,7 +486,16 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       if (!ctx->plan.mats[idx[e]].has_projector) return fail(ctx, FIRA_ERR_NO_PROJECTOR, "fira_set_projector was never called for a listed matrix");
     }
   }
+  // Listed matrices whose second gate value this step will measure and read back (FiraScal::gram_err is +inf).
+  const bool only_scaling = ctx->variant == FIRA_VARIANT_ONLY_SCALING;
+  bool any_unmeasured = false, all_unmeasured = true;
+  for (int e = 0; e < count; ++e) {
+    any_unmeasured = any_unmeasured || ctx->unmeasured[idx[e]];
+    all_unmeasured = all_unmeasured && ctx->unmeasured[idx[e]];
+  }
   fira_status st;
+  if (!only_scaling && ctx->norm_mode == FIRA_NORM_GRAM && any_unmeasured &&
+      (st = refuse_capture(ctx, "the first step after a projector was installed")) != FIRA_OK) return st;
   ListSlot* s = acquire_list(ctx, count, idx, dev_W, dev_G, &st);
   if (!s) return fail(ctx, st, "building the work list failed");
   FiraHp hp = make_hp(ctx);
@@ -505,15 +523,12 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       hipLaunchKernelGGL(fira_project_small_kernel, dim3(bl + br), blk, FIRA_PROJ_SMALL_LDS, q, ctx->d_mats, s->d_ents,
                          s->d_tiles[kTilesProjSmallLeft], nl, bl, s->d_tiles[kTilesProjSmallRight], nr, norm_arg, (const FiraScal*)ctx->d_scal, hp);
   };
-  const bool only_scaling = ctx->variant == FIRA_VARIANT_ONLY_SCALING;
   const int want_g2 = (ctx->norm_mode == FIRA_NORM_GRAM || only_scaling) ? 1 : 0;   // ||G_i||^2 per factor
   // Which listed matrices take the Gram route to ||S|| (the kernels apply the same test per matrix: both
   // gate values of FiraScal within FiraHp's tolerances).  A matrix whose second gate value is still to be
   // measured takes the residual route in this step, and the limiter measures it.
   bool need_residual = !only_scaling;
   bool any_gram = false, measures = false;
-  bool all_unmeasured = true;
-  for (int e = 0; e < count; ++e) all_unmeasured = all_unmeasured && ctx->unmeasured[idx[e]];
   if (need_residual && ctx->norm_mode == FIRA_NORM_GRAM && all_unmeasured) {
     measures = true;            // (whatever the first gate value will turn out to be)
   } else if (need_residual && ctx->norm_mode == FIRA_NORM_GRAM) {
@@ -873,6 +888,10 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
                         const RefreshPlan& rp, char* ws) {
   const int nmat = (int)ctx->plan.mats.size();
   hipStream_t q = ctx->stream;
+  // A recorded upload would read the host image below when the graph is replayed, and by then a later call may have
+  // rewritten it for another list and workspace.
+  const fira_status captured = refuse_capture(ctx, "a projector refresh");
+  if (captured != FIRA_OK) return captured;
 
   // Host image of the small tables: everything in front of the packed operands, in one upload from pinned memory, so that
   // nothing here waits for the stream.

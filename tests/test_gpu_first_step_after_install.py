@@ -53,3 +53,49 @@ def test_steps_after_installation_need_no_synchronisation(dtype, r):
     assert ga == gb
     assert all(torch.equal(a, b) for a, b in zip(Wa, Wb))
     assert all(np.isinf(g[1]) for g in seen[0]) and all(np.isfinite(seen[1][i][1]) for i in (0, 1))
+
+
+def test_what_a_graph_cannot_hold_is_refused_under_capture():
+    """A refresh and a first step after an installation are refused while the stream is being captured; the capture goes on
+    without them, replays, and the context goes on as a twin that was never asked."""
+    side = torch.cuda.Stream(device=H.DEV)
+    out = []
+    for ask in (True, False):
+        rng = np.random.default_rng(8)
+        W = [H.to_device(synth.as_bf16_values(0.02 * rng.standard_normal(s)), fira.FIRA_BF16) for s in SHAPES]
+        G = [[H.to_device(synth.as_bf16_values(1e-2 * rng.standard_normal(s)), fira.FIRA_BF16) for s in SHAPES] for _ in range(3)]
+        ctx = fira.FiraContext(SHAPES, 40, fira.FIRA_BF16, device=H.DEV, stream=side)
+        ws = torch.empty(ctx.fira_refresh_workspace_bytes([0, 1, 2]), dtype=torch.uint8, device=H.DEV)
+        x = torch.zeros(64, device=H.DEV)
+
+        def asked(*calls):
+            if not ask:
+                return
+            x.zero_()
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                for call in calls:
+                    with pytest.raises(fira.FiraError) as ei:
+                        call()
+                    assert ei.value.status == fira.FIRA_ERR_HIP and "captured" in str(ei.value)
+                x.add_(1.0)
+            for rep in range(3):
+                graph.replay()
+                torch.cuda.synchronize()
+                assert float(x.sum()) == 64.0 * (rep + 1)
+
+        refresh = lambda: ctx.fira_refresh_projectors([0, 1, 2], G[0], iters=2, seed=3, workspace=ws)
+        refresh_static = lambda: ctx.fira_refresh_projectors_static([0, 1, 2], G[0], iters=2, seed=3)
+        step = lambda: ctx.fira_step([0, 1, 2], W, G[0])
+        asked(refresh, refresh_static)
+        torch.cuda.synchronize()
+        refresh()
+        asked(step, refresh)
+        torch.cuda.synchronize()
+        for g in G:
+            ctx.fira_step([0, 1, 2], W, g)
+        torch.cuda.synchronize()
+        out.append(([w.clone() for w in W], [ctx.fira_get_gate(i) for i in range(3)], [ctx.fira_get_projector(i) for i in range(3)]))
+    assert out[0][1] == out[1][1]
+    assert all(torch.equal(a, b) for k in (0, 2) for a, b in zip(out[0][k], out[1][k]))
