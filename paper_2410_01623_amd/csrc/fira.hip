@@ -255,13 +255,12 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   Plan& p = ctx->plan;
   for (HostMat& h : p.mats) {
     FiraMat& m = h.dev;
-    // offsets were stored in the pointer fields; Gx is null for bf16 matrices and stays null
+    // offsets were stored in the pointer fields
     m.M = (float*)(ctx->slab + (size_t)m.M); m.V = (float*)(ctx->slab + (size_t)m.V);
     m.Rt = (float*)(ctx->slab + (size_t)m.Rt); m.phi = (float*)(ctx->slab + (size_t)m.phi);
     m.g2 = (float*)(ctx->slab + (size_t)m.g2); m.q = (float*)(ctx->slab + (size_t)m.q);
     m.Nb = (bf16_raw*)(ctx->slab + (size_t)m.Nb); m.Rb = (bf16_raw*)(ctx->slab + (size_t)m.Rb);
     m.Pn = (bf16_raw*)(ctx->slab + (size_t)m.Pn); m.PT = (bf16_raw*)(ctx->slab + (size_t)m.PT);
-    if (m.kx > 1) m.Gx = (bf16_raw*)(ctx->slab + (size_t)m.Gx);
   }
   ctx->d_mats = (FiraMat*)(ctx->slab + p.off_mats);
   ctx->d_scal = (FiraScal*)(ctx->slab + p.off_scal);

@@ -26,6 +26,7 @@ typedef f32x4 __attribute__((aligned(4))) f32x4_a4;
 // projector operands use sequence B; position p of A meets position p of B in the contraction.
 //   A: h h m h l m        B: h m h l h m
 #define FIRA_KX_SPLIT 6
+#define FIRA_SPLIT_PLANES 3   // planes that the data operands store (the sequences repeat them)
 #define FIRA_ZREADY_MAX_R 1024
 #define FIRA_ZREADY_MAX_R_F32 512   // fp32 rows have three planes: 48 KB of LDS for sixteen of them
 
@@ -36,7 +37,6 @@ struct FiraMat {
   int L, S;            // long side max(m,n) (number of factors), short side min(m,n)
   int rp, Sp;          // rank and short side rounded up to 64 (zero padded operand rows)
   int kx, dtype;       // K-expansion (1: bf16, 6: fp32 split); dtype of W and G (0 f32, 1 bf16)
-  long long gx_ld;     // leading dimension of Gx
   // The library's own bf16 operand arrays are stored K-blocked, [K/32][rows][32]: the 32 k of one
   // row are 64 contiguous bytes and consecutive rows follow each other, so the 16 rows x 32 k that
   // one LDS-direct load instruction moves are 1 KB of contiguous memory (see kblk_index).  Row
@@ -55,14 +55,12 @@ struct FiraMat {
   float* phi;          // [L]      scaling factors k_i of this step
   float* g2;           // [L]      ||G_i||^2 (Gram mode)
   float* q;            // [L]      k_i^2 (||G_i||^2 - ||R_i||^2), the terms of ||S||^2 (Gram mode)
-  // fp32 matrices store the three planes h, m, l of Nb and Rb; the contraction runs over them in sequence A
-  bf16_raw* Nb;        // [kx*rp/32][Lq][32] Z = N - c k_i R_i of this step (MFMA operand); bf16 matrices have room for a
-                       // second plane of K blocks, Z's rounding remainder, used when FiraHp::zsplit is set
-  bf16_raw* Rb;        // [kx*rp/32][Lq][32] R of this step as MFMA operand (residual route)
+  bf16_raw* Nb;        // [planes*rp/32][Lq][32] Z = N - c k_i R_i of this step (MFMA operand).  fp32 matrices: the planes h, m, l,
+                       // over which the contraction runs in sequence A; bf16 matrices: one plane, and room for a
+                       // second one, Z's rounding remainder, used when FiraHp::zsplit is set
+  bf16_raw* Rb;        // [planes*rp/32][Lq][32] R of this step as MFMA operand (residual route): h, m, l, or one plane (bf16)
   bf16_raw* Pn;        // [kx*rp/32][Sq][32] projector, rank along K (operand of the back-projection)
   bf16_raw* PT;        // [kx*Sp/32][rq][32] projector transposed, short side along K (operand of R)
-  bf16_raw* Gx;        // fp32 matrices: room for a split copy of G ([kx*Sp][gx_ld] if left, [m][gx_ld] else); no kernel uses it,
-                       // the projection splits the gradient on its way through registers
 };
 
 // Element (row, k) of a K-blocked operand with `rows` (padded) rows.

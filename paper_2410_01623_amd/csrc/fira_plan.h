@@ -21,13 +21,6 @@ constexpr int kSlots = 4;  // cached work lists (a training loop alternates betw
 
 inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }
 inline int round_up_int(long long x, int a) { return (int)((x + a - 1) / a * a); }
-// Row pitch (bf16 elements) for an operand row of k values: a whole number of 256-byte L2-channel
-// lines, and an odd number of them, so that consecutive rows walk through all sixteen channels.
-inline int operand_pitch(long long k) {
-  long long lines = (k * 2 + 255) / 256;
-  if (lines % 2 == 0) ++lines;
-  return (int)(lines * 128);
-}
 
 // Workgroups of the kernel that makes a projector's operand copies: tiles of 32 (short side) x 64 (rank).
 inline int prep_tiles(int S, int r) { return ((S + 31) / 32) * ((r + 63) / 64); }
@@ -94,7 +87,6 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     m.zready = ((m.r & 3) == 0 && m.r <= (m.kx == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32)) ? 1 : 0;
     if (m.zready && m.kx != 1) plan->adam_lds_f32 = std::max(plan->adam_lds_f32, FIRA_ROWS_PER_WG * m.rp * 6);
     if (m.zready && m.kx == 1) plan->adam_lds = std::max(plan->adam_lds, FIRA_ROWS_PER_WG * m.rp * 2);   // (twice that with Z in two planes)
-    m.gx_ld = m.left ? round_up_int(m.n, 8) : operand_pitch((long long)m.kx * m.Sp);
     const size_t Lr = (size_t)m.L * m.r;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     m.M = (float*)take(Lr * 4);
@@ -103,14 +95,10 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     m.phi = (float*)take((size_t)m.L * 4);
     m.g2 = (float*)take((size_t)m.L * 4);
     m.q = (float*)take((size_t)m.L * 4);
-    m.Nb = (bf16_raw*)take((size_t)m.Lq * (m.kx == 1 ? 2 : m.kx) * m.rp * 2);   // bf16 matrices: room for the hi + lo form of Z
-    m.Rb = (bf16_raw*)take((size_t)m.Lq * m.kx * m.rp * 2);
+    m.Nb = (bf16_raw*)take((size_t)m.Lq * (m.kx == 1 ? 2 : FIRA_SPLIT_PLANES) * m.rp * 2);   // bf16 matrices: room for the hi + lo form of Z
+    m.Rb = (bf16_raw*)take((size_t)m.Lq * (m.kx == 1 ? 1 : FIRA_SPLIT_PLANES) * m.rp * 2);
     m.Pn = (bf16_raw*)take((size_t)m.Sq * m.kx * m.rp * 2);
     m.PT = (bf16_raw*)take((size_t)m.rq * m.kx * m.Sp * 2);
-    if (m.kx > 1) {
-      const size_t gx = m.left ? (size_t)m.kx * m.Sp * m.gx_ld : (size_t)m.m * m.gx_ld;
-      m.Gx = (bf16_raw*)take(gx * 2);
-    }
     h.ta_project = (m.L + FIRA_PA - 1) / FIRA_PA; h.tb_project = (m.r + FIRA_PB - 1) / FIRA_PB;
     h.ta_back = (m.n + FIRA_BA - 1) / FIRA_BA;    h.tb_back = (m.m + FIRA_BB - 1) / FIRA_BB;
     h.tiles_project = h.ta_project * h.tb_project;

@@ -27,7 +27,14 @@ int failures = 0;
 
 struct Piece { size_t off, bytes; const char* what; int mat; };
 
-void check_pieces(std::vector<Piece> pieces, size_t total, const char* where) {
+// Every piece aligned, inside the total and disjoint from the others; with `whole`, nothing in the total but the pieces
+// and the padding to their alignment.
+void check_pieces(std::vector<Piece> pieces, size_t total, const char* where, bool whole = false) {
+  if (whole) {
+    size_t used = 0;
+    for (const Piece& p : pieces) used += p.bytes;
+    CHECK(total <= used + 512 * pieces.size(), "%s: %zu of %zu bytes belong to no piece", where, total - used, total);
+  }
   std::sort(pieces.begin(), pieces.end(), [](const Piece& a, const Piece& b) { return a.off < b.off; });
   for (size_t i = 0; i < pieces.size(); ++i) {
     const Piece& p = pieces[i];
@@ -93,17 +100,11 @@ void check_plan(const std::vector<fira_matrix_desc>& descs, std::mt19937_64& rng
     pieces.push_back({(size_t)m.g2, (size_t)m.L * 4, "g2", i});
     pieces.push_back({(size_t)m.q, (size_t)m.L * 4, "q", i});
     // operands: whole tiles of rows (what the ring loaders of the contraction kernels fetch), K padded to 64
-    pieces.push_back({(size_t)m.Nb, (size_t)m.Lq * m.kx * m.rp * 2, "Nb", i});
-    pieces.push_back({(size_t)m.Rb, (size_t)m.Lq * m.kx * m.rp * 2, "Rb", i});
+    // (Z: h, m, l for fp32 matrices, hi and lo for bf16 ones; R: h, m, l or one plane)
+    pieces.push_back({(size_t)m.Nb, (size_t)m.Lq * (m.kx > 1 ? 3 : 2) * m.rp * 2, "Nb", i});
+    pieces.push_back({(size_t)m.Rb, (size_t)m.Lq * (m.kx > 1 ? 3 : 1) * m.rp * 2, "Rb", i});
     pieces.push_back({(size_t)m.Pn, (size_t)m.Sq * m.kx * m.rp * 2, "Pn", i});
     pieces.push_back({(size_t)m.PT, (size_t)m.rq * m.kx * m.Sp * 2, "PT", i});
-    if (m.kx > 1) {
-      CHECK(m.gx_ld >= (m.left ? m.n : (long long)m.kx * m.Sp), "matrix %d: pitch of the split gradient", i);
-      const size_t gx = m.left ? (size_t)m.kx * m.Sp * m.gx_ld : (size_t)m.m * m.gx_ld;
-      pieces.push_back({(size_t)m.Gx, gx * 2, "Gx", i});
-    } else {
-      CHECK(m.Gx == nullptr, "matrix %d: bf16 matrices have no split gradient", i);
-    }
     CHECK(h.ta_project == (m.L + FIRA_PA - 1) / FIRA_PA && h.tb_project == (m.r + FIRA_PB - 1) / FIRA_PB, "matrix %d: projection tiles", i);
     CHECK(h.ta_back == (m.n + FIRA_BA - 1) / FIRA_BA && h.tb_back == (m.m + FIRA_BB - 1) / FIRA_BB, "matrix %d: back-projection tiles", i);
     // the last tile's operand rows must exist (zero padding): rows are padded to whole tiles
@@ -126,7 +127,7 @@ void check_plan(const std::vector<fira_matrix_desc>& descs, std::mt19937_64& rng
   pieces.push_back({plan.off_install, sizeof(FiraRefreshEnt) * (size_t)count, "installation table", -1});
   pieces.push_back({plan.off_dyn, 4, "step size", -1});
   for (int k = 0; k < kSlots; ++k) pieces.push_back({plan.off_slots + plan.slot_bytes * k, plan.slot_bytes, "work-list slot", k});
-  check_pieces(pieces, plan.total, "slab");
+  check_pieces(pieces, plan.total, "slab", true);
 
   // ---- a step's work list over a random subset, in random order, in a block of exactly slot_bytes
   std::vector<int> idx(count);
