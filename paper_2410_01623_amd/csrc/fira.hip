@@ -64,7 +64,7 @@ struct ListSlot {
   std::vector<void*> W;
   std::vector<const void*> G;
   int ntiles[kNumTileLists] = {};
-  int rowblocks = 0, g2blocks = 0;
+  int rowblocks = 0;
   // device views (inside the slab)
   FiraEnt* d_ents = nullptr;
   FiraTile* d_tiles[kNumTileLists] = {};
@@ -210,7 +210,7 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
   s->W.assign(W, W + count);
   s->G.assign(G, G + count);
   const Plan& p = ctx->plan;
-  build_work_list(p, count, idx, W, G, s->h_stage, s->ntiles, &s->rowblocks, &s->g2blocks);
+  build_work_list(p, count, idx, W, G, s->h_stage, s->ntiles, &s->rowblocks);
   if (hipMemcpyAsync(s->d_block, s->h_stage, p.slot_bytes, hipMemcpyHostToDevice, ctx->stream) != hipSuccess ||
       hipEventRecord(s->uploaded, ctx->stream) != hipSuccess) { *st = FIRA_ERR_HIP; return nullptr; }
   s->valid = true;

@@ -92,8 +92,6 @@ struct FiraEnt {
   int part0;        // first partial-sum slot of this entry
   int npart;        // number of partial-sum slots
   int row0;         // first row-block (elementwise kernels) of this entry
-  int g2b0;         // first block of the ||G_i||^2 kernel of this entry
-  int pad;
   void* W;
   const void* G;
 };
@@ -144,7 +142,6 @@ __device__ __forceinline__ bool calibrates_gram(const FiraHp& hp, const FiraScal
 #define FIRA_BA 256          // rank-axis contractions (back-projection): tile rows on the A side (n)
 #define FIRA_BB 128          // ... and on the B side (m)
 #define FIRA_ROWS_PER_WG 16  // Adam pass: 4 wavefronts x 4 rows
-#define FIRA_G2_ROWS_PER_WG 32   // ||G_i||^2 kernel, right orientation: rows per workgroup (8 per wavefront)
 #define FIRA_FUSE_MAX_R 512  // largest rank of the fused projection/Adam kernel
 #define FIRA_FUSE_MIN_R 128  // below half a rank tile its epilogue works mostly on padding; the two-kernel path is faster
 #define FIRA_ORTHO_SPLITS 64 // workgroups of the orthonormality estimate's second phase

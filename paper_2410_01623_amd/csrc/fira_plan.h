@@ -33,7 +33,6 @@ struct HostMat {
   int tiles_back = 0;         // tiles of the back-projection (and of the residual-norm pass)
   int ta_project = 0, tb_project = 0, ta_back = 0, tb_back = 0;
   int rowblocks = 0;
-  int g2blocks = 0;           // blocks of the ||G_i||^2 kernel
   int fuse_list = -1;         // tile list of the fused projection/Adam kernel, or -1 if the matrix cannot take it
   bool small_proj = false;    // bf16 with r <= 64: projected by the small-rank kernel
 };
@@ -104,7 +103,6 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     h.tiles_project = h.ta_project * h.tb_project;
     h.tiles_back = h.ta_back * h.tb_back;
     h.rowblocks = (m.L + FIRA_ROWS_PER_WG - 1) / FIRA_ROWS_PER_WG;
-    h.g2blocks = m.left ? (m.n + 255) / 256 : (m.m + FIRA_G2_ROWS_PER_WG - 1) / FIRA_G2_ROWS_PER_WG;
     total_tiles[m.left ? kTilesProjectLeft : kTilesProjectRight] += h.tiles_project;
     h.small_proj = m.kx == 1 && m.r <= FIRA_PS;
     total_tiles[(h.small_proj ? kTilesProjSmallLeft : kTilesProjBigLeft) + (m.left ? 0 : 1)] += h.tiles_project;
@@ -150,19 +148,18 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
 // `stage` (Plan::slot_bytes bytes: the entries, then the tile lists at Plan::slot_off_tiles).  ntiles[l] =
 // tiles written to list l.
 void build_work_list(const Plan& p, int count, const int* idx, void* const* W, const void* const* G, char* stage,
-                     int (&ntiles)[kNumTileLists], int* rowblocks_out, int* g2blocks_out) {
+                     int (&ntiles)[kNumTileLists], int* rowblocks_out) {
   FiraEnt* ents = reinterpret_cast<FiraEnt*>(stage);
   FiraTile* tl[kNumTileLists];
   int nt[kNumTileLists] = {};
   for (int l = 0; l < kNumTileLists; ++l) tl[l] = reinterpret_cast<FiraTile*>(stage + p.slot_off_tiles[l]);
-  int nparts = 0, rowblocks = 0, g2blocks = 0;
+  int nparts = 0, rowblocks = 0;
   for (int e = 0; e < count; ++e) {
     const HostMat& h = p.mats[idx[e]];
     FiraEnt& en = ents[e];
-    en.mat = idx[e]; en.part0 = nparts; en.npart = h.tiles_back; en.row0 = rowblocks; en.g2b0 = g2blocks; en.pad = 0;
+    en.mat = idx[e]; en.part0 = nparts; en.npart = h.tiles_back; en.row0 = rowblocks;
     en.W = W[e]; en.G = G[e];
     rowblocks += h.rowblocks;
-    g2blocks += h.g2blocks;
     // R contraction: rank tiles innermost, so the tiles that share a panel of G are neighbours
     const int lp = h.dev.left ? kTilesProjectLeft : kTilesProjectRight;
     for (int ta = 0; ta < h.ta_project; ++ta)
@@ -181,7 +178,6 @@ void build_work_list(const Plan& p, int count, const int* idx, void* const* W, c
   }
   for (int l = 0; l < kNumTileLists; ++l) ntiles[l] = nt[l];
   *rowblocks_out = rowblocks;
-  *g2blocks_out = g2blocks;
 }
 
 struct RefreshPlan {

@@ -138,14 +138,14 @@ void check_plan(const std::vector<fira_matrix_desc>& descs, std::mt19937_64& rng
   std::vector<void*> W(listed);
   std::vector<const void*> G(listed);
   for (int e = 0; e < listed; ++e) { W[e] = (void*)(uintptr_t)(0x1000 + 16 * e); G[e] = (const void*)(uintptr_t)(0x2000 + 16 * e); }
-#ifdef FIRA_PLAN_CHECK_SHORT_STAGE   // planted mistake for the test of this check: the block is too small
-  char* stage = (char*)std::malloc(plan.slot_bytes / 8 + 1);
+#ifdef FIRA_PLAN_CHECK_SHORT_STAGE   // planted mistake for the test of this check: the block ends inside the last entry
+  char* stage = (char*)std::malloc(sizeof(FiraEnt) * (size_t)listed - 1);
 #else
   char* stage = (char*)std::malloc(plan.slot_bytes ? plan.slot_bytes : 1);
 #endif
   int ntiles[kNumTileLists] = {};
-  int rowblocks = 0, g2blocks = 0;
-  build_work_list(plan, listed, idx.data(), W.data(), G.data(), stage, ntiles, &rowblocks, &g2blocks);
+  int rowblocks = 0;
+  build_work_list(plan, listed, idx.data(), W.data(), G.data(), stage, ntiles, &rowblocks);
   std::vector<Piece> sp;
   sp.push_back({0, sizeof(FiraEnt) * (size_t)listed, "entries", -1});
   for (int l = 0; l < kNumTileLists; ++l) {
@@ -154,14 +154,14 @@ void check_plan(const std::vector<fira_matrix_desc>& descs, std::mt19937_64& rng
   }
   check_pieces(sp, plan.slot_bytes, "work-list slot");
   const FiraEnt* ents = reinterpret_cast<const FiraEnt*>(stage);
-  int rb = 0, g2b = 0, np = 0;
+  int rb = 0, np = 0;
   for (int e = 0; e < listed; ++e) {
     const HostMat& h = plan.mats[idx[e]];
     CHECK(ents[e].mat == idx[e] && ents[e].W == W[e] && ents[e].G == G[e], "entry %d", e);
-    CHECK(ents[e].row0 == rb && ents[e].g2b0 == g2b && ents[e].part0 == np && ents[e].npart == h.tiles_back, "entry %d: prefix sums", e);
-    rb += h.rowblocks; g2b += h.g2blocks; np += h.tiles_back;
+    CHECK(ents[e].row0 == rb && ents[e].part0 == np && ents[e].npart == h.tiles_back, "entry %d: prefix sums", e);
+    rb += h.rowblocks; np += h.tiles_back;
   }
-  CHECK(rb == rowblocks && g2b == g2blocks, "row-block totals");
+  CHECK(rb == rowblocks, "row-block totals");
   // coverage: every (entry, ta, tb) of each grid exactly once; partial slots unique and inside the entry's range
   for (int l = 0; l < kNumTileLists; ++l) {
     const FiraTile* tl = reinterpret_cast<const FiraTile*>(stage + plan.slot_off_tiles[l]);
