@@ -4,6 +4,7 @@ next one), leading dimensions, and matrices too small for a 16-byte load.  Again
 of the fp32 stages (sums of products that are exact to 2^-24, 1e-5 of the largest entry)."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import fira_oracle as orc
 from paper_2410_01623_amd import fira, synth
@@ -19,6 +20,7 @@ CASES = [
     (96, 131, 96, 131), (131, 99, 99, 102),          # full rank; a last group of three along either side
     (161, 385, 129, 388), (385, 162, 128, 163),      # large rank tile by one; r on the edge of the middle one
     (300, 333, 257, 333), (333, 301, 300, 301),      # two rank tiles
+    (600, 700, 512, 701), (700, 600, 516, 603),      # largest rank of the register-resident Adam rows, and the first past it
     (31, 40, 5, 40), (33, 32, 7, 35),                # a single block of k; one and a remainder of one
     (5, 6, 2, 9), (4, 4, 3, 4), (3, 3, 1, 3), (2, 70, 2, 71), (70, 3, 2, 3), (1, 130, 1, 130),
 ]
@@ -44,3 +46,32 @@ def test_fp32_step_at_the_edges(m, n, r, ld, norm):
     assert res.worst["k"] <= (1e-5 if r >= 32 else 1e-4)
     if r < S:                       # at full rank S is what rounding leaves of it
         assert res.c_min < 1.0 and res.worst["s_pre"] <= 1e-4 and res.worst["c"] <= 1e-4
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")], ids=["nan", "inf"])
+@pytest.mark.parametrize("m,n,r,ld", [(130, 259, 65, 261), (259, 130, 65, 131), (96, 161, 32, 161), (161, 99, 99, 99)],
+                         ids=["130x259r65", "259x130r65", "96x161r32", "161x99r99"])
+def test_fp32_non_finite_gradient_stays_in_its_factor(m, n, r, ld, bad):
+    """One non-finite entry in the last row and column, whose loads are shared with the padding past both: its factor
+    becomes non-finite, the others stay finite, a second matrix of the same call is bit for bit what it is without it."""
+    rng = np.random.default_rng(31 * m + n)
+    W0 = H.to_device((0.02 * rng.standard_normal((m, n))).astype(np.float32), fira.FIRA_F32, ld)
+    P = H.to_device(synth.store_projector(np.linalg.qr(rng.standard_normal((min(m, n), r)))[0], "f32").astype(np.float32), fira.FIRA_F32)
+    Gs = [H.to_device((1e-2 * rng.standard_normal((m, n))).astype(np.float32), fira.FIRA_F32, ld) for _ in range(3)]
+    out = []
+    for poison in (False, True):
+        ctx = fira.FiraContext([(m, n)] * 2, r, fira.FIRA_F32, device=H.DEV, lds=[ld] * 2)
+        ctx.fira_set_projectors([0, 1], [P, P])
+        buf = [W0.as_strided((m, ld), (ld, 1)).clone() for _ in range(2)]
+        W = [b[:, :n] for b in buf]
+        for s, g in enumerate(Gs):
+            b = g.as_strided((m, ld), (ld, 1)).clone()[:, :n]
+            if poison and s == 1:
+                b[m - 1, n - 1] = bad
+            ctx.fira_step([0, 1], W, [b, g])
+            torch.cuda.synchronize()
+        out.append(W)
+    assert torch.equal(out[0][1], out[1][1])
+    w = out[1][0]
+    own, others = (w[:, n - 1], w[:, :n - 1]) if m <= n else (w[m - 1], w[:m - 1])
+    assert not torch.isfinite(own).any() and torch.isfinite(others).all() and torch.isfinite(out[0][0]).all()

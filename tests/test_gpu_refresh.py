@@ -25,12 +25,14 @@ def _gapped_gradient(rng, m, n, r, tail=0.05):
 
 
 @pytest.mark.parametrize("m,n,r", [(300, 517, 40), (517, 300, 40), (256, 256, 64), (1024, 2736, 128), (2736, 1024, 128),
-                                   (330, 650, 200), (2048, 5461, 512), (5461, 2048, 512)],
+                                   (330, 650, 200), (2048, 5461, 512), (5461, 2048, 512),
+                                   (330, 650, 131), (650, 331, 131), (700, 900, 610), (900, 700, 610)],
                          ids=["300x517r40", "517x300r40", "256x256r64", "1024x2736r128", "2736x1024r128", "330x650r200",
-                              "2048x5461r512", "5461x2048r512"])
+                              "2048x5461r512", "5461x2048r512", "330x650r131", "650x331r131", "700x900r610", "900x700r610"])
 def test_refreshed_projector_spans_the_leading_singular_subspace(m, n, r):
-    """(The last two cases are the headline workload's rectangular shapes at its rank, the configuration whose
-    refresh bench.py times.)"""
+    """(2048 x 5461 at r = 512 are the headline workload's rectangular shapes at its rank, the configuration whose
+    refresh bench.py times; an odd rank above 64 takes the solve's element-wise loads; at r = 610 the first panels of
+    the Cholesky factorisation do not fit in LDS, the later ones do, and the last block is a partial one.)"""
     rng = np.random.default_rng(1000 + m + n)
     G = _gapped_gradient(rng, m, n, r)
     ctx = fira.FiraContext([(m, n)], r, fira.FIRA_BF16, device=H.DEV)
@@ -154,7 +156,7 @@ def test_refresh_argument_errors():
 
 @pytest.mark.parametrize("m,n,r", [(256, 688, 64), (688, 256, 64), (100, 333, 24)], ids=["256x688r64", "688x256r64", "100x333r24"])
 def test_refresh_of_fp32_matrices(m, n, r):
-    """fp32 matrices: the way there runs on the split planes of G (as a step does), the way back on a bf16
+    """fp32 matrices: the way there runs on G itself, split in registers as in a step, the way back on a bf16
     rounding of G, the orthonormalisation in fp64; the installed projector is orthonormal to fp32 accuracy,
     spans the leading subspace, and is the one the following steps use (10 steps against the oracle, to the
     fp32 gate).  A list that mixes an fp32 and a bf16 matrix goes through one call."""
