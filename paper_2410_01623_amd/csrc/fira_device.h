@@ -143,7 +143,11 @@ __device__ __forceinline__ bool calibrates_gram(const FiraHp& hp, const FiraScal
 #define FIRA_BB 128          // ... and on the B side (m)
 #define FIRA_ROWS_PER_WG 16  // Adam pass: 4 wavefronts x 4 rows
 #define FIRA_FUSE_MAX_R 512  // largest rank of the fused projection/Adam kernel
-#define FIRA_FUSE_MIN_R 128  // below half a rank tile its epilogue works mostly on padding; the two-kernel path is faster
+// Smallest rank of the fused kernel.  The line is the interface's, not speed's: below it every step leaves a copy of R for
+// fira_get_lowrank.  Measured with the line at 68, the fused kernel is the faster one there too (a step at r = 96: 91 us
+// against 111 with two kernels over 8 blocks of 512 x 1376, 654 against 785 over 24 of 1024 x 2736, 2345 against 2580 over 24
+// of 2048 x 5461; the same share at 68 and 124); at 128 it is 96 against 113, 673 against 802 and 2375 against 2608.
+#define FIRA_FUSE_MIN_R 128
 #define FIRA_ORTHO_SPLITS 64 // workgroups of the orthonormality estimate's second phase
 #define FIRA_SOLVE_JB 64     // projector refresh: column block of the triangular solve
 

@@ -507,8 +507,9 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 __device__ __forceinline__ int split_b(int t) { return (t & 3) | ((t >> 5) << 2); }
 __device__ __forceinline__ int split_kq(int t) { return (t >> 2) & 7; }
 
-// The lane number, formed anew at each call: the multiply loops leave no registers for addresses that would be
-// kept from one block to the next, and one reloaded from scratch would wait for every load in flight.
+// The lane number, formed anew at each call, so that no address made from it is kept from one block to the next: one
+// reloaded from scratch waits for every load in flight.  Kept, the fp32 update spills 41 registers instead of 15 and the fp32
+// norm pass 23 instead of 7; the fp32 projection takes 204 registers instead of 188 and spills none either way.
 __device__ __forceinline__ int fresh_lane() {
   unsigned zero = 0;
   asm volatile("" : "+s"(zero));

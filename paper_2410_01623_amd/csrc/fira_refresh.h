@@ -178,8 +178,9 @@ __device__ __forceinline__ bool refresh_pass_done(const FiraRefreshEnt& e) { ret
 
 // In-place Cholesky factorisation of the lower triangle of C (fp64), one workgroup per matrix, blocked by 32
 // columns: factor the diagonal block, solve the panel below it one row per thread, update the trailing triangle from
-// the panel.  A pivot that is not safely positive (Y numerically rank deficient) is replaced by a small multiple of
-// the largest diagonal entry, which keeps the factor finite; the directions it affects carry no energy of G.
+// the panel.  A pivot that is not safely positive is replaced by a small multiple of the largest diagonal entry.  That
+// carries a Y that is deficient by rounding, not one whose gradient has a numerical rank below r: the rounding left of
+// the missing directions, divided by such pivots, grows from panel to panel and can end in a basis of NaNs.
 //
 // What bounds it is the chain of dependent steps of one panel, not its arithmetic, so both triangular parts work in
 // registers: the diagonal block with one row per lane and the column's entries handed round by lane reads, the panel
