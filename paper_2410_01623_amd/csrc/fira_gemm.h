@@ -482,8 +482,8 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 // LDS tile.  The six plane products run one after the other over the whole contraction, the largest first (sequences A
 // and B): what the small ones add meets a sum that is already whole, and is rounded at the size of the result, where
 // all six taken together per block of k round six times as often at the size of the running sum (twice the error of R
-// where it cancels).  So G is read six times, from the memory-side cache as far as it holds it; that and the
-// latency of a stage bound the kernel, and it still takes about half of what the way through memory took (six
+// where it cancels).  So G is read six times (8.2 GB through the fabric where G is 1.2, measured at the size below); that and the
+// latency of a stage, whose operands were requested one stage earlier, bound the kernel, and it still takes about half of what the way through memory took (six
 // planes written, read back, and a pass of its own for ||G_i||^2, which falls out of the first product here): 1808 us over
 // the 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256, against 1361 + 1123 + 918; one 256 x 688 matrix at r = 64:
 // 45 us against 5 + 60 + 30.  (Sums of all six products per block of 32 k, apart from the running sum: 930 us and a quarter
