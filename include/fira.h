@@ -56,7 +56,8 @@ typedef enum {
   FIRA_ERR_NO_PROJECTOR = -3, /* fira_step on a matrix whose projector was never set            */
   FIRA_ERR_DTYPE = -4,        /* unsupported dtype combination                                  */
   FIRA_ERR_WORKSPACE = -5,    /* dev_state_bytes too small or slab misaligned (256 B)           */
-  FIRA_ERR_HIP = -6           /* a HIP runtime call or kernel launch failed                     */
+  FIRA_ERR_HIP = -6           /* a HIP runtime call or kernel launch failed, or the stream is being
+                                 captured and the call cannot be recorded                        */
 } fira_status;
 
 typedef enum { FIRA_F32 = 0, FIRA_BF16 = 1 } fira_dtype;
