@@ -512,10 +512,10 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
     if (nl + nr && s->ntiles[kTilesBackBf16])
       hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), blk, FIRA_PROJ_LDS, q, ctx->d_mats, s->d_ents,
-                         s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, (const FiraScal*)ctx->d_scal, hp);
+                         s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, 0, (const FiraScal*)ctx->d_scal, hp);
     if (nl + nr && s->ntiles[kTilesBackF32])
       hipLaunchKernelGGL(fira_fp32_project_kernel, dim3(bl + br), blk, FIRA_SPLIT_LDS, q, ctx->d_mats, s->d_ents,
-                         s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg);
+                         s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, 0);
     nl = s->ntiles[kTilesProjSmallLeft]; nr = s->ntiles[kTilesProjSmallRight];
     bl = (nl + 7) / 8 * 8; br = (nr + 7) / 8 * 8;
     if (nl + nr)
@@ -825,12 +825,6 @@ size_t fira_refresh_workspace_bytes(const fira_ctx* ctx, int count, const int* i
 
 namespace {
 
-// 16-byte pieces [0, n16) of p set to zero (a kernel rather than hipMemsetAsync, so that it is an ordinary
-// kernel node wherever the stream's work is recorded).
-__global__ __launch_bounds__(256) void fira_zero_fill_kernel(u32x4* __restrict__ p, size_t n16) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)gridDim.x * 256) p[i] = u32x4{0u, 0u, 0u, 0u};
-}
-
 // Argument checks shared by the two refresh entry points; on success *rp is the workspace layout.
 fira_status refresh_check(fira_ctx* ctx, int count, const int* idx, const void* const* dev_G, int iters, RefreshPlan* rp) {
   const int nmat = (int)ctx->plan.mats.size();
@@ -904,13 +898,12 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   FiraMat* vmats = (FiraMat*)(ctx->h_refresh + rp.off_vmats);
   FiraEnt* vents = (FiraEnt*)(ctx->h_refresh + rp.off_vents);
   FiraTile* vtiles[2] = {(FiraTile*)(ctx->h_refresh + rp.off_vtiles[0]), (FiraTile*)(ctx->h_refresh + rp.off_vtiles[1])};
-  int max_S = 0, max_r = 0, max_Lp = 0;
+  int max_S = 0, max_r = 0;
   for (int e = 0; e < count; ++e) {
     const FiraMat& m = ctx->plan.mats[idx[e]].dev;
     FiraRefreshEnt& re = ents[e];
     std::memset(&re, 0, sizeof(re));
     re.S = m.S; re.L = m.L; re.r = m.r; re.left = m.left; re.Lp = round_up_int(m.L, 64); re.rq = m.rq; re.mat = idx[e];
-    re.T = m.Rt;
     re.Top = (bf16_raw*)(ws + rp.off_top[e]);
     re.Y = (float*)(ws + rp.off_y[e]);
     re.Q = (float*)(ws + rp.off_q[e]);
@@ -921,7 +914,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     // ... which is left out for a matrix whose basis is orthonormal already, to the accuracy its storage can hold
     ents2[e].done = (int*)(ws + rp.off_done) + e;
     ents2[e].done_tol = m.kx == 1 ? 1e-4f : 1e-6f;
-    max_S = std::max(max_S, m.S); max_r = std::max(max_r, m.r); max_Lp = std::max(max_Lp, re.Lp);
+    max_S = std::max(max_S, m.S); max_r = std::max(max_r, m.r);
     // The way back, Y[s][a] = sum_i G(s, i) T[i][a], is the projection kernel on the other orientation
     // of the same gradient: long side L' = S, contraction over S' = L, operand "PT" = Top, output "Rt" = Y.
     FiraMat& v = vmats[e];
@@ -943,11 +936,6 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   FIRA_HIP(ctx, hipMemcpyAsync(ws, ctx->h_refresh, rp.top_begin, hipMemcpyHostToDevice, q));
   FIRA_HIP(ctx, hipEventRecord(ctx->refresh_event, q));
   ctx->refresh_pending = true;
-  {   // padding rows of the packed operand must read as zero (the workspace keeps whatever it held before)
-    const size_t n16 = (rp.top_end - rp.top_begin) / 16;
-    const unsigned grid = (unsigned)std::min<size_t>((n16 + 255) / 256, 8192);
-    if (n16) hipLaunchKernelGGL(fira_zero_fill_kernel, dim3(grid), dim3(256), 0, q, reinterpret_cast<u32x4*>(ws + rp.top_begin), n16);
-  }
 
   for (int e = 0; e < count; ++e) {   // fp32 matrices: a bf16 rounding for the way back
     const FiraMat& m = ctx->plan.mats[idx[e]].dev;
@@ -963,11 +951,11 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   const FiraMat* d_vmats = (const FiraMat*)(ws + rp.off_vmats);
   const FiraEnt* d_vents = (const FiraEnt*)(ws + rp.off_vents);
 
-  // the forward product uses the step's own work-list machinery (W is not touched by the projection)
-  std::vector<void*> fakeW(count);
-  for (int e = 0; e < count; ++e) fakeW[e] = const_cast<void*>(dev_G[e]);
+  // the way there uses the step's own work-list machinery, with the packed operand it writes in the place of W
+  std::vector<void*> top(count);
+  for (int e = 0; e < count; ++e) top[e] = ws + rp.off_top[e];
   fira_status st;
-  ListSlot* s = acquire_list(ctx, count, idx, fakeW.data(), dev_G, &st);
+  ListSlot* s = acquire_list(ctx, count, idx, top.data(), dev_G, &st);
   if (!s) return fail(ctx, st, "building the work list failed");
 
   {
@@ -989,25 +977,23 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
       hipLaunchKernelGGL(fira_refresh_solve_kernel, dim3((max_S + 63) / 64, count), dim3(256), FIRA_SOLVE_LDS, q, de, J);
   };
   const FiraHp refresh_hp = make_hp(ctx);   // (mixed = 0: the projection kernel serves every listed matrix)
-  auto launch_project = [&](const FiraMat* mats, const FiraEnt* ents_d, const FiraTile* tl, int nl, const FiraTile* tr, int nr, bool bf16, bool fp32) {
+  auto launch_project = [&](const FiraMat* mats, const FiraEnt* ents_d, const FiraTile* tl, int nl, const FiraTile* tr, int nr, bool bf16, bool fp32, int pack) {
     const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
     if (nl + nr && bf16)
-      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_PROJ_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0,
+      hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_PROJ_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0, pack,
                          (const FiraScal*)ctx->d_scal, refresh_hp);
     if (nl + nr && fp32)
-      hipLaunchKernelGGL(fira_fp32_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_SPLIT_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0);
+      hipLaunchKernelGGL(fira_fp32_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_SPLIT_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0, pack);
   };
   for (int it = 0; it < iters; ++it) {
     // operands of Q (the fp32 Q becomes the matrix's projector copies; no gate estimate needed here)
     hipLaunchKernelGGL(fira_refresh_prep_kernel, dim3(prep_blocks, count), dim3(256), 0, q, ctx->d_mats, d_ents);
-    // T = G^T Q (or G Q): the projection kernel, norm route off
+    // T = G^T Q (or G Q): the projection kernel, norm route off, its result packed as the K-blocked operand of the way back
     launch_project(ctx->d_mats, s->d_ents, s->d_tiles[kTilesProjectLeft], s->ntiles[kTilesProjectLeft],
-                   s->d_tiles[kTilesProjectRight], s->ntiles[kTilesProjectRight], s->ntiles[kTilesBackBf16] > 0, s->ntiles[kTilesBackF32] > 0);
-    // pack T as the K-blocked operand of the way back
-    hipLaunchKernelGGL(fira_refresh_pack_kernel, dim3((max_Lp / 32) * nt64, count), dim3(256), 0, q, d_ents);
+                   s->d_tiles[kTilesProjectRight], s->ntiles[kTilesProjectRight], s->ntiles[kTilesBackBf16] > 0, s->ntiles[kTilesBackF32] > 0, 1);
     // Y = G T (or G^T T): the projection kernel on the other orientation (list [1] is the K-slow one)
     launch_project(d_vmats, d_vents, (const FiraTile*)(ws + rp.off_vtiles[1]), rp.ntiles[1],
-                   (const FiraTile*)(ws + rp.off_vtiles[0]), rp.ntiles[0], true, false);
+                   (const FiraTile*)(ws + rp.off_vtiles[0]), rp.ntiles[0], true, false, 0);
     // Q = orth(Y): CholeskyQR in fp64
     orthonormalise(d_ents);
   }

@@ -689,9 +689,45 @@ __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds
   stage(std::true_type{}, pos, kb, slot);
 }
 
+// A wave's 32 TM x 64 block of R, from row row0 and column col0: into Rt, or (the projector refresh) rounded to bf16 into the
+// K-blocked operand of the way back, `top` (rows = rank, K = factors).  A lane holds four consecutive factors of a
+// rank row, and a 32 x 32 block of the operand is 2 KB of contiguous memory.  Factors past the end are the
+// contraction's padding and are written as zeros; rank rows past r only feed columns that nobody stores.
+// (168 matrices of the 1B shapes at r = 512, twice a refresh: with T in fp32, a pass that packed it and one that cleared
+// the padding the way there took 1375 + 464 us, and 83 once; with the operand written here 1360.)
+template <int TM>
+__device__ __forceinline__ void store_projection(const f32x16_t (&acc)[TM][2], const FiraMat& mt, bf16_raw* top, int row0, int col0) {
+  const int lane = threadIdx.x & 63, hi4 = 4 * (lane >> 5);
+  gptr<float> Rt = as_global(mt.Rt);
+  gptr<bf16_raw> Top = as_global(top);
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < 2; ++tn) {
+      const int col = col0 + 32 * tn + (lane & 31), rb = row0 + 32 * tm;
+      const f32x16_t& a = acc[tm][tn];
+      if (top) {
+        if (rb >= ((mt.L + 63) & ~63)) continue;
+#pragma unroll
+        for (int vg = 0; vg < 4; ++vg) {
+          const int row = rb + 8 * vg + hi4, live = mt.L - row;
+          *reinterpret_cast<gptr<u32x2>>(Top + kblk_index(mt.rq, col, row)) =
+              u32x2{pack_bf16x2(live > 0 ? a[4 * vg] : 0.0f, live > 1 ? a[4 * vg + 1] : 0.0f),
+                    pack_bf16x2(live > 2 ? a[4 * vg + 2] : 0.0f, live > 3 ? a[4 * vg + 3] : 0.0f)};
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int row = rb + 8 * (v >> 2) + hi4 + (v & 3);
+          if (row < mt.L && col < mt.r) Rt[(long long)row * mt.r + col] = a[v];
+        }
+      }
+    }
+}
+
 template <bool LEFT, int TM>
-__device__ __forceinline__ void project_split_tile(char* lds, const FiraMat& mt, const FiraEnt& ent, const FiraTile& tile, int norm_mode) {
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+__device__ __forceinline__ void project_split_tile(char* lds, const FiraMat& mt, const FiraEnt& ent, const FiraTile& tile, int norm_mode, int pack) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int a_row0 = tile.ta * FIRA_PA, b_row0 = tile.tb * FIRA_PB;
   const int a0 = 32 * TM * (wave % (4 / TM)), b0 = 64 * (wave / (4 / TM));
   const float* G = reinterpret_cast<const float*>(ent.G);
@@ -717,24 +753,13 @@ __device__ __forceinline__ void project_split_tile(char* lds, const FiraMat& mt,
       if (split_kq(threadIdx.x) == 0 && row < mt.L) g2[row] = s;
     }
   }
-  gptr<float> Rt = as_global(mt.Rt);
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < 2; ++tn) {
-      const int col = b_row0 + b0 + 32 * tn + (lane & 31);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = a_row0 + a0 + 32 * tm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (row < mt.L && col < mt.r) Rt[(long long)row * mt.r + col] = acc[tm][tn][v];
-      }
-    }
+  store_projection<TM>(acc, mt, pack ? reinterpret_cast<bf16_raw*>(ent.W) : nullptr, a_row0 + a0, b_row0 + b0);
 }
 
 // bf16 matrices: TM = 2 where the rank fits half a rank tile (64 < r <= 128 in a step; a refresh also brings smaller
 // ones), else 4.  (Both orientations of 56 matrices of 512 x 512 and 512 x 1376 at r = 128: 31 us; 38 us with TM = 4.)
 template <bool LEFT, int TM>
-__device__ __forceinline__ void project_tile_as(char* lds, const FiraMat& mt, const FiraEnt& ent, const FiraTile& tile, int norm_mode) {
+__device__ __forceinline__ void project_tile_as(char* lds, const FiraMat& mt, const FiraEnt& ent, const FiraTile& tile, int norm_mode, int pack) {
   GemmOperands g;
   g.a_row0 = tile.ta * FIRA_PA;
   g.a_rows = mt.L;
@@ -779,52 +804,42 @@ __device__ __forceinline__ void project_tile_as(char* lds, const FiraMat& mt, co
       if (lane < 32 && row < mt.L) g2[row] = tot;
     }
   }
-  gptr<float> Rt = as_global(mt.Rt);
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < 2; ++tn) {
-      const int col = g.b_row0 + b0 + 32 * tn + (lane & 31);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = g.a_row0 + a0 + 32 * tm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (row < mt.L && col < mt.r) Rt[(long long)row * mt.r + col] = acc[tm][tn][v];
-      }
-    }
+  store_projection<TM>(acc, mt, pack ? reinterpret_cast<bf16_raw*>(ent.W) : nullptr, g.a_row0 + a0, g.b_row0 + b0);
 }
 
 template <bool LEFT>
 __device__ __forceinline__ void project_tile(char* lds, const FiraMat* __restrict__ mats, const FiraEnt* __restrict__ ents,
-                                             const FiraTile& tile, int norm_mode, const FiraScal* __restrict__ scal, const FiraHp& hp) {
+                                             const FiraTile& tile, int norm_mode, int pack, const FiraScal* __restrict__ scal, const FiraHp& hp) {
   const FiraEnt ent = ents[tile.ent];
   if (hp.mixed && use_gram(hp, scal[ent.mat])) return;   // the fused kernel serves this matrix
   const FiraMat mt = mats[ent.mat];
 
   if (mt.kx != 1) return;                                // fira_fp32_project_kernel's
-  if (mt.r <= 128) project_tile_as<LEFT, 2>(lds, mt, ent, tile, norm_mode);
-  else project_tile_as<LEFT, 4>(lds, mt, ent, tile, norm_mode);
+  if (mt.r <= 128) project_tile_as<LEFT, 2>(lds, mt, ent, tile, norm_mode, pack);
+  else project_tile_as<LEFT, 4>(lds, mt, ent, tile, norm_mode, pack);
 }
 
 // One grid for both orientations: workgroups [0, blocks_left) take the tiles of the matrices with
 // m <= n (gradient K-slow), the rest those with m > n, so that only one partly filled round of
 // workgroups ends the launch.  blocks_left is a multiple of 8, which keeps the XCD-aware mapping of
 // each part.  scal is read only when hp.mixed is set (a step in which the fused kernel serves the
-// matrices on the Gram route and this kernel the others).
+// matrices on the Gram route and this kernel the others).  pack (the projector refresh's way there): the product leaves
+// rounded to bf16 as the operand of the way back, at the address in the entry's W, instead of in fp32.
 __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_project_kernel(const FiraMat* __restrict__ mats,
                                                                             const FiraEnt* __restrict__ ents,
                                                                             const FiraTile* __restrict__ tiles_left, int ntiles_left,
                                                                             int blocks_left,
                                                                             const FiraTile* __restrict__ tiles_right, int ntiles_right,
-                                                                            int norm_mode, const FiraScal* __restrict__ scal, FiraHp hp) {
+                                                                            int norm_mode, int pack, const FiraScal* __restrict__ scal, FiraHp hp) {
   extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_PROJ_LDS bytes
   if ((int)blockIdx.x < blocks_left) {
     const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
     if (ti < 0) return;
-    project_tile<true>(lds, mats, ents, tiles_left[ti], norm_mode, scal, hp);
+    project_tile<true>(lds, mats, ents, tiles_left[ti], norm_mode, pack, scal, hp);
   } else {
     const int ti = xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
     if (ti < 0) return;
-    project_tile<false>(lds, mats, ents, tiles_right[ti], norm_mode, scal, hp);
+    project_tile<false>(lds, mats, ents, tiles_right[ti], norm_mode, pack, scal, hp);
   }
 }
 
@@ -832,29 +847,29 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_project_kernel(cons
 // one kernel for both the two forms together took more registers than either).
 template <bool LEFT>
 __device__ __forceinline__ void project_fp32_tile(char* lds, const FiraMat* __restrict__ mats, const FiraEnt* __restrict__ ents,
-                                                  const FiraTile& tile, int norm_mode) {
+                                                  const FiraTile& tile, int norm_mode, int pack) {
   const FiraEnt ent = ents[tile.ent];
   const FiraMat mt = mats[ent.mat];
   if (mt.kx == 1) return;
-  if (mt.r <= 64) project_split_tile<LEFT, 1>(lds, mt, ent, tile, norm_mode);
-  else if (mt.r <= 128) project_split_tile<LEFT, 2>(lds, mt, ent, tile, norm_mode);
-  else project_split_tile<LEFT, 4>(lds, mt, ent, tile, norm_mode);
+  if (mt.r <= 64) project_split_tile<LEFT, 1>(lds, mt, ent, tile, norm_mode, pack);
+  else if (mt.r <= 128) project_split_tile<LEFT, 2>(lds, mt, ent, tile, norm_mode, pack);
+  else project_split_tile<LEFT, 4>(lds, mt, ent, tile, norm_mode, pack);
 }
 __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_fp32_project_kernel(const FiraMat* __restrict__ mats,
                                                                                  const FiraEnt* __restrict__ ents,
                                                                                  const FiraTile* __restrict__ tiles_left, int ntiles_left,
                                                                                  int blocks_left,
                                                                                  const FiraTile* __restrict__ tiles_right, int ntiles_right,
-                                                                                 int norm_mode) {
+                                                                                 int norm_mode, int pack) {
   extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_SPLIT_LDS bytes
   if ((int)blockIdx.x < blocks_left) {
     const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
     if (ti < 0) return;
-    project_fp32_tile<true>(lds, mats, ents, tiles_left[ti], norm_mode);
+    project_fp32_tile<true>(lds, mats, ents, tiles_left[ti], norm_mode, pack);
   } else {
     const int ti = xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
     if (ti < 0) return;
-    project_fp32_tile<false>(lds, mats, ents, tiles_right[ti], norm_mode);
+    project_fp32_tile<false>(lds, mats, ents, tiles_right[ti], norm_mode, pack);
   }
 }
 

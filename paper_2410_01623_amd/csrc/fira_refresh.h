@@ -8,7 +8,8 @@
 //
 // a fixed number of times from a seeded random start.  The two big products are the projection
 // kernel itself: T = (G applied along the short side) is exactly R for the projector Q, and the way
-// back is the same kernel run on the other orientation of G with T packed as its K-blocked operand.
+// back is the same kernel run on the other orientation of G with T as its K-blocked operand, which the way there writes
+// from its accumulators (store_projection).
 // The small dense algebra of the orthonormalisation (CholeskyQR: C = Y^T Y, C = L L^T, Q = Y L^-T by forward substitution) is
 // done in fp64 so that it survives gradients with a steep spectrum; the kernels below are plain
 // (no MFMA): r^2 S flops per matrix, every listed matrix in one grouped launch.
@@ -36,34 +37,6 @@ __global__ __launch_bounds__(256) void fira_refresh_init_kernel(const FiraRefres
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
     const unsigned long long h = refresh_mix64(key + (unsigned long long)i);
     Q[i] = (float)((double)(h >> 11) * (2.0 / 9007199254740992.0) - 1.0);
-  }
-}
-
-// Top[a][i] = bf16(T[i][a]) in the K-blocked layout; k >= L is zero.  (Rows a >= r stay zero from the
-// workspace clear.)  One workgroup per 32 (i) x 64 (a) tile.
-__global__ __launch_bounds__(256) void fira_refresh_pack_kernel(const FiraRefreshEnt* __restrict__ ents) {
-  __shared__ float tile[32][65];
-  const FiraRefreshEnt e = ents[blockIdx.y];
-  const int atiles = (e.r + 63) / 64;
-  const int ib = blockIdx.x / atiles, ab = blockIdx.x % atiles;
-  if (ib * 32 >= e.Lp) return;
-  gptr<const float> T = as_global<const float>(e.T);
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int p = 0; p < 8; ++p) {
-    const int il = (t >> 6) + 4 * p, al = t & 63;
-    const int i = ib * 32 + il, a = ab * 64 + al;
-    tile[il][al] = (i < e.L && a < e.r) ? T[(long long)i * e.r + a] : 0.0f;
-  }
-  __syncthreads();
-  const int al = t >> 2, i8 = (t & 3) * 8;
-  const int a = ab * 64 + al;
-  if (a < e.r) {
-    unsigned w[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) w[d] = pack_bf16x2(tile[i8 + 2 * d][al], tile[i8 + 2 * d + 1][al]);
-    gptr<bf16_raw> Top = as_global(e.Top);
-    *reinterpret_cast<gptr<u32x4>>(Top + kblk_index(e.rq, a, ib * 32 + i8)) = u32x4{w[0], w[1], w[2], w[3]};
   }
 }
 
