@@ -958,11 +958,6 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   ListSlot* s = acquire_list(ctx, count, idx, top.data(), dev_G, &st);
   if (!s) return fail(ctx, st, "building the work list failed");
 
-  {
-    const long long mx = (long long)max_S * max_r;
-    hipLaunchKernelGGL(fira_refresh_init_kernel, dim3((unsigned)std::min<long long>((mx + 255) / 256, 4096), count), dim3(256), 0, q,
-                       d_ents, (unsigned long long)seed, (int*)(ws + rp.off_done));
-  }
   const int nt64 = (max_r + 63) / 64;
   const int prep_blocks = prep_tiles(max_S, max_r);
   auto orthonormalise = [&](const FiraRefreshEnt* de) {
@@ -986,8 +981,12 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
       hipLaunchKernelGGL(fira_fp32_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_SPLIT_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0, pack);
   };
   for (int it = 0; it < iters; ++it) {
-    // operands of Q (the fp32 Q becomes the matrix's projector copies; no gate estimate needed here)
-    hipLaunchKernelGGL(fira_refresh_prep_kernel, dim3(prep_blocks, count), dim3(256), 0, q, ctx->d_mats, d_ents);
+    // the basis as the projection's operand (in the place of the matrix's projector; no gate estimate needed here)
+    if (it == 0)
+      hipLaunchKernelGGL(fira_refresh_start_kernel, dim3(prep_blocks, count), dim3(256), 0, q, ctx->d_mats, d_ents,
+                         (unsigned long long)seed, (int*)(ws + rp.off_done));
+    else
+      hipLaunchKernelGGL(fira_refresh_round_kernel, dim3(prep_blocks, count), dim3(256), 0, q, ctx->d_mats, d_ents);
     // T = G^T Q (or G Q): the projection kernel, norm route off, its result packed as the K-blocked operand of the way back
     launch_project(ctx->d_mats, s->d_ents, s->d_tiles[kTilesProjectLeft], s->ntiles[kTilesProjectLeft],
                    s->d_tiles[kTilesProjectRight], s->ntiles[kTilesProjectRight], s->ntiles[kTilesBackBf16] > 0, s->ntiles[kTilesBackF32] > 0, 1);

@@ -670,8 +670,9 @@ __global__ __launch_bounds__(256) void fira_scale_update_kernel(const FiraMat* _
 // A memory-bound transposition: tiles of 32 (s) x 64 (a) go through LDS, so that both operands leave in 16-byte
 // pieces of 2 and 4 KB contiguous runs (the operands' padding inside the last tile is written with its zeros).  All
 // 168 projectors of the 1B shapes at r = 512: 344 us; 1039 us with one element per thread and 2-byte stores.
-template <typename TP>
-__device__ __forceinline__ void prep_projector_body(const FiraMat& mt, const TP* __restrict__ P) {
+// value(idx): element idx of the projector, row-major.  BOTH: Pn as well as PT (the rounds of a refresh contract PT only).
+template <bool BOTH, typename F>
+__device__ __forceinline__ void prep_projector_tiles(const FiraMat& mt, F value) {
   __shared__ float tile[32][65];
   const int atiles = (mt.r + 63) / 64, tiles = ((mt.S + 31) / 32) * atiles;
   const int t = threadIdx.x;
@@ -684,8 +685,7 @@ __device__ __forceinline__ void prep_projector_body(const FiraMat& mt, const TP*
       const int sl = (t >> 6) + 4 * p, al = t & 63;
       const bool in = s0 + sl < mt.S && a0 + al < mt.r;
       const long long idx = (long long)(s0 + sl) * mt.r + a0 + al;
-      if (sizeof(TP) == 2) tile[sl][al] = in ? bf16_to_f32(as_global(reinterpret_cast<const bf16_raw*>(P))[idx]) : 0.0f;
-      else tile[sl][al] = in ? as_global(reinterpret_cast<const float*>(P))[idx] : 0.0f;
+      tile[sl][al] = in ? value(idx) : 0.0f;
     }
     __syncthreads();
     // Pn: row s, eight a;  PT: row a, eight s
@@ -700,7 +700,7 @@ __device__ __forceinline__ void prep_projector_body(const FiraMat& mt, const TP*
     const int planes = mt.kx == 1 ? 1 : 3;
     u32x2 h0[3], h1[3];
 #pragma unroll
-    for (int side = 0; side < 2; ++side) {
+    for (int side = BOTH ? 0 : 1; side < 2; ++side) {
       bf16_planes<FIRA_KX_SPLIT>(side ? t0 : n0, planes, h0);
       bf16_planes<FIRA_KX_SPLIT>(side ? t1 : n1, planes, h1);
 #pragma unroll
@@ -715,8 +715,15 @@ __device__ __forceinline__ void prep_projector_body(const FiraMat& mt, const TP*
     __syncthreads();
   }
 }
+template <bool BOTH, typename TP>
+__device__ __forceinline__ void prep_projector_body(const FiraMat& mt, const TP* __restrict__ P) {
+  prep_projector_tiles<BOTH>(mt, [&](long long idx) {
+    if (sizeof(TP) == 2) return bf16_to_f32(as_global(reinterpret_cast<const bf16_raw*>(P))[idx]);
+    return as_global(reinterpret_cast<const float*>(P))[idx];
+  });
+}
 template <typename TP>
-__global__ __launch_bounds__(256) void fira_prep_projector_kernel(FiraMat mt, const TP* __restrict__ P) { prep_projector_body<TP>(mt, P); }
+__global__ __launch_bounds__(256) void fira_prep_projector_kernel(FiraMat mt, const TP* __restrict__ P) { prep_projector_body<true, TP>(mt, P); }
 
 // One float in device memory (the step size lr * alpha), written in stream order.
 __global__ void fira_store_float_kernel(float* __restrict__ dst, float value) {

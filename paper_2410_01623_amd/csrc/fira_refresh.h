@@ -15,6 +15,7 @@
 // (no MFMA): r^2 S flops per matrix, every listed matrix in one grouped launch.
 #pragma once
 #include "fira_device.h"
+#include "fira_elementwise.h"
 
 
 // splitmix64 finaliser: one independent 64-bit value per counter
@@ -25,19 +26,18 @@ __device__ __forceinline__ unsigned long long refresh_mix64(unsigned long long z
   return z ^ (z >> 31);
 }
 
-// Q0: uniform(-1, 1) entries, a function of (seed, matrix, element) only.
-// Also clears the flags of the second orthonormalisation pass.
-__global__ __launch_bounds__(256) void fira_refresh_init_kernel(const FiraRefreshEnt* __restrict__ ents, unsigned long long seed,
-                                                                int* __restrict__ done) {
+// The first round's basis as the projection's operand PT: uniform(-1, 1) entries, a function of (seed, matrix, element)
+// only, which nothing else reads.  Also clears the flags of the second orthonormalisation pass.
+// (168 bases of the 1B shapes at r = 512: 181 us; 335 + 329 as an fp32 basis and a pass that made both operand copies of it.)
+__global__ __launch_bounds__(256) void fira_refresh_start_kernel(const FiraMat* __restrict__ mats, const FiraRefreshEnt* __restrict__ ents,
+                                                                 unsigned long long seed, int* __restrict__ done) {
   const FiraRefreshEnt e = ents[blockIdx.y];
   if (blockIdx.x == 0 && threadIdx.x == 0) as_global(done)[blockIdx.y] = 0;
-  const long long total = (long long)e.S * e.r;
-  gptr<float> Q = as_global(e.Q);
   const unsigned long long key = refresh_mix64(seed ^ ((unsigned long long)(unsigned)e.mat << 32));
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
-    const unsigned long long h = refresh_mix64(key + (unsigned long long)i);
-    Q[i] = (float)((double)(h >> 11) * (2.0 / 9007199254740992.0) - 1.0);
-  }
+  prep_projector_tiles<false>(mats[e.mat], [&](long long idx) {
+    const unsigned long long h = refresh_mix64(key + (unsigned long long)idx);
+    return (float)((double)(h >> 11) * (2.0 / 9007199254740992.0) - 1.0);
+  });
 }
 
 // 64 x 64 tile of a product accumulated in fp64 on the matrix pipe (v_mfma_f64_16x16x4_f64): 256 threads, wave w
@@ -521,8 +521,13 @@ __global__ __launch_bounds__(256) void fira_refresh_solve_kernel(const FiraRefre
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void fira_refresh_prep_kernel(const FiraMat* __restrict__ mats, const FiraRefreshEnt* __restrict__ ents) {
   const FiraRefreshEnt e = ents[blockIdx.y];
-  if (e.q_dtype == 1) prep_projector_body<bf16_raw>(mats[e.mat], reinterpret_cast<const bf16_raw*>(e.Q));
-  else prep_projector_body<float>(mats[e.mat], refresh_pass_done(e) ? e.Y : e.Q);   // (a second pass that had nothing to do left its input as the result)
+  if (e.q_dtype == 1) prep_projector_body<true>(mats[e.mat], reinterpret_cast<const bf16_raw*>(e.Q));
+  else prep_projector_body<true>(mats[e.mat], (const float*)(refresh_pass_done(e) ? e.Y : e.Q));   // (a second pass that had nothing to do left its input as the result)
+}
+// Between two rounds: the basis as PT only (271 us there, 329 with both copies).
+__global__ __launch_bounds__(256) void fira_refresh_round_kernel(const FiraMat* __restrict__ mats, const FiraRefreshEnt* __restrict__ ents) {
+  const FiraRefreshEnt e = ents[blockIdx.y];
+  prep_projector_body<false>(mats[e.mat], (const float*)e.Q);
 }
 __global__ __launch_bounds__(256) void fira_refresh_ortho_y_kernel(const FiraMat* __restrict__ mats, const FiraRefreshEnt* __restrict__ ents) {
   const FiraRefreshEnt e = ents[blockIdx.y];
