@@ -295,7 +295,6 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<0, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<1, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_chol_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_CHOL_PAN_ROWS * (FIRA_CHOL_NB + 1) * 8));
-  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_solve_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_SOLVE_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(1)));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(2)));
@@ -968,8 +967,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     }
     const int nj = (max_r + FIRA_SOLVE_JB - 1) / FIRA_SOLVE_JB;
     hipLaunchKernelGGL(fira_refresh_diaginv_kernel, dim3(nj, count), dim3(256), 0, q, de);
-    for (int J = 0; J < nj; ++J)
-      hipLaunchKernelGGL(fira_refresh_solve_kernel, dim3((max_S + 63) / 64, count), dim3(256), FIRA_SOLVE_LDS, q, de, J);
+    hipLaunchKernelGGL(fira_refresh_solve_kernel, dim3((max_S + 63) / 64, count), dim3(256), 0, q, de);
   };
   const FiraHp refresh_hp = make_hp(ctx);   // (mixed = 0: the projection kernel serves every listed matrix)
   auto launch_project = [&](const FiraMat* mats, const FiraEnt* ents_d, const FiraTile* tl, int nl, const FiraTile* tr, int nr, bool bf16, bool fp32, int pack) {

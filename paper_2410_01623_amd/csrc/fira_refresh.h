@@ -54,6 +54,12 @@ __device__ __forceinline__ void refresh_acc_zero(RefreshAcc& acc) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc.v[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
 }
+__device__ __forceinline__ void refresh_acc_step(RefreshAcc& acc, double a0, double a1, double b0, double b1) {
+  acc.v[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc.v[0][0], 0, 0, 0);
+  acc.v[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc.v[0][1], 0, 0, 0);
+  acc.v[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc.v[1][0], 0, 0, 0);
+  acc.v[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc.v[1][1], 0, 0, 0);
+}
 // K steps [0, KN) of a staged pair of operands: A(k, m) = sa[k * ak + m * am], B(k, n) = sb[k * bk + n * bn],
 // m and n counted inside the workgroup's 64 x 64 tile.
 template <int KN, typename TA, typename TB>
@@ -65,10 +71,7 @@ __device__ __forceinline__ void refresh_acc_steps(RefreshAcc& acc, const TA* sa,
     const int k = k4 + kq;
     const double a0 = (double)sa[k * ak + m0 * am], a1 = (double)sa[k * ak + (m0 + 16) * am];
     const double b0 = (double)sb[k * bk + n0 * bn], b1 = (double)sb[k * bk + (n0 + 16) * bn];
-    acc.v[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc.v[0][0], 0, 0, 0);
-    acc.v[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc.v[0][1], 0, 0, 0);
-    acc.v[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc.v[1][0], 0, 0, 0);
-    acc.v[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc.v[1][1], 0, 0, 0);
+    refresh_acc_step(acc, a0, a1, b0, b1);
   }
 }
 // Calls f(row, col, value) for every element of the workgroup's tile that this lane holds.
@@ -95,9 +98,11 @@ __device__ __forceinline__ f32x4 refresh_load4(gptr<const float> A, int row, int
 }
 
 // C = Y^T Y (lower triangle tiles only), fp64.  K stages of 32 rows; the next stage's rows are requested into
-// registers before the current one is multiplied.
+// registers before the current one is multiplied.  What is not a multiply on the matrix pipe costs here: with the
+// register count left to the compiler it kept the sums in the other half of the register file between stages and moved all
+// of them there and back per stage (168 matrices of 2048 rows at r = 512: 1.82 ms, 2.04 before; five workgroups per CU).
 #define FIRA_GRAM_KS 32
-__global__ __launch_bounds__(256) void fira_refresh_gram_kernel(const FiraRefreshEnt* __restrict__ ents) {
+__global__ __launch_bounds__(256, 5) void fira_refresh_gram_kernel(const FiraRefreshEnt* __restrict__ ents) {
   __shared__ __attribute__((aligned(16))) float sa[FIRA_GRAM_KS * FIRA_STAGE_LD], sb[FIRA_GRAM_KS * FIRA_STAGE_LD];
   const FiraRefreshEnt e = ents[blockIdx.y];
   const int nt = (e.r + 63) / 64;
@@ -110,6 +115,7 @@ __global__ __launch_bounds__(256) void fira_refresh_gram_kernel(const FiraRefres
   const int t = threadIdx.x;
   RefreshAcc acc;
   refresh_acc_zero(acc);
+  const bool upper = ta == tb && (t >> 6) == 1;      // the wave above the diagonal: nobody stores its block
   f32x4 ra[2], rb[2];
   auto fetch = [&](int s0) {
 #pragma unroll
@@ -129,7 +135,7 @@ __global__ __launch_bounds__(256) void fira_refresh_gram_kernel(const FiraRefres
     }
     __syncthreads();
     if (s0 + FIRA_GRAM_KS < e.S) fetch(s0 + FIRA_GRAM_KS);
-    refresh_acc_steps<FIRA_GRAM_KS>(acc, sa, FIRA_STAGE_LD, 1, sb, FIRA_STAGE_LD, 1);
+    if (!upper) refresh_acc_steps<FIRA_GRAM_KS>(acc, sa, FIRA_STAGE_LD, 1, sb, FIRA_STAGE_LD, 1);
     __syncthreads();
   }
   gptr<double> C = as_global(e.C);
@@ -308,10 +314,7 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
             const int k = k4 + (lane >> 4);
             const double a0 = chol_pan[m0 * PP + k], a1 = chol_pan[m1 * PP + k];
             const double b0 = chol_pan[n0 * PP + k], b1 = chol_pan[n1 * PP + k];
-            acc.v[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc.v[0][0], 0, 0, 0);
-            acc.v[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc.v[0][1], 0, 0, 0);
-            acc.v[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc.v[1][0], 0, 0, 0);
-            acc.v[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc.v[1][1], 0, 0, 0);
+            refresh_acc_step(acc, a0, a1, b0, b1);
           }
 #pragma unroll
           for (int i = 0; i < 2; ++i)
@@ -359,18 +362,23 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
 
 // Q = Y L^-T, i.e. every row solves  q L^T = y  by forward substitution, done in column blocks of 64:
 //     Q_J = (Y_J - Q_{<J} L_{J,<J}^T) inv(L_JJ)^T.
-// Everything but the 64 x 64 inverses of the diagonal blocks is a dense product, so the work is tiled like
-// the Gram kernel (64 x 64 output tile, fp64 on the matrix pipe, operands staged through LDS with the next
-// stage's values requested into registers meanwhile): one launch per column block J, in order, each reading the blocks of Q written by the launches
-// before it (fp32, as the result is stored).  The inverses of the diagonal blocks come from a small
+// Rows do not depend on each other, so a workgroup takes 64 of them through all column blocks, reading back the blocks of Q
+// that it wrote before (fp32, as the result is stored).  Everything but the 64 x 64 inverses of the diagonal blocks is a dense
+// product, tiled like the Gram kernel (64 x 64 output tile, fp64 on the matrix pipe, operands staged through LDS
+// with the next stage's values requested into registers meanwhile).  The inverses of the diagonal blocks come from a small
 // kernel of their own (one thread per column of an inverse) and live in the scratch of the installation,
 // which is idle until the solves are done.  (Forms that kept a workgroup's rows in LDS and walked along
 // the columns, one row per lane with L read from memory or staged in LDS, ran at a tenth of the fp64
 // rate: bound by the latency, or the LDS bandwidth, of the operand every lane shares.)
 // The staged operands and, after them, Y_J - update share the LDS (33 KB, four workgroups per CU: the stages of 16 k
-// are short, and what hides their barriers is other workgroups); the inverse is read from L2 as it is multiplied.
-// 168 matrices of 2048 rows at r = 512, the eight launches: 2.4 ms; 3.2 ms with 79 KB and two workgroups per CU.
-#define FIRA_SOLVE_LDS (64 * 65 * 8)   // [64][65] Y_J - update; before that staged Q (rows of FIRA_STAGE_LD floats) and L
+// are short, and what hides their barriers is other workgroups); the first half of the inverse is requested before
+// the barrier in front of the products it meets.  168 matrices of 2048 rows at r = 512: 1.95 ms; 2.45 ms with a
+// launch per column block, whose staged operands met in LDS four to a bank.
+#define FIRA_SOLVE_LD 66   // doubles per row of Y_J - update: the fragment reads of 16 rows x 2 columns fall on distinct banks
+#define FIRA_SOLVE_LDS (64 * FIRA_SOLVE_LD * 8)   // [64][FIRA_SOLVE_LD] Y_J - update; before that the staged Q and L
+// Column swizzle of a staged K row: four rows that one store instruction touches fall on distinct banks.
+__device__ __forceinline__ int solve_swz_q(int k) { return 16 * ((k >> 2) & 3); }
+__device__ __forceinline__ int solve_swz_l(int k) { return 8 * ((k >> 2) & 3); }
 
 // inv(L_JJ) for every diagonal block J of a matrix: inv[J][k][c], k >= c (zero above the diagonal).
 // Rows and columns beyond r act as an identity.  By halves: the inverses of the two 32 x 32 triangles A and B, one
@@ -434,83 +442,102 @@ __global__ __launch_bounds__(256) void fira_refresh_diaginv_kernel(const FiraRef
   }
 }
 
-// Column block J of Q for 64 rows.
-__global__ __launch_bounds__(256) void fira_refresh_solve_kernel(const FiraRefreshEnt* __restrict__ ents, int J) {
-  extern __shared__ __attribute__((aligned(16))) char solve_lds[];
+// All of Q for 64 rows.
+__global__ __launch_bounds__(256, 4) void fira_refresh_solve_kernel(const FiraRefreshEnt* __restrict__ ents) {
+  __shared__ __attribute__((aligned(16))) char solve_lds[FIRA_SOLVE_LDS];
   float* sa = reinterpret_cast<float*>(solve_lds);                                   // [16][FIRA_STAGE_LD]  Q[s0 + i][k0 + kk]
-  double* sb = reinterpret_cast<double*>(solve_lds + 16 * FIRA_STAGE_LD * 4);        // [16][64]  L[j0 + j][k0 + kk]
-  double (*st)[65] = reinterpret_cast<double (*)[65]>(solve_lds);                    // [64][65] Y_J - update
+  double* sb = reinterpret_cast<double*>(solve_lds + 16 * FIRA_STAGE_LD * 4);        // [16][FIRA_STAGE_LD]  L[j0 + j][k0 + kk]
+  double (*st)[FIRA_SOLVE_LD] = reinterpret_cast<double (*)[FIRA_SOLVE_LD]>(solve_lds);   // Y_J - update
   const FiraRefreshEnt e = ents[blockIdx.y];
-  const int r = e.r, s0 = blockIdx.x * 64, j0 = J * FIRA_SOLVE_JB;
-  if (s0 >= e.S || j0 >= r || refresh_pass_done(e)) return;
+  const int r = e.r, s0 = blockIdx.x * 64;
+  if (s0 >= e.S || refresh_pass_done(e)) return;
   gptr<const float> Y = as_global<const float>(e.Y);
   gptr<const double> Lm = as_global<const double>(e.C);
   gptr<float> Q = as_global(e.Q);
-  gptr<const double> inv = reinterpret_cast<gptr<const double>>(as_global(e.inst)) + (size_t)J * 64 * 64;
-  const int t = threadIdx.x;
-  RefreshAcc acc;
-  refresh_acc_zero(acc);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int m0 = 32 * (wave >> 1) + (lane & 15), n0 = 32 * (wave & 1) + (lane & 15), kq = lane >> 4;
   const int lr = t >> 2, lk = (t & 3) * 4;      // staging: row (or column of the block) lr, four k from lk
-  // (j0 is a multiple of 64: whole tiles along k, all inside the matrix.)  The next stage's values are requested
-  // into registers before the current one is multiplied.
-  f32x4 rq;
-  double rl[4];
-  auto fetch = [&](int k0) {
-    rq = refresh_load4(Q, s0 + lr, k0 + lk, e.S, r, r);
-    if (j0 + lr < r) {
-      gptr<const double> pl = Lm + (long long)(j0 + lr) * r + k0 + lk;
-      if ((r & 1) == 0) {
-        typedef double f64x2_t __attribute__((ext_vector_type(2)));
-        const f64x2_t u = *reinterpret_cast<gptr<const f64x2_t>>(pl), w = *reinterpret_cast<gptr<const f64x2_t>>(pl + 2);
-        rl[0] = u.x; rl[1] = u.y; rl[2] = w.x; rl[3] = w.y;
+  for (int j0 = 0; j0 < r; j0 += FIRA_SOLVE_JB) {
+    RefreshAcc acc;
+    refresh_acc_zero(acc);
+    // (j0 is a multiple of 64: whole tiles along k, all inside the matrix.)  The next stage's values are requested
+    // into registers before the current one is multiplied.
+    f32x4 rq;
+    double rl[4];
+    auto fetch = [&](int k0) {
+      rq = refresh_load4(Q + (long long)s0 * r + k0, lr, lk, e.S - s0, r, r);
+      if (j0 + lr < r) {
+        gptr<const double> pl = Lm + (long long)j0 * r + k0 + (unsigned)(lr * r + lk);
+        if ((r & 1) == 0) {
+          typedef double f64x2_t __attribute__((ext_vector_type(2)));
+          const f64x2_t u = *reinterpret_cast<gptr<const f64x2_t>>(pl), w = *reinterpret_cast<gptr<const f64x2_t>>(pl + 2);
+          rl[0] = u.x; rl[1] = u.y; rl[2] = w.x; rl[3] = w.y;
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) rl[q] = pl[q];
+        }
       } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) rl[q] = pl[q];
+        for (int q = 0; q < 4; ++q) rl[q] = 0.0;
       }
-    } else {
+    };
+    if (j0 > 0) fetch(0);
+    for (int k0 = 0; k0 < j0; k0 += 16) {
+      const float qv[4] = {rq.x, rq.y, rq.z, rq.w};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) rl[q] = 0.0;
-    }
-  };
-  if (j0 > 0) fetch(0);
-  for (int k0 = 0; k0 < j0; k0 += 16) {
-    const float qv[4] = {rq.x, rq.y, rq.z, rq.w};
+      for (int q = 0; q < 4; ++q) {
+        sa[(lk + q) * FIRA_STAGE_LD + (lr ^ solve_swz_q(lk))] = qv[q];
+        sb[(lk + q) * FIRA_STAGE_LD + (lr ^ solve_swz_l(lk))] = rl[q];
+      }
+      __syncthreads();
+      if (k0 + 16 < j0) fetch(k0 + 16);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      sa[(lk + q) * FIRA_STAGE_LD + lr] = qv[q];
-      sb[(lk + q) * 64 + lr] = rl[q];
+      for (int k4 = 0; k4 < 16; k4 += 4) {       // sum_k Q[row][k] L[j0 + col][k]
+        const int k = k4 + kq;
+        const float* pa = sa + k * FIRA_STAGE_LD;
+        const double* pb = sb + k * FIRA_STAGE_LD;
+        refresh_acc_step(acc, (double)pa[m0 ^ solve_swz_q(k4)], (double)pa[(m0 + 16) ^ solve_swz_q(k4)],
+                         pb[n0 ^ solve_swz_l(k4)], pb[(n0 + 16) ^ solve_swz_l(k4)]);
+      }
+      __syncthreads();
     }
+    // T = Y_J - update  (the last stage's barrier has freed the staged operands)
+    gptr<const double> inv = reinterpret_cast<gptr<const double>>(as_global(e.inst)) + (size_t)j0 * 64;
+    double b0[8], b1[8];
+    auto fetch_inv = [&](int k0) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        b0[i] = inv[n0 * 64 + k0 + 4 * i + kq];
+        b1[i] = inv[(n0 + 16) * 64 + k0 + 4 * i + kq];
+      }
+    };
+    gptr<const float> Yb = Y + (long long)s0 * r + j0;
+    gptr<float> Qb = Q + (long long)s0 * r + j0;
+    refresh_acc_foreach(acc, [&](int row, int col, double v) {
+      const double yv = (s0 + row < e.S && j0 + col < r) ? (double)Yb[row * r + col] : 0.0;
+      st[row][col] = yv - v;
+    });
+    fetch_inv(0);
     __syncthreads();
-    if (k0 + 16 < j0) fetch(k0 + 16);
-    refresh_acc_steps<16>(acc, sa, FIRA_STAGE_LD, 1, sb, 64, 1);   // sum_k Q[row][k] L[j0 + col][k]
-    __syncthreads();
-  }
-  // T = Y_J - update  (the last stage's barrier has freed the staged operands)
-  refresh_acc_foreach(acc, [&](int row, int col, double v) {
-    const double y = (s0 + row < e.S && j0 + col < r) ? (double)Y[(long long)(s0 + row) * r + j0 + col] : 0.0;
-    st[row][col] = y - v;
-  });
-  __syncthreads();
-  // Q_J = T inv^T:  q[row][k] = sum_{c <= k} T[row][c] inv[k][c]
-  refresh_acc_zero(acc);
-  {
-    const int lane = t & 63, wave = t >> 6;
-    const int m0 = 32 * (wave >> 1) + (lane & 15), n0 = 32 * (wave & 1) + (lane & 15), kq = lane >> 4;
-    const int kn = 32 * ((wave & 1) + 1);          // (inv is zero above its diagonal)
-#pragma unroll 4
-    for (int k4 = 0; k4 < kn; k4 += 4) {
-      const int k = k4 + kq;
-      const double b0 = inv[n0 * 64 + k], b1 = inv[(n0 + 16) * 64 + k];
-      const double a0 = st[m0][k], a1 = st[m0 + 16][k];
-      acc.v[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc.v[0][0], 0, 0, 0);
-      acc.v[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc.v[0][1], 0, 0, 0);
-      acc.v[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc.v[1][0], 0, 0, 0);
-      acc.v[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc.v[1][1], 0, 0, 0);
+    // Q_J = T inv^T:  q[row][k] = sum_{c <= k} T[row][c] inv[k][c]   (inv is zero above its diagonal: the left columns take half the c)
+    refresh_acc_zero(acc);
+    auto half = [&](int k0) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int k = k0 + 4 * i + kq;
+        refresh_acc_step(acc, st[m0][k], st[m0 + 16][k], b0[i], b1[i]);
+      }
+    };
+    half(0);
+    if (wave & 1) {
+      fetch_inv(32);
+      half(32);
     }
+    refresh_acc_foreach(acc, [&](int row, int k, double v) {
+      if (s0 + row < e.S && j0 + k < r) Qb[row * r + k] = (float)v;
+    });
+    __syncthreads();   // this block of Q is there for the whole workgroup, and T has been read
   }
-  refresh_acc_foreach(acc, [&](int row, int k, double v) {
-    if (s0 + row < e.S && j0 + k < r) Q[(long long)(s0 + row) * r + j0 + k] = (float)v;
-  });
 }
 
 // ------------------------------------------------------------------------------------------------
