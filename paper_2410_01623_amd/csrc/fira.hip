@@ -996,6 +996,10 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   }
   // A second pass over the final basis (CholeskyQR2) brings ||Q^T Q - I|| down to rounding level even
   // when Y was ill conditioned; its result lands in the Y buffers.
+  {
+    const int nt128 = (max_r + 127) / 128;
+    hipLaunchKernelGGL(fira_refresh_check_kernel, dim3(nt128 * (nt128 + 1) / 2, count), dim3(256), 0, q, d_ents2);
+  }
   orthonormalise(d_ents2);
   // The rounds above worked in the listed matrices' operand copies of P.  If anything failed to launch, what
   // they hold now is not a projector: mark the matrices as having none rather than leave a half-made basis

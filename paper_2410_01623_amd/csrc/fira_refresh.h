@@ -16,6 +16,7 @@
 #pragma once
 #include "fira_device.h"
 #include "fira_elementwise.h"
+#include "fira_gemm.h"
 
 
 // splitmix64 finaliser: one independent 64-bit value per counter
@@ -97,6 +98,101 @@ __device__ __forceinline__ f32x4 refresh_load4(gptr<const float> A, int row, int
   return f32x4{p[0], col + 1 < cols ? p[1] : 0.f, col + 2 < cols ? p[2] : 0.f, col + 3 < cols ? p[3] : 0.f};
 }
 
+// The second orthonormalisation pass asks of the basis it is given whether max |Y^T Y - I| is within done_tol, and for
+// bf16 matrices (1e-4) three bf16 plane products h h + h m + m h answer that as surely as fp64 does: what they leave out is
+// at most 3 * 2^-18 of ||y_a|| ||y_b||, and the running sum of h h, S / 16 multiplies of at most that size, rounds by 2^-23 twice each.  A
+// matrix that passes with that much to spare needs no fp64 Gram matrix; any other (FIRA_PASS_UNSURE, and every fp32
+// matrix, whose 1e-6 lies below that margin) is decided by it.
+// Tiles of 128 x 128, a wavefront 64 x 64 of it; K stages of 32 rows, split in registers on the way into LDS, as the fp32
+// projection's.  168 matrices of 2048 rows at r = 512: 593 us; the fp64 Gram matrices 1820.
+#define FIRA_PASS_NEEDED 1
+#define FIRA_PASS_UNSURE 2
+__global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRefreshEnt* __restrict__ ents) {
+  __shared__ __attribute__((aligned(16))) char lds[4 * FIRA_SPLIT_PLANE];
+  const FiraRefreshEnt e = ents[blockIdx.y];
+  const int nt = (e.r + 127) / 128;
+  int ta = 0, rem = blockIdx.x;                     // linear index -> (ta >= tb)
+  while (ta < nt && rem > ta) { rem -= ta + 1; ++ta; }
+  if (ta >= nt) return;
+  const int tb = rem;
+  const float tol = e.done_tol - 1.2e-5f - (float)e.S * 1.5e-8f;
+  if (!(tol > 0.0f)) {
+    if (threadIdx.x == 0) *as_global(e.done) = FIRA_PASS_UNSURE;
+    return;
+  }
+  gptr<const float> Y = as_global<const float>(e.Y);
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int a0 = 64 * (wave >> 1), b0 = 64 * (wave & 1), b = split_b(t), kq = split_kq(t);
+  const bool diag = ta == tb, upper = diag && wave == 1;      // (nobody asks for the wave above the diagonal)
+  char* lb = diag ? lds : lds + 2 * FIRA_SPLIT_PLANE;
+  f32x16_t hh[2][2], hm[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) hh[i][j][v] = hm[i][j][v] = 0.0f;
+  f32x4 va[4], vb[4];
+  auto fetch = [&](int s0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      va[j] = refresh_load4(Y, s0 + 4 * kq + j, ta * 128 + 4 * b, e.S, e.r, e.r);
+      if (!diag) vb[j] = refresh_load4(Y, s0 + 4 * kq + j, tb * 128 + 4 * b, e.S, e.r, e.r);
+    }
+  };
+  auto store = [&](char* dst, const f32x4 (&v)[4]) {
+    float x[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i][j] = v[j][i];
+    split_store_a(dst, x, 0, t);
+    split_store_a(dst + FIRA_SPLIT_PLANE, x, 1, t);
+  };
+  fetch(0);
+  for (int s0 = 0; s0 < e.S; s0 += 32) {
+    store(lds, va);
+    if (!diag) store(lb, vb);
+    __syncthreads();
+    if (s0 + 32 < e.S) fetch(s0 + 32);
+    if (!upper) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        bf16x8_t fa[2][2], fb[2][2];          // [plane][block]
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int off = p * FIRA_SPLIT_PLANE + (32 * i + (lane & 31)) * FIRA_SPLIT_PITCH + (2 * kk + (lane >> 5)) * 16;
+            fa[p][i] = *reinterpret_cast<const bf16x8_t*>(lds + a0 * FIRA_SPLIT_PITCH + off);
+            fb[p][i] = *reinterpret_cast<const bf16x8_t*>(lb + b0 * FIRA_SPLIT_PITCH + off);
+          }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            hh[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][i], fb[0][j], hh[i][j], 0, 0, 0);
+            hm[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][i], fb[1][j], hm[i][j], 0, 0, 0);
+            hm[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1][i], fb[0][j], hm[i][j], 0, 0, 0);
+          }
+      }
+    }
+    __syncthreads();
+  }
+  bool off = false;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = ta * 128 + a0 + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), col = tb * 128 + b0 + 32 * j + (lane & 31);
+        const float d = hh[i][j][v] + hm[i][j][v] - (row == col ? 1.0f : 0.0f);
+        off = off || (!upper && row < e.r && col <= row && !(fabsf(d) <= tol));      // (true for a NaN)
+      }
+  if (off) *as_global(e.done) = FIRA_PASS_UNSURE;
+}
+
 // C = Y^T Y (lower triangle tiles only), fp64.  K stages of 32 rows; the next stage's rows are requested into
 // registers before the current one is multiplied.  What is not a multiply on the matrix pipe costs here: with the
 // register count left to the compiler it kept the sums in the other half of the register file between stages and moved all
@@ -105,6 +201,7 @@ __device__ __forceinline__ f32x4 refresh_load4(gptr<const float> A, int row, int
 __global__ __launch_bounds__(256, 5) void fira_refresh_gram_kernel(const FiraRefreshEnt* __restrict__ ents) {
   __shared__ __attribute__((aligned(16))) float sa[FIRA_GRAM_KS * FIRA_STAGE_LD], sb[FIRA_GRAM_KS * FIRA_STAGE_LD];
   const FiraRefreshEnt e = ents[blockIdx.y];
+  if (e.done && !(*as_global<const int>(e.done) & FIRA_PASS_UNSURE)) return;
   const int nt = (e.r + 63) / 64;
   // linear index -> (ta >= tb)
   int ta = 0, rem = blockIdx.x;
@@ -149,11 +246,11 @@ __global__ __launch_bounds__(256, 5) void fira_refresh_gram_kernel(const FiraRef
   });
   // Second pass only: is the basis that the pass was given orthonormal already, max |C - I| within the entry's tolerance?
   // (Every tile that finds it is not stores the same value.)
-  if (e.done && off) *as_global(e.done) = 1;
+  if (e.done && off) *as_global(e.done) = FIRA_PASS_UNSURE | FIRA_PASS_NEEDED;
 }
 
-// (*done counts against the pass: 0 until a tile of the Gram matrix shows that the basis is not orthonormal yet)
-__device__ __forceinline__ bool refresh_pass_done(const FiraRefreshEnt& e) { return e.done && *as_global<const int>(e.done) == 0; }
+// (FIRA_PASS_NEEDED counts against the pass: unset until a tile of the Gram matrix shows that the basis is not orthonormal yet)
+__device__ __forceinline__ bool refresh_pass_done(const FiraRefreshEnt& e) { return e.done && !(*as_global<const int>(e.done) & FIRA_PASS_NEEDED); }
 
 // In-place Cholesky factorisation of the lower triangle of C (fp64), one workgroup per matrix, blocked by 32
 // columns: factor the diagonal block, solve the panel below it one row per thread, update the trailing triangle from
