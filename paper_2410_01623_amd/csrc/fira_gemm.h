@@ -236,11 +236,7 @@ __device__ __forceinline__ void gload16_async(u32x4& dst, const void* base, unsi
 }
 template <int N>
 __device__ __forceinline__ void wait_loads(u32x4 (&r)[4]) {
-  static_assert(N == 4 || N == 2 || N == 1 || N == 0, "queue depths used by the projection pipelines");
-  if (N == 4) asm volatile("s_waitcnt vmcnt(4) ; %0 %1 %2 %3" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) :: "memory");
-  else if (N == 2) asm volatile("s_waitcnt vmcnt(2) ; %0 %1 %2 %3" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) :: "memory");
-  else if (N == 1) asm volatile("s_waitcnt vmcnt(1) ; %0 %1 %2 %3" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) :: "memory");
-  else asm volatile("s_waitcnt vmcnt(0) ; %0 %1 %2 %3" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) :: "memory");
+  asm volatile("s_waitcnt vmcnt(%4) ; %0 %1 %2 %3" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]) : "n"(N) : "memory");
 }
 
 // Thread -> element mapping of the A loaders (256 threads, 64 k x 128 rows per stage):
@@ -482,25 +478,25 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 // LDS tile.  The six plane products run one after the other over the whole contraction, the largest first (sequences A
 // and B): what the small ones add meets a sum that is already whole, and is rounded at the size of the result, where
 // all six taken together per block of k round six times as often at the size of the running sum (twice the error of R
-// where it cancels).  So G is read six times (8.2 GB through the fabric where G is 1.2, measured at the size below); that and the
-// latency of a stage, whose operands were requested one stage earlier, bound the kernel, and it still takes about half of what the way through memory took (six
-// planes written, read back, and a pass of its own for ||G_i||^2, which falls out of the first product here): 1808 us over
-// the 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256, against 1361 + 1123 + 918; one 256 x 688 matrix at r = 64:
-// 45 us against 5 + 60 + 30.  (Sums of all six products per block of 32 k, apart from the running sum: 930 us and a quarter
+// where it cancels).  So G is read six times (8.2 GB through the fabric where G is 1.2, measured at the size below), which with
+// the requests of two stages in flight is what bounds the kernel: 1491 us over the 168 matrices of 1024 x 1024 and
+// 1024 x 2736 at r = 256, 1807 with one stage's; the way through memory took 1361 + 1123 + 918 (six planes written, read
+// back, and a pass of its own for ||G_i||^2, which falls out of the first product here).
+// (Sums of all six products per block of 32 k, apart from the running sum: 930 us and a quarter
 // of the error of R, but single weights then differ from the former results by more than rounding explains locally:
 // an element whose R is tiny in every step hands its relative error on to N.)
 //
 // Tile: 128 factors x 64 TM rank components; wave w holds 32 TM factors x 64 rank components, TM = 4, 2
 // or 1 (the smallest that covers r, so that no wavefront multiplies padding only).  A stage is one product over 32 k:
 //   registers -> LDS tile [128][32 k], 80 bytes per row (conflict-free for the 8-byte writes of
-//   four rows and the 16-byte fragment reads of sixteen), the projector's plane beside it; both doubled, one barrier
-//   per stage; the next stage's operands are requested between the multiplies.
+//   four rows and the 16-byte fragment reads of sixteen), doubled, the projector's plane beside it in a ring of three; one
+//   barrier per stage; the operands of the stage after next are requested between the multiplies.
 // Loads never leave the matrix: a group of four that would is moved back and shifted in registers, rows
 // past the end read the last row; values past the contraction length are set to zero.
 // ------------------------------------------------------------------------------------------------
 #define FIRA_SPLIT_PITCH 80
 #define FIRA_SPLIT_PLANE (FIRA_PA * FIRA_SPLIT_PITCH)
-#define FIRA_SPLIT_LDS (2 * FIRA_SPLIT_PLANE + 2 * FIRA_PROJ_RING_STAGE)
+#define FIRA_SPLIT_LDS (2 * FIRA_SPLIT_PLANE + FIRA_RING_STAGES * FIRA_PROJ_RING_STAGE)
 
 // Thread t holds rows 4 b .. 4 b + 3 and k = 4 kq .. 4 kq + 3 of the tile; 32 consecutive threads write
 // four rows' whole 64 bytes.
@@ -653,40 +649,52 @@ __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds
               (unsigned)__builtin_amdgcn_readfirstlane((int)(lb0 + (unsigned)(slot * SLOT + (TM * wave + q) * 1024))));
   };
   SplitALoader<LEFT, ASYNC> al{as_global(G), mt.ld, a_row0, mt.L, mt.S};
-  u32x4 ra[4];
+  // Block of 32 k of a plane product: requests of two stages are in flight while one is multiplied, each stage's the
+  // projector's plane (TM instructions per wavefront), then the gradient's block (4, into the set of registers that is free).
+  // The last two stages request the first two blocks again, which nobody reads: every stage is the same code, with no
+  // copy of a register that a load is on its way to (and no line is requested twice at a time).
+  struct Block { int pos, kb; };
+  auto next = [&](Block b) { return b.kb + 1 < nblocks ? Block{b.pos, b.kb + 1} : Block{b.pos == 5 ? 0 : b.pos + 1, 0}; };
+  u32x4 ra[2][4];
+  auto request = [&](u32x4 (&r)[4], Block b, int bslot) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) al.load_one(ra, 0, q, fresh_thread());
+    for (int q = 0; q < TM; ++q) request_b(b.pos, b.kb, bslot, q);
 #pragma unroll
-  for (int q = 0; q < TM; ++q) request_b(0, 0, 0, q);
-  // The last stage is written out separately so that on every path a request is followed by its wait.
-  auto stage = [&](auto last, int pos, int kb, int slot) {
-    constexpr bool LAST = decltype(last)::value;
-    wait_loads<0>(ra);                           // this stage's operands have landed
+    for (int q = 0; q < 4; ++q) al.load_one(r, 32 * b.kb, q, fresh_thread());
+  };
+  auto stage = [&](u32x4 (&r)[4], int aslot, int bslot, Block b) {
+    if (nblocks == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (two stages would have the same lines of G in flight)
+    wait_loads<ASYNC ? TM + 4 : 0>(r);           // this stage's operands have landed (guarded loads are the compiler's, of whatever number)
     float x[4][4];
     const int t = fresh_thread();
-    al.unpack(ra, 32 * kb, x, t);
-    if (pos == 0) {
+    al.unpack(r, 32 * b.kb, x, t);
+    if (b.pos == 0) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) sq[e] += (x[e][0] * x[e][0] + x[e][1] * x[e][1]) + (x[e][2] * x[e][2] + x[e][3] * x[e][3]);
     }
-    split_store_a(lds + slot * FIRA_SPLIT_PLANE, x, (0x610 >> (2 * pos)) & 3, t);   // sequence A: planes 0 0 1 0 2 1
-    // everybody's share is there, and everybody is done with the other slot's stage
+    split_store_a(lds + aslot * FIRA_SPLIT_PLANE, x, (0x610 >> (2 * b.pos)) & 3, t);   // sequence A: planes 0 0 1 0 2 1
+    // everybody's share is there, and everybody is done with the stage before
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    const bool wrap = kb + 1 == nblocks;
-    const int npos = wrap ? pos + 1 : pos, nkb = wrap ? 0 : kb + 1;
-    split_compute<TM>(acc, lds + slot * FIRA_SPLIT_PLANE, lb + slot * SLOT, a0, b0, [&](int j) {
-      if (LAST) return;
-      if (j < TM) request_b(npos, nkb, slot ^ 1, j);
-      else if (j >= 4) al.load_one(ra, 32 * nkb, j - 4, fresh_thread());
+    const Block b2 = next(next(b));
+    const int bslot2 = bslot == 0 ? 2 : bslot - 1;   // (bslot + 2) % 3: the slot of the stage before
+    split_compute<TM>(acc, lds + aslot * FIRA_SPLIT_PLANE, lb + bslot * SLOT, a0, b0, [&](int j) {
+      if (j < TM) request_b(b2.pos, b2.kb, bslot2, j);
+      else if (j >= 4) al.load_one(r, 32 * b2.kb, j - 4, fresh_thread());
     });
   };
-  int pos = 0, kb = 0, slot = 0;
-  for (int s = 0; s + 1 < 6 * nblocks; ++s) {
-    stage(std::false_type{}, pos, kb, slot);
-    slot ^= 1;
-    if (++kb == nblocks) { kb = 0; ++pos; }
-  }
-  stage(std::true_type{}, pos, kb, slot);
+  Block b{0, 0};
+  int bslot = 0, left = 3 * nblocks;             // 6 nblocks stages, two at a time
+  auto step = [&]() { b = next(b); bslot = bslot == 2 ? 0 : bslot + 1; };
+  request(ra[0], b, 0);
+  request(ra[1], next(b), 1);
+  do {
+    stage(ra[0], 0, bslot, b);
+    step();
+    stage(ra[1], 1, bslot, b);
+    step();
+  } while (--left > 0);
+  wait_loads<0>(ra[0]);
+  wait_loads<0>(ra[1]);
 }
 
 // A wave's 32 TM x 64 block of R, from row row0 and column col0: into Rt, or (the projector refresh) rounded to bf16 into the
