@@ -514,23 +514,45 @@ __device__ __forceinline__ int fresh_lane() {
 __device__ __forceinline__ int fresh_thread() { return fresh_lane() + 64 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // ASYNC: 16-byte inline-assembly loads (at least four elements along the contiguous axis); otherwise
-// element by element (matrices with fewer).
+// element by element (matrices with fewer).  What does not change from block to block is formed once: 300 vector instructions a
+// stage, most of them addresses, were what bounded the kernel once its loads ran ahead.
 template <bool LEFT, bool ASYNC>
 struct SplitALoader {
   gptr<const float> G;
   long long ld;
-  int row0, L, S;
-  // request q (of 4) of the block of 32 k that starts at k0; t: the thread
-  __device__ __forceinline__ void load_one(u32x4 (&ra)[4], int k0, int q, int t) {
-    const int b = split_b(t), kq = split_kq(t);
+  int row0, L, S, b, kq;    // b, kq: this thread's place in the tile (split_b, split_kq)
+  unsigned off[LEFT ? 1 : 4];
+  __device__ __forceinline__ SplitALoader(gptr<const float> G_, long long ld_, int row0_, int L_, int S_)
+      : G(G_), ld(ld_), row0(row0_), L(L_), S(S_), b(split_b(threadIdx.x)), kq(split_kq(threadIdx.x)) {
+    if (LEFT) off[0] = (unsigned)(min(row0 + 4 * b, L - 4) - min(row0, L - 4)) * 4u;
+    else
+#pragma unroll
+      for (int q = 0; q < 4; ++q) off[LEFT ? 0 : q] = (unsigned)(min(row0 + 4 * b + q, L - 1) - row0) * (unsigned)(ld * 4);
+    if (!LEFT)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) off[LEFT ? 0 : q] += 16u * (unsigned)kq;
+    else off[0] += 4u * (unsigned)kq * (unsigned)(ld * 4);
+  }
+  // request q (of 4) of the block of 32 k that starts at k0
+  __device__ __forceinline__ void load_one(u32x4 (&ra)[4], int k0, int q) {
     if (ASYNC) {
+      // (a block that ends past S takes its last rows or columns again instead)
       if (LEFT) {
-        const int c0 = min(row0, L - 4);
-        gload16_async(ra[q], reinterpret_cast<const char*>((const float*)G + (long long)k0 * ld + c0),
-                      (unsigned)(min(row0 + 4 * b, L - 4) - c0) * 4u + (unsigned)min(4 * kq + q, S - 1 - k0) * (unsigned)(ld * 4));
+        unsigned o = off[0];
+        const char* base = reinterpret_cast<const char*>((const float*)G + (long long)(k0 + q) * ld + min(row0, L - 4));
+        if (k0 + 32 > S) {
+          base -= (long long)q * ld * 4;
+          o = (unsigned)(min(row0 + 4 * b, L - 4) - min(row0, L - 4)) * 4u + (unsigned)min(4 * kq + q, S - 1 - k0) * (unsigned)(ld * 4);
+        }
+        gload16_async(ra[q], base, o);
       } else {
-        gload16_async(ra[q], reinterpret_cast<const char*>((const float*)G + (long long)row0 * ld),
-                      (unsigned)(min(row0 + 4 * b + q, L - 1) - row0) * (unsigned)(ld * 4) + (unsigned)min(k0 + 4 * kq, S - 4) * 4u);
+        unsigned o = off[LEFT ? 0 : q];
+        const char* base = reinterpret_cast<const char*>((const float*)G + (long long)row0 * ld + k0);
+        if (k0 + 32 > S) {
+          base -= (long long)k0 * 4;
+          o += (unsigned)(min(k0 + 4 * kq, S - 4) - 4 * kq) * 4u;
+        }
+        gload16_async(ra[q], base, o);
       }
     } else {
       unsigned w[4];
@@ -548,12 +570,11 @@ struct SplitALoader {
     return d < 4 ? v : u32x4{0u, 0u, 0u, 0u};
   }
   // after the wait: the loaded groups as x[e][j] = element (row 4 b + e, k = k0 + 4 kq + j), zeros past S
-  __device__ __forceinline__ void unpack(u32x4 (&ra)[4], int k0, float (&x)[4][4], int t) {
-    const int kq = split_kq(t);
+  __device__ __forceinline__ void unpack(u32x4 (&ra)[4], int k0, float (&x)[4][4]) {
     if (ASYNC) {
       if (LEFT) {
         if (row0 + FIRA_PA > L) {            // a group of four columns that was moved back
-          const int c = row0 + 4 * split_b(t), shift = c - min(c, L - 4);
+          const int c = row0 + 4 * b, shift = c - min(c, L - 4);
 #pragma unroll
           for (int q = 0; q < 4; ++q) ra[q] = shifted(ra[q], shift);
         }
@@ -577,22 +598,19 @@ struct SplitALoader {
   }
 };
 
-// Plane pl (0, 1, 2: h, m, l) of the block -> its tile.
-__device__ __forceinline__ void split_store_a(char* la, const float (&x)[4][4], int pl, int t) {
-  char* dst = la + 4 * split_b(t) * FIRA_SPLIT_PITCH + 8 * split_kq(t);
+// Plane PL (0, 1, 2: h, m, l) of the block -> its tile.  dst: the thread's first row there (split_store_at).
+__device__ __forceinline__ int split_store_at(int t) { return 4 * split_b(t) * FIRA_SPLIT_PITCH + 8 * split_kq(t); }
+template <int PL>
+__device__ __forceinline__ void split_store_plane(char* dst, const float (&x)[4][4]) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    u32x2 v = u32x2{pack_bf16x2(x[e][0], x[e][1]), pack_bf16x2(x[e][2], x[e][3])};
-    if (pl != 0) {
-      float d[4];
-      d[0] = x[e][0] - __uint_as_float(v.x << 16); d[1] = x[e][1] - __uint_as_float(v.x & 0xffff0000u);
-      d[2] = x[e][2] - __uint_as_float(v.y << 16); d[3] = x[e][3] - __uint_as_float(v.y & 0xffff0000u);
+    float d[4] = {x[e][0], x[e][1], x[e][2], x[e][3]};
+    u32x2 v = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
+#pragma unroll
+    for (int p = 0; p < PL; ++p) {
+      d[0] -= __uint_as_float(v.x << 16); d[1] -= __uint_as_float(v.x & 0xffff0000u);
+      d[2] -= __uint_as_float(v.y << 16); d[3] -= __uint_as_float(v.y & 0xffff0000u);
       v = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
-      if (pl == 2) {
-        d[0] -= __uint_as_float(v.x << 16); d[1] -= __uint_as_float(v.x & 0xffff0000u);
-        d[2] -= __uint_as_float(v.y << 16); d[3] -= __uint_as_float(v.y & 0xffff0000u);
-        v = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
-      }
     }
     *reinterpret_cast<u32x2*>(dst + e * FIRA_SPLIT_PITCH) = v;
   }
@@ -601,7 +619,7 @@ __device__ __forceinline__ void split_store_a(char* la, const float (&x)[4][4], 
 // One stage: 32 k of a plane product, `piece(j)`, j = 0..7, between its first multiplies (see proj_compute).
 template <int TM, typename Piece>
 __device__ __forceinline__ void split_compute(f32x16_t (&acc)[TM][2], const char* la, const char* lb, int a0, int b0, Piece piece) {
-  const int lane = fresh_lane();
+  const int lane = threadIdx.x & 63;
   bf16x8_t fa[2][TM], fb[2][2];
   auto read_a = [&](int kk, int t) {
     fa[kk][t] = *reinterpret_cast<const bf16x8_t*>(la + (a0 + 32 * t + (lane & 31)) * FIRA_SPLIT_PITCH + (2 * kk + (lane >> 5)) * 16);
@@ -641,14 +659,13 @@ __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds
   const unsigned lb0 = (unsigned)(size_t)(lds_ptr)lb;
   const int nblocks = (mt.S + 31) / 32, planes = mt.Sp / 32;
   const char* pb = reinterpret_cast<const char*>(mt.PT) + ((long long)b_row0 + 16 * TM * wave) * 64;
+  const int lane = threadIdx.x & 63, lrow = lane >> 2, store_at = split_store_at(threadIdx.x);
+  const unsigned offb = (unsigned)(lrow * 64 + ((lane & 3) ^ ring_swz(lrow)) * 16);
   // request q (of TM) of this wave's share of the projector's plane `pos` of sequence B, block kb
   auto request_b = [&](int pos, int kb, int slot, int q) {
-    const int lane = fresh_lane(), lrow = lane >> 2;
-    const unsigned offb = (unsigned)(lrow * 64 + ((lane & 3) ^ ring_swz(lrow)) * 16);
-    lds_dma16(pb + ((long long)(pos * planes + kb) * mt.rq) * 64 + q * 1024, offb,
-              (unsigned)__builtin_amdgcn_readfirstlane((int)(lb0 + (unsigned)(slot * SLOT + (TM * wave + q) * 1024))));
+    lds_dma16(pb + ((long long)(pos * planes + kb) * mt.rq) * 64 + q * 1024, offb, lb0 + (unsigned)(slot * SLOT + (TM * wave + q) * 1024));
   };
-  SplitALoader<LEFT, ASYNC> al{as_global(G), mt.ld, a_row0, mt.L, mt.S};
+  SplitALoader<LEFT, ASYNC> al(as_global(G), mt.ld, a_row0, mt.L, mt.S);
   // Block of 32 k of a plane product: requests of two stages are in flight while one is multiplied, each stage's the
   // projector's plane (TM instructions per wavefront), then the gradient's block (4, into the set of registers that is free).
   // The last two stages request the first two blocks again, which nobody reads: every stage is the same code, with no
@@ -660,26 +677,28 @@ __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds
 #pragma unroll
     for (int q = 0; q < TM; ++q) request_b(b.pos, b.kb, bslot, q);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) al.load_one(r, 32 * b.kb, q, fresh_thread());
+    for (int q = 0; q < 4; ++q) al.load_one(r, 32 * b.kb, q);
   };
   auto stage = [&](u32x4 (&r)[4], int aslot, int bslot, Block b) {
     if (nblocks == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (two stages would have the same lines of G in flight)
     wait_loads<ASYNC ? TM + 4 : 0>(r);           // this stage's operands have landed (guarded loads are the compiler's, of whatever number)
     float x[4][4];
-    const int t = fresh_thread();
-    al.unpack(r, 32 * b.kb, x, t);
+    al.unpack(r, 32 * b.kb, x);
     if (b.pos == 0) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) sq[e] += (x[e][0] * x[e][0] + x[e][1] * x[e][1]) + (x[e][2] * x[e][2] + x[e][3] * x[e][3]);
     }
-    split_store_a(lds + aslot * FIRA_SPLIT_PLANE, x, (0x610 >> (2 * b.pos)) & 3, t);   // sequence A: planes 0 0 1 0 2 1
+    char* dst = lds + aslot * FIRA_SPLIT_PLANE + store_at;       // sequence A: planes 0 0 1 0 2 1
+    if (b.pos == 4) split_store_plane<2>(dst, x);
+    else if (b.pos == 2 || b.pos == 5) split_store_plane<1>(dst, x);
+    else split_store_plane<0>(dst, x);
     // everybody's share is there, and everybody is done with the stage before
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const Block b2 = next(next(b));
     const int bslot2 = bslot == 0 ? 2 : bslot - 1;   // (bslot + 2) % 3: the slot of the stage before
     split_compute<TM>(acc, lds + aslot * FIRA_SPLIT_PLANE, lb + bslot * SLOT, a0, b0, [&](int j) {
       if (j < TM) request_b(b2.pos, b2.kb, bslot2, j);
-      else if (j >= 4) al.load_one(r, 32 * b2.kb, j - 4, fresh_thread());
+      else if (j >= 4) al.load_one(r, 32 * b2.kb, j - 4);
     });
   };
   Block b{0, 0};

@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRe
   }
   gptr<const float> Y = as_global<const float>(e.Y);
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int a0 = 64 * (wave >> 1), b0 = 64 * (wave & 1), b = split_b(t), kq = split_kq(t);
+  const int a0 = 64 * (wave >> 1), b0 = 64 * (wave & 1), b = split_b(t), kq = split_kq(t), store_at = split_store_at(t);
   const bool diag = ta == tb, upper = diag && wave == 1;      // (nobody asks for the wave above the diagonal)
   char* lb = diag ? lds : lds + 2 * FIRA_SPLIT_PLANE;
   f32x16_t hh[2][2], hm[2][2];
@@ -146,8 +146,8 @@ __global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRe
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i) x[i][j] = v[j][i];
-    split_store_a(dst, x, 0, t);
-    split_store_a(dst + FIRA_SPLIT_PLANE, x, 1, t);
+    split_store_plane<0>(dst + store_at, x);
+    split_store_plane<1>(dst + store_at + FIRA_SPLIT_PLANE, x);
   };
   fetch(0);
   for (int s0 = 0; s0 < e.S; s0 += 32) {
