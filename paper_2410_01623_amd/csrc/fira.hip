@@ -59,12 +59,16 @@ void* static_scratch_address(int* device_out, std::string* why) {
 
 namespace {
 
+constexpr int kComputeUnits = 256, kLdsPerCu = 160 * 1024;
+
 struct ListSlot {
   std::vector<int> idx;
   std::vector<void*> W;
   std::vector<const void*> G;
   int ntiles[kNumTileLists] = {};
   int rowblocks = 0;
+  int panel_lds = 0;           // LDS of the panel projection's widest listed matrix, 0 if none is listed
+  bool split_proj = false;     // fp32 matrices that it does not serve are listed
   // device views (inside the slab)
   FiraEnt* d_ents = nullptr;
   FiraTile* d_tiles[kNumTileLists] = {};
@@ -188,6 +192,17 @@ fira_status read_back_gates(fira_ctx* ctx) {
   return FIRA_OK;
 }
 
+// The projection of the listed fp32 matrices over the tile lists tl (left) and tr.
+void launch_fp32_project(hipStream_t q, const ListSlot* s, const FiraMat* mats, const FiraTile* tl, int nl, const FiraTile* tr, int nr, int norm_mode, int pack) {
+  const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
+  if (nl + nr == 0) return;
+  if (s->split_proj)
+    hipLaunchKernelGGL(fira_fp32_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_SPLIT_LDS, q, mats, s->d_ents, tl, nl, bl, tr, nr, norm_mode, pack,
+                       s->panel_lds != 0);
+  if (s->panel_lds)
+    hipLaunchKernelGGL(fira_panel_project_kernel, dim3(2 * (nl + nr)), dim3(256), s->panel_lds, q, mats, s->d_ents, tl, nl, tr, norm_mode, pack);
+}
+
 // Builds the work list of one fira_step call in pinned staging and returns its slot.
 ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W, const void* const* G,
                        fira_status* st) {
@@ -211,6 +226,23 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
   s->G.assign(G, G + count);
   const Plan& p = ctx->plan;
   build_work_list(p, count, idx, W, G, s->h_stage, s->ntiles, &s->rowblocks);
+  // fp32 projection: whole panels where all of them run at once, tiles otherwise (fira_panel_project_kernel)
+  long long panels = 0;
+  s->panel_lds = 0;
+  s->split_proj = false;
+  for (int e = 0; e < count; ++e) {
+    const FiraMat& m = p.mats[idx[e]].dev;
+    if (panel_projection(m)) {
+      panels += (m.L + FIRA_PANEL_F - 1) / FIRA_PANEL_F;
+      s->panel_lds = std::max(s->panel_lds, panel_lds(m.S));
+    } else if (m.kx != 1) {
+      s->split_proj = true;
+    }
+  }
+  if (s->panel_lds && panels > kComputeUnits * (kLdsPerCu / s->panel_lds)) {
+    s->panel_lds = 0;
+    s->split_proj = true;
+  }
   if (hipMemcpyAsync(s->d_block, s->h_stage, p.slot_bytes, hipMemcpyHostToDevice, ctx->stream) != hipSuccess ||
       hipEventRecord(s->uploaded, ctx->stream) != hipSuccess) { *st = FIRA_ERR_HIP; return nullptr; }
   s->valid = true;
@@ -289,6 +321,7 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   } while (0)
   // the contraction kernels use more dynamic LDS than the 64 KB default (gfx950 has 160 KB per CU)
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_PROJ_LDS));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_panel_project_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, panel_lds(FIRA_PANEL_MAX_S)));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_fp32_project_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_SPLIT_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<0, bf16_raw>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<1, bf16_raw>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
@@ -512,9 +545,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     if (nl + nr && s->ntiles[kTilesBackBf16])
       hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), blk, FIRA_PROJ_LDS, q, ctx->d_mats, s->d_ents,
                          s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, 0, (const FiraScal*)ctx->d_scal, hp);
-    if (nl + nr && s->ntiles[kTilesBackF32])
-      hipLaunchKernelGGL(fira_fp32_project_kernel, dim3(bl + br), blk, FIRA_SPLIT_LDS, q, ctx->d_mats, s->d_ents,
-                         s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, 0);
+    launch_fp32_project(q, s, ctx->d_mats, s->d_tiles[kTilesProjBigLeft], nl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, 0);
     nl = s->ntiles[kTilesProjSmallLeft]; nr = s->ntiles[kTilesProjSmallRight];
     bl = (nl + 7) / 8 * 8; br = (nr + 7) / 8 * 8;
     if (nl + nr)
@@ -975,8 +1006,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     if (nl + nr && bf16)
       hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_PROJ_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0, pack,
                          (const FiraScal*)ctx->d_scal, refresh_hp);
-    if (nl + nr && fp32)
-      hipLaunchKernelGGL(fira_fp32_project_kernel, dim3(bl + br), dim3(FIRA_PROJ_THREADS), FIRA_SPLIT_LDS, q, mats, ents_d, tl, nl, bl, tr, nr, 0, pack);
+    if (fp32) launch_fp32_project(q, s, mats, tl, nl, tr, nr, 0, pack);
   };
   for (int it = 0; it < iters; ++it) {
     // the basis as the projection's operand (in the place of the matrix's projector; no gate estimate needed here)

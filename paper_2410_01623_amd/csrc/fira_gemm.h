@@ -494,6 +494,9 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 // Loads never leave the matrix: a group of four that would is moved back and shifted in registers, rows
 // past the end read the last row; values past the contraction length are set to zero.
 // ------------------------------------------------------------------------------------------------
+#define FIRA_PANEL_MAX_S 416
+// fp32 matrices whose short side the panel kernel below can take
+__host__ __device__ __forceinline__ bool panel_projection(const FiraMat& mt) { return mt.kx != 1 && mt.S <= FIRA_PANEL_MAX_S; }
 #define FIRA_SPLIT_PITCH 80
 #define FIRA_SPLIT_PLANE (FIRA_PA * FIRA_SPLIT_PITCH)
 #define FIRA_SPLIT_LDS (2 * FIRA_SPLIT_PLANE + FIRA_RING_STAGES * FIRA_PROJ_RING_STAGE)
@@ -616,6 +619,16 @@ __device__ __forceinline__ void split_store_plane(char* dst, const float (&x)[4]
   }
 }
 
+// All three planes of four values.
+__device__ __forceinline__ void split3_planes(const float (&x)[4], u32x2 (&pl)[3]) {
+  float d[4] = {x[0], x[1], x[2], x[3]};
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    pl[p] = u32x2{pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3])};
+    d[0] -= __uint_as_float(pl[p].x << 16); d[1] -= __uint_as_float(pl[p].x & 0xffff0000u);
+    d[2] -= __uint_as_float(pl[p].y << 16); d[3] -= __uint_as_float(pl[p].y & 0xffff0000u);
+  }
+}
 // One stage: 32 k of a plane product, `piece(j)`, j = 0..7, between its first multiplies (see proj_compute).
 template <int TM, typename Piece>
 __device__ __forceinline__ void split_compute(f32x16_t (&acc)[TM][2], const char* la, const char* lb, int a0, int b0, Piece piece) {
@@ -716,21 +729,21 @@ __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds
   wait_loads<0>(ra[1]);
 }
 
-// A wave's 32 TM x 64 block of R, from row row0 and column col0: into Rt, or (the projector refresh) rounded to bf16 into the
+// A wave's 32 TM x 32 TN block of R, from row row0 and column col0: into Rt, or (the projector refresh) rounded to bf16 into the
 // K-blocked operand of the way back, `top` (rows = rank, K = factors).  A lane holds four consecutive factors of a
 // rank row, and a 32 x 32 block of the operand is 2 KB of contiguous memory.  Factors past the end are the
 // contraction's padding and are written as zeros; rank rows past r only feed columns that nobody stores.
 // (168 matrices of the 1B shapes at r = 512, twice a refresh: with T in fp32, a pass that packed it and one that cleared
 // the padding the way there took 1375 + 464 us, and 83 once; with the operand written here 1360.)
-template <int TM>
-__device__ __forceinline__ void store_projection(const f32x16_t (&acc)[TM][2], const FiraMat& mt, bf16_raw* top, int row0, int col0) {
+template <int TM, int TN = 2>
+__device__ __forceinline__ void store_projection(const f32x16_t (&acc)[TM][TN], const FiraMat& mt, bf16_raw* top, int row0, int col0) {
   const int lane = threadIdx.x & 63, hi4 = 4 * (lane >> 5);
   gptr<float> Rt = as_global(mt.Rt);
   gptr<bf16_raw> Top = as_global(top);
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-    for (int tn = 0; tn < 2; ++tn) {
+    for (int tn = 0; tn < TN; ++tn) {
       const int col = col0 + 32 * tn + (lane & 31), rb = row0 + 32 * tm;
       const f32x16_t& a = acc[tm][tn];
       if (top) {
@@ -870,14 +883,15 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_project_kernel(cons
   }
 }
 
+// panels: fira_panel_project_kernel serves the matrices that it can take.
 // The fp32 matrices of the same tile lists (the tiles of bf16 matrices leave at once, as those of fp32 ones do above; in
 // one kernel for both the two forms together took more registers than either).
 template <bool LEFT>
 __device__ __forceinline__ void project_fp32_tile(char* lds, const FiraMat* __restrict__ mats, const FiraEnt* __restrict__ ents,
-                                                  const FiraTile& tile, int norm_mode, int pack) {
+                                                  const FiraTile& tile, int norm_mode, int pack, int panels) {
   const FiraEnt ent = ents[tile.ent];
   const FiraMat mt = mats[ent.mat];
-  if (mt.kx == 1) return;
+  if (mt.kx == 1 || (panels && panel_projection(mt))) return;
   if (mt.r <= 64) project_split_tile<LEFT, 1>(lds, mt, ent, tile, norm_mode, pack);
   else if (mt.r <= 128) project_split_tile<LEFT, 2>(lds, mt, ent, tile, norm_mode, pack);
   else project_split_tile<LEFT, 4>(lds, mt, ent, tile, norm_mode, pack);
@@ -887,17 +901,194 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_fp32_project_kernel
                                                                                  const FiraTile* __restrict__ tiles_left, int ntiles_left,
                                                                                  int blocks_left,
                                                                                  const FiraTile* __restrict__ tiles_right, int ntiles_right,
-                                                                                 int norm_mode, int pack) {
+                                                                                 int norm_mode, int pack, int panels) {
   extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_SPLIT_LDS bytes
   if ((int)blockIdx.x < blocks_left) {
     const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
     if (ti < 0) return;
-    project_fp32_tile<true>(lds, mats, ents, tiles_left[ti], norm_mode, pack);
+    project_fp32_tile<true>(lds, mats, ents, tiles_left[ti], norm_mode, pack, panels);
   } else {
     const int ti = xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
     if (ti < 0) return;
-    project_fp32_tile<false>(lds, mats, ents, tiles_right[ti], norm_mode, pack);
+    project_fp32_tile<false>(lds, mats, ents, tiles_right[ti], norm_mode, pack, panels);
   }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Kernel 1 for fp32 matrices whose short side is at most FIRA_PANEL_MAX_S: the three planes of 64 whole factors fit in LDS.
+// A workgroup reads its panel of the gradient once and splits it once; the six plane products then run from LDS over all
+// rank columns, wave w with 32 factors x 32 TN rank components, the projector's fragments straight from memory into
+// registers (a 32 x 32 block of a plane is 2 KB of contiguous memory), U blocks of 32 k ahead.  No barrier after the
+// split, and a tenth of the instructions per multiply of the kernel above, whose 6 S / 32 stages in turn are what a small
+// matrix waits for.  Same products in the same order: R is the same bit for bit.
+// It holds a CU's LDS, so it is for lists whose panels all run at once (host: acquire_list); with more of them to a CU the
+// smaller tiles above keep the chip busier.  A step of 256 x 256 and 256 x 688 matrices at r = 64, with tiles and with panels:
+// 67 and 48 us for 49 panels, 78 and 60 for 196, 89 and 86 for 392, 130 and 143 for 784; of 400 x 400 and 400 x 800 at
+// r = 128: 103 and 75 us for 67 panels, 126 and 127 for 268, 197 and 220 for 536.  256 x 688 alone: 35 and 13 us of projection.
+// Row pitch of a plane: an odd number of 16-byte chunks, so that the fragment reads of sixteen rows are conflict-free.
+// ------------------------------------------------------------------------------------------------
+#define FIRA_PANEL_F 64
+__host__ __device__ __forceinline__ int panel_pitch(int S) { return ((S + 31) & ~31) * 2 + 16; }
+__host__ __device__ __forceinline__ int panel_lds(int S) { return FIRA_SPLIT_PLANES * FIRA_PANEL_F * panel_pitch(S); }
+
+template <int TN>
+__device__ __forceinline__ void panel_products(const char* lds, const FiraMat& mt, const FiraEnt& ent, int a_row0, int col0, int pack) {
+  constexpr int U = 6 / TN;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), hi = lane >> 5;
+  const int nblocks = (mt.S + 31) / 32, planes = mt.Sp / 32, pitch = panel_pitch(mt.S);
+  const int a0 = 32 * (wave & 1), b0 = col0 + 32 * TN * (wave >> 1);
+  const char* la = lds + (a0 + (lane & 31)) * pitch + hi * 16;
+  gptr<const char> pb = reinterpret_cast<gptr<const char>>(as_global<const bf16_raw>(mt.PT)) + (b0 + (lane & 31)) * 64 + hi * 16;
+  f32x16_t acc[1][TN];
+#pragma unroll
+  for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[0][tn][v] = 0.0f;
+  // the projector's plane pos of sequence B (as stored), block kb
+  struct Block { int pos, kb; };
+  auto next = [&](Block b) { return b.kb + 1 < nblocks ? Block{b.pos, b.kb + 1} : Block{b.pos == 5 ? 0 : b.pos + 1, 0}; };
+  u32x4 fb[2][U][2][TN];
+  Block ahead{0, 0}, b{0, 0};
+  auto request = [&](u32x4 (&f)[U][2][TN]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      gptr<const char> p = pb + (long long)(ahead.pos * planes + ahead.kb) * mt.rq * 64;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) f[u][kk][tn] = *reinterpret_cast<gptr<const u32x4>>(p + tn * 2048 + kk * 32);
+      ahead = next(ahead);
+    }
+  };
+  auto multiply = [&](const u32x4 (&f)[U][2][TN]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const char* pa = la + ((0x610 >> (2 * b.pos)) & 3) * (FIRA_PANEL_F * pitch) + b.kb * 64;   // sequence A: planes 0 0 1 0 2 1
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf16x8_t fa = *reinterpret_cast<const bf16x8_t*>(pa + kk * 32);
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+          acc[0][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, __builtin_bit_cast(bf16x8_t, f[u][kk][tn]), acc[0][tn], 0, 0, 0);
+      }
+      b = next(b);
+    }
+  };
+  // 6 nblocks blocks in groups of U, two groups at a time; an odd last group is multiplied by itself
+  const int groups = 6 * nblocks / U;
+  request(fb[0]);
+  for (int g = 0; g < groups; g += 2) {
+    if (g + 1 < groups) request(fb[1]);
+    multiply(fb[0]);
+    if (g + 1 < groups) {
+      if (g + 2 < groups) request(fb[0]);
+      multiply(fb[1]);
+    }
+  }
+  store_projection<1, TN>(acc, mt, pack ? reinterpret_cast<bf16_raw*>(ent.W) : nullptr, a_row0 + a0, b0);
+}
+
+template <bool LEFT>
+__device__ __forceinline__ void project_panel(char* lds, const FiraMat& mt, const FiraEnt& ent, int a_row0, int norm_mode, int pack) {
+  // Thread t: rows 4 b .. 4 b + 3 and k = 4 kq .. 4 kq + 3 of every second block of 32 k (b, kq as in the tiles above)
+  const int t = threadIdx.x & 127, half = threadIdx.x >> 7, b = split_b(t), kq = split_kq(t), pitch = panel_pitch(mt.S);
+  const int nblocks = (mt.S + 31) / 32, L = mt.L, S = mt.S;
+  gptr<const float> G = as_global(reinterpret_cast<const float*>(ent.G));
+  const bool wide = (LEFT ? L : S) >= 4;
+  float sq[4] = {0.f, 0.f, 0.f, 0.f};
+  char* dst = lds + 4 * b * pitch + 8 * kq;
+  constexpr int U = 4;                       // blocks in flight
+  for (int kb0 = half; kb0 < nblocks; kb0 += 2 * U) {
+    f32x4 v[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k0 = 32 * (kb0 + 2 * u);
+        v[u][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (k0 >= S) continue;
+        if (wide) {                          // a group of four that would leave the matrix is moved back (and shifted below)
+          const int row = LEFT ? min(a_row0 + 4 * b, L - 4) : min(a_row0 + 4 * b + q, L - 1);
+          const int k = LEFT ? min(k0 + 4 * kq + q, S - 1) : min(k0 + 4 * kq, S - 4);
+          v[u][q] = *reinterpret_cast<gptr<const f32x4_a4>>(G + (LEFT ? (long long)k * mt.ld + row : (long long)row * mt.ld + k));
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int k = k0 + 4 * kq + (LEFT ? q : e), row = a_row0 + 4 * b + (LEFT ? e : q);
+            if (k < S && row < L) v[u][q][e] = LEFT ? G[(long long)k * mt.ld + row] : G[(long long)row * mt.ld + k];
+          }
+        }
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k0 = 32 * (kb0 + 2 * u);
+      if (k0 >= S) break;
+      float x[4][4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        u32x4 w = __builtin_bit_cast(u32x4, v[u][q]);
+        if (wide) {
+          const int at = LEFT ? a_row0 + 4 * b : k0 + 4 * kq;
+          w = SplitALoader<LEFT, true>::shifted(w, at - min(at, (LEFT ? L : S) - 4));
+          if (LEFT && k0 + 4 * kq + q >= S) w = u32x4{0u, 0u, 0u, 0u};
+        }
+        const unsigned ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) (LEFT ? x[e][q] : x[q][e]) = __uint_as_float(ww[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sq[e] += (x[e][0] * x[e][0] + x[e][1] * x[e][1]) + (x[e][2] * x[e][2] + x[e][3] * x[e][3]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        u32x2 pl[3];
+        split3_planes(x[e], pl);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(dst + p * (FIRA_PANEL_F * pitch) + e * pitch + 2 * k0) = pl[p];
+      }
+    }
+  }
+  __syncthreads();
+  for (int col0 = 0; col0 < mt.r; ) {
+    if (mt.r - col0 <= 64) {
+      panel_products<1>(lds, mt, ent, a_row0, col0, pack);
+      col0 += 64;
+    } else {
+      panel_products<2>(lds, mt, ent, a_row0, col0, pack);
+      col0 += 128;
+    }
+  }
+  if (norm_mode == 1) {
+    float* part = reinterpret_cast<float*>(lds);      // [2][64]
+    __syncthreads();                                  // the products are done with the panel
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {                     // the eight threads that share a row, then the two halves
+      float s = sq[e];
+      s += __shfl_xor(s, 4, 64);
+      s += __shfl_xor(s, 8, 64);
+      s += __shfl_xor(s, 16, 64);
+      if (kq == 0) part[64 * half + 4 * b + e] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < FIRA_PANEL_F && a_row0 + (int)threadIdx.x < L) as_global(mt.g2)[a_row0 + threadIdx.x] = part[threadIdx.x] + part[64 + threadIdx.x];
+  }
+}
+
+// Two workgroups per tile of the projection's lists (which also hold other matrices and, above r = 256, further rank tiles).
+__global__ __launch_bounds__(256, 2) void fira_panel_project_kernel(const FiraMat* __restrict__ mats,
+                                                                    const FiraEnt* __restrict__ ents,
+                                                                    const FiraTile* __restrict__ tiles_left, int ntiles_left,
+                                                                    const FiraTile* __restrict__ tiles_right, int norm_mode, int pack) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];   // panel_lds(S) of the widest listed matrix
+  const int ti = blockIdx.x >> 1;
+  const bool left = ti < ntiles_left;
+  const FiraTile tile = left ? tiles_left[ti] : tiles_right[ti - ntiles_left];
+  if (tile.tb != 0) return;
+  const FiraEnt ent = ents[tile.ent];
+  const FiraMat mt = mats[ent.mat];
+  const int a_row0 = tile.ta * FIRA_PA + FIRA_PANEL_F * (blockIdx.x & 1);
+  if (!panel_projection(mt) || a_row0 >= mt.L) return;
+  if (left) project_panel<true>(lds, mt, ent, a_row0, norm_mode, pack);
+  else project_panel<false>(lds, mt, ent, a_row0, norm_mode, pack);
 }
 
 // ------------------------------------------------------------------------------------------------
