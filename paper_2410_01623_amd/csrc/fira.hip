@@ -60,6 +60,10 @@ void* static_scratch_address(int* device_out, std::string* why) {
 namespace {
 
 constexpr int kComputeUnits = 256, kLdsPerCu = 160 * 1024;
+// Back-projection tiles of a list up to which the update takes quarter tiles: three rounds of the whole tiles' 512 workgroups,
+// or, where bf16 operands of a rank above 256 are read twice as often for nothing by smaller tiles, not quite one
+// (fira_backproject_kernel has both sides measured).
+constexpr int kQuarterTiles = 1536, kQuarterTilesLongRank = 384;
 
 struct ListSlot {
   std::vector<int> idx;
@@ -67,6 +71,7 @@ struct ListSlot {
   std::vector<const void*> G;
   int ntiles[kNumTileLists] = {};
   int rowblocks = 0;
+  int max_r = 0;               // largest rank listed
   int panel_lds = 0;           // LDS of the panel projection's widest listed matrix, 0 if none is listed
   bool split_proj = false;     // fp32 matrices that it does not serve are listed
   // device views (inside the slab)
@@ -203,6 +208,18 @@ void launch_fp32_project(hipStream_t q, const ListSlot* s, const FiraMat* mats, 
     hipLaunchKernelGGL(fira_panel_project_kernel, dim3(2 * (nl + nr)), dim3(256), s->panel_lds, q, mats, s->d_ents, tl, nl, tr, norm_mode, pack);
 }
 
+// W -= lr alpha (P Z + c k G) over one of the back-projection's tile lists.
+template <typename T>
+void launch_update(hipStream_t q, fira_ctx* ctx, const ListSlot* s, int list, const FiraHp& hp) {
+  const int n = s->ntiles[list];
+  if (n <= (sizeof(T) == 2 && s->max_r > 256 ? kQuarterTilesLongRank : kQuarterTiles))
+    hipLaunchKernelGGL((fira_backproject_kernel<1, T, 2, 1>), dim3((4 * n + 7) / 8 * 8), dim3(FIRA_BACK_THREADS), (EpiShape<2, 1>::ALL), q,
+                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[list], n, ctx->d_partial, hp);
+  else
+    hipLaunchKernelGGL((fira_backproject_kernel<1, T>), dim3((n + 7) / 8 * 8), dim3(FIRA_BACK_THREADS), FIRA_BACK_LDS, q,
+                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[list], n, ctx->d_partial, hp);
+}
+
 // Builds the work list of one fira_step call in pinned staging and returns its slot.
 ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W, const void* const* G,
                        fira_status* st) {
@@ -228,10 +245,12 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
   build_work_list(p, count, idx, W, G, s->h_stage, s->ntiles, &s->rowblocks);
   // fp32 projection: whole panels where all of them run at once, tiles otherwise (fira_panel_project_kernel)
   long long panels = 0;
+  s->max_r = 0;
   s->panel_lds = 0;
   s->split_proj = false;
   for (int e = 0; e < count; ++e) {
     const FiraMat& m = p.mats[idx[e]].dev;
+    s->max_r = std::max(s->max_r, m.r);
     if (panel_projection(m)) {
       panels += (m.L + FIRA_PANEL_F - 1) / FIRA_PANEL_F;
       s->panel_lds = std::max(s->panel_lds, panel_lds(m.S));
@@ -642,14 +661,8 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       hipLaunchKernelGGL(fira_scale_update_kernel<float>, grid8(s->ntiles[kTilesBackF32]), dim3(256), 0, q,
                          ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[kTilesBackF32], s->ntiles[kTilesBackF32], hp);
   } else {
-    if (s->ntiles[kTilesBackBf16])
-      hipLaunchKernelGGL((fira_backproject_kernel<1, bf16_raw>), grid8(s->ntiles[kTilesBackBf16]), dim3(FIRA_BACK_THREADS), FIRA_BACK_LDS, q,
-                         ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[kTilesBackBf16], s->ntiles[kTilesBackBf16],
-                         ctx->d_partial, hp);
-    if (s->ntiles[kTilesBackF32])
-      hipLaunchKernelGGL((fira_backproject_kernel<1, float>), grid8(s->ntiles[kTilesBackF32]), dim3(FIRA_BACK_THREADS), FIRA_BACK_LDS, q,
-                         ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[kTilesBackF32], s->ntiles[kTilesBackF32],
-                         ctx->d_partial, hp);
+    if (s->ntiles[kTilesBackBf16]) launch_update<bf16_raw>(q, ctx, s, kTilesBackBf16, hp);
+    if (s->ntiles[kTilesBackF32]) launch_update<float>(q, ctx, s, kTilesBackF32, hp);
   }
   mark(6);
   FIRA_HIP(ctx, hipGetLastError());

@@ -72,13 +72,15 @@ struct GemmOperands {
   int wrapA = 0, wrapB = 0;   // ring core only: K blocks of 32 after which the operand repeats (Z in two planes meets P twice); 0 = never
 };
 
-// Fragments of one k-slice (16) of a wave's 128 (A) x 64 (B) block and its 8 MFMAs.
-struct Frags { bf16x8_t a[4], b[2]; };
-__device__ __forceinline__ void gemm_mfma_slice(f32x16_t (&acc)[4][2], const Frags& f) {
+// Fragments of one k-slice (16) of a wave's 32 TM (A) x 32 TN (B) block and its TM TN MFMAs.
+template <int TM, int TN>
+struct Frags { bf16x8_t a[TM], b[TN]; };
+template <int TM, int TN>
+__device__ __forceinline__ void gemm_mfma_slice(f32x16_t (&acc)[TM][TN], const Frags<TM, TN>& f) {
 #pragma unroll
-  for (int tm = 0; tm < 4; ++tm)
+  for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-    for (int tn = 0; tn < 2; ++tn)
+    for (int tn = 0; tn < TN; ++tn)
       acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[tm], f.b[tn], acc[tm][tn], 0, 0, 0);
 }
 // Sum of squares of the A fragments (v_dot2c_f32_bf16: two bf16 products per instruction): with the
@@ -121,11 +123,7 @@ __device__ __forceinline__ float frag_sumsq(const bf16x8_t& f, float sq) {
 // ------------------------------------------------------------------------------------------------
 #define FIRA_BACK_THREADS 256
 #define FIRA_RK 32
-#define FIRA_RING_A (FIRA_BA * 64)
-#define FIRA_RING_B (FIRA_BB * 64)
-#define FIRA_RING_STAGE (FIRA_RING_A + FIRA_RING_B)
 #define FIRA_RING_STAGES 3
-#define FIRA_RING_LDS (FIRA_RING_STAGES * FIRA_RING_STAGE)
 
 typedef __attribute__((address_space(3))) char* lds_ptr;
 
@@ -141,21 +139,28 @@ __device__ __forceinline__ void lds_dma16(const void* base, unsigned voff, unsig
                :: "v"(voff), "s"(base), "s"(lds_addr) : "memory");
 }
 
-__device__ __forceinline__ void ring_compute(f32x16_t (&acc)[4][2], const char* stage) {
+// Two wavefronts along either side, each with 32 TM (A) x 32 TN (B): (4, 2) is the tile above, (2, 1) a quarter of it for
+// launches that leave the chip idle otherwise.
+template <int TM, int TN>
+struct RingShape {
+  static constexpr int A = 64 * TM * 64, B = 64 * TN * 64, STAGE = A + B;   // bytes of a stage
+};
+template <int TM, int TN>
+__device__ __forceinline__ void ring_compute(f32x16_t (&acc)[TM][TN], const char* stage) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave & 1, wn = wave >> 1;
   const char* la = stage;
-  const char* lb = stage + FIRA_RING_A;
-  Frags f[2];
+  const char* lb = stage + RingShape<TM, TN>::A;
+  Frags<TM, TN> f[2];
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk) {
     const int chunk = 2 * kk + (lane >> 5);
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-      f[kk].a[t] = *reinterpret_cast<const bf16x8_t*>(la + ring_tile_off(wm * 128 + 32 * t + (lane & 31), chunk));
+    for (int t = 0; t < TM; ++t)
+      f[kk].a[t] = *reinterpret_cast<const bf16x8_t*>(la + ring_tile_off(wm * 32 * TM + 32 * t + (lane & 31), chunk));
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-      f[kk].b[t] = *reinterpret_cast<const bf16x8_t*>(lb + ring_tile_off(wn * 64 + 32 * t + (lane & 31), chunk));
+    for (int t = 0; t < TN; ++t)
+      f[kk].b[t] = *reinterpret_cast<const bf16x8_t*>(lb + ring_tile_off(wn * 32 * TN + 32 * t + (lane & 31), chunk));
   }
   gemm_mfma_slice(acc, f[0]);
   gemm_mfma_slice(acc, f[1]);
@@ -163,11 +168,13 @@ __device__ __forceinline__ void ring_compute(f32x16_t (&acc)[4][2], const char* 
 
 // Both operands K-blocked with lda / ldb padded rows (multiples of 256) and KB stored k (a multiple
 // of 64).
-__device__ __forceinline__ void ring_mainloop(f32x16_t (&acc)[4][2], char* lds, const GemmOperands& g) {
+template <int TM, int TN>
+__device__ __forceinline__ void ring_mainloop(f32x16_t (&acc)[TM][TN], char* lds, const GemmOperands& g) {
+  typedef RingShape<TM, TN> Shape;
 #pragma unroll
-  for (int tm = 0; tm < 4; ++tm)
+  for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-    for (int tn = 0; tn < 2; ++tn)
+    for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.0f;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -177,26 +184,27 @@ __device__ __forceinline__ void ring_mainloop(f32x16_t (&acc)[4][2], char* lds, 
   const int chunk = (lane & 3) ^ ring_swz(lrow);
   const unsigned off = (unsigned)(lrow * 64 + chunk * 16);   // inside a 16-row group (1 KB, contiguous)
   // this wave's first group of each operand in K block 0; a K block is rows * 64 bytes further
-  const char* pa = reinterpret_cast<const char*>((const bf16_raw*)g.A) + ((long long)g.a_row0 + 64 * wave) * 64;
-  const char* pb = reinterpret_cast<const char*>((const bf16_raw*)g.B) + ((long long)g.b_row0 + 32 * wave) * 64;
+  const char* pa = reinterpret_cast<const char*>((const bf16_raw*)g.A) + ((long long)g.a_row0 + 16 * TM * wave) * 64;
+  const char* pb = reinterpret_cast<const char*>((const bf16_raw*)g.B) + ((long long)g.b_row0 + 16 * TN * wave) * 64;
   auto issue = [&](int s) {
-    const unsigned dst = lds0 + (unsigned)((s % FIRA_RING_STAGES) * FIRA_RING_STAGE);
+    const unsigned dst = lds0 + (unsigned)((s % FIRA_RING_STAGES) * Shape::STAGE);
     const int sa = (g.wrapA && s >= g.wrapA) ? s - g.wrapA : s, sb = (g.wrapB && s >= g.wrapB) ? s - g.wrapB : s;
     const char* ka = pa + (long long)sa * g.lda * 64;
     const char* kb = pb + (long long)sb * g.ldb * 64;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) lds_dma16(ka + q * 1024, off, dst + (unsigned)((4 * wave + q) * 1024));
+    for (int q = 0; q < TM; ++q) lds_dma16(ka + q * 1024, off, dst + (unsigned)((TM * wave + q) * 1024));
 #pragma unroll
-    for (int q = 0; q < 2; ++q) lds_dma16(kb + q * 1024, off, dst + (unsigned)(FIRA_RING_A + (2 * wave + q) * 1024));
+    for (int q = 0; q < TN; ++q) lds_dma16(kb + q * 1024, off, dst + (unsigned)(Shape::A + (TN * wave + q) * 1024));
   };
   issue(0);
   if (KT > 1) issue(1);
   for (int s = 0; s < KT; ++s) {
-    // stage s has landed (this wave's share), then everybody's; everybody is also done with stage s-1
-    if (s + 1 < KT) asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");
+    // stage s has landed (this wave's share; the TM + TN requests of stage s + 1 may be in flight), then everybody's;
+    // everybody is also done with stage s-1
+    if (s + 1 < KT) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(TM + TN) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     if (s + 2 < KT) issue(s + 2);            // into the buffer of stage s-1
-    ring_compute(acc, lds + (s % FIRA_RING_STAGES) * FIRA_RING_STAGE);
+    ring_compute(acc, lds + (s % FIRA_RING_STAGES) * Shape::STAGE);
   }
 }
 
@@ -1242,30 +1250,31 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 4) void fira_project_small_kerne
 // block's A l and B h arrive in the places that are free by then.  350M shapes at r = 256, update: 1240 us, against
 // 1293 us with the six products one after the other through the ring.
 // ------------------------------------------------------------------------------------------------
-template <bool FIRST>
-__device__ __forceinline__ void back_split_compute(f32x16_t (&acc)[4][2], const char* la, const char* lb) {
+template <bool FIRST, int TM, int TN>
+__device__ __forceinline__ void back_split_compute(f32x16_t (&acc)[TM][TN], const char* la, const char* lb) {
   const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int a0 = 128 * (wave & 1), b0 = 64 * (wave >> 1);
+  const int a0 = 32 * TM * (wave & 1), b0 = 32 * TN * (wave >> 1);
+  constexpr int BLOCKS = TM * TN;
   // product i: A fragment FA(i) = 2 * plane (of la) + slice, B fragment FB(i) = 2 * plane (of lb) + slice
   constexpr int NA = FIRST ? 6 : 4, NB = FIRST ? 2 : 4;
   constexpr int FA[6] = {FIRST ? 4 : 2, FIRST ? 5 : 3, FIRST ? 2 : 0, FIRST ? 3 : 1, 0, 1};
   constexpr int FB[6] = {0, 1, FIRST ? 0 : 2, FIRST ? 1 : 3, 0, 1};
-  bf16x8_t fa[NA], fb[2][NB];
+  bf16x8_t fa[NA], fb[TN][NB];
   auto read_a = [&](int f, int t) {
-    fa[f] = *reinterpret_cast<const bf16x8_t*>(la + (f >> 1) * FIRA_RING_A + ring_tile_off(a0 + 32 * t + (lane & 31), 2 * (f & 1) + (lane >> 5)));
+    fa[f] = *reinterpret_cast<const bf16x8_t*>(la + (f >> 1) * RingShape<TM, TN>::A + ring_tile_off(a0 + 32 * t + (lane & 31), 2 * (f & 1) + (lane >> 5)));
   };
 #pragma unroll
   for (int f = 0; f < NA; ++f) read_a(f, 0);
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < TN; ++t)
 #pragma unroll
     for (int f = 0; f < NB; ++f)
-      fb[t][f] = *reinterpret_cast<const bf16x8_t*>(lb + (f >> 1) * FIRA_RING_B + ring_tile_off(b0 + 32 * t + (lane & 31), 2 * (f & 1) + (lane >> 5)));
+      fb[t][f] = *reinterpret_cast<const bf16x8_t*>(lb + (f >> 1) * RingShape<TM, TN>::B + ring_tile_off(b0 + 32 * t + (lane & 31), 2 * (f & 1) + (lane >> 5)));
   __builtin_amdgcn_sched_barrier(0);
   f32x16_t part[2];
 #pragma unroll
-  for (int blk = 0; blk < 8; ++blk) {
-    const int tm = blk >> 1, tn = blk & 1;
+  for (int blk = 0; blk < BLOCKS; ++blk) {
+    const int tm = blk / TN, tn = blk % TN;
     f32x16_t& p = part[blk & 1];
 #pragma unroll
     for (int v = 0; v < 16; ++v) p[v] = 0.0f;
@@ -1273,32 +1282,34 @@ __device__ __forceinline__ void back_split_compute(f32x16_t (&acc)[4][2], const 
     for (int i = 0; i < 6; ++i) {
       p = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[FA[i]], fb[tn][FB[i]], p, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
-      if (tn == 1 && tm < 3 && (FIRST || i < 2 || i > 3)) read_a(FA[i], tm + 1);   // after this fragment's last use
+      if (tn == TN - 1 && tm < TM - 1 && (FIRST || i < 2 || i > 3)) read_a(FA[i], tm + 1);   // after this fragment's last use
       if (blk > 0 && i >= 2) {
-        f32x16_t& d = acc[(blk - 1) >> 1][(blk - 1) & 1];
+        f32x16_t& d = acc[(blk - 1) / TN][(blk - 1) % TN];
 #pragma unroll
         for (int v = 4 * (i - 2); v < 4 * (i - 1); ++v) d[v] += part[(blk - 1) & 1][v];
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  acc[3][1] += part[1];
+  acc[TM - 1][TN - 1] += part[(BLOCKS - 1) & 1];
 }
 
 // nblocks: blocks of 32 k in use; kplane: blocks per stored plane.  The low-rank operand (A if left) stores the planes
 // h, m, l one after the other, the projector in sequence B (h m . l).
-__device__ __forceinline__ void split_mainloop(f32x16_t (&acc)[4][2], char* lds, const GemmOperands& g, int nblocks, int kplane, bool left) {
+template <int TM, int TN>
+__device__ __forceinline__ void split_mainloop(f32x16_t (&acc)[TM][TN], char* lds, const GemmOperands& g, int nblocks, int kplane, bool left) {
 #pragma unroll
-  for (int tm = 0; tm < 4; ++tm)
+  for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-    for (int tn = 0; tn < 2; ++tn)
+    for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.0f;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const unsigned lds0 = (unsigned)(size_t)(lds_ptr)lds;
-  const char* pa = reinterpret_cast<const char*>((const bf16_raw*)g.A) + ((long long)g.a_row0 + 64 * wave) * 64;
-  const char* pb = reinterpret_cast<const char*>((const bf16_raw*)g.B) + ((long long)g.b_row0 + 32 * wave) * 64;
-  // this wave's share of a plane of block kb: four requests of A's, two of B's
+  const char* pa = reinterpret_cast<const char*>((const bf16_raw*)g.A) + ((long long)g.a_row0 + 16 * TM * wave) * 64;
+  const char* pb = reinterpret_cast<const char*>((const bf16_raw*)g.B) + ((long long)g.b_row0 + 16 * TN * wave) * 64;
+  constexpr int RA = RingShape<TM, TN>::A, RB = RingShape<TM, TN>::B;
+  // this wave's share of a plane of block kb: TM requests of A's, TN of B's
   auto request = [&](const char* base, long long ld, bool lowrank, int pl, int kb, int dst, int n) {
     const int lane = fresh_lane(), lrow = lane >> 2;
     const unsigned off = (unsigned)(lrow * 64 + ((lane & 3) ^ ring_swz(lrow)) * 16);
@@ -1307,8 +1318,8 @@ __device__ __forceinline__ void split_mainloop(f32x16_t (&acc)[4][2], char* lds,
     for (int q = 0; q < 4; ++q)
       if (q < n) lds_dma16(src + q * 1024, off, (unsigned)__builtin_amdgcn_readfirstlane((int)(lds0 + (unsigned)(dst + (n * wave + q) * 1024))));
   };
-  auto request_a = [&](int pl, int kb) { request(pa, g.lda, left, pl, kb, pl * FIRA_RING_A, 4); };
-  auto request_b = [&](int pl, int kb) { request(pb, g.ldb, !left, pl, kb, 3 * FIRA_RING_A + pl * FIRA_RING_B, 2); };
+  auto request_a = [&](int pl, int kb) { request(pa, g.lda, left, pl, kb, pl * RA, TM); };
+  auto request_b = [&](int pl, int kb) { request(pb, g.ldb, !left, pl, kb, 3 * RA + pl * RB, TN); };
   request_a(2, 0);
   request_b(0, 0);
   auto block = [&](auto last, int kb) {
@@ -1317,14 +1328,14 @@ __device__ __forceinline__ void split_mainloop(f32x16_t (&acc)[4][2], char* lds,
     request_a(1, kb);
     request_b(1, kb);
     request_b(2, kb);
-    asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");   // all but B's m and l (four requests) have landed
-    back_split_compute<true>(acc, lds, lds + 3 * FIRA_RING_A);
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(2 * TN) : "memory");   // all but B's m and l have landed
+    back_split_compute<true>(acc, lds, lds + 3 * RA);
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     if (!decltype(last)::value) {
       request_a(2, kb + 1);
       request_b(0, kb + 1);
     }
-    back_split_compute<false>(acc, lds, lds + 3 * FIRA_RING_A + FIRA_RING_B);
+    back_split_compute<false>(acc, lds, lds + 3 * RA + RB);
   };
   for (int kb = 0; kb + 1 < nblocks; ++kb) block(std::false_type{}, kb);
   block(std::true_type{}, nblocks - 1);
@@ -1417,39 +1428,46 @@ struct Elem8<float> {
 // many passes before it is consumed, across the change of slab.
 // (The norm pass, MODE 0, over 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256: 271 us = 0.57 PFLOP/s; 628 us
 // while it had no loads in flight and spilled 72 registers.)
-#define FIRA_EPI_STRIDE 260   // floats per staged row: 256 + 4 (keeps 16-byte alignment, shifts banks)
-#define FIRA_EPI_SLAB (2 * 32 * FIRA_EPI_STRIDE * 4)
-#define FIRA_EPI_LDS (FIRA_EPI_SLAB + FIRA_BB * 4)   // the slabs, then one factor per tile row (matrices with m > n)
-#define FIRA_BACK_LDS (FIRA_EPI_LDS > FIRA_RING_LDS ? FIRA_EPI_LDS : FIRA_RING_LDS)
-template <int MODE, typename T, bool INTERIOR>
-__device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[4][2], char* lds, const FiraMat& mt,
+template <int TM, int TN>
+struct EpiShape {
+  static constexpr int COLS = 64 * TM, ROWS = 64 * TN;         // of the tile (n side, m side)
+  static constexpr int STRIDE = COLS + 4;                      // floats per staged row (keeps 16-byte alignment, shifts banks)
+  static constexpr int SLAB = 2 * 32 * STRIDE * 4;
+  static constexpr int LDS = SLAB + ROWS * 4;                  // the slabs, then one factor per tile row (matrices with m > n)
+  static constexpr int RING = FIRA_RING_STAGES * RingShape<TM, TN>::STAGE, ALL = LDS > RING ? LDS : RING;
+};
+#define FIRA_BACK_LDS (EpiShape<4, 2>::ALL)
+template <int MODE, typename T, bool INTERIOR, int TM, int TN>
+__device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[TM][TN], char* lds, const FiraMat& mt,
                                                       const FiraEnt& ent, int i0, int j0, float c, float lr_alpha, bool unitk) {
   typedef typename Elem8<T>::Raw Raw;
   // passes in flight: 64 registers of G and W values beside the accumulators
-  constexpr int DEPTH = sizeof(T) == 2 ? 8 : 4;
+  typedef EpiShape<TM, TN> Shape;
+  constexpr int LANES = 8 * TM, PROWS = 64 / LANES, PASSES = 16 / PROWS;   // lanes of a row, rows of a pass, passes of a wave's share of a slab
+  constexpr int DEPTH = PASSES * TN < 8 ? PASSES * TN : sizeof(T) == 2 ? 8 : 4;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave & 1, wn = wave >> 1;
-  float* buf = reinterpret_cast<float*>(lds) + wn * (32 * FIRA_EPI_STRIDE);
-  float* rowphi = reinterpret_cast<float*>(lds + FIRA_EPI_SLAB);
+  float* buf = reinterpret_cast<float*>(lds) + wn * (32 * Shape::STRIDE);
+  float* rowphi = reinterpret_cast<float*>(lds + Shape::SLAB);
   gptr<const T> G = as_global(reinterpret_cast<const T*>(ent.G));
   gptr<T> W = as_global(reinterpret_cast<T*>(ent.W));
   gptr<const float> phi = as_global<const float>(mt.phi);
-  const int jl = 8 * (lane & 31);             // this lane's 8 columns inside the staged 256
-  const int ih = lane >> 5;                   // which of the two rows of a pass
+  const int jl = 8 * (lane % LANES);          // this lane's 8 columns inside the staged 64 TM
+  const int ih = lane / LANES;                // which of the rows of a pass
   const long long j = (long long)j0 + jl;
-  // slab tn holds tile rows wn*64 + 32*tn .. +31; this wave consumes 16 of them, two per pass.
+  // slab tn holds tile rows 32 TN wn + 32 tn .. +31; this wave consumes 16 of them.
   // Interior tiles address a pass as a wave-uniform row pointer plus one 32-bit lane offset.
-  const long long wave_row0 = (long long)i0 + wn * 64 + 16 * wm;
+  const long long wave_row0 = (long long)i0 + wn * 32 * TN + 16 * wm;
   const long long lane_off = (unsigned)(ih * (int)mt.ld + jl);
-  auto slab_row = [&](int p) { return 16 * wm + 2 * p + ih; };
-  auto fetch = [&](int q, Raw& gr, Raw& wr) {   // pass q = 8 * slab + pass of the slab
-    const int tn = q >> 3, p = q & 7;
+  auto slab_row = [&](int p) { return 16 * wm + PROWS * p + ih; };
+  auto fetch = [&](int q, Raw& gr, Raw& wr) {   // pass q = PASSES * slab + pass of the slab
+    const int tn = q / PASSES, p = q % PASSES;
     if (INTERIOR) {
-      const long long base = (wave_row0 + 32 * tn + 2 * p) * mt.ld + j0;
+      const long long base = (wave_row0 + 32 * tn + PROWS * p) * mt.ld + j0;
       gr = Elem8<T>::template load_raw<true>(G + base, lane_off, 0);
       if (MODE == 1) wr = Elem8<T>::template load_raw<true>(W + base, lane_off, 0);
     } else {
-      const long long i = (long long)i0 + wn * 64 + 32 * tn + slab_row(p);
+      const long long i = (long long)i0 + wn * 32 * TN + 32 * tn + slab_row(p);
       const bool ok = i < mt.m && j < mt.n;
       gr = ok ? Elem8<T>::template load_raw<false>(G + i * mt.ld, j, mt.n) : Elem8<T>::zero();
       if (MODE == 1) wr = ok ? Elem8<T>::template load_raw<false>(W + i * mt.ld, j, mt.n) : Elem8<T>::zero();
@@ -1465,39 +1483,39 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[4][2], cha
   }
   float sum = 0.0f;
 #pragma unroll
-  for (int tn = 0; tn < 2; ++tn) {
+  for (int tn = 0; tn < TN; ++tn) {
     __syncthreads();  // previous slab fully consumed (first time: the main loop's LDS reads are done)
-    // One factor per row (m > n): the tile's 128 go through LDS.  Loaded from global memory inside a pass
+    // One factor per row (m > n): the tile's go through LDS.  Loaded from global memory inside a pass
     // they would have to be waited for there, and the memory counter being in order, that wait would
     // cover every request in flight for the later passes.
-    if (tn == 0 && !mt.left && threadIdx.x < FIRA_BB) {
+    if (tn == 0 && !mt.left && threadIdx.x < Shape::ROWS) {
       const long long i = (long long)i0 + threadIdx.x;
       rowphi[threadIdx.x] = (INTERIOR || i < mt.m) ? (unitk ? c : c * phi[i]) : 0.0f;
     }
 #pragma unroll
-    for (int tm = 0; tm < 4; ++tm)
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
       for (int vg = 0; vg < 4; ++vg) {
         const f32x16_t& a = acc[tm][tn];
         const f32x4 val = f32x4{a[4 * vg], a[4 * vg + 1], a[4 * vg + 2], a[4 * vg + 3]};
-        *reinterpret_cast<f32x4*>(buf + (lane & 31) * FIRA_EPI_STRIDE + 128 * wm + 32 * tm + 8 * vg + 4 * (lane >> 5)) = val;
+        *reinterpret_cast<f32x4*>(buf + (lane & 31) * Shape::STRIDE + 32 * TM * wm + 32 * tm + 8 * vg + 4 * (lane >> 5)) = val;
       }
     __syncthreads();
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
+    for (int p = 0; p < PASSES; ++p) {
       const int il = slab_row(p);
-      const long long i = (long long)i0 + wn * 64 + 32 * tn + il;
-      const int q = 8 * tn + p;
+      const long long i = (long long)i0 + wn * 32 * TN + 32 * tn + il;
+      const int q = PASSES * tn + p;
       Raw& gr = gbuf[q % DEPTH];
       Raw& wr = wbuf[MODE == 1 ? q % DEPTH : 0];
       if (INTERIOR || (i < mt.m && j < mt.n)) {
-        const f32x4 u0 = *reinterpret_cast<const f32x4*>(buf + il * FIRA_EPI_STRIDE + jl);
-        const f32x4 u1 = *reinterpret_cast<const f32x4*>(buf + il * FIRA_EPI_STRIDE + jl + 4);
+        const f32x4 u0 = *reinterpret_cast<const f32x4*>(buf + il * Shape::STRIDE + jl);
+        const f32x4 u1 = *reinterpret_cast<const f32x4*>(buf + il * Shape::STRIDE + jl + 4);
         const float u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
         float g[8];
         Elem8<T>::unpack(gr, g);
         if (!mt.left) {
-          const float f = rowphi[wn * 64 + 32 * tn + il];
+          const float f = rowphi[wn * 32 * TN + 32 * tn + il];
 #pragma unroll
           for (int e = 0; e < 8; ++e) cphi[e] = f;
         }
@@ -1512,11 +1530,11 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[4][2], cha
           Elem8<T>::unpack(wr, w);
 #pragma unroll
           for (int e = 0; e < 8; ++e) w[e] = w[e] - lr_alpha * (u[e] + cphi[e] * g[e]);
-          if (INTERIOR) Elem8<T>::template store<true>(w, W + ((wave_row0 + 32 * tn + 2 * p) * mt.ld + j0), lane_off, 0);
+          if (INTERIOR) Elem8<T>::template store<true>(w, W + ((wave_row0 + 32 * tn + PROWS * p) * mt.ld + j0), lane_off, 0);
           else Elem8<T>::template store<false>(w, W + i * mt.ld, j, mt.n);
         }
       }
-      if (q + DEPTH < 16) fetch(q + DEPTH, gr, wr);
+      if (q + DEPTH < PASSES * TN) fetch(q + DEPTH, gr, wr);
       // Nothing is stored in the norm pass, so nothing but this keeps the compiler from gathering every pass's loads at
       // the top and the whole chain of additions at the end, with all values spilled in between.
       if (MODE == 0) asm volatile("" : "+v"(sum) :: "memory");
@@ -1526,8 +1544,15 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[4][2], cha
 }
 
 // T: storage type of W and G of every matrix in the tile list (the host keeps one list per type).
-template <int MODE, typename T>
-__global__ __launch_bounds__(FIRA_BACK_THREADS, 2) void fira_backproject_kernel(const FiraMat* __restrict__ mats,
+// (TM, TN) = (2, 1): four workgroups of 128 x 64 per listed tile, which fill the chip for lists of few tiles (host: launch_update);
+// the norm pass, whose partial sums are laid out by tile, has the one form.  A step with whole and with quarter tiles, by
+// the whole tiles of its list: 256 x 688 in fp32 (6) 42 and 31 us; bf16, 512 x 512 and 512 x 1376 at r = 128: 59 and 51 (102),
+// 95 and 90 (816); 1024 x 1024 and 1024 x 2736: r = 192 172 and 166 (1568), 320 and 323 (3136); r = 256 137 and 130 (784), 192 and
+// 187 (1568), 255 and 261 (2352), 1156 and 1207 (12544); r = 512 222 and 230 (1176); 1024 x 1024 at r = 512 98 and 102 (448);
+// 2048 x 5461 at r = 512 196 and 183 (352), with 2048 x 2048 510 and 534 (3120); fp32, 1024 x 2736: r = 512 523 and 510 (784),
+// r = 400 698 and 700 (1176), r = 256 3143 and 3212 (9408).
+template <int MODE, typename T, int TM = 4, int TN = 2>
+__global__ __launch_bounds__(FIRA_BACK_THREADS, TM == 4 ? 2 : sizeof(T) == 4 ? 3 : 4) void fira_backproject_kernel(const FiraMat* __restrict__ mats,
                                                                            const FiraScal* __restrict__ scal,
                                                                            const FiraEnt* __restrict__ ents,
                                                                            const FiraTile* __restrict__ tiles,
@@ -1535,21 +1560,25 @@ __global__ __launch_bounds__(FIRA_BACK_THREADS, 2) void fira_backproject_kernel(
                                                                            FiraHp hp) {
   extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_BACK_LDS bytes
   __shared__ float red[4];
-  const int ti = xcd_chunked_index(blockIdx.x, ntiles);
-  if (ti < 0) return;
-  const FiraTile tile = tiles[ti];
+  static_assert(TM == 4 || MODE == 1, "partial sums are laid out by tile");
+  constexpr int PARTS = 8 / (TM * TN);           // workgroups of a listed tile
+  const int wi = xcd_chunked_index(blockIdx.x, ntiles * PARTS);
+  if (wi < 0) return;
+  const int sub = wi % PARTS;
+  const FiraTile tile = tiles[wi / PARTS];
   const FiraEnt ent = ents[tile.ent];
   if (MODE == 0 && use_gram(hp, scal[ent.mat])) return;   // this matrix takes the Gram route to ||S||
   const FiraMat mt = mats[ent.mat];
+  if (PARTS > 1 && (tile.ta * FIRA_BA + 64 * TM * (sub & 1) >= mt.n || tile.tb * FIRA_BB + 64 * TN * (sub >> 1) >= mt.m)) return;
   const float lr_alpha = MODE == 1 ? *hp.lr_alpha : 0.0f;
 
   // Y (n side) is the A operand, X (m side) the B operand.
   gptr<const bf16_raw> lowrank = as_global<const bf16_raw>((MODE == 0) ? mt.Rb : mt.Nb);
   gptr<const bf16_raw> proj = as_global<const bf16_raw>(mt.Pn);
   GemmOperands g;
-  g.a_row0 = tile.ta * FIRA_BA;
+  g.a_row0 = tile.ta * FIRA_BA + 64 * TM * (sub & 1);
   g.a_rows = mt.n;
-  g.b_row0 = tile.tb * FIRA_BB;
+  g.b_row0 = tile.tb * FIRA_BB + 64 * TN * (sub >> 1);
   g.b_rows = mt.m;
   // Z in two planes (hi + lo): the contraction runs over 2 rp, and the projector's K blocks are used twice
   const bool split = MODE == 1 && hp.zsplit && mt.zready && mt.kx == 1 && hp.scaling != 1;
@@ -1560,18 +1589,18 @@ __global__ __launch_bounds__(FIRA_BACK_THREADS, 2) void fira_backproject_kernel(
   g.B = mt.left ? proj : lowrank;
   g.lda = mt.left ? mt.Lq : mt.Sq;
   g.ldb = mt.left ? mt.Sq : mt.Lq;
-  f32x16_t acc[4][2];
+  f32x16_t acc[TM][TN];
   if (sizeof(T) == 4) split_mainloop(acc, lds, g, (mt.r + 31) / 32, mt.rp / 32, mt.left != 0);
   else ring_mainloop(acc, lds, g);
 
   const float c = (MODE == 0) ? 1.0f : scal[ent.mat].c;
   const int i0 = g.b_row0, j0 = g.a_row0;
-  const bool interior = i0 + FIRA_BB <= mt.m && j0 + FIRA_BA <= mt.n;
+  const bool interior = i0 + 64 * TN <= mt.m && j0 + 64 * TM <= mt.n;
   float sum;
   // matrix-level factor: the residual norm is taken with unit factors and scaled by the limiter kernel
   const bool unitk = MODE == 0 && hp.scaling == 1;
-  if (interior) sum = backproject_epilogue<MODE, T, true>(acc, lds, mt, ent, i0, j0, c, lr_alpha, unitk);
-  else sum = backproject_epilogue<MODE, T, false>(acc, lds, mt, ent, i0, j0, c, lr_alpha, unitk);
+  if (interior) sum = backproject_epilogue<MODE, T, true, TM, TN>(acc, lds, mt, ent, i0, j0, c, lr_alpha, unitk);
+  else sum = backproject_epilogue<MODE, T, false, TM, TN>(acc, lds, mt, ent, i0, j0, c, lr_alpha, unitk);
 
   if (MODE == 0) {
     // deterministic workgroup reduction: xor-butterfly inside each wave, then waves in order
