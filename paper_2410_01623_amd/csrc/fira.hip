@@ -624,12 +624,15 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     launch_project(want_g2);
     mark(1);
     // 2. Adam on R, factor norms
-    if (s->ntiles[kTilesBackBf16])
-      hipLaunchKernelGGL(fira_adam_kernel<1>, dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds * (ctx->zsplit ? 2 : 1), q, ctx->d_mats, ctx->d_scal,
-                         s->d_ents, count, s->rowblocks, hp);
+    if (s->ntiles[kTilesBackBf16]) {
+      const int planes = ctx->zsplit ? 2 : 1;
+      const int lds = std::max(ctx->plan.adam_lds * planes, need_residual ? ctx->plan.adam_lds_staged * (planes + 1) : 0);
+      hipLaunchKernelGGL(fira_adam_kernel<1>, dim3(s->rowblocks), dim3(256), lds, q, ctx->d_mats, ctx->d_scal,
+                         s->d_ents, count, s->rowblocks, need_residual ? 1 : 0, hp);
+    }
     if (s->ntiles[kTilesBackF32])
       hipLaunchKernelGGL(fira_adam_kernel<FIRA_KX_SPLIT>, dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds_f32, q, ctx->d_mats, ctx->d_scal,
-                         s->d_ents, count, s->rowblocks, hp);
+                         s->d_ents, count, s->rowblocks, 0, hp);
     mark(2);
   } else {
     mark(1);

@@ -28,6 +28,7 @@ typedef f32x4 __attribute__((aligned(4))) f32x4_a4;
 #define FIRA_KX_SPLIT 6
 #define FIRA_SPLIT_PLANES 3   // planes that the data operands store (the sequences repeat them)
 #define FIRA_ZREADY_MAX_R 1024
+#define FIRA_RSTAGE_MAX_R 512  // largest rank whose R the Adam kernel collects in LDS on the residual route
 #define FIRA_ZREADY_MAX_R_F32 512   // fp32 rows have three planes: 48 KB of LDS for sixteen of them
 
 // Immutable description of one weight matrix (device array, one element per matrix).

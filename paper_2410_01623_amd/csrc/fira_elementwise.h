@@ -159,9 +159,10 @@ __device__ __forceinline__ void bf16_planes(const f32x4& z, int planes, u32x2 (&
 // block, so the workgroup's 16 rows are collected in LDS ([K block][16 rows][32]) and leave as
 // 1 KB contiguous pieces (fira_adam_kernel).  fp32 matrices move 26 bytes per element here; with N and R written
 // as planes and turned into Z by a pass of their own it was 92 (350M shapes at r = 256: 916 + 602 -> 364 us).
+// rl: the same image of R for bf16 matrices on the residual route (null: R goes out from here, in 64-byte pieces).
 template <int KX, int NIT>   // 256 * NIT >= r
 __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp& hp, float bias, long long row, bool gram,
-                                                bf16_raw* zl, int rowlocal) {
+                                                bf16_raw* zl, bf16_raw* rl, int rowlocal) {
   const int lane = threadIdx.x & 63;
   const int r = mt.r;
   gptr<const float> R = as_global<const float>(mt.Rt) + row * r;
@@ -201,7 +202,7 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
       zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};
       if (a < r) {
         bf16_planes<KX>(nv[it] - k * rv[it], planes, zp);
-        if (!gram) {
+        if (!gram && !rl) {
           u32x2 rb[3];
           bf16_planes<KX>(rv[it], KX == 1 ? 1 : 3, rb);
 #pragma unroll
@@ -209,10 +210,11 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
             *reinterpret_cast<gptr<u32x2>>(Rb + kblk_index(mt.Lq, row, p * mt.rp + a)) = rb[p];
         }
       }
-      bf16_raw* dst = zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + rowlocal * 32 + (a & 31);
+      const int at = (a >> 5) * (FIRA_ROWS_PER_WG * 32) + rowlocal * 32 + (a & 31);
 #pragma unroll
       for (int p = 0; p < (KX == 1 ? 2 : 3); ++p)
-        if (p < planes) *reinterpret_cast<u32x2*>(dst + p * plane_off) = zp[p];
+        if (p < planes) *reinterpret_cast<u32x2*>(zl + at + p * plane_off) = zp[p];
+      if (KX == 1 && rl) *reinterpret_cast<u32x2*>(rl + at) = a < r ? pack_bf16x4(rv[it]) : u32x2{0u, 0u};
     }
   }
   if (lane == 0) {
@@ -225,7 +227,7 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
 // a wavefront takes its four rows at once, 16 lanes per row, instead of one after the other.
 template <int KX>
 __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp& hp, float bias, long long row_base,
-                                                 bool gram, bf16_raw* zl, int wave) {
+                                                 bool gram, bf16_raw* zl, bf16_raw* rl, int wave) {
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4, a = (lane & 15) * 4;
   const int r = mt.r;
@@ -263,7 +265,7 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
     zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};   // rows beyond L and columns beyond r: the operand's zero padding
     if (live) {
       bf16_planes<KX>(nv - k * rv, planes, zp);
-      if (!gram) {
+      if (!gram && !rl) {
         u32x2 rb[3];
         bf16_planes<KX>(rv, KX == 1 ? 1 : 3, rb);
 #pragma unroll
@@ -271,10 +273,11 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
           *reinterpret_cast<gptr<u32x2>>(as_global(mt.Rb) + kblk_index(mt.Lq, row, p * mt.rp + a)) = rb[p];
       }
     }
-    bf16_raw* dst = zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + g) * 32 + (a & 31);
+    const int at = (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + g) * 32 + (a & 31);
 #pragma unroll
     for (int p = 0; p < (KX == 1 ? 2 : 3); ++p)
-      if (p < planes) *reinterpret_cast<u32x2*>(dst + p * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32)) = zp[p];
+      if (p < planes) *reinterpret_cast<u32x2*>(zl + at + p * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32)) = zp[p];
+    if (KX == 1 && rl) *reinterpret_cast<u32x2*>(rl + at) = live ? pack_bf16x4(rv) : u32x2{0u, 0u};
   }
   if ((lane & 15) == 0 && row < mt.L) {
     as_global(mt.phi)[row] = k;
@@ -282,14 +285,17 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
   }
 }
 
+// stage_r: the launch's LDS has room for R beside Z (bf16 matrices with r <= FIRA_RSTAGE_MAX_R on the residual route): R, too, then
+// leaves in pieces of 1 KB.  Above that rank the image would halve the wavefronts in flight.  Adam on the residual route over
+// 168 matrices of the 1B shapes at r = 512: 1420 us, 1725 with R in 64-byte pieces; 350M shapes at r = 256: 346, 397.
 // KX: the matrices that this launch serves, bf16 (1) or fp32 (FIRA_KX_SPLIT); the row-blocks of the others leave.
 // (One kernel for both took ten registers too many for four wavefronts per SIMD, and 2 % of the bf16 time.)
 template <int KX>
 __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __restrict__ mats,
                                                         const FiraScal* __restrict__ scal,
                                                         const FiraEnt* __restrict__ ents, int count,
-                                                        int total_rowblocks, FiraHp hp) {
-  extern __shared__ __attribute__((aligned(16))) char adam_lds[];   // zready matrices: 16 rows x planes x rp bf16
+                                                        int total_rowblocks, int stage_r, FiraHp hp) {
+  extern __shared__ __attribute__((aligned(16))) char adam_lds[];   // zready matrices: 16 rows x planes x rp bf16 (and R's)
   const int rb = blockIdx.x;
   if (rb >= total_rowblocks) return;
   const int e = find_entry(ents, count, rb);
@@ -308,20 +314,22 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const int wave = threadIdx.x >> 6;
   const long long row_base = (long long)(rb - ent.row0) * FIRA_ROWS_PER_WG + wave * 4;
   const int planes = z_planes<KX>(hp);
-  if (zready && mt.r <= 64) adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, wave);
+  const bool staged = KX == 1 && stage_r && zready && !gram && mt.r <= FIRA_RSTAGE_MAX_R;
+  bf16_raw* rl = staged ? zl + planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32) : nullptr;
+  if (zready && mt.r <= 64) adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, rl, wave);
   else for (int i = 0; i < 4; ++i) {
     const long long row = row_base + i;
     if (row >= mt.L) {
       if (zready)   // rows of the padding: zeros
-        for (int a = (threadIdx.x & 63) * 4; a < planes * mt.rp; a += 256)
+        for (int a = (threadIdx.x & 63) * 4; a < (planes + (staged ? 1 : 0)) * mt.rp; a += 256)
           *reinterpret_cast<u32x2*>(zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + i) * 32 + (a & 31)) = u32x2{0u, 0u};
       continue;
     }
     if (zready) {
       constexpr int max_nit = (KX == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32) / 256;
-      if (mt.r <= 256) adam_row_zready<KX, 1>(mt, hp, bias, row, gram, zl, wave * 4 + i);
-      else if (mt.r <= 512) adam_row_zready<KX, 2>(mt, hp, bias, row, gram, zl, wave * 4 + i);
-      else if (max_nit > 2) adam_row_zready<KX, max_nit>(mt, hp, bias, row, gram, zl, wave * 4 + i);
+      if (mt.r <= 256) adam_row_zready<KX, 1>(mt, hp, bias, row, gram, zl, rl, wave * 4 + i);
+      else if (mt.r <= 512) adam_row_zready<KX, 2>(mt, hp, bias, row, gram, zl, rl, wave * 4 + i);
+      else if (max_nit > 2) adam_row_zready<KX, max_nit>(mt, hp, bias, row, gram, zl, rl, wave * 4 + i);
     } else if (KX == 1) {
       if ((mt.r & 3) == 0) adam_row<1, 4>(mt, hp, bias, row, gram); else adam_row<1, 1>(mt, hp, bias, row, gram);
     } else {
@@ -331,14 +339,17 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   if (zready) {
     __syncthreads();
     // the 16 rows of one K block are 1 KB of contiguous memory
-    gptr<char> nb = reinterpret_cast<gptr<char>>(as_global(mt.Nb));
     const long long row0 = (long long)(rb - ent.row0) * FIRA_ROWS_PER_WG;
-    const int nbytes = planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 64);   // plane p: K blocks from p rp/32
-    for (int o = threadIdx.x * 16; o < nbytes; o += 256 * 16) {
-      const int kb = o / (FIRA_ROWS_PER_WG * 64), w = o % (FIRA_ROWS_PER_WG * 64);
-      *reinterpret_cast<gptr<u32x4>>(nb + ((long long)kb * mt.Lq + row0) * 64 + w) =
-          *reinterpret_cast<const u32x4*>(adam_lds + o);
-    }
+    auto flush = [&](bf16_raw* op, const char* image, int nplanes) {      // plane p: K blocks from p rp/32
+      gptr<char> out = reinterpret_cast<gptr<char>>(as_global(op));
+      const int nbytes = nplanes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 64);
+      for (int o = threadIdx.x * 16; o < nbytes; o += 256 * 16) {
+        const int kb = o / (FIRA_ROWS_PER_WG * 64), w = o % (FIRA_ROWS_PER_WG * 64);
+        *reinterpret_cast<gptr<u32x4>>(out + ((long long)kb * mt.Lq + row0) * 64 + w) = *reinterpret_cast<const u32x4*>(image + o);
+      }
+    };
+    flush(mt.Nb, adam_lds, planes);
+    if (staged) flush(mt.Rb, reinterpret_cast<const char*>(rl), 1);
   }
 }
 

@@ -746,29 +746,35 @@ __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds
 template <int TM, int TN = 2>
 __device__ __forceinline__ void store_projection(const f32x16_t (&acc)[TM][TN], const FiraMat& mt, bf16_raw* top, int row0, int col0) {
   const int lane = threadIdx.x & 63, hi4 = 4 * (lane >> 5);
-  gptr<float> Rt = as_global(mt.Rt);
-  gptr<bf16_raw> Top = as_global(top);
+  if (top) {
+    gptr<bf16_raw> Top = as_global(top);
 #pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn) {
-      const int col = col0 + 32 * tn + (lane & 31), rb = row0 + 32 * tm;
-      const f32x16_t& a = acc[tm][tn];
-      if (top) {
+      for (int tn = 0; tn < TN; ++tn) {
+        const int col = col0 + 32 * tn + (lane & 31), rb = row0 + 32 * tm;
         if (rb >= ((mt.L + 63) & ~63)) continue;
 #pragma unroll
         for (int vg = 0; vg < 4; ++vg) {
+          const f32x16_t& a = acc[tm][tn];
           const int row = rb + 8 * vg + hi4, live = mt.L - row;
           *reinterpret_cast<gptr<u32x2>>(Top + kblk_index(mt.rq, col, row)) =
               u32x2{pack_bf16x2(live > 0 ? a[4 * vg] : 0.0f, live > 1 ? a[4 * vg + 1] : 0.0f),
                     pack_bf16x2(live > 2 ? a[4 * vg + 2] : 0.0f, live > 3 ? a[4 * vg + 3] : 0.0f)};
         }
-      } else {
+      }
+    return;
+  }
+  gptr<float> Rt = as_global(mt.Rt);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = rb + 8 * (v >> 2) + hi4 + (v & 3);
-          if (row < mt.L && col < mt.r) Rt[(long long)row * mt.r + col] = a[v];
-        }
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) {
+      const int col = col0 + 32 * tn + (lane & 31);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = row0 + 32 * tm + 8 * (v >> 2) + hi4 + (v & 3);
+        if (row < mt.L && col < mt.r) Rt[(long long)row * mt.r + col] = acc[tm][tn][v];
       }
     }
 }

@@ -52,6 +52,7 @@ struct Plan {
   std::vector<HostMat> mats;
   int max_tiles[kNumTileLists] = {};
   int adam_lds = 0, adam_lds_f32 = 0;   // dynamic LDS of the Adam kernel: 16 rows of the widest register-resident matrix
+  int adam_lds_staged = 0;              // ... of the widest bf16 one whose R it also collects there
 };
 
 bool valid_desc(const fira_matrix_desc& d, std::string* why) {
@@ -86,6 +87,7 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     m.zready = ((m.r & 3) == 0 && m.r <= (m.kx == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32)) ? 1 : 0;
     if (m.zready && m.kx != 1) plan->adam_lds_f32 = std::max(plan->adam_lds_f32, FIRA_ROWS_PER_WG * m.rp * 6);
     if (m.zready && m.kx == 1) plan->adam_lds = std::max(plan->adam_lds, FIRA_ROWS_PER_WG * m.rp * 2);   // (twice that with Z in two planes)
+    if (m.zready && m.kx == 1 && m.r <= FIRA_RSTAGE_MAX_R) plan->adam_lds_staged = std::max(plan->adam_lds_staged, FIRA_ROWS_PER_WG * m.rp * 2);
     const size_t Lr = (size_t)m.L * m.r;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     m.M = (float*)take(Lr * 4);
