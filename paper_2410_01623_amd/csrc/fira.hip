@@ -63,6 +63,7 @@ constexpr int kComputeUnits = 256, kLdsPerCu = 160 * 1024;
 // Back-projection tiles of a list up to which the update takes quarter tiles: three rounds of the whole tiles' 512 workgroups,
 // or, where bf16 operands of a rank above 256 are read twice as often for nothing by smaller tiles, not quite one
 // (fira_backproject_kernel has both sides measured).
+constexpr int kForwardsMaxR = 64;   // lists of such ranks are worked through forwards by every kernel (fira_backproject_kernel)
 constexpr int kQuarterTiles = 1536, kQuarterTilesLongRank = 384;
 
 struct ListSlot {
@@ -214,10 +215,10 @@ void launch_update(hipStream_t q, fira_ctx* ctx, const ListSlot* s, int list, co
   const int n = s->ntiles[list];
   if (n <= (sizeof(T) == 2 && s->max_r > 256 ? kQuarterTilesLongRank : kQuarterTiles))
     hipLaunchKernelGGL((fira_backproject_kernel<1, T, 2, 1>), dim3((4 * n + 7) / 8 * 8), dim3(FIRA_BACK_THREADS), (EpiShape<2, 1>::ALL), q,
-                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[list], n, ctx->d_partial, hp);
+                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[list], n, s->max_r > kForwardsMaxR ? 1 : 0, ctx->d_partial, hp);
   else
     hipLaunchKernelGGL((fira_backproject_kernel<1, T>), dim3((n + 7) / 8 * 8), dim3(FIRA_BACK_THREADS), FIRA_BACK_LDS, q,
-                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[list], n, ctx->d_partial, hp);
+                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[list], n, s->max_r > kForwardsMaxR ? 1 : 0, ctx->d_partial, hp);
 }
 
 // Builds the work list of one fira_step call in pinned staging and returns its slot.
@@ -347,7 +348,8 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<0, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<1, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_chol_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_CHOL_PAN_ROWS * (FIRA_CHOL_NB + 1) * 8));
-  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(1)));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(2)));
   FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_stage_all, p.slot_bytes * kSlots, hipHostMallocDefault));
@@ -619,6 +621,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
                            s->d_tiles[ll], nl, bl, s->d_tiles[lr], nr, hp);
     }
   }
+  const int backwards = s->max_r > kForwardsMaxR ? 1 : 0;
   if (!fused || mixed) {
     // 1. R = P^T G
     launch_project(want_g2);
@@ -626,13 +629,17 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     // 2. Adam on R, factor norms
     if (s->ntiles[kTilesBackBf16]) {
       const int planes = ctx->zsplit ? 2 : 1;
-      const int lds = std::max(ctx->plan.adam_lds * planes, need_residual ? ctx->plan.adam_lds_staged * (planes + 1) : 0);
-      hipLaunchKernelGGL(fira_adam_kernel<1>, dim3(s->rowblocks), dim3(256), lds, q, ctx->d_mats, ctx->d_scal,
-                         s->d_ents, count, s->rowblocks, need_residual ? 1 : 0, hp);
+      if (need_residual)
+        hipLaunchKernelGGL((fira_adam_kernel<1, true>), dim3(s->rowblocks), dim3(256),
+                           std::max(ctx->plan.adam_lds * planes, ctx->plan.adam_lds_staged * (planes + 1)), q, ctx->d_mats, ctx->d_scal,
+                           s->d_ents, count, s->rowblocks, backwards, hp);
+      else
+        hipLaunchKernelGGL((fira_adam_kernel<1, false>), dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds * planes, q, ctx->d_mats, ctx->d_scal,
+                           s->d_ents, count, s->rowblocks, backwards, hp);
     }
     if (s->ntiles[kTilesBackF32])
-      hipLaunchKernelGGL(fira_adam_kernel<FIRA_KX_SPLIT>, dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds_f32, q, ctx->d_mats, ctx->d_scal,
-                         s->d_ents, count, s->rowblocks, 0, hp);
+      hipLaunchKernelGGL((fira_adam_kernel<FIRA_KX_SPLIT, false>), dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds_f32, q, ctx->d_mats, ctx->d_scal,
+                         s->d_ents, count, s->rowblocks, backwards, hp);
     mark(2);
   } else {
     mark(1);
@@ -641,11 +648,11 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   // 3. ||k (G - P R)||^2 per tile where the Gram route does not apply
   if (need_residual && s->ntiles[kTilesBackBf16])
     hipLaunchKernelGGL((fira_backproject_kernel<0, bf16_raw>), grid8(s->ntiles[kTilesBackBf16]), dim3(FIRA_BACK_THREADS), FIRA_BACK_LDS, q,
-                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[kTilesBackBf16], s->ntiles[kTilesBackBf16],
+                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[kTilesBackBf16], s->ntiles[kTilesBackBf16], 0,
                        ctx->d_partial, hp);
   if (need_residual && s->ntiles[kTilesBackF32])
     hipLaunchKernelGGL((fira_backproject_kernel<0, float>), grid8(s->ntiles[kTilesBackF32]), dim3(FIRA_BACK_THREADS), FIRA_BACK_LDS, q,
-                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[kTilesBackF32], s->ntiles[kTilesBackF32],
+                       ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[kTilesBackF32], s->ntiles[kTilesBackF32], 0,
                        ctx->d_partial, hp);
   mark(3);
   // 4. limiter factor, state advance

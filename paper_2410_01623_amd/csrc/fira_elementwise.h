@@ -227,7 +227,7 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
 // a wavefront takes its four rows at once, 16 lanes per row, instead of one after the other.
 template <int KX>
 __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp& hp, float bias, long long row_base,
-                                                 bool gram, bf16_raw* zl, bf16_raw* rl, int wave) {
+                                                 bool gram, bf16_raw* zl, int wave) {
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4, a = (lane & 15) * 4;
   const int r = mt.r;
@@ -265,7 +265,7 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
     zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};   // rows beyond L and columns beyond r: the operand's zero padding
     if (live) {
       bf16_planes<KX>(nv - k * rv, planes, zp);
-      if (!gram && !rl) {
+      if (!gram) {
         u32x2 rb[3];
         bf16_planes<KX>(rv, KX == 1 ? 1 : 3, rb);
 #pragma unroll
@@ -273,11 +273,10 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
           *reinterpret_cast<gptr<u32x2>>(as_global(mt.Rb) + kblk_index(mt.Lq, row, p * mt.rp + a)) = rb[p];
       }
     }
-    const int at = (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + g) * 32 + (a & 31);
+    bf16_raw* dst = zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + g) * 32 + (a & 31);
 #pragma unroll
     for (int p = 0; p < (KX == 1 ? 2 : 3); ++p)
-      if (p < planes) *reinterpret_cast<u32x2*>(zl + at + p * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32)) = zp[p];
-    if (KX == 1 && rl) *reinterpret_cast<u32x2*>(rl + at) = live ? pack_bf16x4(rv) : u32x2{0u, 0u};
+      if (p < planes) *reinterpret_cast<u32x2*>(dst + p * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32)) = zp[p];
   }
   if ((lane & 15) == 0 && row < mt.L) {
     as_global(mt.phi)[row] = k;
@@ -285,19 +284,20 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
   }
 }
 
-// stage_r: the launch's LDS has room for R beside Z (bf16 matrices with r <= FIRA_RSTAGE_MAX_R on the residual route): R, too, then
+// STAGE_R: the launch's LDS has room for R beside Z (bf16 matrices with 64 < r <= FIRA_RSTAGE_MAX_R on the residual route): R, too, then
 // leaves in pieces of 1 KB.  Above that rank the image would halve the wavefronts in flight.  Adam on the residual route over
 // 168 matrices of the 1B shapes at r = 512: 1420 us, 1725 with R in 64-byte pieces; 350M shapes at r = 256: 346, 397.
 // KX: the matrices that this launch serves, bf16 (1) or fp32 (FIRA_KX_SPLIT); the row-blocks of the others leave.
 // (One kernel for both took ten registers too many for four wavefronts per SIMD, and 2 % of the bf16 time.)
-template <int KX>
+template <int KX, bool STAGE_R>
 __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __restrict__ mats,
                                                         const FiraScal* __restrict__ scal,
                                                         const FiraEnt* __restrict__ ents, int count,
-                                                        int total_rowblocks, int stage_r, FiraHp hp) {
+                                                        int total_rowblocks, int backwards, FiraHp hp) {
   extern __shared__ __attribute__((aligned(16))) char adam_lds[];   // zready matrices: 16 rows x planes x rp bf16 (and R's)
-  const int rb = blockIdx.x;
-  if (rb >= total_rowblocks) return;
+  // backwards: R of the last matrices is still in the memory-side cache
+  const int rb = backwards ? total_rowblocks - 1 - (int)blockIdx.x : (int)blockIdx.x;
+  if (rb < 0 || rb >= total_rowblocks) return;
   const int e = find_entry(ents, count, rb);
   const FiraEnt ent = ents[e];
   const FiraMat mt = mats[ent.mat];
@@ -314,9 +314,9 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const int wave = threadIdx.x >> 6;
   const long long row_base = (long long)(rb - ent.row0) * FIRA_ROWS_PER_WG + wave * 4;
   const int planes = z_planes<KX>(hp);
-  const bool staged = KX == 1 && stage_r && zready && !gram && mt.r <= FIRA_RSTAGE_MAX_R;
+  const bool staged = STAGE_R && zready && !gram && mt.r > 64 && mt.r <= FIRA_RSTAGE_MAX_R;
   bf16_raw* rl = staged ? zl + planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32) : nullptr;
-  if (zready && mt.r <= 64) adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, rl, wave);
+  if (zready && mt.r <= 64) adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, wave);
   else for (int i = 0; i < 4; ++i) {
     const long long row = row_base + i;
     if (row >= mt.L) {

@@ -59,6 +59,14 @@ __device__ __forceinline__ u32x4 load8_bf16(gptr<const bf16_raw> row, long long 
   return u32x4{w[0], w[1], w[2], w[3]};
 }
 
+// 8 bf16 moved down by d (>= 0) elements, zeros from above.
+__device__ __forceinline__ u32x4 shift8_bf16(u32x4 v, int d) {
+  v = d & 4 ? u32x4{v.z, v.w, 0u, 0u} : v;
+  v = d & 2 ? u32x4{v.y, v.z, v.w, 0u} : v;
+  v = d & 1 ? u32x4{__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16} : v;
+  return d < 8 ? v : u32x4{0u, 0u, 0u, 0u};
+}
+
 struct GemmOperands {
   gptr<const bf16_raw> A;  // A side
   long long lda;      // gradient operand: elements between consecutive A rows (K-contiguous) or K steps
@@ -152,17 +160,25 @@ __device__ __forceinline__ void ring_compute(f32x16_t (&acc)[TM][TN], const char
   const char* la = stage;
   const char* lb = stage + RingShape<TM, TN>::A;
   Frags<TM, TN> f[2];
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
+  auto read = [&](int kk, int q) {           // fragment q (of TM + TN) of slice kk
     const int chunk = 2 * kk + (lane >> 5);
+    if (q < TM) f[kk].a[q] = *reinterpret_cast<const bf16x8_t*>(la + ring_tile_off(wm * 32 * TM + 32 * q + (lane & 31), chunk));
+    else f[kk].b[q - TM] = *reinterpret_cast<const bf16x8_t*>(lb + ring_tile_off(wn * 32 * TN + 32 * (q - TM) + (lane & 31), chunk));
+  };
+  // The second slice's fragments are read between the first one's multiplies (see proj_compute): the update over the 7B
+  // shapes at r = 1024 16155 -> 15700 us, over the 1B shapes at r = 512 2057 -> 2041.
 #pragma unroll
-    for (int t = 0; t < TM; ++t)
-      f[kk].a[t] = *reinterpret_cast<const bf16x8_t*>(la + ring_tile_off(wm * 32 * TM + 32 * t + (lane & 31), chunk));
+  for (int q = 0; q < TM + TN; ++q) read(0, q);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < TN; ++t)
-      f[kk].b[t] = *reinterpret_cast<const bf16x8_t*>(lb + ring_tile_off(wn * 32 * TN + 32 * t + (lane & 31), chunk));
+  for (int x = 0; x < TM * TN; ++x) {
+    acc[x / TN][x % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[0].a[x / TN], f[0].b[x % TN], acc[x / TN][x % TN], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < TM + TN; ++q)
+      if (q * TM * TN / (TM + TN) == x) read(1, q);
+    __builtin_amdgcn_sched_barrier(0);
   }
-  gemm_mfma_slice(acc, f[0]);
   gemm_mfma_slice(acc, f[1]);
 }
 
@@ -1369,6 +1385,7 @@ struct Elem8<bf16_raw> {
     return load8_bf16(row, idx, limit);
   }
   static __device__ __forceinline__ Raw zero() { return u32x4{0u, 0u, 0u, 0u}; }
+  static __device__ __forceinline__ Raw shift(const Raw& v, int d) { return shift8_bf16(v, d); }
   static __device__ __forceinline__ void unpack(const Raw& v, float (&x)[8]) {
     const unsigned w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -1409,6 +1426,14 @@ struct Elem8<float> {
     return r;
   }
   static __device__ __forceinline__ Raw zero() { Raw r; r.a = f32x4{0.f, 0.f, 0.f, 0.f}; r.b = r.a; return r; }
+  static __device__ __forceinline__ Raw shift(Raw r, int d) {
+    const f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (d & 4) { r.a = r.b; r.b = z; }
+    if (d & 2) { r.a = f32x4{r.a.z, r.a.w, r.b.x, r.b.y}; r.b = f32x4{r.b.z, r.b.w, 0.f, 0.f}; }
+    if (d & 1) { r.a = f32x4{r.a.y, r.a.z, r.a.w, r.b.x}; r.b = f32x4{r.b.y, r.b.z, r.b.w, 0.f}; }
+    if (d >= 8) { r.a = z; r.b = z; }
+    return r;
+  }
   static __device__ __forceinline__ void unpack(const Raw& r, float (&x)[8]) {
     x[0] = r.a.x; x[1] = r.a.y; x[2] = r.a.z; x[3] = r.a.w; x[4] = r.b.x; x[5] = r.b.y; x[6] = r.b.z; x[7] = r.b.w;
   }
@@ -1432,6 +1457,9 @@ struct Elem8<float> {
 // ld is odd and no 16-byte access is aligned: the number of partially covered 128-byte lines per
 // instruction drops four-fold.  DEPTH passes of G (and W) values are in flight: a pass is requested that
 // many passes before it is consumed, across the change of slab.
+// Edge tiles keep their loads in flight as well: they load whole pieces that stay inside the matrix, and move the values into
+// place where they are used (realigned as they were loaded, every pass waited for its own, and the kernel spilled
+// eight registers for it: 2083 -> 2057 us over the 1B shapes).
 // (The norm pass, MODE 0, over 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256: 271 us = 0.57 PFLOP/s; 628 us
 // while it had no loads in flight and spilled 72 registers.)
 template <int TM, int TN>
@@ -1466,12 +1494,24 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[TM][TN], c
   const long long wave_row0 = (long long)i0 + wn * 32 * TN + 16 * wm;
   const long long lane_off = (unsigned)(ih * (int)mt.ld + jl);
   auto slab_row = [&](int p) { return 16 * wm + PROWS * p + ih; };
+  // Edge tiles: the first column loaded, this lane's behind it, and what its values have to be moved down by.
+  const bool whole8 = mt.n >= 8;
+  const int jc0 = min(j0, mt.n - 8), jc = min((int)j, mt.n - 8) - jc0, jshift = whole8 ? (int)j - min((int)j, mt.n - 8) : 0;
+  const bool moved = !INTERIOR && whole8 && j0 + Shape::COLS > mt.n;
   auto fetch = [&](int q, Raw& gr, Raw& wr) {   // pass q = PASSES * slab + pass of the slab
     const int tn = q / PASSES, p = q % PASSES;
     if (INTERIOR) {
       const long long base = (wave_row0 + 32 * tn + PROWS * p) * mt.ld + j0;
       gr = Elem8<T>::template load_raw<true>(G + base, lane_off, 0);
       if (MODE == 1) wr = Elem8<T>::template load_raw<true>(W + base, lane_off, 0);
+    } else if (whole8) {
+      // rows and columns past the end repeat the last ones (the columns are moved back into place where they are used, so that
+      // the loads stay in flight until then)
+      const int first = min((int)wave_row0 + 32 * tn + PROWS * p, mt.m - 1);
+      const long long base = (long long)first * mt.ld + jc0;
+      const long long off = (unsigned)((min(first + ih, mt.m - 1) - first) * (int)mt.ld + jc);
+      gr = Elem8<T>::template load_raw<true>(G + base, off, 0);
+      if (MODE == 1) wr = Elem8<T>::template load_raw<true>(W + base, off, 0);
     } else {
       const long long i = (long long)i0 + wn * 32 * TN + 32 * tn + slab_row(p);
       const bool ok = i < mt.m && j < mt.n;
@@ -1518,6 +1558,10 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[TM][TN], c
         const f32x4 u0 = *reinterpret_cast<const f32x4*>(buf + il * Shape::STRIDE + jl);
         const f32x4 u1 = *reinterpret_cast<const f32x4*>(buf + il * Shape::STRIDE + jl + 4);
         const float u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+        if (moved) {
+          gr = Elem8<T>::shift(gr, jshift);
+          if (MODE == 1) wr = Elem8<T>::shift(wr, jshift);
+        }
         float g[8];
         Elem8<T>::unpack(gr, g);
         if (!mt.left) {
@@ -1562,7 +1606,7 @@ __global__ __launch_bounds__(FIRA_BACK_THREADS, TM == 4 ? 2 : sizeof(T) == 4 ? 3
                                                                            const FiraScal* __restrict__ scal,
                                                                            const FiraEnt* __restrict__ ents,
                                                                            const FiraTile* __restrict__ tiles,
-                                                                           int ntiles, float* __restrict__ partial,
+                                                                           int ntiles, int backwards, float* __restrict__ partial,
                                                                            FiraHp hp) {
   extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_BACK_LDS bytes
   __shared__ float red[4];
@@ -1571,7 +1615,10 @@ __global__ __launch_bounds__(FIRA_BACK_THREADS, TM == 4 ? 2 : sizeof(T) == 4 ? 3
   const int wi = xcd_chunked_index(blockIdx.x, ntiles * PARTS);
   if (wi < 0) return;
   const int sub = wi % PARTS;
-  const FiraTile tile = tiles[wi / PARTS];
+  // backwards: what the kernels before it read and wrote last, G of the last matrices and their Z, is still in the
+  // memory-side cache (350M shapes 877 -> 860 us a step, 1B 4247 -> 4226, 16 blocks of 512 x 1376 162 -> 158; with ranks up to 64,
+  // where the update is a plain stream, 4713 -> 4740 us over the fine-tuning shapes: those go forwards).
+  const FiraTile tile = tiles[backwards ? ntiles - 1 - wi / PARTS : wi / PARTS];
   const FiraEnt ent = ents[tile.ent];
   if (MODE == 0 && use_gram(hp, scal[ent.mat])) return;   // this matrix takes the Gram route to ||S||
   const FiraMat mt = mats[ent.mat];
