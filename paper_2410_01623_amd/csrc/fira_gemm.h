@@ -532,13 +532,12 @@ __device__ __forceinline__ int split_kq(int t) { return (t >> 2) & 7; }
 
 // The lane number, formed anew at each call, so that no address made from it is kept from one block to the next: one
 // reloaded from scratch waits for every load in flight.  Kept, the fp32 update spills 41 registers instead of 15 and the fp32
-// norm pass 23 instead of 7; the fp32 projection takes 204 registers instead of 188 and spills none either way.
+// norm pass 23 instead of 7.
 __device__ __forceinline__ int fresh_lane() {
   unsigned zero = 0;
   asm volatile("" : "+s"(zero));
   return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
 }
-__device__ __forceinline__ int fresh_thread() { return fresh_lane() + 64 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // ASYNC: 16-byte inline-assembly loads (at least four elements along the contiguous axis); otherwise
 // element by element (matrices with fewer).  What does not change from block to block is formed once: 300 vector instructions a
