@@ -99,14 +99,25 @@ __device__ __forceinline__ f32x4 refresh_load4(gptr<const float> A, int row, int
 }
 
 // The second orthonormalisation pass asks of the basis it is given whether max |Y^T Y - I| is within done_tol, and for
-// bf16 matrices (1e-4) three bf16 plane products h h + h m + m h answer that as surely as fp64 does: what they leave out is
-// at most 3 * 2^-18 of ||y_a|| ||y_b||, and the running sum of h h, S / 16 multiplies of at most that size, rounds by 2^-23 twice each.  A
-// matrix that passes with that much to spare needs no fp64 Gram matrix; any other (FIRA_PASS_UNSURE, and every fp32
-// matrix, whose 1e-6 lies below that margin) is decided by it.
+// bf16 matrices (1e-4) three bf16 plane products h h + h m + m h answer that: a matrix whose products come out within
+// refresh_check_tolerance, done_tol less all that they can be off by, is within done_tol, so it needs no fp64 Gram matrix; any
+// other (FIRA_PASS_UNSURE, and every fp32 matrix, whose 1e-6 lies below that margin) is decided by it.
+//
+// What they can be off by, in units of ||y_a|| ||y_b|| (a matrix that is let through has squared norms within 1e-4 of 1):
+//   2^-15 = 3.052e-5 for what the products leave out: bf16 has eight significant bits, so |m| <= 2^-8 |y| and |l| <= 2^-17 |y|,
+//     and a product loses |m_a m_b + l_a y_b + y_a l_b - l_a l_b| <= (2^-16 + 2 * 2^-17) |y_a y_b|;
+//   4.2e-6 for the sums of 32 rows, which start from zero, the small products first.  However a multiply adds its sixteen products up, each of
+//     them and the result cost at most a unit in the last place, 2^-23, of the largest number there is at that point, and none
+//     is larger than 1.016 (2^-7 while only h m and m h are there) of the 32 rows' share of ||y_a|| ||y_b||: 17 (2 * 1.016 + 4 * 2^-7) 2^-23
+//     of that share, and the shares add up to ||y_a|| ||y_b|| at most (Cauchy and Schwarz);
+//   2^-24 for each of the S / 32 additions of those sums, 1.863e-9 per row.
 // Tiles of 128 x 128, a wavefront 64 x 64 of it; K stages of 32 rows, split in registers on the way into LDS, as the fp32
-// projection's.  168 matrices of 2048 rows at r = 512: 593 us; the fp64 Gram matrices 1820.
+// projection's.  168 matrices of 2048 rows at r = 512: 592 us; the fp64 Gram matrices 1820.
 #define FIRA_PASS_NEEDED 1
 #define FIRA_PASS_UNSURE 2
+__host__ __device__ __forceinline__ float refresh_check_tolerance(float done_tol, int S) {
+  return done_tol - 3.06e-5f - 4.3e-6f - 1.87e-9f * (float)((S + 31) & ~31);
+}
 __global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRefreshEnt* __restrict__ ents) {
   __shared__ __attribute__((aligned(16))) char lds[4 * FIRA_SPLIT_PLANE];
   const FiraRefreshEnt e = ents[blockIdx.y];
@@ -115,7 +126,7 @@ __global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRe
   while (ta < nt && rem > ta) { rem -= ta + 1; ++ta; }
   if (ta >= nt) return;
   const int tb = rem;
-  const float tol = e.done_tol - 1.2e-5f - (float)e.S * 1.5e-8f;
+  const float tol = refresh_check_tolerance(e.done_tol, e.S);
   if (!(tol > 0.0f)) {
     if (threadIdx.x == 0) *as_global(e.done) = FIRA_PASS_UNSURE;
     return;
@@ -125,13 +136,13 @@ __global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRe
   const int a0 = 64 * (wave >> 1), b0 = 64 * (wave & 1), b = split_b(t), kq = split_kq(t), store_at = split_store_at(t);
   const bool diag = ta == tb, upper = diag && wave == 1;      // (nobody asks for the wave above the diagonal)
   char* lb = diag ? lds : lds + 2 * FIRA_SPLIT_PLANE;
-  f32x16_t hh[2][2], hm[2][2];
+  f32x16_t sum[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) hh[i][j][v] = hm[i][j][v] = 0.0f;
+      for (int v = 0; v < 16; ++v) sum[i][j][v] = 0.0f;
   f32x4 va[4], vb[4];
   auto fetch = [&](int s0) {
 #pragma unroll
@@ -156,26 +167,33 @@ __global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRe
     __syncthreads();
     if (s0 + 32 < e.S) fetch(s0 + 32);
     if (!upper) {
+      bf16x8_t fa[2][2][2], fb[2][2][2];     // [slice][plane][block]
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        bf16x8_t fa[2][2], fb[2][2];          // [plane][block]
+      for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
           for (int i = 0; i < 2; ++i) {
             const int off = p * FIRA_SPLIT_PLANE + (32 * i + (lane & 31)) * FIRA_SPLIT_PITCH + (2 * kk + (lane >> 5)) * 16;
-            fa[p][i] = *reinterpret_cast<const bf16x8_t*>(lds + a0 * FIRA_SPLIT_PITCH + off);
-            fb[p][i] = *reinterpret_cast<const bf16x8_t*>(lb + b0 * FIRA_SPLIT_PITCH + off);
+            fa[kk][p][i] = *reinterpret_cast<const bf16x8_t*>(lds + a0 * FIRA_SPLIT_PITCH + off);
+            fb[kk][p][i] = *reinterpret_cast<const bf16x8_t*>(lb + b0 * FIRA_SPLIT_PITCH + off);
           }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            hh[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][i], fb[0][j], hh[i][j], 0, 0, 0);
-            hm[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][i], fb[1][j], hm[i][j], 0, 0, 0);
-            hm[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1][i], fb[0][j], hm[i][j], 0, 0, 0);
+        for (int j = 0; j < 2; ++j) {
+          f32x16_t part;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) part[v] = 0.0f;
+#pragma unroll
+          for (int kk = 0; kk < 2; ++kk) {
+            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][0][i], fb[kk][1][j], part, 0, 0, 0);
+            part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][1][i], fb[kk][0][j], part, 0, 0, 0);
           }
-      }
+#pragma unroll
+          for (int kk = 0; kk < 2; ++kk) part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][0][i], fb[kk][0][j], part, 0, 0, 0);
+          sum[i][j] += part;
+        }
     }
     __syncthreads();
   }
@@ -187,7 +205,7 @@ __global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRe
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = ta * 128 + a0 + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), col = tb * 128 + b0 + 32 * j + (lane & 31);
-        const float d = hh[i][j][v] + hm[i][j][v] - (row == col ? 1.0f : 0.0f);
+        const float d = sum[i][j][v] - (row == col ? 1.0f : 0.0f);
         off = off || (!upper && row < e.r && col <= row && !(fabsf(d) <= tol));      // (true for a NaN)
       }
   if (off) *as_global(e.done) = FIRA_PASS_UNSURE;
