@@ -652,6 +652,11 @@ __device__ __forceinline__ void split3_planes(const float (&x)[4], u32x2 (&pl)[3
     d[2] -= __uint_as_float(pl[p].y << 16); d[3] -= __uint_as_float(pl[p].y & 0xffff0000u);
   }
 }
+// ||G_i||^2 over the four k that a thread holds of a block.  Spelled out, and added up block after block in both projection kernels:
+// which of the two serves a matrix depends on what else is listed, its norms must not.
+__device__ __forceinline__ float split_sumsq(const float (&x)[4]) {
+  return __builtin_fmaf(x[0], x[0], x[1] * x[1]) + __builtin_fmaf(x[2], x[2], x[3] * x[3]);
+}
 // One stage: 32 k of a plane product, `piece(j)`, j = 0..7, between its first multiplies (see proj_compute).
 template <int TM, typename Piece>
 __device__ __forceinline__ void split_compute(f32x16_t (&acc)[TM][2], const char* la, const char* lb, int a0, int b0, Piece piece) {
@@ -722,7 +727,7 @@ __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds
     al.unpack(r, 32 * b.kb, x);
     if (b.pos == 0) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sq[e] += (x[e][0] * x[e][0] + x[e][1] * x[e][1]) + (x[e][2] * x[e][2] + x[e][3] * x[e][3]);
+      for (int e = 0; e < 4; ++e) sq[e] += split_sumsq(x[e]);
     }
     char* dst = lds + aslot * FIRA_SPLIT_PLANE + store_at;       // sequence A: planes 0 0 1 0 2 1
     if (b.pos == 4) split_store_plane<2>(dst, x);
@@ -949,7 +954,7 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_fp32_project_kernel
 // rank columns, wave w with 32 factors x 32 TN rank components, the projector's fragments straight from memory into
 // registers (a 32 x 32 block of a plane is 2 KB of contiguous memory), U blocks of 32 k ahead.  No barrier after the
 // split, and a tenth of the instructions per multiply of the kernel above, whose 6 S / 32 stages in turn are what a small
-// matrix waits for.  Same products in the same order: R is the same bit for bit.
+// matrix waits for.  Same products and sums in the same order: R and ||G_i||^2 are the same bit for bit.
 // It holds a CU's LDS, so it is for lists whose panels all run at once (host: acquire_list); with more of them to a CU the
 // smaller tiles above keep the chip busier.  A step of 256 x 256 and 256 x 688 matrices at r = 64, with tiles and with panels:
 // 67 and 48 us for 49 panels, 78 and 60 for 196, 89 and 86 for 392, 130 and 143 for 784; of 400 x 400 and 400 x 800 at
@@ -1024,10 +1029,14 @@ __device__ __forceinline__ void project_panel(char* lds, const FiraMat& mt, cons
   const int nblocks = (mt.S + 31) / 32, L = mt.L, S = mt.S;
   gptr<const float> G = as_global(reinterpret_cast<const float*>(ent.G));
   const bool wide = (LEFT ? L : S) >= 4;
-  float sq[4] = {0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 4, GROUPS = 2;           // blocks in flight; groups of them
+  static_assert(64 * U * GROUPS >= FIRA_PANEL_MAX_S, "every block of this half belongs to a group");
+  f32x4 sq[GROUPS][U];                       // this thread's share of ||G_i||^2 by block
   char* dst = lds + 4 * b * pitch + 8 * kq;
-  constexpr int U = 4;                       // blocks in flight
-  for (int kb0 = half; kb0 < nblocks; kb0 += 2 * U) {
+#pragma unroll
+  for (int g = 0; g < GROUPS; ++g) {
+    const int kb0 = half + 2 * U * g;
+    if (kb0 >= nblocks) break;
     f32x4 v[U][4];
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -1066,7 +1075,7 @@ __device__ __forceinline__ void project_panel(char* lds, const FiraMat& mt, cons
         for (int e = 0; e < 4; ++e) (LEFT ? x[e][q] : x[q][e]) = __uint_as_float(ww[e]);
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sq[e] += (x[e][0] * x[e][0] + x[e][1] * x[e][1]) + (x[e][2] * x[e][2] + x[e][3] * x[e][3]);
+      for (int e = 0; e < 4; ++e) sq[g][u][e] = split_sumsq(x[e]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         u32x2 pl[3];
@@ -1087,18 +1096,29 @@ __device__ __forceinline__ void project_panel(char* lds, const FiraMat& mt, cons
     }
   }
   if (norm_mode == 1) {
-    float* part = reinterpret_cast<float*>(lds);      // [2][64]
+    f32x4* odd = reinterpret_cast<f32x4*>(lds);       // [odd block][128]
     __syncthreads();                                  // the products are done with the panel
+    if (half) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {                     // the eight threads that share a row, then the two halves
-      float s = sq[e];
-      s += __shfl_xor(s, 4, 64);
-      s += __shfl_xor(s, 8, 64);
-      s += __shfl_xor(s, 16, 64);
-      if (kq == 0) part[64 * half + 4 * b + e] = s;
+      for (int i = 0; i < GROUPS * U; ++i)
+        if (2 * i + 1 < nblocks) odd[128 * i + t] = sq[i / U][i % U];
     }
     __syncthreads();
-    if (threadIdx.x < FIRA_PANEL_F && a_row0 + (int)threadIdx.x < L) as_global(mt.g2)[a_row0 + threadIdx.x] = part[threadIdx.x] + part[64 + threadIdx.x];
+    if (half) return;
+    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < GROUPS * U; ++i) {            // block after block, as the tiles above add them
+      if (2 * i < nblocks) s += sq[i / U][i % U];
+      if (2 * i + 1 < nblocks) s += odd[128 * i + t];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {                     // the eight threads that share a row
+      float x = s[e];
+      x += __shfl_xor(x, 4, 64);
+      x += __shfl_xor(x, 8, 64);
+      x += __shfl_xor(x, 16, 64);
+      if (kq == 0 && a_row0 + 4 * b + e < L) as_global(mt.g2)[a_row0 + 4 * b + e] = x;
+    }
   }
 }
 

@@ -57,3 +57,51 @@ def test_a_list_with_matrices_on_either_side():
         if dtypes[i] == fira.FIRA_F32:
             # each product exact to 2^-24, sums of at most 450 of them in fp32
             assert (out[0][i][1].double() - R).abs().max() <= 1e-5 * R.abs().max()
+
+
+# every shape of test_gpu_fp32_split.py and of the list above whose short side a panel holds
+SMALL = [c for c in split.CASES + CASES if min(c[:2]) <= 416]
+FILLER = (2, 64 * 2600)       # more panels than the chip takes at once at any width: the list goes through tiles
+
+
+@pytest.mark.parametrize("norm", [fira.FIRA_NORM_GRAM, fira.FIRA_NORM_RESIDUAL], ids=["gram", "residual"])
+def test_panels_and_tiles_give_the_same_bits(norm):
+    """R, the factors, the norms, c and W of matrices stepped alone (whole panels) and in a list of more panels than run at once (tiles,
+    down to one block of k, one group of four and fewer than four elements), over four steps of which one is limited."""
+    shapes, ranks, lds = [c[:2] for c in SMALL], [c[2] for c in SMALL], [c[3] for c in SMALL]
+    gen = torch.Generator(device=H.DEV)
+    gen.manual_seed(17)
+    randn = lambda *s: torch.randn(*s, device=H.DEV, generator=gen)
+    Ps = [torch.linalg.qr(randn(min(s), r))[0].contiguous() for s, r in zip(shapes + [FILLER], ranks + [1])]
+    W0 = [0.02 * randn(s[0], ld) for s, ld in zip(shapes, lds)]
+    Gs = [[1e-2 * randn(s[0], ld) for s, ld in zip(shapes, lds)] for _ in range(4)]
+    for (m, n), p, g in zip(shapes, Ps, Gs[2]):       # limited: the part outside the subspace is eight times larger
+        v = g[:, :n]
+        v.copy_(8.0 * v - 7.0 * (p @ (p.t() @ v) if m <= n else (v @ p) @ p.t()))
+    fw, fg = 0.02 * randn(*FILLER), 1e-2 * randn(*FILLER)
+    out = []
+    for long_list in (False, True):
+        ids = list(range(len(shapes)))
+        ctx = fira.FiraContext(shapes + [FILLER], ranks + [1], fira.FIRA_F32, device=H.DEV, lds=lds + [FILLER[1]])
+        ctx.fira_set_options(norm_mode=norm)
+        ctx.fira_set_projectors(ids + [len(ids)], Ps)
+        W = [w.clone() for w in W0]
+        Wv = [w[:, :s[1]] for w, s in zip(W, shapes)]
+        seen = []
+        for G in Gs:
+            Gv = [g[:, :s[1]] for g, s in zip(G, shapes)]
+            if long_list:
+                ctx.fira_step(ids + [len(ids)], Wv + [fw], Gv + [fg])
+            else:
+                for i in ids:
+                    ctx.fira_step([i], [Wv[i]], [Gv[i]])
+            torch.cuda.synchronize()
+            seen.append([(ctx.fira_get_lowrank(i), ctx.fira_get_factors(i), ctx.fira_get_diag(i)) for i in ids])
+        out.append((W, seen))
+    for i, c in enumerate(SMALL):
+        for t, (a, b) in enumerate(zip(out[0][1], out[1][1])):
+            assert torch.equal(a[i][0], b[i][0]), f"R of {c} at step {t}"
+            assert torch.equal(a[i][1], b[i][1]), f"k of {c} at step {t}"
+            assert a[i][2] == b[i][2], f"norms of {c} at step {t}: {a[i][2]} and {b[i][2]}"
+        assert torch.equal(out[0][0][i], out[1][0][i]), f"W of {c}"
+    assert min(d[2][2] for d in out[0][1][2]) < 1.0
