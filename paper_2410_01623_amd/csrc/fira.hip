@@ -73,6 +73,7 @@ struct ListSlot {
   int ntiles[kNumTileLists] = {};
   int rowblocks = 0;
   int max_r = 0;               // largest rank listed
+  int max_r_bf16 = 0;          // ... of the bf16 matrices
   int panel_lds = 0;           // LDS of the panel projection's widest listed matrix, 0 if none is listed
   bool split_proj = false;     // fp32 matrices that it does not serve are listed
   // device views (inside the slab)
@@ -213,7 +214,7 @@ void launch_fp32_project(hipStream_t q, const ListSlot* s, const FiraMat* mats, 
 template <typename T>
 void launch_update(hipStream_t q, fira_ctx* ctx, const ListSlot* s, int list, const FiraHp& hp) {
   const int n = s->ntiles[list];
-  if (n <= (sizeof(T) == 2 && s->max_r > 256 ? kQuarterTilesLongRank : kQuarterTiles))
+  if (n <= (sizeof(T) == 2 && s->max_r_bf16 > 256 ? kQuarterTilesLongRank : kQuarterTiles))
     hipLaunchKernelGGL((fira_backproject_kernel<1, T, 2, 1>), dim3((4 * n + 7) / 8 * 8), dim3(FIRA_BACK_THREADS), (EpiShape<2, 1>::ALL), q,
                        ctx->d_mats, ctx->d_scal, s->d_ents, s->d_tiles[list], n, s->max_r > kForwardsMaxR ? 1 : 0, ctx->d_partial, hp);
   else
@@ -246,12 +247,13 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
   build_work_list(p, count, idx, W, G, s->h_stage, s->ntiles, &s->rowblocks);
   // fp32 projection: whole panels where all of them run at once, tiles otherwise (fira_panel_project_kernel)
   long long panels = 0;
-  s->max_r = 0;
+  s->max_r = s->max_r_bf16 = 0;
   s->panel_lds = 0;
   s->split_proj = false;
   for (int e = 0; e < count; ++e) {
     const FiraMat& m = p.mats[idx[e]].dev;
     s->max_r = std::max(s->max_r, m.r);
+    if (m.kx == 1) s->max_r_bf16 = std::max(s->max_r_bf16, m.r);
     if (panel_projection(m)) {
       panels += (m.L + FIRA_PANEL_F - 1) / FIRA_PANEL_F;
       s->panel_lds = std::max(s->panel_lds, panel_lds(m.S));

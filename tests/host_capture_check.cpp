@@ -4,59 +4,7 @@
 // run on the CPU by tests/test_host_capture.py.
 #include "../paper_2410_01623_amd/csrc/fira.hip"
 
-#include <cstdlib>
-
-namespace {
-bool capturing = false;
-long enqueued = 0;      // kernels, copies, fills and event records
-int failures = 0;
-#define CHECK(cond)                                                                       \
-  do {                                                                                    \
-    if (!(cond)) { ++failures; std::printf("FAIL line %d: %s\n", __LINE__, #cond); }      \
-  } while (0)
-alignas(256) char static_area[256];
-}  // namespace
-
-extern "C" {
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
-  *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
-  return hipSuccess;
-}
-hipError_t hipStreamSynchronize(hipStream_t) { return capturing ? hipErrorStreamCaptureUnsupported : hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t* e) { *e = nullptr; return hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; return hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { ++enqueued; return hipSuccess; }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.0f; return hipSuccess; }
-hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
-hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
-const char* hipGetErrorString(hipError_t) { return "stand-in"; }
-hipError_t hipGetLastError(void) { return hipSuccess; }
-hipError_t hipGetSymbolAddress(void** p, const void*) { *p = static_area; return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
-hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { ++enqueued; return hipSuccess; }
-hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
-// (copies into the static scratch's stand-in are counted only: it is not the real size)
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
-  ++enqueued;
-  if (d != static_area) std::memcpy(d, s, n);
-  return hipSuccess;
-}
-hipError_t hipMemcpy2DAsync(void* d, size_t dp, const void* s, size_t sp, size_t w, size_t h, hipMemcpyKind, hipStream_t) {
-  ++enqueued;
-  for (size_t i = 0; i < h; ++i) std::memcpy((char*)d + i * dp, (const char*)s + i * sp, w);
-  return hipSuccess;
-}
-hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { ++enqueued; std::memset(d, v, n); return hipSuccess; }
-hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
-hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
-void** __hipRegisterFatBinary(const void*) { static void* h = nullptr; return &h; }
-void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
-void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
-void __hipUnregisterFatBinary(void**) {}
-}
+#include "host_hip.h"
 
 int main() {
   const fira_matrix_desc descs[2] = {{96, 160, 160, 16, FIRA_BF16}, {160, 96, 96, 16, FIRA_F32}};
