@@ -245,23 +245,24 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
   s->G.assign(G, G + count);
   const Plan& p = ctx->plan;
   build_work_list(p, count, idx, W, G, s->h_stage, s->ntiles, &s->rowblocks);
-  // fp32 projection: whole panels where all of them run at once, tiles otherwise (fira_panel_project_kernel)
-  long long panels = 0;
+  // fp32 projection: whole panels where all of their workgroups run at once, tiles otherwise (fira_panel_project_kernel)
+  long long panel_groups = 0;
   s->max_r = s->max_r_bf16 = 0;
   s->panel_lds = 0;
   s->split_proj = false;
   for (int e = 0; e < count; ++e) {
-    const FiraMat& m = p.mats[idx[e]].dev;
+    const HostMat& h = p.mats[idx[e]];
+    const FiraMat& m = h.dev;
     s->max_r = std::max(s->max_r, m.r);
     if (m.kx == 1) s->max_r_bf16 = std::max(s->max_r_bf16, m.r);
     if (panel_projection(m)) {
-      panels += (m.L + FIRA_PANEL_F - 1) / FIRA_PANEL_F;
+      panel_groups += 2 * h.ta_project;
       s->panel_lds = std::max(s->panel_lds, panel_lds(m.S));
     } else if (m.kx != 1) {
       s->split_proj = true;
     }
   }
-  if (s->panel_lds && panels > kComputeUnits * (kLdsPerCu / s->panel_lds)) {
+  if (s->panel_lds && panel_groups > kComputeUnits * std::min(kLdsPerCu / s->panel_lds, FIRA_PANEL_WG_PER_CU)) {
     s->panel_lds = 0;
     s->split_proj = true;
   }

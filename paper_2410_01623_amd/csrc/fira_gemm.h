@@ -519,8 +519,9 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 // past the end read the last row; values past the contraction length are set to zero.
 // ------------------------------------------------------------------------------------------------
 #define FIRA_PANEL_MAX_S 416
-// fp32 matrices whose short side the panel kernel below can take
-__host__ __device__ __forceinline__ bool panel_projection(const FiraMat& mt) { return mt.kx != 1 && mt.S <= FIRA_PANEL_MAX_S; }
+#define FIRA_PANEL_MAX_R 256
+// fp32 matrices that the panel kernel below takes
+__host__ __device__ __forceinline__ bool panel_projection(const FiraMat& mt) { return mt.kx != 1 && mt.S <= FIRA_PANEL_MAX_S && mt.r <= FIRA_PANEL_MAX_R; }
 #define FIRA_SPLIT_PITCH 80
 #define FIRA_SPLIT_PLANE (FIRA_PA * FIRA_SPLIT_PITCH)
 #define FIRA_SPLIT_LDS (2 * FIRA_SPLIT_PLANE + FIRA_RING_STAGES * FIRA_PROJ_RING_STAGE)
@@ -949,19 +950,26 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 2) void fira_fp32_project_kernel
 }
 
 // ------------------------------------------------------------------------------------------------
-// Kernel 1 for fp32 matrices whose short side is at most FIRA_PANEL_MAX_S: the three planes of 64 whole factors fit in LDS.
+// Kernel 1 for fp32 matrices whose short side is at most FIRA_PANEL_MAX_S (the three planes of 64 whole factors fit in LDS) and
+// whose rank is at most FIRA_PANEL_MAX_R.
 // A workgroup reads its panel of the gradient once and splits it once; the six plane products then run from LDS over all
 // rank columns, wave w with 32 factors x 32 TN rank components, the projector's fragments straight from memory into
 // registers (a 32 x 32 block of a plane is 2 KB of contiguous memory), U blocks of 32 k ahead.  No barrier after the
 // split, and a tenth of the instructions per multiply of the kernel above, whose 6 S / 32 stages in turn are what a small
 // matrix waits for.  Same products and sums in the same order: R and ||G_i||^2 are the same bit for bit.
-// It holds a CU's LDS, so it is for lists whose panels all run at once (host: acquire_list); with more of them to a CU the
-// smaller tiles above keep the chip busier.  A step of 256 x 256 and 256 x 688 matrices at r = 64, with tiles and with panels:
+// It holds a CU's LDS, or half its registers, so it is for lists whose workgroups all run at once (host: acquire_list); with more of them the
+// smaller tiles above keep the chip busier.  What counts is the workgroups that are launched, with those that have no panel: they take
+// their turns on the XCDs.  A step of 256 x 256 and 256 x 688 matrices at r = 64, with tiles and with panels:
 // 67 and 48 us for 49 panels, 78 and 60 for 196, 89 and 86 for 392, 130 and 143 for 784; of 400 x 400 and 400 x 800 at
 // r = 128: 103 and 75 us for 67 panels, 126 and 127 for 268, 197 and 220 for 536.  256 x 688 alone: 35 and 13 us of projection.
+// The projection alone, with tiles and with panels: 400 x 800 at r = 256 73 and 56 us for 252 workgroups, 75 and 105 for 266; at two to
+// a CU 64 x 30000 at r = 16 14.4 and 12.6 us (470 workgroups), 16 x 40000 13.0 and 15.9 (626), 128 x 40000 at r = 128 31 and 35 (626).
+// Above r = 256 a panel takes a third and fourth pass over rank columns, where tiles take more workgroups: 400 x 800 at r = 260 71 and 61 us for one
+// matrix, 72 and 71 (73 and 80 with cold operands) at r = 384, 73 and 176 for eighteen at r = 400.
 // Row pitch of a plane: an odd number of 16-byte chunks, so that the fragment reads of sixteen rows are conflict-free.
 // ------------------------------------------------------------------------------------------------
 #define FIRA_PANEL_F 64
+#define FIRA_PANEL_WG_PER_CU 2
 __host__ __device__ __forceinline__ int panel_pitch(int S) { return ((S + 31) & ~31) * 2 + 16; }
 __host__ __device__ __forceinline__ int panel_lds(int S) { return FIRA_SPLIT_PLANES * FIRA_PANEL_F * panel_pitch(S); }
 
@@ -1122,8 +1130,8 @@ __device__ __forceinline__ void project_panel(char* lds, const FiraMat& mt, cons
   }
 }
 
-// Two workgroups per tile of the projection's lists (which also hold other matrices and, above r = 256, further rank tiles).
-__global__ __launch_bounds__(256, 2) void fira_panel_project_kernel(const FiraMat* __restrict__ mats,
+// Two workgroups per tile of the projection's lists (which also hold other matrices and their further rank tiles).
+__global__ __launch_bounds__(256, FIRA_PANEL_WG_PER_CU) void fira_panel_project_kernel(const FiraMat* __restrict__ mats,
                                                                     const FiraEnt* __restrict__ ents,
                                                                     const FiraTile* __restrict__ tiles_left, int ntiles_left,
                                                                     const FiraTile* __restrict__ tiles_right, int norm_mode, int pack) {

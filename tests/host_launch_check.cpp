@@ -66,6 +66,24 @@ int main() {
     c.step({0, 2});
     CHECK(times(fira_panel_project_kernel) == 1 && times(fira_fp32_project_kernel) == 1);
   }
+  {   // ... "at once" counts the workgroups that are launched, two a CU at most, and ranks above 256 take tiles
+    auto copies = [](fira_matrix_desc d, int n) { return std::vector<fira_matrix_desc>(n, d); };
+    auto all = [](int n) { std::vector<int> v(n); for (int i = 0; i < n; ++i) v[i] = i; return v; };
+    struct { fira_matrix_desc d; int n; bool panels; } lists[] = {
+        {desc(400, 800, 256, FIRA_F32), 18, true},    {desc(400, 800, 256, FIRA_F32), 19, false},   // 252 and 266 workgroups, one a CU
+        {desc(800, 400, 256, FIRA_F32), 18, true},    {desc(800, 400, 256, FIRA_F32), 19, false},
+        {desc(400, 800, 257, FIRA_F32), 1, false},    {desc(400, 800, 400, FIRA_F32), 18, false},
+        {desc(64, 32768, 64, FIRA_F32), 1, true},     {desc(64, 32769, 64, FIRA_F32), 1, false},    // 512 and 514, of which LDS alone would take five a CU
+        {desc(16, 32768, 16, FIRA_F32), 1, true},     {desc(16, 150000, 16, FIRA_F32), 1, false},
+        {desc(64, 64, 16, FIRA_F32), 256, true},      {desc(64, 64, 16, FIRA_F32), 257, false},     // every second workgroup has a panel
+    };
+    for (auto& l : lists) {
+      Case c(copies(l.d, l.n));
+      c.step(all(l.n));
+      const bool panels = times(fira_panel_project_kernel) == 1, tiles = times(fira_fp32_project_kernel) == 1;
+      if (panels != l.panels || tiles == l.panels) { ++failures; std::printf("FAIL: %d matrices of %lld x %lld, r = %d\n", l.n, (long long)l.d.m, (long long)l.d.n, (int)l.d.r); }
+    }
+  }
   std::printf("%d failure(s)\n", failures);
   return failures ? 1 : 0;
 }
