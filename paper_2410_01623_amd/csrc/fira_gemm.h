@@ -1411,6 +1411,7 @@ struct Elem8<bf16_raw> {
     if (INTERIOR) return __builtin_nontemporal_load(reinterpret_cast<gptr<const u32x4_a2>>(row + idx));
     return load8_bf16(row, idx, limit);
   }
+  static __device__ __forceinline__ Raw load_edge(gptr<const bf16_raw> row, long long idx) { return *reinterpret_cast<gptr<const u32x4_a2>>(row + idx); }
   static __device__ __forceinline__ Raw zero() { return u32x4{0u, 0u, 0u, 0u}; }
   static __device__ __forceinline__ Raw shift(const Raw& v, int d) { return shift8_bf16(v, d); }
   static __device__ __forceinline__ void unpack(const Raw& v, float (&x)[8]) {
@@ -1452,6 +1453,7 @@ struct Elem8<float> {
     }
     return r;
   }
+  static __device__ __forceinline__ Raw load_edge(gptr<const float> row, long long idx) { return load_raw<true>(row, idx, 0); }
   static __device__ __forceinline__ Raw zero() { Raw r; r.a = f32x4{0.f, 0.f, 0.f, 0.f}; r.b = r.a; return r; }
   static __device__ __forceinline__ Raw shift(Raw r, int d) {
     const f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1485,8 +1487,12 @@ struct Elem8<float> {
 // instruction drops four-fold.  DEPTH passes of G (and W) values are in flight: a pass is requested that
 // many passes before it is consumed, across the change of slab.
 // Edge tiles keep their loads in flight as well: they load whole pieces that stay inside the matrix, and move the values into
-// place where they are used (realigned as they were loaded, every pass waited for its own, and the kernel spilled
-// eight registers for it: 2083 -> 2057 us over the 1B shapes).
+// place where they are used, if the row's end is not a whole piece (realigned as they were loaded, every pass waited for its own).  The
+// element-by-element loads of matrices with fewer than eight columns are a form of their own: a copy of them beside every pass made
+// launches with many edge tiles wait for instructions.  Edge pieces are loaded through the caches, since a tile covers their lines in
+// part.  8 blocks of 1003 x 1003 and 1003 x 3001 at r = 64, update and norm pass: 146 and 73 us; 190 and 88 with one form for both and non-temporal loads, 210
+// and 99 realigned while loading; 31 matrices of 384 x 1168 at r = 4 22.8 and 14.5, 23.8 and 17.3, 24.7 and 14.4; the update over the 1B shapes
+// 2019, 2033 and 2071 us.
 // (The norm pass, MODE 0, over 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256: 271 us = 0.57 PFLOP/s; 628 us
 // while it had no loads in flight and spilled 72 registers.)
 template <int TM, int TN>
@@ -1498,10 +1504,12 @@ struct EpiShape {
   static constexpr int RING = FIRA_RING_STAGES * RingShape<TM, TN>::STAGE, ALL = LDS > RING ? LDS : RING;
 };
 #define FIRA_BACK_LDS (EpiShape<4, 2>::ALL)
-template <int MODE, typename T, bool INTERIOR, int TM, int TN>
+enum EpiForm { kInside, kEdge, kNarrow };   // tiles inside the matrix, at its edge, of matrices with fewer than eight columns
+template <int MODE, typename T, EpiForm FORM, int TM, int TN>
 __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[TM][TN], char* lds, const FiraMat& mt,
                                                       const FiraEnt& ent, int i0, int j0, float c, float lr_alpha, bool unitk) {
   typedef typename Elem8<T>::Raw Raw;
+  constexpr bool INTERIOR = FORM == kInside;
   // passes in flight: 64 registers of G and W values beside the accumulators
   typedef EpiShape<TM, TN> Shape;
   constexpr int LANES = 8 * TM, PROWS = 64 / LANES, PASSES = 16 / PROWS;   // lanes of a row, rows of a pass, passes of a wave's share of a slab
@@ -1522,23 +1530,21 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[TM][TN], c
   const long long lane_off = (unsigned)(ih * (int)mt.ld + jl);
   auto slab_row = [&](int p) { return 16 * wm + PROWS * p + ih; };
   // Edge tiles: the first column loaded, this lane's behind it, and what its values have to be moved down by.
-  const bool whole8 = mt.n >= 8;
-  const int jc0 = min(j0, mt.n - 8), jc = min((int)j, mt.n - 8) - jc0, jshift = whole8 ? (int)j - min((int)j, mt.n - 8) : 0;
-  const bool moved = !INTERIOR && whole8 && j0 + Shape::COLS > mt.n;
+  const int jc0 = min(j0, mt.n - 8), jc = min((int)j, mt.n - 8) - jc0, jshift = (int)j - min((int)j, mt.n - 8);
+  const bool moved = FORM == kEdge && (mt.n & 7) != 0 && j0 + Shape::COLS > mt.n;
   auto fetch = [&](int q, Raw& gr, Raw& wr) {   // pass q = PASSES * slab + pass of the slab
     const int tn = q / PASSES, p = q % PASSES;
-    if (INTERIOR) {
+    if constexpr (FORM == kInside) {
       const long long base = (wave_row0 + 32 * tn + PROWS * p) * mt.ld + j0;
       gr = Elem8<T>::template load_raw<true>(G + base, lane_off, 0);
       if (MODE == 1) wr = Elem8<T>::template load_raw<true>(W + base, lane_off, 0);
-    } else if (whole8) {
-      // rows and columns past the end repeat the last ones (the columns are moved back into place where they are used, so that
-      // the loads stay in flight until then)
+    } else if constexpr (FORM == kEdge) {
+      // rows and columns past the end repeat the last ones
       const int first = min((int)wave_row0 + 32 * tn + PROWS * p, mt.m - 1);
       const long long base = (long long)first * mt.ld + jc0;
       const long long off = (unsigned)((min(first + ih, mt.m - 1) - first) * (int)mt.ld + jc);
-      gr = Elem8<T>::template load_raw<true>(G + base, off, 0);
-      if (MODE == 1) wr = Elem8<T>::template load_raw<true>(W + base, off, 0);
+      gr = Elem8<T>::load_edge(G + base, off);
+      if (MODE == 1) wr = Elem8<T>::load_edge(W + base, off);
     } else {
       const long long i = (long long)i0 + wn * 32 * TN + 32 * tn + slab_row(p);
       const bool ok = i < mt.m && j < mt.n;
@@ -1679,8 +1685,9 @@ __global__ __launch_bounds__(FIRA_BACK_THREADS, TM == 4 ? 2 : sizeof(T) == 4 ? 3
   float sum;
   // matrix-level factor: the residual norm is taken with unit factors and scaled by the limiter kernel
   const bool unitk = MODE == 0 && hp.scaling == 1;
-  if (interior) sum = backproject_epilogue<MODE, T, true, TM, TN>(acc, lds, mt, ent, i0, j0, c, lr_alpha, unitk);
-  else sum = backproject_epilogue<MODE, T, false, TM, TN>(acc, lds, mt, ent, i0, j0, c, lr_alpha, unitk);
+  if (mt.n < 8) sum = backproject_epilogue<MODE, T, kNarrow, TM, TN>(acc, lds, mt, ent, i0, j0, c, lr_alpha, unitk);
+  else if (interior) sum = backproject_epilogue<MODE, T, kInside, TM, TN>(acc, lds, mt, ent, i0, j0, c, lr_alpha, unitk);
+  else sum = backproject_epilogue<MODE, T, kEdge, TM, TN>(acc, lds, mt, ent, i0, j0, c, lr_alpha, unitk);
 
   if (MODE == 0) {
     // deterministic workgroup reduction: xor-butterfly inside each wave, then waves in order
