@@ -28,14 +28,11 @@ def pytest_collection_modifyitems(config, items):
             it.add_marker(skip)
 
 
-@pytest.fixture(autouse=True)
-def no_automatic_collection_in_gpu_tests(request):
-    """A test that captures two graphs leaves the first one in a reference cycle (exception info and its frame); a garbage
-    collection that happens to start inside the second capture destroys it there, and the destructor's synchronisation, which a
-    capture forbids, ends the process.  GPU tests therefore run without automatic collections, each from a clean start."""
-    if request.node.get_closest_marker("gpu") is None:
-        yield
-        return
+@pytest.fixture
+def no_automatic_collection():
+    """For tests that capture graphs.  A graph that is left in a reference cycle (by exception info and its frame) is destroyed by
+    whatever garbage collection comes next; if that starts inside a capture, the destructor's synchronisation, which a capture
+    forbids, ends the process."""
     gc.collect()
     gc.disable()
     try:

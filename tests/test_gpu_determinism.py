@@ -43,6 +43,7 @@ def test_twin_matrices_stay_bit_identical(norm_mode):
     assert all(bool(torch.isfinite(W[j]).all()) for j in range(nb))
 
 
+@pytest.mark.usefixtures("no_automatic_collection")
 def test_step_replays_from_a_hip_graph():
     """fira_step only enqueues kernels once its work list is cached and the projectors' gate values are in
     (from the second step after an installation on), so a training loop can capture it in a HIP graph.  Three replays with fresh gradients (copied into the

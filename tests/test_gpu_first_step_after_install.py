@@ -55,6 +55,7 @@ def test_steps_after_installation_need_no_synchronisation(dtype, r):
     assert all(np.isinf(g[1]) for g in seen[0]) and all(np.isfinite(seen[1][i][1]) for i in (0, 1))
 
 
+@pytest.mark.usefixtures("no_automatic_collection")
 def test_what_a_graph_cannot_hold_is_refused_under_capture():
     """A refresh and a first step after an installation are refused while the stream is being captured; the capture goes on
     without them, replays, and the context goes on as a twin that was never asked."""
