@@ -60,10 +60,10 @@ void* static_scratch_address(int* device_out, std::string* why) {
 namespace {
 
 constexpr int kComputeUnits = 256, kLdsPerCu = 160 * 1024;
-// Back-projection tiles of a list up to which the update takes quarter tiles: three rounds of the whole tiles' 512 workgroups,
-// or, where bf16 operands of a rank above 256 are read twice as often for nothing by smaller tiles, not quite one
-// (fira_backproject_kernel has both sides measured).
-constexpr int kForwardsMaxR = 64;   // lists of such ranks are worked through forwards by every kernel (fira_backproject_kernel)
+// Largest rank of the lists that every kernel works through forwards, and back-projection tiles of a list up to which the update
+// takes quarter tiles: three rounds of the whole tiles' 512 workgroups, or, where bf16 operands of a rank above 256 are read
+// twice as often for nothing by smaller tiles, not quite one (fira_backproject_kernel has both sides of each measured).
+constexpr int kForwardsMaxR = 64;
 constexpr int kQuarterTiles = 1536, kQuarterTilesLongRank = 384;
 
 struct ListSlot {

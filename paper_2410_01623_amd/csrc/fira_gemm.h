@@ -711,7 +711,8 @@ __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds
   // Block of 32 k of a plane product: requests of two stages are in flight while one is multiplied, each stage's the
   // projector's plane (TM instructions per wavefront), then the gradient's block (4, into the set of registers that is free).
   // The last two stages request the first two blocks again, which nobody reads: every stage is the same code, with no
-  // copy of a register that a load is on its way to (and no line is requested twice at a time).
+  // copy of a register that a load is on its way to.  (Neighbouring blocks may share lines of the gradient, and a last block asks
+  // for its last row or column several times: these are loads into registers, which return in order whatever they ask for.)
   struct Block { int pos, kb; };
   auto next = [&](Block b) { return b.kb + 1 < nblocks ? Block{b.pos, b.kb + 1} : Block{b.pos == 5 ? 0 : b.pos + 1, 0}; };
   u32x4 ra[2][4];
@@ -722,7 +723,7 @@ __device__ __forceinline__ void split_pipeline(f32x16_t (&acc)[TM][2], char* lds
     for (int q = 0; q < 4; ++q) al.load_one(r, 32 * b.kb, q);
   };
   auto stage = [&](u32x4 (&r)[4], int aslot, int bslot, Block b) {
-    if (nblocks == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (two stages would have the same lines of G in flight)
+    if (nblocks == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the next stage's block of G is this one again)
     wait_loads<ASYNC ? TM + 4 : 0>(r);           // this stage's operands have landed (guarded loads are the compiler's, of whatever number)
     float x[4][4];
     al.unpack(r, 32 * b.kb, x);
@@ -1633,7 +1634,9 @@ __device__ __forceinline__ float backproject_epilogue(f32x16_t (&acc)[TM][TN], c
 // 95 and 90 (816); 1024 x 1024 and 1024 x 2736: r = 192 172 and 166 (1568), 320 and 323 (3136); r = 256 137 and 130 (784), 192 and
 // 187 (1568), 255 and 261 (2352), 1156 and 1207 (12544); r = 512 222 and 230 (1176); 1024 x 1024 at r = 512 98 and 102 (448);
 // 2048 x 5461 at r = 512 196 and 183 (352), with 2048 x 2048 510 and 534 (3120); fp32, 1024 x 2736: r = 512 523 and 510 (784),
-// r = 400 698 and 700 (1176), r = 256 3143 and 3212 (9408).
+// r = 400 698 and 700 (1176), r = 256 3143 and 3212 (9408).  With operands that are in no cache: 512 x 512 and 512 x 1376 at r = 128
+// 75 and 66 (102), 124 and 119 (816), 161 and 152 (1224); 1024 x 1024 and 1024 x 2736 at r = 256 143 and 138 (784), 281 and 286 (2352);
+// 2048 x 5461 at r = 512 208 and 203 (352), 1024 x 1024 112 and 115 (384); fp32, 1024 x 2736 at r = 256 276 and 257 (392).
 template <int MODE, typename T, int TM = 4, int TN = 2>
 __global__ __launch_bounds__(FIRA_BACK_THREADS, TM == 4 ? 2 : sizeof(T) == 4 ? 3 : 4) void fira_backproject_kernel(const FiraMat* __restrict__ mats,
                                                                            const FiraScal* __restrict__ scal,
@@ -1648,9 +1651,12 @@ __global__ __launch_bounds__(FIRA_BACK_THREADS, TM == 4 ? 2 : sizeof(T) == 4 ? 3
   const int wi = xcd_chunked_index(blockIdx.x, ntiles * PARTS);
   if (wi < 0) return;
   const int sub = wi % PARTS;
-  // backwards: what the kernels before it read and wrote last, G of the last matrices and their Z, is still in the
-  // memory-side cache (350M shapes 877 -> 860 us a step, 1B 4247 -> 4226, 16 blocks of 512 x 1376 162 -> 158; with ranks up to 64,
-  // where the update is a plain stream, 4713 -> 4740 us over the fine-tuning shapes: those go forwards).
+  // backwards: what the kernels before it read last, G of the last matrices, is still in the memory-side cache.  Update over the
+  // 350M shapes at r = 256 435 -> 423 us, 1B 2098 -> 2078, residual route 420 -> 412.  That holds after Adam on the Gram route as well, which
+  // has then come back to the first matrices (forwards / backwards, 350M shapes: two planes 544 / 534, r = 96 380 / 370, 8 blocks at r = 768
+  // 242 / 236; with Adam forwards as well 545, 381 and 245).  At ranks up to 64 the update is a plain stream and the direction is worth 1 % on one
+  // shape and nothing on another: steps 607 / 602 us over the 350M shapes at r = 16, 657 / 647 at r = 64, 2290 / 2287 over the 1B
+  // shapes at r = 64, 6819 / 6856 over the fine-tuning shapes at r = 16, 7199 / 7183 at r = 64 (runs differ by 60): those go forwards.
   const FiraTile tile = tiles[backwards ? ntiles - 1 - wi / PARTS : wi / PARTS];
   const FiraEnt ent = ents[tile.ent];
   if (MODE == 0 && use_gram(hp, scal[ent.mat])) return;   // this matrix takes the Gram route to ||S||

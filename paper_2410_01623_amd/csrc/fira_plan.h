@@ -189,7 +189,7 @@ struct RefreshPlan {
   int ntiles[2] = {0, 0};                 // virtual launches: [0] K-contiguous (real left), [1] K-slow (real right)
   std::vector<size_t> off_top, off_y, off_q, off_c, off_linv;
   std::vector<size_t> off_gb;             // fp32 matrices: bf16 rounding of the gradient, rows of gb_ld elements (else unused)
-  size_t top_begin = 0, top_end = 0;
+  size_t top_begin = 0;                   // the tables before it go up in one copy
 };
 
 // Row pitch (elements) of the bf16 rounding of an fp32 gradient that the refresh's way back reads.
@@ -220,7 +220,6 @@ bool make_refresh_plan(const Plan& plan, int count, const int* idx, RefreshPlan*
     const FiraMat& m = plan.mats[idx[e]].dev;
     rp->off_top[e] = take((size_t)round_up_int(m.L, 64) * m.rq * 2);
   }
-  rp->top_end = off;
   for (int e = 0; e < count; ++e) {
     const FiraMat& m = plan.mats[idx[e]].dev;
     rp->off_y[e] = take((size_t)m.S * m.r * 4);

@@ -11,8 +11,8 @@
 // back is the same kernel run on the other orientation of G with T as its K-blocked operand, which the way there writes
 // from its accumulators (store_projection).
 // The small dense algebra of the orthonormalisation (CholeskyQR: C = Y^T Y, C = L L^T, Q = Y L^-T by forward substitution) is
-// done in fp64 so that it survives gradients with a steep spectrum; the kernels below are plain
-// (no MFMA): r^2 S flops per matrix, every listed matrix in one grouped launch.
+// done in fp64, on the matrix pipe, so that it survives gradients with a steep spectrum: r^2 S flops per matrix, every listed
+// matrix in one grouped launch.  Whether a second orthonormalisation is needed is asked of bf16 plane products first.
 #pragma once
 #include "fira_device.h"
 #include "fira_elementwise.h"
