@@ -502,7 +502,7 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 // LDS tile.  The six plane products run one after the other over the whole contraction, the largest first (sequences A
 // and B): what the small ones add meets a sum that is already whole, and is rounded at the size of the result, where
 // all six taken together per block of k round six times as often at the size of the running sum (twice the error of R
-// where it cancels).  So G is read six times (8.2 GB through the fabric where G is 1.2, measured at the size below), which with
+// where it cancels).  So G is read six times (9.7 GB through the fabric where G is 1.2, measured at the size below), which with
 // the requests of two stages in flight is what bounds the kernel: 1491 us over the 168 matrices of 1024 x 1024 and
 // 1024 x 2736 at r = 256, 1807 with one stage's; the way through memory took 1361 + 1123 + 918 (six planes written, read
 // back, and a pass of its own for ||G_i||^2, which falls out of the first product here).
