@@ -502,7 +502,7 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 // LDS tile.  The six plane products run one after the other over the whole contraction, the largest first (sequences A
 // and B): what the small ones add meets a sum that is already whole, and is rounded at the size of the result, where
 // all six taken together per block of k round six times as often at the size of the running sum (twice the error of R
-// where it cancels).  So G is read six times (9.7 GB through the fabric where G is 1.2, measured at the size below), which with
+// where it cancels).  So G is read six times (10 GB through the fabric where G is 1.2, measured at the size below), which with
 // the requests of two stages in flight is what bounds the kernel: 1491 us over the 168 matrices of 1024 x 1024 and
 // 1024 x 2736 at r = 256, 1807 with one stage's; the way through memory took 1361 + 1123 + 918 (six planes written, read
 // back, and a pass of its own for ||G_i||^2, which falls out of the first product here).
@@ -1491,7 +1491,9 @@ struct Elem8<float> {
 // place where they are used, if the row's end is not a whole piece (realigned as they were loaded, every pass waited for its own).  The
 // element-by-element loads of matrices with fewer than eight columns are a form of their own: a copy of them beside every pass made
 // launches with many edge tiles wait for instructions.  Edge pieces are loaded through the caches, since a tile covers their lines in
-// part.  8 blocks of 1003 x 1003 and 1003 x 3001 at r = 64, update and norm pass: 146 and 73 us; 190 and 88 with one form for both and non-temporal loads, 210
+// part: past them, repeated steps of lists that fit the memory-side cache took 2 to 7 % longer (60M shapes 117 and 107 us, 21 matrices
+// of 704 x 704 and 704 x 1736 at r = 144 106 and 100), ones whose arrays just exceed it up to 2 % less (112 of 335 x 335 and 335 x 482 at r = 66
+// 130 and 133), large ones and first passes neither.  8 blocks of 1003 x 1003 and 1003 x 3001 at r = 64, update and norm pass: 146 and 73 us; 190 and 88 with one form for both and non-temporal loads, 210
 // and 99 realigned while loading; 31 matrices of 384 x 1168 at r = 4 22.8 and 14.5, 23.8 and 17.3, 24.7 and 14.4; the update over the 1B shapes
 // 2019, 2033 and 2071 us.
 // (The norm pass, MODE 0, over 168 matrices of 1024 x 1024 and 1024 x 2736 at r = 256: 271 us = 0.57 PFLOP/s; 628 us
