@@ -179,7 +179,7 @@ FIRA_API fira_status fira_set_variant(fira_ctx* ctx, fira_variant variant);
  * kernel that keeps R in registers, provided each of them is bf16 with r % 4 == 0 and 128 <= r <= 512;
  * the listed matrices on the residual route (e.g. in the first step after their projector was
  * installed) run them as two kernels with R in memory in the same step.  Any other step, and every
- * step with enable == 0, runs two kernels for all.  Both compute the same quantities; sums are taken in
+ * step with enable == 0, runs two kernels for all (bf16 matrices with r <= 64: one, which leaves R in memory as two do).  Both compute the same quantities; sums are taken in
  * a different order, so results agree to rounding, not bit for bit.  fira_last_step_fused: 1 if the
  * last fira_step on ctx took the fused kernel for every listed matrix, 0 if not (or ctx is NULL).  A
  * fused step keeps no copy of R: fira_get_lowrank then returns what an earlier two-kernel step left
@@ -194,7 +194,7 @@ FIRA_API int fira_last_step_fused(const fira_ctx* ctx);
  * for as long as that lasts.  planes = 2: Z is kept as two bf16 planes, its rounding and the rounding of the
  * remainder (16 mantissa bits), the contraction runs over both, and W follows exact arithmetic over long
  * runs; the back-projection does twice the multiplies and the fused projection/Adam kernel is not used.
- * Applies to bf16 matrices with r % 4 == 0, r <= 1024 and column or no factors; others keep one plane. */
+ * Applies to bf16 matrices with r <= 64, or r % 4 == 0 and r <= 1024, and column or no factors; others keep one plane. */
 FIRA_API fira_status fira_set_z_planes(fira_ctx* ctx, int planes);
 
 /* Copy the state of matrix idx to host memory.  Synchronises the stream.

@@ -76,6 +76,7 @@ struct ListSlot {
   int max_r_bf16 = 0;          // ... of the bf16 matrices
   int panel_lds = 0;           // LDS of the panel projection's widest listed matrix, 0 if none is listed
   bool split_proj = false;     // fp32 matrices that it does not serve are listed
+  bool general_bf16 = false;   // bf16 matrices that the small-rank kernel does not serve are listed
   // device views (inside the slab)
   FiraEnt* d_ents = nullptr;
   FiraTile* d_tiles[kNumTileLists] = {};
@@ -249,12 +250,13 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
   long long panel_groups = 0;
   s->max_r = s->max_r_bf16 = 0;
   s->panel_lds = 0;
-  s->split_proj = false;
+  s->split_proj = s->general_bf16 = false;
   for (int e = 0; e < count; ++e) {
     const HostMat& h = p.mats[idx[e]];
     const FiraMat& m = h.dev;
     s->max_r = std::max(s->max_r, m.r);
     if (m.kx == 1) s->max_r_bf16 = std::max(s->max_r_bf16, m.r);
+    s->general_bf16 = s->general_bf16 || (m.kx == 1 && !h.small_proj);
     if (panel_projection(m)) {
       panel_groups += 2 * h.ta_project;
       s->panel_lds = std::max(s->panel_lds, panel_lds(m.S));
@@ -566,7 +568,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   auto launch_project = [&](int norm_arg) {
     int nl = s->ntiles[kTilesProjBigLeft], nr = s->ntiles[kTilesProjBigRight];
     int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
-    if (nl + nr && s->ntiles[kTilesBackBf16])
+    if (s->general_bf16)
       hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), blk, FIRA_PROJ_LDS, q, ctx->d_mats, s->d_ents,
                          s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, 0, (const FiraScal*)ctx->d_scal, hp);
     launch_fp32_project(q, s, ctx->d_mats, s->d_tiles[kTilesProjBigLeft], nl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, 0);
@@ -630,7 +632,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     launch_project(want_g2);
     mark(1);
     // 2. Adam on R, factor norms
-    if (s->ntiles[kTilesBackBf16]) {
+    if (s->general_bf16) {
       const int planes = ctx->zsplit ? 2 : 1;
       if (need_residual)
         hipLaunchKernelGGL((fira_adam_kernel<1, true>), dim3(s->rowblocks), dim3(256),

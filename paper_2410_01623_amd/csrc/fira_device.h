@@ -45,9 +45,9 @@ struct FiraMat {
   int Lq;              // rows of Nb and Rb: L rounded up to 256
   int Sq;              // rows of Pn: S rounded up to 256
   int rq;              // rows of PT: r rounded up to 256
-  // 1: the Adam kernel keeps a factor's row in registers and writes Z for c = 1 directly (r a multiple of 4,
-  // up to FIRA_ZREADY_MAX_R, or FIRA_ZREADY_MAX_R_F32 for fp32 matrices); the Z kernel then only corrects
-  // the matrices whose limiter factor came out below 1.
+  // 1: the kernel that runs Adam keeps a factor's row in registers and writes Z for c = 1 directly (bf16 matrices with r <= FIRA_PS;
+  // r a multiple of 4, up to FIRA_ZREADY_MAX_R, or FIRA_ZREADY_MAX_R_F32 for fp32 matrices); the Z kernel then only
+  // corrects the matrices whose limiter factor came out below 1.
   int zready;
   // low-rank arrays, all "long-side major": row i holds the r values of factor i
   float* M;            // [L][r]   first moment
@@ -139,7 +139,7 @@ __device__ __forceinline__ bool calibrates_gram(const FiraHp& hp, const FiraScal
 // ---- tile geometry shared by the kernels and the host planner -----------------------------------
 #define FIRA_PA 128          // projection: tile rows on the gradient (long) side
 #define FIRA_PB 256          // projection: tile rows on the rank side
-#define FIRA_PS 64           // projection at small ranks (r <= 64): rank columns of the tile
+#define FIRA_PS 64           // projection and Adam at small ranks (bf16, r <= 64): rank columns of the tile
 #define FIRA_BA 256          // rank-axis contractions (back-projection): tile rows on the A side (n)
 #define FIRA_BB 128          // ... and on the B side (m)
 #define FIRA_ROWS_PER_WG 16  // Adam pass: 4 wavefronts x 4 rows

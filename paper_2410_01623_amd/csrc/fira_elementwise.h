@@ -33,11 +33,52 @@ __device__ __forceinline__ float adam_direction(float m1, float v1, float bias, 
   return bias * m1 * __builtin_amdgcn_rcpf(s + eps);
 }
 
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
+// A lane's double, in every lane.
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
+// Adam's bias correction after t steps (Eq. 4), in double: 1 - beta2^t loses all accuracy in fp32 at small t.  Called by whole
+// wavefronts, whose halves take one power each: a power is a chain of some three hundred instructions, which a launch of few tiles waits for.
+__device__ __forceinline__ float bias_correction(const FiraHp& hp, int t) {
+  const double p = 1.0 - pow((threadIdx.x & 32) ? hp.beta1 : hp.beta2, (double)t);
+  return (float)(sqrt(lane_value(p, 0)) / lane_value(p, 32));
+}
+
+// x of lane l ^ OFF, and x plus that, between registers (a shuffle goes through LDS, ten times as far): sums over the lanes of a factor
+// are chains of them.  Called by whole wavefronts.
+typedef unsigned u32x2_s __attribute__((__vector_size__(2 * sizeof(unsigned))));
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) { return __uint_as_float((unsigned)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), CTRL, 0xf, 0xf, true)); }
+template <int OFF>
+__device__ __forceinline__ float lane_xor(float x) {
+  static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8, "inside a row of 16 lanes");
+  if (OFF == 1) return dpp_move<0xb1>(x);                       // quad_perm 1 0 3 2
+  if (OFF == 2) return dpp_move<0x4e>(x);                       // quad_perm 2 3 0 1
+  if (OFF == 4) return dpp_move<0x1b>(dpp_move<0x141>(x));      // l ^ 7 (row_half_mirror), then ^ 3 (quad_perm 3 2 1 0)
+  return dpp_move<0x128>(x);                                    // row_ror 8
+}
+template <int OFF>
+__device__ __forceinline__ float add_xor(float x) {
+  if constexpr (OFF < 16) {
+    return x + lane_xor<OFF>(x);
+  } else {      // the swap leaves both lanes' values in every lane
+    const unsigned u = __float_as_uint(x);
+    const u32x2_s s = OFF == 16 ? __builtin_amdgcn_permlane16_swap(u, u, false, false) : __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+}
+// Sum over the LPR lanes that share a factor's row.
+template <int LPR>
+__device__ __forceinline__ float row_sum(float x) {
+  static_assert(LPR == 8 || LPR == 16 || LPR == 64, "");
+  if (LPR == 64) x = add_xor<16>(add_xor<32>(x));
+  if (LPR >= 16) x = add_xor<8>(x);
+  return add_xor<1>(add_xor<2>(add_xor<4>(x)));
+}
+__device__ __forceinline__ float wave_sum(float x) { return row_sum<64>(x); }
 
 // store one low-rank value as an MFMA operand element (plain bf16, or the three planes of the split)
 // (`op` is a K-blocked array with `rows` padded rows; plane p of the split occupies k = p*rp + a.)
@@ -223,7 +264,7 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
   }
 }
 
-// Small ranks (r <= 64, e.g. the fine-tuning setting's r = 32): a factor's row is at most 256 bytes, so
+// Small ranks (r <= 64) of fp32 matrices: a factor's row is at most 256 bytes, so
 // a wavefront takes its four rows at once, 16 lanes per row, instead of one after the other.
 template <int KX>
 __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp& hp, float bias, long long row_base,
@@ -253,11 +294,8 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
     *reinterpret_cast<gptr<f32x4>>(M + a) = mv;
     *reinterpret_cast<gptr<f32x4>>(V + a) = vv;
   }
-#pragma unroll
-  for (int off = 8; off >= 1; off >>= 1) {   // sums within the 16 lanes of a row
-    nn += __shfl_xor(nn, off, 64);
-    rr += __shfl_xor(rr, off, 64);
-  }
+  nn = row_sum<16>(nn);
+  rr = row_sum<16>(rr);
   const float k = (hp.scaling == 2) ? 1.0f : sqrtf(nn) / (sqrtf(rr) + hp.epsf);
   if (a < mt.rp) {
     const int planes = z_planes<KX>(hp);
@@ -301,22 +339,19 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const int e = find_entry(ents, count, rb);
   const FiraEnt ent = ents[e];
   const FiraMat mt = mats[ent.mat];
-  if ((mt.kx == 1) != (KX == 1)) return;
+  if ((mt.kx == 1) != (KX == 1) || (KX == 1 && mt.r <= FIRA_PS)) return;   // (small ranks: fira_project_small_kernel)
   bf16_raw* zl = reinterpret_cast<bf16_raw*>(adam_lds);
   const bool zready = mt.zready && hp.scaling != 1;   // the matrix-level factor is not known in this kernel
-  // bias correction with the 1-based step count (Eq. 4), in double: 1 - beta2^t loses all
-  // accuracy in fp32 at small t.
   const FiraScal sc = scal[ent.mat];
-  const int t = sc.t + 1;
   const bool gram = use_gram(hp, sc);
   if (hp.mixed && gram) return;                // the fused kernel has served this matrix
-  const float bias = (float)(sqrt(1.0 - pow(hp.beta2, (double)t)) / (1.0 - pow(hp.beta1, (double)t)));
+  const float bias = bias_correction(hp, sc.t + 1);   // (the step count is 1-based)
   const int wave = threadIdx.x >> 6;
   const long long row_base = (long long)(rb - ent.row0) * FIRA_ROWS_PER_WG + wave * 4;
   const int planes = z_planes<KX>(hp);
   const bool staged = STAGE_R && zready && !gram && mt.r > 64 && mt.r <= FIRA_RSTAGE_MAX_R;
   bf16_raw* rl = staged ? zl + planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32) : nullptr;
-  if (zready && mt.r <= 64) adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, wave);
+  if (KX != 1 && zready && mt.r <= 64) adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, wave);
   else for (int i = 0; i < 4; ++i) {
     const long long row = row_base + i;
     if (row >= mt.L) {
@@ -481,7 +516,12 @@ __device__ __forceinline__ void fixz_row(const FiraMat& mt, float f, long long r
   for (int a = lane * 4; a < mt.r; a += 256) {
     const long long o = kblk_index(mt.Lq, row, a), ol = kblk_index(mt.Lq, row, mt.rp + a);
     const u32x2 zv = *reinterpret_cast<gptr<const u32x2>>(Nb + o);
-    const f32x4 rv = *reinterpret_cast<gptr<const f32x4>>(R + a);
+    f32x4 rv = f32x4{0.f, 0.f, 0.f, 0.f};      // (the operand's columns past r stay zero)
+    if ((mt.r & 3) == 0) rv = *reinterpret_cast<gptr<const f32x4>>(R + a);
+    else
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (a + e < mt.r) rv[e] = R[a + e];
     f32x4 z = f32x4{__uint_as_float(zv.x << 16), __uint_as_float(zv.x & 0xffff0000u), __uint_as_float(zv.y << 16),
                     __uint_as_float(zv.y & 0xffff0000u)};
     if (zsplit) {
@@ -590,7 +630,7 @@ __global__ __launch_bounds__(256) void fira_makez_kernel(const FiraMat* __restri
   const int rowblocks = (mt.L + FIRA_ROWS_PER_WG - 1) / FIRA_ROWS_PER_WG;
   // the limiter has already advanced t: the bias correction of this step uses the count as it stands now
   const int t = scal[ent.mat].t;
-  const float bias = fused_here || mt.kx != 1 ? (float)(sqrt(1.0 - pow(hp.beta2, (double)t)) / (1.0 - pow(hp.beta1, (double)t))) : 0.0f;
+  const float bias = fused_here || mt.kx != 1 ? bias_correction(hp, t) : 0.0f;
   for (int rb = part; rb < rowblocks; rb += FIRA_MAKEZ_PARTS) {
     if (zready && fused_here) {
       fixz_block_from_moments(mt, hp, c, bias, (long long)rb * FIRA_ROWS_PER_WG);

@@ -47,20 +47,17 @@ __device__ __forceinline__ float half_wave_reduce8(const float (&x)[8]) {
   const int lane = threadIdx.x & 63;
   float a[4], b[2];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float keep = (lane & 16) ? x[4 + j] : x[j], send = (lane & 16) ? x[j] : x[4 + j];
-    a[j] = keep + __shfl_xor(send, 16, 64);
+  for (int j = 0; j < 4; ++j) {          // x[j] stays in the even rows of 16 lanes, x[4 + j] in the odd ones
+    const u32x2_s s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[j]), __float_as_uint(x[4 + j]), false, false);
+    a[j] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
   }
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const float keep = (lane & 8) ? a[2 + j] : a[j], send = (lane & 8) ? a[j] : a[2 + j];
-    b[j] = keep + __shfl_xor(send, 8, 64);
+    b[j] = keep + lane_xor<8>(send);
   }
   const float keep = (lane & 4) ? b[1] : b[0], send = (lane & 4) ? b[0] : b[1];
-  float d = keep + __shfl_xor(send, 4, 64);
-  d += __shfl_xor(d, 2, 64);
-  d += __shfl_xor(d, 1, 64);
-  return d;
+  return add_xor<1>(add_xor<2>(keep + lane_xor<4>(send)));
 }
 
 // A wave-uniform pointer, in scalar registers whatever the compiler holds it in.
@@ -279,9 +276,12 @@ __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& m
   g.A = as_global(reinterpret_cast<const bf16_raw*>(ent.G));
   g.lda = mt.ld;
   g.KA = mt.S;
-  // bias correction with the 1-based step count (Eq. 4), in double as in fira_adam_kernel
-  const int t = scal[ent.mat].t + 1;
-  const float bias = (float)(sqrt(1.0 - pow(hp.beta2, (double)t)) / (1.0 - pow(hp.beta1, (double)t)));
+  const int t = scal[ent.mat].t + 1;             // 1-based
+  float bias;
+  auto prologue = [&] {
+    bias = bias_correction(hp, t);
+    asm volatile("" : "+v"(bias));               // (here, not where it is used)
+  };
   f32x16_t acc[TM][2];
   float sq[TM];
 #pragma unroll
@@ -296,13 +296,13 @@ __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& m
   const bool sumsq = TM == 2 ? (wave & 1) == 0 : wave == 0;      // the waves of the first 64 rank columns
   const bool interior = g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB;
   if (interior) {
-    if (sumsq) proj_pipeline<LEFT, true, true, RT, true, TM>(acc, lds, g, sq);
-    else if (RT == 1 || wave < 4) proj_pipeline<LEFT, true, false, RT, true, TM>(acc, lds, g, sq);
-    else if constexpr (RT == 2) proj_pipeline<LEFT, true, false, 2, false, TM>(acc, lds, g, sq);
+    if (sumsq) proj_pipeline<LEFT, true, true, RT, true, TM>(acc, lds, g, sq, prologue);
+    else if (RT == 1 || wave < 4) proj_pipeline<LEFT, true, false, RT, true, TM>(acc, lds, g, sq, prologue);
+    else if constexpr (RT == 2) proj_pipeline<LEFT, true, false, 2, false, TM>(acc, lds, g, sq, prologue);
   } else {
-    if (sumsq) proj_pipeline<LEFT, false, true, RT, true, TM>(acc, lds, g, sq);
-    else if (RT == 1 || wave < 4) proj_pipeline<LEFT, false, false, RT, true, TM>(acc, lds, g, sq);
-    else if constexpr (RT == 2) proj_pipeline<LEFT, false, false, 2, false, TM>(acc, lds, g, sq);
+    if (sumsq) proj_pipeline<LEFT, false, true, RT, true, TM>(acc, lds, g, sq, prologue);
+    else if (RT == 1 || wave < 4) proj_pipeline<LEFT, false, false, RT, true, TM>(acc, lds, g, sq, prologue);
+    else if constexpr (RT == 2) proj_pipeline<LEFT, false, false, 2, false, TM>(acc, lds, g, sq, prologue);
   }
   if (g.a_row0 + FIRA_PA <= mt.L && mt.r == 64 * TM * RT) project_adam_epilogue<RT, TM, true>(acc, lds, mt, hp, bias, g.a_row0, sq);
   else project_adam_epilogue<RT, TM, false>(acc, lds, mt, hp, bias, g.a_row0, sq);
@@ -342,4 +342,267 @@ __global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_project_adam_k
     if (ti < 0) return;
     project_adam_tile<false, RT>(lds, mats, scal, ents, tiles_right[ti], hp);
   }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Projection and Adam for small ranks (r <= 64, the fine-tuning setting's r = 32), bf16 matrices on every route and with any
+// rank.  The tile is 128 (gradient side) x 64 (rank): with a 256-wide rank tile three quarters or more of the multiplies
+// would work on padding.  Wave w owns gradient rows 32 w .. 32 w + 31 and all 64 rank columns (two accumulator
+// blocks), so the kernel needs few registers and 28 KB of LDS, several workgroups share a CU, and the
+// gradient stream is what bounds it.  Same pipeline as proj_pipeline (single gradient tile, E and O halves);
+// a ring stage is 64 rows x 32 k = 4 KB, one request instruction per wavefront, so the E-half wait is
+// vmcnt(1) and the O-half wait vmcnt(5) (one ring request and the four of A(S+1) are younger).
+//
+// A wave holds the whole rows R_i of its factors, so Adam runs on them there, without a barrier: the rows pass through LDS, so that
+// a factor's row is 8 or 16 lanes' four values each, and M, V, R and Z come and go in 16- and 8-byte pieces of whole rows.  R is
+// written, since fira_get_lowrank and the limited steps read it, but no pass of its own reads it back.
+// A step with the projection and Adam in two launches and in this one: 160 matrices of 4096 x 4096 and 4096 x 11008 at r = 32 6830 and 6700 us
+// (the projection alone 1745, Adam 334, this kernel 1958); 350M shapes at r = 16, 32 and 64 602, 612, 644 and 525, 540, 590, on the residual
+// route at r = 32 790 and 701; 8 blocks of 512 x 512 and 512 x 1376 at r = 64 87 and 74; one block of 256 x 256 and 256 x 688
+// 26.8 and 24.4 at r = 16, 26.0 and 26.1 at r = 64.  Ranks that are no multiple of four, whose N and R went out as operands
+// for a pass of their own to form Z from: 350M shapes at r = 50 791 and 577, the 1B shapes 2595 and 2165.
+// ------------------------------------------------------------------------------------------------
+#define FIRA_PROJ_SMALL_STAGE (FIRA_PS * 64)
+#define FIRA_PROJ_SMALL_PITCH 68   // floats of a factor's row in LDS: 16-byte alignment, banks shifted from row to row
+#define FIRA_PROJ_SMALL_LDS (FIRA_PA * FIRA_PROJ_SMALL_PITCH * 4)   // more than the gradient tile and the ring take
+static_assert(FIRA_PROJ_SMALL_LDS >= FIRA_PROJ_LDS_A + FIRA_RING_STAGES * FIRA_PROJ_SMALL_STAGE, "the multiply phase fits");
+
+template <bool SUMSQ>
+__device__ __forceinline__ void proj_compute_small(f32x16_t (&acc)[2], const char* la, const char* lb, int kk4, float& sq) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  bf16x8_t fa[2], fb[2][2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    fa[kk] = *reinterpret_cast<const bf16x8_t*>(la + lds_tile_off(32 * wave + (lane & 31), 2 * (kk4 + kk) + (lane >> 5)));
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      fb[kk][t] = *reinterpret_cast<const bf16x8_t*>(lb + ring_tile_off(32 * t + (lane & 31), 2 * kk + (lane >> 5)));
+  }
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk], fb[kk][t], acc[t], 0, 0, 0);
+    if (SUMSQ) sq = frag_sumsq(fa[kk], sq);
+  }
+}
+
+template <bool LEFT, bool FAST, bool SUMSQ, typename Prologue>
+__device__ __forceinline__ void proj_pipeline_small(f32x16_t (&acc)[2], char* lds, const GemmOperands& g, float& sq, Prologue prologue) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char* la = lds;
+  char* ring = lds + FIRA_PROJ_LDS_A;
+  const unsigned ring0 = (unsigned)(size_t)(lds_ptr)ring;
+  const int SS = g.KB / 64;
+  const int lrow = lane >> 2;
+  const int chunk = (lane & 3) ^ ring_swz(lrow);
+  const unsigned offb = (unsigned)(lrow * 64 + chunk * 16);
+  const char* pb = reinterpret_cast<const char*>((const bf16_raw*)g.B) + ((long long)g.b_row0 + 16 * wave) * 64;
+  auto request_b = [&](int s) {   // this wave's 16 of the stage's 64 rows
+    lds_dma16(pb + (long long)s * g.ldb * 64, offb, ring0 + (unsigned)((s % FIRA_RING_STAGES) * FIRA_PROJ_SMALL_STAGE + wave * 1024));
+  };
+  ProjALoader<LEFT, FAST> al(g);
+  u32x4 ra[4];
+  al.load(ra);                                 // A(0)
+  request_b(0);
+  request_b(1);
+  prologue();
+  auto stage = [&](auto last, int S) {
+    constexpr bool LAST = decltype(last)::value;
+    wait_loads<1>(ra);                         // A(S) and D(2S) have landed; D(2S+1) may be in flight
+    asm volatile("s_barrier" ::: "memory");
+    proj_store_a<LEFT>(la, ra);
+    if (!LAST) {
+      request_b(2 * S + 2);
+      al.load(ra);                             // A(S+1)
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    proj_compute_small<SUMSQ>(acc, la, ring + ((2 * S) % FIRA_RING_STAGES) * FIRA_PROJ_SMALL_STAGE, 0, sq);
+    // D(2S+1) has landed (guarded A loads may be fewer than 4 instructions: the edge path lets one stay)
+    if (LAST) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    else if (FAST) asm volatile("s_waitcnt vmcnt(5)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(1)\n\ts_barrier" ::: "memory");
+    if (!LAST) request_b(2 * S + 3);
+    proj_compute_small<SUMSQ>(acc, la, ring + ((2 * S + 1) % FIRA_RING_STAGES) * FIRA_PROJ_SMALL_STAGE, 2, sq);
+  };
+  for (int S = 0; S + 1 < SS; ++S) stage(std::false_type{}, S);
+  stage(std::true_type{}, SS - 1);
+}
+
+// Adam on the wave's 32 factors, row0 the first one: LPR lanes to a row of r <= 4 LPR, two passes of 64 / LPR rows at a time, the next two's M
+// and V requested before.  What a launch of few tiles waits for here is instructions, so what can be is formed once: offsets are
+// 32 bits (L r <= 2^28), the factors k_i are stored in one piece at the end, and ||N_i|| and ||R_i|| share a square root.
+// rows: [32][FIRA_PROJ_SMALL_PITCH], for R's way through LDS, k_i and ||R_i||^2 behind it.  g2: ||G_i||^2 of factor row0 + lane % 32.
+template <int LPR>
+__device__ __forceinline__ void small_adam_rows(const f32x16_t (&acc)[2], float* rows, const FiraMat& mt, const FiraScal& sc, const FiraHp& hp,
+                                                float bias, int row0, float g2) {
+  const int lane = threadIdx.x & 63, a = 4 * (lane % LPR), lrow = lane / LPR, r = mt.r;
+  constexpr int ROWS = 64 / LPR, PASSES = 32 / ROWS;
+  const bool matrix = hp.scaling == 1;              // one factor per matrix: the limiter kernel forms it from the rows' sums
+  const bool operand_r = matrix || !use_gram(hp, sc), two_planes = hp.zsplit && !matrix;
+  const int mine = min(max(r - a, 0), 4);           // this lane's values of a row
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto load4 = [&](gptr<char> base, unsigned off) {
+    gptr<const float> p = reinterpret_cast<gptr<const float>>(base + off);
+    if (mine == 4) return (f32x4)*reinterpret_cast<gptr<const f32x4_a4>>(p);
+    f32x4 v = zero;
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (e < mine) v[e] = p[e];
+    return v;
+  };
+  auto store4 = [&](gptr<char> base, unsigned off, const f32x4& v) {
+    gptr<float> p = reinterpret_cast<gptr<float>>(base + off);
+    if (mine == 4) *reinterpret_cast<gptr<f32x4_a4>>(p) = v;
+    else
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (e < mine) p[e] = v[e];
+  };
+  gptr<char> M = reinterpret_cast<gptr<char>>(as_global(mt.M)), V = reinterpret_cast<gptr<char>>(as_global(mt.V));
+  gptr<char> Rt = reinterpret_cast<gptr<char>>(as_global(mt.Rt)), Nb = reinterpret_cast<gptr<char>>(as_global(mt.Nb)), Rb = reinterpret_cast<gptr<char>>(as_global(mt.Rb));
+#pragma unroll
+  for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      rows[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * FIRA_PROJ_SMALL_PITCH + 32 * tn + (lane & 31)] = acc[tn][v];
+  // of this lane's next pass: its place in M, V and Rt, in the operands (whose second plane lies mt.rp / 32 K blocks on), and how many
+  // factors there are from its own
+  unsigned off = (unsigned)((row0 + lrow) * r + a) * 4u, op = (unsigned)(((a >> 5) * mt.Lq + row0 + lrow) * 32 + (a & 31)) * 2u;
+  const unsigned step = (unsigned)(ROWS * r) * 4u, plane = (unsigned)((mt.rp >> 5) * mt.Lq) * 64u;
+  int left = mt.L - row0 - lrow;
+  // the operand's columns past r stay zero, even for a non-finite factor
+  const u32x2 keep = u32x2{mine == 0 ? 0u : mine == 1 ? 0xffffu : ~0u, mine < 3 ? 0u : mine == 3 ? 0xffffu : ~0u};
+  f32x4 mnext[2], wnext[2];
+  auto request = [&](unsigned o, int n) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      mnext[p] = wnext[p] = zero;
+      if (n > ROWS * p && mine > 0) {
+        mnext[p] = load4(M, o + p * step);
+        wnext[p] = load4(V, o + p * step);
+      }
+    }
+  };
+  request(off, left);
+  float* here = rows + lrow * FIRA_PROJ_SMALL_PITCH;
+  // (the wave's lanes meet in LDS: its own accesses are in order, so a wait before the reads is all they need)
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll 1
+  for (int p0 = 0; p0 < PASSES; p0 += 2) {
+    f32x4 m[2], x[2];
+    float nn[2], rr[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const bool live = left > ROWS * p && mine > 0;
+      x[p] = *reinterpret_cast<const f32x4*>(here + p * ROWS * FIRA_PROJ_SMALL_PITCH + a);
+      f32x4 w;
+      nn[p] = rr[p] = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {                 // (the operand's padding multiplies a non-finite gradient to NaN)
+        x[p][e] = live && e < mine ? x[p][e] : 0.0f;
+        m[p][e] = hp.b1 * mnext[p][e] + hp.omb1 * x[p][e];
+        w[e] = hp.b2 * wnext[p][e] + hp.omb2 * (x[p][e] * x[p][e]);
+      }
+      if (live) {
+        store4(M, off + p * step, m[p]);
+        store4(V, off + p * step, w);
+        store4(Rt, off + p * step, x[p]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {                 // (zero where m is)
+        m[p][e] = adam_direction(m[p][e], w[e], bias, hp.epsf);
+        nn[p] += m[p][e] * m[p][e];
+        rr[p] += x[p][e] * x[p][e];
+      }
+    }
+    if (p0 + 2 < PASSES) request(off + 2 * step, left - 2 * ROWS);
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const float snn = row_sum<LPR>(nn[p]), srr = row_sum<LPR>(rr[p]);
+      const float root = sqrtf((lane & 1) ? srr : snn), other = lane_xor<1>(root);
+      const float k = hp.scaling == 2 ? 1.0f : ((lane & 1) ? other : root) / (((lane & 1) ? root : other) + hp.epsf);
+      if (a == 0) *reinterpret_cast<float2*>(here + p * ROWS * FIRA_PROJ_SMALL_PITCH + 64) = float2{matrix ? snn : k, srr};
+      const f32x4 z = matrix ? m[p] : m[p] - k * x[p];
+      const bool live = left > ROWS * p;
+      // rows past L are zero; the rows of a K block follow each other, 64 bytes each (a second block that is all padding holds the zeros
+      // it was initialised with)
+      const u32x2 h = pack_bf16x4(z), mask = live ? keep : u32x2{0u, 0u};
+      *reinterpret_cast<gptr<u32x2>>(Nb + (op + p * ROWS * 64)) = h & mask;
+      if (two_planes) *reinterpret_cast<gptr<u32x2>>(Nb + (op + p * ROWS * 64 + plane)) = split_remainder(z, h) & mask;
+      if (operand_r) *reinterpret_cast<gptr<u32x2>>(Rb + (op + p * ROWS * 64)) = pack_bf16x4(x[p]);
+    }
+    off += 2 * step;
+    op += 2 * ROWS * 64;
+    left -= 2 * ROWS;
+    here += 2 * ROWS * FIRA_PROJ_SMALL_PITCH;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  if (lane < 32 && row0 + lane < mt.L) {
+    const float2 kr = *reinterpret_cast<const float2*>(rows + lane * FIRA_PROJ_SMALL_PITCH + 64);
+    as_global(mt.phi)[row0 + lane] = kr.x;
+    if (matrix) as_global(mt.q)[row0 + lane] = kr.y;
+    else if (have_g2(hp)) as_global(mt.q)[row0 + lane] = kr.x * kr.x * residual_sq(hp, g2, kr.y);
+  }
+}
+
+template <bool LEFT, typename Prologue>
+__device__ __forceinline__ void project_small_tile(f32x16_t (&acc)[2], char* lds, const FiraMat& mt, const FiraEnt& ent, const FiraTile& tile,
+                                                   bool sumsq, float& sq, Prologue prologue) {
+  GemmOperands g;
+  g.a_row0 = tile.ta * FIRA_PA;
+  g.a_rows = mt.L;
+  g.b_row0 = 0;
+  g.b_rows = mt.r;
+  g.B = as_global<const bf16_raw>(mt.PT);
+  g.ldb = mt.rq;
+  g.KB = mt.Sp;
+  g.A = as_global(reinterpret_cast<const bf16_raw*>(ent.G));
+  g.lda = mt.ld;
+  g.KA = mt.S;
+  const bool interior = g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB;
+  if (interior) {
+    if (sumsq) proj_pipeline_small<LEFT, true, true>(acc, lds, g, sq, prologue);
+    else proj_pipeline_small<LEFT, true, false>(acc, lds, g, sq, prologue);
+  } else {
+    if (sumsq) proj_pipeline_small<LEFT, false, true>(acc, lds, g, sq, prologue);
+    else proj_pipeline_small<LEFT, false, false>(acc, lds, g, sq, prologue);
+  }
+}
+
+// Both orientations in one grid, as in fira_project_kernel.
+__global__ __launch_bounds__(FIRA_PROJ_THREADS, 4) void fira_project_small_kernel(const FiraMat* __restrict__ mats,
+                                                                                  const FiraEnt* __restrict__ ents,
+                                                                                  const FiraTile* __restrict__ tiles_left, int ntiles_left,
+                                                                                  int blocks_left,
+                                                                                  const FiraTile* __restrict__ tiles_right, int ntiles_right,
+                                                                                  int norm_mode, const FiraScal* __restrict__ scal, FiraHp hp) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_PROJ_SMALL_LDS bytes
+  const bool left = (int)blockIdx.x < blocks_left;
+  const int ti = left ? xcd_chunked_index(blockIdx.x, ntiles_left) : xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
+  if (ti < 0) return;
+  const FiraTile tile = left ? tiles_left[ti] : tiles_right[ti];
+  const FiraEnt ent = ents[tile.ent];
+  const FiraMat mt = mats[ent.mat];
+  f32x16_t acc[2];
+  float sq = 0.0f;
+#pragma unroll
+  for (int tn = 0; tn < 2; ++tn)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[tn][v] = 0.0f;
+  const bool sumsq = norm_mode == 1;           // every wave owns its own 32 factors
+  const int t = scal[ent.mat].t + 1;           // 1-based
+  float bias;
+  auto prologue = [&] {
+    bias = bias_correction(hp, t);
+    asm volatile("" : "+v"(bias));             // (here, not where it is used)
+  };
+  if (left) project_small_tile<true>(acc, lds, mt, ent, tile, sumsq, sq, prologue);
+  else project_small_tile<false>(acc, lds, mt, ent, tile, sumsq, sq, prologue);
+  const int lane = threadIdx.x & 63, row0 = tile.ta * FIRA_PA + 32 * (threadIdx.x >> 6);
+  const float g2 = sq + __shfl_xor(sq, 32, 64);
+  if (sumsq && lane < 32 && row0 + lane < mt.L) as_global(mt.g2)[row0 + lane] = g2;
+  __syncthreads();                             // the multiplies are done with LDS
+  float* rows = reinterpret_cast<float*>(lds) + 32 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * FIRA_PROJ_SMALL_PITCH;
+  if (mt.r <= 32) small_adam_rows<8>(acc, rows, mt, scal[ent.mat], hp, bias, row0, g2);
+  else small_adam_rows<16>(acc, rows, mt, scal[ent.mat], hp, bias, row0, g2);
 }

@@ -76,7 +76,7 @@ struct GemmOperands {
   gptr<const bf16_raw> B;  // B side: always K-blocked, zero padded to a multiple of 64 in K
   long long ldb;      // padded row count of B
   int b_row0, b_rows;
-  int KB;             // stored contraction length of B (>= KA, a multiple of 64)
+  int KB;             // stored contraction length of B (>= KA, a multiple of 64; ring core: of 32)
   int wrapA = 0, wrapB = 0;   // ring core only: K blocks of 32 after which the operand repeats (Z in two planes meets P twice); 0 = never
 };
 
@@ -182,8 +182,7 @@ __device__ __forceinline__ void ring_compute(f32x16_t (&acc)[TM][TN], const char
   gemm_mfma_slice(acc, f[1]);
 }
 
-// Both operands K-blocked with lda / ldb padded rows (multiples of 256) and KB stored k (a multiple
-// of 64).
+// Both operands K-blocked with lda / ldb padded rows (multiples of 256); KB of the stored k (a multiple of 32).
 template <int TM, int TN>
 __device__ __forceinline__ void ring_mainloop(f32x16_t (&acc)[TM][TN], char* lds, const GemmOperands& g) {
   typedef RingShape<TM, TN> Shape;
@@ -422,8 +421,9 @@ __device__ __forceinline__ void proj_compute(f32x16_t (&acc)[TM][2], const char*
 // straight-line code in which every request is followed by its own wait.)
 // TM = 2: half a rank tile (r <= 128), two wavefronts along the factors (64 each) and two along the rank; a ring
 // stage is 128 rows, two requests per wave, and the queue depths are TM where four requests make them 4 above.
-template <bool LEFT, bool FAST, bool SUMSQ, int RT = 1, bool LOADER = true, int TM = 4>
-__device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds, const GemmOperands& g, float (&sq)[TM]) {
+// prologue(): called when the first operands have been requested, for work that would otherwise stand before or after the contraction.
+template <bool LEFT, bool FAST, bool SUMSQ, int RT = 1, bool LOADER = true, int TM = 4, typename Prologue>
+__device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds, const GemmOperands& g, float (&sq)[TM], Prologue prologue) {
   static_assert(LOADER || RT == 2, "only the second rank tile's wavefronts go without the gradient");
   static_assert(TM == 4 || RT == 1, "half a rank tile, or whole ones");
   constexpr int STAGE = RT * TM * 4096;
@@ -453,6 +453,7 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
   if (loader) al.load(ra);                     // A(0)
   request_b(0);
   request_b(1);
+  prologue();
   // LAST: the final K stage requests nothing more.  It is written out separately rather than
   // guarded inside the loop, so that on every path a request is followed by the wait that covers it.
   auto stage = [&](auto last, int S) {
@@ -865,11 +866,11 @@ __device__ __forceinline__ void project_tile_as(char* lds, const FiraMat& mt, co
   // LEFT: the k rows of G are whole rows of the matrix (any ld); RIGHT: a row of G holds KA values
   const bool interior = g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB;
   if (interior) {
-    if (sumsq) proj_pipeline<LEFT, true, true, 1, true, TM>(acc, lds, g, sq);
-    else proj_pipeline<LEFT, true, false, 1, true, TM>(acc, lds, g, sq);
+    if (sumsq) proj_pipeline<LEFT, true, true, 1, true, TM>(acc, lds, g, sq, [] {});
+    else proj_pipeline<LEFT, true, false, 1, true, TM>(acc, lds, g, sq, [] {});
   } else {
-    if (sumsq) proj_pipeline<LEFT, false, true, 1, true, TM>(acc, lds, g, sq);
-    else proj_pipeline<LEFT, false, false, 1, true, TM>(acc, lds, g, sq);
+    if (sumsq) proj_pipeline<LEFT, false, true, 1, true, TM>(acc, lds, g, sq, [] {});
+    else proj_pipeline<LEFT, false, false, 1, true, TM>(acc, lds, g, sq, [] {});
   }
   if (sumsq) {
     gptr<float> g2 = as_global(mt.g2);
@@ -1147,148 +1148,6 @@ __global__ __launch_bounds__(256, FIRA_PANEL_WG_PER_CU) void fira_panel_project_
   if (!panel_projection(mt) || a_row0 >= mt.L) return;
   if (left) project_panel<true>(lds, mt, ent, a_row0, norm_mode, pack);
   else project_panel<false>(lds, mt, ent, a_row0, norm_mode, pack);
-}
-
-// ------------------------------------------------------------------------------------------------
-// Kernel 1 for small ranks (r <= 64, the fine-tuning setting's r = 32): with a 256-wide rank tile three
-// quarters or more of the multiplies would work on padding.  Here the tile is 128 (gradient side) x 64
-// (rank); wave w owns gradient rows 32 w .. 32 w + 31 and all 64 rank columns (two accumulator
-// blocks), so the kernel needs few registers and 28 KB of LDS, several workgroups share a CU, and the
-// gradient stream is what bounds it.  Same pipeline as above (single gradient tile, E and O halves);
-// a ring stage is 64 rows x 32 k = 4 KB, one request instruction per wavefront, so the E-half wait is
-// vmcnt(1) and the O-half wait vmcnt(5) (one ring request and the four of A(S+1) are younger).
-// ------------------------------------------------------------------------------------------------
-#define FIRA_PROJ_SMALL_STAGE (FIRA_PS * 64)
-#define FIRA_PROJ_SMALL_LDS (FIRA_PROJ_LDS_A + FIRA_RING_STAGES * FIRA_PROJ_SMALL_STAGE)
-
-template <bool SUMSQ>
-__device__ __forceinline__ void proj_compute_small(f32x16_t (&acc)[2], const char* la, const char* lb, int kk4, float& sq) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  bf16x8_t fa[2], fb[2][2];
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
-    fa[kk] = *reinterpret_cast<const bf16x8_t*>(la + lds_tile_off(32 * wave + (lane & 31), 2 * (kk4 + kk) + (lane >> 5)));
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-      fb[kk][t] = *reinterpret_cast<const bf16x8_t*>(lb + ring_tile_off(32 * t + (lane & 31), 2 * kk + (lane >> 5)));
-  }
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk], fb[kk][t], acc[t], 0, 0, 0);
-    if (SUMSQ) sq = frag_sumsq(fa[kk], sq);
-  }
-}
-
-template <bool LEFT, bool FAST, bool SUMSQ>
-__device__ __forceinline__ void proj_pipeline_small(f32x16_t (&acc)[2], char* lds, const GemmOperands& g, float& sq) {
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  char* la = lds;
-  char* ring = lds + FIRA_PROJ_LDS_A;
-  const unsigned ring0 = (unsigned)(size_t)(lds_ptr)ring;
-  const int SS = g.KB / 64;
-  const int lrow = lane >> 2;
-  const int chunk = (lane & 3) ^ ring_swz(lrow);
-  const unsigned offb = (unsigned)(lrow * 64 + chunk * 16);
-  const char* pb = reinterpret_cast<const char*>((const bf16_raw*)g.B) + ((long long)g.b_row0 + 16 * wave) * 64;
-  auto request_b = [&](int s) {   // this wave's 16 of the stage's 64 rows
-    lds_dma16(pb + (long long)s * g.ldb * 64, offb, ring0 + (unsigned)((s % FIRA_RING_STAGES) * FIRA_PROJ_SMALL_STAGE + wave * 1024));
-  };
-  ProjALoader<LEFT, FAST> al(g);
-  u32x4 ra[4];
-  al.load(ra);                                 // A(0)
-  request_b(0);
-  request_b(1);
-  auto stage = [&](auto last, int S) {
-    constexpr bool LAST = decltype(last)::value;
-    wait_loads<1>(ra);                         // A(S) and D(2S) have landed; D(2S+1) may be in flight
-    asm volatile("s_barrier" ::: "memory");
-    proj_store_a<LEFT>(la, ra);
-    if (!LAST) {
-      request_b(2 * S + 2);
-      al.load(ra);                             // A(S+1)
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    proj_compute_small<SUMSQ>(acc, la, ring + ((2 * S) % FIRA_RING_STAGES) * FIRA_PROJ_SMALL_STAGE, 0, sq);
-    // D(2S+1) has landed (guarded A loads may be fewer than 4 instructions: the edge path lets one stay)
-    if (LAST) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    else if (FAST) asm volatile("s_waitcnt vmcnt(5)\n\ts_barrier" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(1)\n\ts_barrier" ::: "memory");
-    if (!LAST) request_b(2 * S + 3);
-    proj_compute_small<SUMSQ>(acc, la, ring + ((2 * S + 1) % FIRA_RING_STAGES) * FIRA_PROJ_SMALL_STAGE, 2, sq);
-  };
-  for (int S = 0; S + 1 < SS; ++S) stage(std::false_type{}, S);
-  stage(std::true_type{}, SS - 1);
-}
-
-template <bool LEFT>
-__device__ __forceinline__ void project_small_tile(char* lds, const FiraMat* __restrict__ mats, const FiraEnt* __restrict__ ents,
-                                                   const FiraTile& tile, int norm_mode, const FiraScal* __restrict__ scal, const FiraHp& hp) {
-  const FiraEnt ent = ents[tile.ent];
-  if (hp.mixed && use_gram(hp, scal[ent.mat])) return;   // (never the case today: the fused kernel takes no rank this small)
-  const FiraMat mt = mats[ent.mat];
-  GemmOperands g;
-  g.a_row0 = tile.ta * FIRA_PA;
-  g.a_rows = mt.L;
-  g.b_row0 = 0;
-  g.b_rows = mt.r;
-  g.B = as_global<const bf16_raw>(mt.PT);
-  g.ldb = mt.rq;
-  g.KB = mt.Sp;
-  g.A = as_global(reinterpret_cast<const bf16_raw*>(ent.G));
-  g.lda = mt.ld;
-  g.KA = mt.S;
-  f32x16_t acc[2];
-  float sq = 0.0f;
-#pragma unroll
-  for (int tn = 0; tn < 2; ++tn)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[tn][v] = 0.0f;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bool sumsq = norm_mode == 1;           // every wave owns its own 32 factors
-  const bool interior = g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB;
-  if (interior) {
-    if (sumsq) proj_pipeline_small<LEFT, true, true>(acc, lds, g, sq);
-    else proj_pipeline_small<LEFT, true, false>(acc, lds, g, sq);
-  } else {
-    if (sumsq) proj_pipeline_small<LEFT, false, true>(acc, lds, g, sq);
-    else proj_pipeline_small<LEFT, false, false>(acc, lds, g, sq);
-  }
-  if (sumsq) {
-    const float tot = sq + __shfl_xor(sq, 32, 64);
-    const int row = g.a_row0 + 32 * wave + (lane & 31);
-    if (lane < 32 && row < mt.L) as_global(mt.g2)[row] = tot;
-  }
-  gptr<float> Rt = as_global(mt.Rt);
-#pragma unroll
-  for (int tn = 0; tn < 2; ++tn) {
-    const int col = 32 * tn + (lane & 31);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = g.a_row0 + 32 * wave + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      if (row < mt.L && col < mt.r) Rt[(long long)row * mt.r + col] = acc[tn][v];
-    }
-  }
-}
-
-// bf16 matrices with r <= 64 only (the host keeps their tiles in lists of their own); both orientations
-// in one grid, as in fira_project_kernel.
-__global__ __launch_bounds__(FIRA_PROJ_THREADS, 4) void fira_project_small_kernel(const FiraMat* __restrict__ mats,
-                                                                                  const FiraEnt* __restrict__ ents,
-                                                                                  const FiraTile* __restrict__ tiles_left, int ntiles_left,
-                                                                                  int blocks_left,
-                                                                                  const FiraTile* __restrict__ tiles_right, int ntiles_right,
-                                                                                  int norm_mode, const FiraScal* __restrict__ scal, FiraHp hp) {
-  extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_PROJ_SMALL_LDS bytes
-  if ((int)blockIdx.x < blocks_left) {
-    const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
-    if (ti < 0) return;
-    project_small_tile<true>(lds, mats, ents, tiles_left[ti], norm_mode, scal, hp);
-  } else {
-    const int ti = xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
-    if (ti < 0) return;
-    project_small_tile<false>(lds, mats, ents, tiles_right[ti], norm_mode, scal, hp);
-  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1676,7 +1535,7 @@ __global__ __launch_bounds__(FIRA_BACK_THREADS, TM == 4 ? 2 : sizeof(T) == 4 ? 3
   g.b_rows = mt.m;
   // Z in two planes (hi + lo): the contraction runs over 2 rp, and the projector's K blocks are used twice
   const bool split = MODE == 1 && hp.zsplit && mt.zready && mt.kx == 1 && hp.scaling != 1;
-  g.KA = g.KB = (split ? 2 : mt.kx) * mt.rp;
+  g.KA = g.KB = split ? 2 * mt.rp : (mt.r + 31) / 32 * 32;   // (fp32 matrices: split_mainloop counts for itself)
   g.wrapA = (split && !mt.left) ? mt.rp / FIRA_RK : 0;
   g.wrapB = (split && mt.left) ? mt.rp / FIRA_RK : 0;
   g.A = mt.left ? lowrank : proj;

@@ -34,7 +34,7 @@ struct HostMat {
   int ta_project = 0, tb_project = 0, ta_back = 0, tb_back = 0;
   int rowblocks = 0;
   int fuse_list = -1;         // tile list of the fused projection/Adam kernel, or -1 if the matrix cannot take it
-  bool small_proj = false;    // bf16 with r <= 64: projected by the small-rank kernel
+  bool small_proj = false;    // bf16 with r <= 64: projection and Adam by the small-rank kernel
 };
 
 // kTilesFuse + (r > 256 ? 2 : 0) + (left ? 0 : 1): tiles of the fused projection/Adam kernel (one per 128 factors)
@@ -84,7 +84,8 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     m.dtype = d[i].wg_dtype;
     m.kx = (m.dtype == FIRA_F32) ? FIRA_KX_SPLIT : 1;
     m.Lq = round_up_int(m.L, 256); m.Sq = round_up_int(m.S, 256); m.rq = round_up_int(m.r, 256);
-    m.zready = ((m.r & 3) == 0 && m.r <= (m.kx == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32)) ? 1 : 0;
+    h.small_proj = m.kx == 1 && m.r <= FIRA_PS;
+    m.zready = (h.small_proj || ((m.r & 3) == 0 && m.r <= (m.kx == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32))) ? 1 : 0;
     if (m.zready && m.kx != 1) plan->adam_lds_f32 = std::max(plan->adam_lds_f32, FIRA_ROWS_PER_WG * m.rp * 6);
     if (m.zready && m.kx == 1) plan->adam_lds = std::max(plan->adam_lds, FIRA_ROWS_PER_WG * m.rp * 2);   // (twice that with Z in two planes)
     if (m.zready && m.kx == 1 && m.r <= FIRA_RSTAGE_MAX_R) plan->adam_lds_staged = std::max(plan->adam_lds_staged, FIRA_ROWS_PER_WG * m.rp * 2);
@@ -106,7 +107,6 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     h.tiles_back = h.ta_back * h.tb_back;
     h.rowblocks = (m.L + FIRA_ROWS_PER_WG - 1) / FIRA_ROWS_PER_WG;
     total_tiles[m.left ? kTilesProjectLeft : kTilesProjectRight] += h.tiles_project;
-    h.small_proj = m.kx == 1 && m.r <= FIRA_PS;
     total_tiles[(h.small_proj ? kTilesProjSmallLeft : kTilesProjBigLeft) + (m.left ? 0 : 1)] += h.tiles_project;
     total_tiles[m.dtype == FIRA_BF16 ? kTilesBackBf16 : kTilesBackF32] += h.tiles_back;
     if (m.zready && m.kx == 1 && m.r >= FIRA_FUSE_MIN_R && m.r <= FIRA_FUSE_MAX_R) {

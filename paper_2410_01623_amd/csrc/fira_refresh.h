@@ -285,12 +285,6 @@ __device__ __forceinline__ bool refresh_pass_done(const FiraRefreshEnt& e) { ret
 #define FIRA_CHOL_NB 32
 #define FIRA_CHOL_PAN_ROWS 544   // panel rows kept in LDS: 544 x 33 doubles = 140 KB (every panel of a matrix with r <= 576)
 
-__device__ __forceinline__ double lane_value(double x, int lane) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
 // sqrt(x) and 1 / sqrt(x) for a normal x > 0: two rounds of Goldschmidt's coupled iteration from the hardware's estimate
 // and a last Newton correction of each (within one ulp), a third of the instructions of a square root and a division.
 __device__ __forceinline__ void sqrt_and_inverse(double x, double& root, double& inv) {
