@@ -45,8 +45,8 @@ struct FiraMat {
   int Lq;              // rows of Nb and Rb: L rounded up to 256
   int Sq;              // rows of Pn: S rounded up to 256
   int rq;              // rows of PT: r rounded up to 256
-  // 1: the kernel that runs Adam keeps a factor's row in registers and writes Z for c = 1 directly (bf16 matrices with r <= FIRA_PS;
-  // r a multiple of 4, up to FIRA_ZREADY_MAX_R, or FIRA_ZREADY_MAX_R_F32 for fp32 matrices); the Z kernel then only
+  // 1: the kernel that runs Adam keeps a factor's row in registers and writes Z for c = 1 directly (r up to
+  // FIRA_ZREADY_MAX_R, or FIRA_ZREADY_MAX_R_F32 for fp32 matrices); the Z kernel then only
   // corrects the matrices whose limiter factor came out below 1.
   int zready;
   // low-rank arrays, all "long-side major": row i holds the r values of factor i

@@ -2,6 +2,7 @@
 // with the per-factor norms, the limiter scalar, the construction of the back-projection operand,
 // and the operand conversions done when a projector is installed.
 #pragma once
+#include <type_traits>
 #include "fira_device.h"
 
 
@@ -179,6 +180,35 @@ __device__ __forceinline__ u32x2 pack_bf16x4(const f32x4& z) { return u32x2{pack
 // hi + lo carries 16 mantissa bits of z.
 __device__ __forceinline__ u32x2 split_remainder(const f32x4& z, const u32x2& hi) { return pack_bf16x4(bf16_remainder(z, hi)); }
 
+// The values a .. a + 3 of a low-rank row of r, `mine` of which exist (a row starts at any element if r is no multiple of four), and back.
+__device__ __forceinline__ f32x4 load_row4(gptr<const float> p, int mine) {
+  if (mine >= 4) return *reinterpret_cast<gptr<const f32x4_a4>>(p);
+  f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int e = 0; e < 3; ++e)
+    if (e < mine) v[e] = p[e];
+  return v;
+}
+__device__ __forceinline__ void store_row4(gptr<float> p, const f32x4& v, int mine) {
+  if (mine >= 4) *reinterpret_cast<gptr<f32x4_a4>>(p) = v;
+  else
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (e < mine) p[e] = v[e];
+}
+// The same without a branch for rows of at least four values: the last four instead of a group that ends past r, moved down.
+__device__ __forceinline__ f32x4 load_row4_inside(gptr<const float> row, int a, int r) {
+  const int at = min(a, r - 4), d = a - at;
+  f32x4 v = *reinterpret_cast<gptr<const f32x4_a4>>(row + at);
+  if (d & 1) v = f32x4{v.y, v.z, v.w, 0.f};
+  if (d & 2) v = f32x4{v.z, v.w, 0.f, 0.f};
+  return v;
+}
+// Mask of their bf16 pairs: an operand's columns past r stay zero, even for a non-finite factor.
+__device__ __forceinline__ u32x2 row4_mask(int mine) {
+  return u32x2{mine <= 0 ? 0u : mine == 1 ? 0xffffu : ~0u, mine < 3 ? 0u : mine == 3 ? 0xffffu : ~0u};
+}
+
 // Planes of an operand row element: 1, 2 (Z of a bf16 matrix with hp.zsplit) or 3 (fp32 matrices).
 template <int KX>
 __device__ __forceinline__ int z_planes(const FiraHp& hp) { return KX == 1 ? (hp.zsplit ? 2 : 1) : 3; }
@@ -193,7 +223,7 @@ __device__ __forceinline__ void bf16_planes(const f32x4& z, int planes, u32x2 (&
   }
 }
 
-// Same update for matrices with r % 4 == 0 and r <= FIRA_ZREADY_MAX_R (fp32: FIRA_ZREADY_MAX_R_F32): the factor's N
+// Same update for matrices with r <= FIRA_ZREADY_MAX_R (fp32: FIRA_ZREADY_MAX_R_F32): the factor's N
 // and R stay in registers until k_i is known, and the row is written once as the back-projection operand for
 // an inactive limiter, Z_i = N_i - k_i R_i, rounded from fp32 a single time.  R is written as an
 // operand only when the residual contraction will need it.  Z is K-blocked, 64 B per row and K
@@ -201,7 +231,7 @@ __device__ __forceinline__ void bf16_planes(const f32x4& z, int planes, u32x2 (&
 // 1 KB contiguous pieces (fira_adam_kernel).  fp32 matrices move 26 bytes per element here; with N and R written
 // as planes and turned into Z by a pass of their own it was 92 (350M shapes at r = 256: 916 + 602 -> 364 us).
 // rl: the same image of R for bf16 matrices on the residual route (null: R goes out from here, in 64-byte pieces).
-template <int KX, int NIT>   // 256 * NIT >= r
+template <int KX, int NIT, bool ODD>   // 256 * NIT >= r; ODD: r is no multiple of four
 __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp& hp, float bias, long long row, bool gram,
                                                 bf16_raw* zl, bf16_raw* rl, int rowlocal) {
   const int lane = threadIdx.x & 63;
@@ -216,9 +246,9 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
   for (int it = 0; it < NIT; ++it) {
     const int a = lane * 4 + 256 * it;
     if (a < r) {
-      rv[it] = *reinterpret_cast<gptr<const f32x4>>(R + a);
-      f32x4 mv = *reinterpret_cast<gptr<const f32x4>>(M + a);
-      f32x4 vv = *reinterpret_cast<gptr<const f32x4>>(V + a);
+      auto load = [&](gptr<const float> p) { return ODD ? load_row4_inside(p, a, r) : (f32x4)*reinterpret_cast<gptr<const f32x4>>(p + a); };
+      rv[it] = load(R);
+      f32x4 mv = load(M), vv = load(V);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         mv[e] = hp.b1 * mv[e] + hp.omb1 * rv[it][e];
@@ -227,8 +257,8 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
         nn += nv[it][e] * nv[it][e];
         rr += rv[it][e] * rv[it][e];
       }
-      *reinterpret_cast<gptr<f32x4>>(M + a) = mv;
-      *reinterpret_cast<gptr<f32x4>>(V + a) = vv;
+      store_row4(M + a, mv, ODD ? r - a : 4);
+      store_row4(V + a, vv, ODD ? r - a : 4);
     }
   }
   nn = wave_sum(nn);
@@ -243,6 +273,11 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
       zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};
       if (a < r) {
         bf16_planes<KX>(nv[it] - k * rv[it], planes, zp);
+        if (ODD) {
+          const u32x2 mask = row4_mask(r - a);
+#pragma unroll
+          for (int p = 0; p < 3; ++p) zp[p] &= mask;
+        }
         if (!gram && !rl) {
           u32x2 rb[3];
           bf16_planes<KX>(rv[it], KX == 1 ? 1 : 3, rb);
@@ -280,9 +315,9 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
   f32x4 nv = f32x4{0.f, 0.f, 0.f, 0.f}, rv = nv;
   float nn = 0.0f, rr = 0.0f;
   if (live) {
-    rv = *reinterpret_cast<gptr<const f32x4>>(R + a);
-    f32x4 mv = *reinterpret_cast<gptr<const f32x4>>(M + a);
-    f32x4 vv = *reinterpret_cast<gptr<const f32x4>>(V + a);
+    rv = load_row4(R + a, r - a);
+    f32x4 mv = load_row4(M + a, r - a);
+    f32x4 vv = load_row4(V + a, r - a);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       mv[e] = hp.b1 * mv[e] + hp.omb1 * rv[e];
@@ -291,8 +326,8 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
       nn += nv[e] * nv[e];
       rr += rv[e] * rv[e];
     }
-    *reinterpret_cast<gptr<f32x4>>(M + a) = mv;
-    *reinterpret_cast<gptr<f32x4>>(V + a) = vv;
+    store_row4(M + a, mv, r - a);
+    store_row4(V + a, vv, r - a);
   }
   nn = row_sum<16>(nn);
   rr = row_sum<16>(rr);
@@ -303,6 +338,9 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
     zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};   // rows beyond L and columns beyond r: the operand's zero padding
     if (live) {
       bf16_planes<KX>(nv - k * rv, planes, zp);
+      const u32x2 mask = row4_mask(r - a);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) zp[p] &= mask;
       if (!gram) {
         u32x2 rb[3];
         bf16_planes<KX>(rv, KX == 1 ? 1 : 3, rb);
@@ -322,6 +360,10 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
   }
 }
 
+// Rows that are no multiple of four values (ODD) have forms of their own, so that the others do not pay for their tails: N and R
+// used to leave as operands there, for a pass of their own to form Z from.  A step over 24 blocks of 1024 x 2736 at r = 97 904 us then, 781
+// now, on the residual route 1056 and 954; 8 blocks of 2048 x 5461 at r = 255, 511 and 770 1277, 1938, 2967 and 1096, 1646, 2447; four
+// blocks of 800 x 2000 in fp32 at r = 130 394 and 334.
 // STAGE_R: the launch's LDS has room for R beside Z (bf16 matrices with 64 < r <= FIRA_RSTAGE_MAX_R on the residual route): R, too, then
 // leaves in pieces of 1 KB.  Above that rank the image would halve the wavefronts in flight.  Adam on the residual route over
 // 168 matrices of the 1B shapes at r = 512: 1420 us, 1725 with R in 64-byte pieces; 350M shapes at r = 256: 346, 397.
@@ -351,24 +393,33 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const int planes = z_planes<KX>(hp);
   const bool staged = STAGE_R && zready && !gram && mt.r > 64 && mt.r <= FIRA_RSTAGE_MAX_R;
   bf16_raw* rl = staged ? zl + planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32) : nullptr;
-  if (KX != 1 && zready && mt.r <= 64) adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, wave);
-  else for (int i = 0; i < 4; ++i) {
-    const long long row = row_base + i;
-    if (row >= mt.L) {
-      if (zready)   // rows of the padding: zeros
-        for (int a = (threadIdx.x & 63) * 4; a < (planes + (staged ? 1 : 0)) * mt.rp; a += 256)
-          *reinterpret_cast<u32x2*>(zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + i) * 32 + (a & 31)) = u32x2{0u, 0u};
-      continue;
-    }
-    if (zready) {
-      constexpr int max_nit = (KX == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32) / 256;
-      if (mt.r <= 256) adam_row_zready<KX, 1>(mt, hp, bias, row, gram, zl, rl, wave * 4 + i);
-      else if (mt.r <= 512) adam_row_zready<KX, 2>(mt, hp, bias, row, gram, zl, rl, wave * 4 + i);
-      else if (max_nit > 2) adam_row_zready<KX, max_nit>(mt, hp, bias, row, gram, zl, rl, wave * 4 + i);
-    } else if (KX == 1) {
-      if ((mt.r & 3) == 0) adam_row<1, 4>(mt, hp, bias, row, gram); else adam_row<1, 1>(mt, hp, bias, row, gram);
-    } else {
-      adam_row<FIRA_KX_SPLIT, 1>(mt, hp, bias, row, gram);
+  if (KX != 1 && zready && mt.r <= 64) {
+    adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, wave);
+  } else if (zready) {
+    auto rows = [&](auto nit, auto odd) __attribute__((always_inline)) {
+      for (int i = 0; i < 4; ++i) {
+        const long long row = row_base + i;
+        if (row < mt.L) {
+          adam_row_zready<KX, decltype(nit)::value, decltype(odd)::value>(mt, hp, bias, row, gram, zl, rl, wave * 4 + i);
+        } else {   // rows of the padding: zeros
+          for (int a = (threadIdx.x & 63) * 4; a < (planes + (staged ? 1 : 0)) * mt.rp; a += 256)
+            *reinterpret_cast<u32x2*>(zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + i) * 32 + (a & 31)) = u32x2{0u, 0u};
+        }
+      }
+    };
+    auto by_rank = [&](auto odd) __attribute__((always_inline)) {
+      if (mt.r <= 256) rows(std::integral_constant<int, 1>{}, odd);
+      else if (mt.r <= 512) rows(std::integral_constant<int, 2>{}, odd);
+      else if constexpr (KX == 1) rows(std::integral_constant<int, FIRA_ZREADY_MAX_R / 256>{}, odd);
+    };
+    if ((mt.r & 3) == 0) by_rank(std::false_type{});
+    else by_rank(std::true_type{});
+  } else {
+    for (int i = 0; i < 4; ++i) {
+      const long long row = row_base + i;
+      if (row >= mt.L) break;
+      if (KX == 1 && (mt.r & 3) == 0) adam_row<1, 4>(mt, hp, bias, row, gram);
+      else adam_row<KX, 1>(mt, hp, bias, row, gram);
     }
   }
   if (zready) {
@@ -516,12 +567,8 @@ __device__ __forceinline__ void fixz_row(const FiraMat& mt, float f, long long r
   for (int a = lane * 4; a < mt.r; a += 256) {
     const long long o = kblk_index(mt.Lq, row, a), ol = kblk_index(mt.Lq, row, mt.rp + a);
     const u32x2 zv = *reinterpret_cast<gptr<const u32x2>>(Nb + o);
-    f32x4 rv = f32x4{0.f, 0.f, 0.f, 0.f};      // (the operand's columns past r stay zero)
-    if ((mt.r & 3) == 0) rv = *reinterpret_cast<gptr<const f32x4>>(R + a);
-    else
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (a + e < mt.r) rv[e] = R[a + e];
+    const f32x4 rv = load_row4(R + a, mt.r - a);
+    const u32x2 mask = row4_mask(mt.r - a);
     f32x4 z = f32x4{__uint_as_float(zv.x << 16), __uint_as_float(zv.x & 0xffff0000u), __uint_as_float(zv.y << 16),
                     __uint_as_float(zv.y & 0xffff0000u)};
     if (zsplit) {
@@ -531,8 +578,8 @@ __device__ __forceinline__ void fixz_row(const FiraMat& mt, float f, long long r
     }
     z += f * rv;
     const u32x2 hi = u32x2{pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3])};
-    *reinterpret_cast<gptr<u32x2>>(Nb + o) = hi;
-    if (zsplit) *reinterpret_cast<gptr<u32x2>>(Nb + ol) = split_remainder(z, hi);
+    *reinterpret_cast<gptr<u32x2>>(Nb + o) = hi & mask;
+    if (zsplit) *reinterpret_cast<gptr<u32x2>>(Nb + ol) = split_remainder(z, hi) & mask;
   }
 }
 
@@ -599,19 +646,19 @@ __device__ __forceinline__ void fixz_row_split(const FiraMat& mt, const FiraHp& 
   gptr<const float> M = as_global<const float>(mt.M) + row * mt.r;
   gptr<const float> V = as_global<const float>(mt.V) + row * mt.r;
   for (int a = lane * 4; a < mt.r; a += 256) {
-    const f32x4 rv = *reinterpret_cast<gptr<const f32x4>>(R + a);
-    const f32x4 mv = *reinterpret_cast<gptr<const f32x4>>(M + a);
-    const f32x4 vv = *reinterpret_cast<gptr<const f32x4>>(V + a);
+    const f32x4 rv = load_row4(R + a, mt.r - a), mv = load_row4(M + a, mt.r - a), vv = load_row4(V + a, mt.r - a);
+    const u32x2 mask = row4_mask(mt.r - a);
     f32x4 z;
 #pragma unroll
     for (int e = 0; e < 4; ++e) z[e] = adam_direction(mv[e], vv[e], bias, hp.epsf) - f * rv[e];
     u32x2 zp[3];
     bf16_planes<FIRA_KX_SPLIT>(z, 3, zp);
 #pragma unroll
-    for (int p = 0; p < 3; ++p) *reinterpret_cast<gptr<u32x2>>(Nb + kblk_index(mt.Lq, row, p * mt.rp + a)) = zp[p];
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<gptr<u32x2>>(Nb + kblk_index(mt.Lq, row, p * mt.rp + a)) = zp[p] & mask;
   }
 }
 
+static_assert(FIRA_ZREADY_MAX_R_F32 == 512, "fira_adam_kernel's forms end there");
 #define FIRA_MAKEZ_PARTS 32   // workgroups per listed matrix
 // One workgroup per (listed matrix, part): it reads the matrix's c once and, in the common case, exits;
 // otherwise it takes every FIRA_MAKEZ_PARTS-th block of 16 rows.

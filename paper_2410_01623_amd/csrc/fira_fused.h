@@ -441,23 +441,8 @@ __device__ __forceinline__ void small_adam_rows(const f32x16_t (&acc)[2], float*
   const bool operand_r = matrix || !use_gram(hp, sc), two_planes = hp.zsplit && !matrix;
   const int mine = min(max(r - a, 0), 4);           // this lane's values of a row
   const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto load4 = [&](gptr<char> base, unsigned off) {
-    gptr<const float> p = reinterpret_cast<gptr<const float>>(base + off);
-    if (mine == 4) return (f32x4)*reinterpret_cast<gptr<const f32x4_a4>>(p);
-    f32x4 v = zero;
-#pragma unroll
-    for (int e = 0; e < 3; ++e)
-      if (e < mine) v[e] = p[e];
-    return v;
-  };
-  auto store4 = [&](gptr<char> base, unsigned off, const f32x4& v) {
-    gptr<float> p = reinterpret_cast<gptr<float>>(base + off);
-    if (mine == 4) *reinterpret_cast<gptr<f32x4_a4>>(p) = v;
-    else
-#pragma unroll
-      for (int e = 0; e < 3; ++e)
-        if (e < mine) p[e] = v[e];
-  };
+  auto load4 = [&](gptr<char> base, unsigned off) { return load_row4(reinterpret_cast<gptr<const float>>(base + off), mine); };
+  auto store4 = [&](gptr<char> base, unsigned off, const f32x4& v) { store_row4(reinterpret_cast<gptr<float>>(base + off), v, mine); };
   gptr<char> M = reinterpret_cast<gptr<char>>(as_global(mt.M)), V = reinterpret_cast<gptr<char>>(as_global(mt.V));
   gptr<char> Rt = reinterpret_cast<gptr<char>>(as_global(mt.Rt)), Nb = reinterpret_cast<gptr<char>>(as_global(mt.Nb)), Rb = reinterpret_cast<gptr<char>>(as_global(mt.Rb));
 #pragma unroll
@@ -470,8 +455,7 @@ __device__ __forceinline__ void small_adam_rows(const f32x16_t (&acc)[2], float*
   unsigned off = (unsigned)((row0 + lrow) * r + a) * 4u, op = (unsigned)(((a >> 5) * mt.Lq + row0 + lrow) * 32 + (a & 31)) * 2u;
   const unsigned step = (unsigned)(ROWS * r) * 4u, plane = (unsigned)((mt.rp >> 5) * mt.Lq) * 64u;
   int left = mt.L - row0 - lrow;
-  // the operand's columns past r stay zero, even for a non-finite factor
-  const u32x2 keep = u32x2{mine == 0 ? 0u : mine == 1 ? 0xffffu : ~0u, mine < 3 ? 0u : mine == 3 ? 0xffffu : ~0u};
+  const u32x2 keep = row4_mask(mine);
   f32x4 mnext[2], wnext[2];
   auto request = [&](unsigned o, int n) {
 #pragma unroll

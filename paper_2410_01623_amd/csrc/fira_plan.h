@@ -85,7 +85,7 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     m.kx = (m.dtype == FIRA_F32) ? FIRA_KX_SPLIT : 1;
     m.Lq = round_up_int(m.L, 256); m.Sq = round_up_int(m.S, 256); m.rq = round_up_int(m.r, 256);
     h.small_proj = m.kx == 1 && m.r <= FIRA_PS;
-    m.zready = (h.small_proj || ((m.r & 3) == 0 && m.r <= (m.kx == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32))) ? 1 : 0;
+    m.zready = m.r <= (m.kx == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32) ? 1 : 0;
     if (m.zready && m.kx != 1) plan->adam_lds_f32 = std::max(plan->adam_lds_f32, FIRA_ROWS_PER_WG * m.rp * 6);
     if (m.zready && m.kx == 1) plan->adam_lds = std::max(plan->adam_lds, FIRA_ROWS_PER_WG * m.rp * 2);   // (twice that with Z in two planes)
     if (m.zready && m.kx == 1 && m.r <= FIRA_RSTAGE_MAX_R) plan->adam_lds_staged = std::max(plan->adam_lds_staged, FIRA_ROWS_PER_WG * m.rp * 2);
@@ -109,7 +109,7 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     total_tiles[m.left ? kTilesProjectLeft : kTilesProjectRight] += h.tiles_project;
     total_tiles[(h.small_proj ? kTilesProjSmallLeft : kTilesProjBigLeft) + (m.left ? 0 : 1)] += h.tiles_project;
     total_tiles[m.dtype == FIRA_BF16 ? kTilesBackBf16 : kTilesBackF32] += h.tiles_back;
-    if (m.zready && m.kx == 1 && m.r >= FIRA_FUSE_MIN_R && m.r <= FIRA_FUSE_MAX_R) {
+    if (m.kx == 1 && (m.r & 3) == 0 && m.r >= FIRA_FUSE_MIN_R && m.r <= FIRA_FUSE_MAX_R) {
       h.fuse_list = kTilesFuse + 2 * (m.r > 256 ? 1 : 0) + (m.left ? 0 : 1);
       total_tiles[h.fuse_list] += h.ta_project;
     }
