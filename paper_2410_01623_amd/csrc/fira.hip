@@ -65,6 +65,8 @@ constexpr int kComputeUnits = 256, kLdsPerCu = 160 * 1024;
 // twice as often for nothing by smaller tiles, not quite one (fira_backproject_kernel has both sides of each measured).
 constexpr int kForwardsMaxR = 64;
 constexpr int kQuarterTiles = 1536, kQuarterTilesLongRank = 384;
+// Tiles of a list from which on the fused projection/Adam kernel serves ranks that leave R in memory (fira_step has both sides).
+constexpr int kFuseMinTiles = 100;
 
 struct ListSlot {
   std::vector<int> idx;
@@ -177,7 +179,7 @@ FiraHp make_hp(const fira_ctx* ctx) {
   h.scaling = ctx->scaling;
   h.norm_mode = ctx->norm_mode;
   h.variant = ctx->variant;
-  h.fused = 0;
+  h.fused = h.keep_r = 0;
   h.ortho_tol = 0.02f;   // bf16-rounded orthonormal projectors measure ~1e-3; a projector beyond 0.02 is not meant to be orthonormal
   h.gram_tol = 2e-3f;    // measured relative error of ||S||^2 by the Gram route: 1e-3 of ||S||
   h.mixed = 0;
@@ -566,14 +568,17 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   const dim3 blk(FIRA_PROJ_THREADS);
   // R = P^T G (long-side major) for both orientations in one launch
   auto launch_project = [&](int norm_arg) {
-    int nl = s->ntiles[kTilesProjBigLeft], nr = s->ntiles[kTilesProjBigRight];
-    int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
+    const int nl = s->ntiles[kTilesProjBigLeft], nr = s->ntiles[kTilesProjBigRight];
+    const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
     if (s->general_bf16)
       hipLaunchKernelGGL(fira_project_kernel, dim3(bl + br), blk, FIRA_PROJ_LDS, q, ctx->d_mats, s->d_ents,
                          s->d_tiles[kTilesProjBigLeft], nl, bl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, 0, (const FiraScal*)ctx->d_scal, hp);
     launch_fp32_project(q, s, ctx->d_mats, s->d_tiles[kTilesProjBigLeft], nl, s->d_tiles[kTilesProjBigRight], nr, norm_arg, 0);
-    nl = s->ntiles[kTilesProjSmallLeft]; nr = s->ntiles[kTilesProjSmallRight];
-    bl = (nl + 7) / 8 * 8; br = (nr + 7) / 8 * 8;
+  };
+  // The same and Adam for small ranks, on every route
+  auto launch_small = [&](int norm_arg) {
+    const int nl = s->ntiles[kTilesProjSmallLeft], nr = s->ntiles[kTilesProjSmallRight];
+    const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
     if (nl + nr)
       hipLaunchKernelGGL(fira_project_small_kernel, dim3(bl + br), blk, FIRA_PROJ_SMALL_LDS, q, ctx->d_mats, s->d_ents,
                          s->d_tiles[kTilesProjSmallLeft], nl, bl, s->d_tiles[kTilesProjSmallRight], nr, norm_arg, (const FiraScal*)ctx->d_scal, hp);
@@ -601,16 +606,29 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     }
   }
   // The fused projection/Adam kernel serves the listed matrices on the Gram route if each of them can take
-  // it; those on the residual route then go through the two-kernel path in the same step (hp.mixed).
+  // it; those on the residual route then go through the two-kernel path in the same step (hp.mixed).  Either all of them leave
+  // R in memory, as small ranks do whatever the path, or none does.  Two kernels and the fused one, a step of 8 blocks of 512 x 1376, 24 of
+  // 1024 x 2736 and 24 of 2048 x 5461: r = 68 105 and 83, 761 and 626, 2524 and 2277; r = 96 106 and 83, 776 and 648, 2556 and 2316;
+  // r = 124 105 and 86, 790 and 687, 2597 and 2403.  Where there are few tiles, a workgroup's passes over its factors one after the
+  // other take longer than a second launch that deals them out (r = 96, by tiles: 32.5 and 35.8 (26), 37.6 and 38.7 (52), 47.0 and 48.8 (49),
+  // 46.2 and 45.7 (78), 59.4 and 59.2 (98), 48.2 and 47.5 (104), 67.2 and 61.7 (147), 104 and 96 (196)).
   bool fused = ctx->fusion && !ctx->zsplit && !only_scaling && ctx->scaling == FIRA_SCALE_COLUMN && ctx->norm_mode == FIRA_NORM_GRAM && any_gram;
+  bool keep_r = false, drop_r = false, any_fused = false;
   for (int e = 0; e < count && fused; ++e) {
     const fira_ctx::Gate gt = ctx->h_gate[idx[e]];
-    if (gt.ortho_err <= hp.ortho_tol && gt.gram_err <= hp.gram_tol) fused = ctx->plan.mats[idx[e]].fuse_list >= 0;
+    if (!(gt.ortho_err <= hp.ortho_tol && gt.gram_err <= hp.gram_tol)) continue;
+    const HostMat& h = ctx->plan.mats[idx[e]];
+    any_fused = any_fused || h.fuse_list >= 0;
+    (h.dev.r < FIRA_FUSE_DROP_R ? keep_r : drop_r) = true;
+    fused = (h.small_proj || h.fuse_list >= 0) && !(keep_r && drop_r);
   }
+  fused = fused && any_fused && !(keep_r && s->ntiles[kTilesFuse] + s->ntiles[kTilesFuse + 1] < kFuseMinTiles);
   const bool mixed = fused && need_residual;
-  ctx->last_step_fused = fused && !mixed;
-  hp.fused = fused ? 1 : 0;
+  ctx->last_step_fused = fused && !keep_r && !mixed;
+  hp.fused = fused && !keep_r ? 1 : 0;
+  hp.keep_r = fused && keep_r ? 1 : 0;
   hp.mixed = mixed ? 1 : 0;
+  launch_small(want_g2);
   if (fused) {
     // 1+2. R = P^T G, Adam on it, factor norms, Z for c = 1
     for (int rt = 1; rt <= 2; ++rt) {

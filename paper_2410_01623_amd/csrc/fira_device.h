@@ -117,7 +117,8 @@ struct FiraHp {     // hyper-parameters as the kernels take them
   int mixed;        // 1: the fused kernel serves the matrices on the Gram route, the two-kernel path the others
   int zsplit;       // 1: Z of the register-resident Adam rows is stored as two bf16 planes, hi + lo (K = 2 rp)
   int variant;      // 0: Algorithm 1; 1: factors on the full gradient, no Adam term ("Fira-only-scaling")
-  int fused;        // 1: this step's projection and Adam ran as one kernel (no copy of R exists)
+  int fused;        // 1: this step's projection and Adam ran as one kernel and no copy of R exists
+  int keep_r;       // 1: ... as one kernel that leaves a copy of R
 };
 
 // Whether matrix `sc` takes the Gram route to ||S||^2 in this step.
@@ -144,11 +145,10 @@ __device__ __forceinline__ bool calibrates_gram(const FiraHp& hp, const FiraScal
 #define FIRA_BB 128          // ... and on the B side (m)
 #define FIRA_ROWS_PER_WG 16  // Adam pass: 4 wavefronts x 4 rows
 #define FIRA_FUSE_MAX_R 512  // largest rank of the fused projection/Adam kernel
-// Smallest rank of the fused kernel.  The line is the interface's, not speed's: below it every step leaves a copy of R for
-// fira_get_lowrank.  Measured with the line at 68, the fused kernel is the faster one there too (a step at r = 96: 91 us
-// against 111 with two kernels over 8 blocks of 512 x 1376, 654 against 785 over 24 of 1024 x 2736, 2345 against 2580 over 24
-// of 2048 x 5461; the same share at 68 and 124); at 128 it is 96 against 113, 673 against 802 and 2375 against 2608.
-#define FIRA_FUSE_MIN_R 128
+// Smallest rank of the fused kernel (fira_project_small_kernel takes the ranks below), and the smallest one whose R it does not leave in
+// memory.  That line is the interface's, not speed's: below it every step leaves a copy of R for fira_get_lowrank.
+#define FIRA_FUSE_MIN_R 65
+#define FIRA_FUSE_DROP_R 128
 #define FIRA_ORTHO_SPLITS 64 // workgroups of the orthonormality estimate's second phase
 #define FIRA_SOLVE_JB 64     // projector refresh: column block of the triangular solve
 

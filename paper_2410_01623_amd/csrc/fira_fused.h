@@ -26,8 +26,9 @@
 // chunk c then stay in flight while chunk c + 1 is processed.  No count of instructions, and no
 // assumption about the order in which loads and stores retire relative to each other, is involved.
 //
-// A step takes this kernel only if every listed matrix is bf16 with r % 4 == 0, 128 <= r <= 512, column
-// factors, Algorithm 1 proper, and the Gram route to ||S|| (no operand copy of R is made here).
+// A step takes this kernel only if every listed matrix is bf16 with r % 4 == 0, 64 < r <= 512, column
+// factors, Algorithm 1 proper, and the Gram route to ||S|| (no operand copy of R is made here).  Lists of ranks below
+// FIRA_FUSE_DROP_R have R written to memory besides, as two kernels leave it (FiraHp::keep_r).
 // The limiter runs after it; for a matrix whose factor c came out below 1, fira_makez_kernel turns the Z
 // written here (for c = 1) into c Z + (1 - c) N, with N formed again from the updated M and V.
 #pragma once
@@ -67,7 +68,7 @@ __device__ __forceinline__ const char* scalar_pointer(const char* p) {
   return (const char*)(((unsigned long long)hi << 32) | lo);
 }
 
-// TM = 4: a wave's factors of a chunk are the chunk's 16.  TM = 2 (r = 128): a chunk is 16 factors of either half of
+// TM = 4: a wave's factors of a chunk are the chunk's 16.  TM = 2 (r <= 128): a chunk is 16 factors of either half of
 // the tile, 32 rows of 128 in the same LDS, and half as many chunks.
 template <int RT, int TM, bool INTERIOR>
 __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], char* lds, const FiraMat& mt, const FiraHp& hp,
@@ -175,6 +176,8 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
         const int idx = lane_idx + dr * C + 32 * tn;
         const bool ok = INTERIOR || (col < r && row_w + 4 * hi + dr < L);
         const float x = cur[tn][v];
+        // (128 bytes of a factor's row per half wave)
+        if (TM == 2 && hp.keep_r && ok) as_global(mt.Rt)[(unsigned)((row_w + 4 * hi + dr) * r + col)] = x;
         const float m0 = ok ? landM[idx] : 0.0f, v0 = ok ? landV[idx] : 0.0f;
         const float m1 = hp.b1 * m0 + hp.omb1 * x;
         const float v1 = hp.b2 * v0 + hp.omb2 * (x * x);
@@ -280,7 +283,7 @@ __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& m
   float bias;
   auto prologue = [&] {
     bias = bias_correction(hp, t);
-    asm volatile("" : "+v"(bias));               // (here, not where it is used)
+    if (RT == 1) asm volatile("" : "+v"(bias));    // (here, not where it is used; RT = 2 has no register to spare)
   };
   f32x16_t acc[TM][2];
   float sq[TM];
@@ -308,8 +311,8 @@ __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& m
   else project_adam_epilogue<RT, TM, false>(acc, lds, mt, hp, bias, g.a_row0, sq);
 }
 
-// r = 128, the smallest rank that comes here, fills half a rank tile; its tiles multiply 64 x 64 per wave and go through
-// Adam in four chunks instead of eight (56 matrices of 512 x 512 and 512 x 1376: 48 us instead of 65).
+// Ranks up to 128 fill half a rank tile; their tiles multiply 64 x 64 per wave and go through
+// Adam in four chunks instead of eight (56 matrices of 512 x 512 and 512 x 1376 at r = 128: 48 us instead of 65).
 template <bool LEFT, int RT>
 __device__ __forceinline__ void project_adam_tile(char* lds, const FiraMat* __restrict__ mats, const FiraScal* __restrict__ scal,
                                                   const FiraEnt* __restrict__ ents, const FiraTile& tile, const FiraHp& hp) {
@@ -578,7 +581,7 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 4) void fira_project_small_kerne
   float bias;
   auto prologue = [&] {
     bias = bias_correction(hp, t);
-    asm volatile("" : "+v"(bias));             // (here, not where it is used)
+    asm volatile("" : "+v"(bias));               // (here, not where it is used)
   };
   if (left) project_small_tile<true>(acc, lds, mt, ent, tile, sumsq, sq, prologue);
   else project_small_tile<false>(acc, lds, mt, ent, tile, sumsq, sq, prologue);
