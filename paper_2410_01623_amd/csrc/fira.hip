@@ -355,6 +355,7 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<0, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<1, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_chol_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_CHOL_PAN_ROWS * (FIRA_CHOL_NB + 1) * 8));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_chol_small_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_CHOL_SMALL_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(1)));
@@ -1038,12 +1039,14 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   const int prep_blocks = prep_tiles(max_S, max_r);
   auto orthonormalise = [&](const FiraRefreshEnt* de) {
     hipLaunchKernelGGL(fira_refresh_gram_kernel, dim3(nt64 * (nt64 + 1) / 2, count), dim3(256), 0, q, de);
-    {
+    if (max_r <= FIRA_CHOL_SMALL_R) {
+      hipLaunchKernelGGL(fira_refresh_chol_small_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), FIRA_CHOL_SMALL_LDS, q, de);
+    } else {
       const int pan_rows = std::min(FIRA_CHOL_PAN_ROWS, std::max(max_r - FIRA_CHOL_NB, 0));
       hipLaunchKernelGGL(fira_refresh_chol_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), (size_t)pan_rows * (FIRA_CHOL_NB + 1) * 8, q, de, pan_rows);
+      const int nj = (max_r + FIRA_SOLVE_JB - 1) / FIRA_SOLVE_JB;
+      hipLaunchKernelGGL(fira_refresh_diaginv_kernel, dim3(nj, count), dim3(256), 0, q, de);
     }
-    const int nj = (max_r + FIRA_SOLVE_JB - 1) / FIRA_SOLVE_JB;
-    hipLaunchKernelGGL(fira_refresh_diaginv_kernel, dim3(nj, count), dim3(256), 0, q, de);
     hipLaunchKernelGGL(fira_refresh_solve_kernel, dim3((max_S + 63) / 64, count), dim3(256), 0, q, de);
   };
   const FiraHp refresh_hp = make_hp(ctx);   // (mixed = 0: the projection kernel serves every listed matrix)

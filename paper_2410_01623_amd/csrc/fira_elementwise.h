@@ -902,11 +902,13 @@ __device__ __forceinline__ void ortho_final_body(const FiraMat& mt, const float*
   const int t = threadIdx.x;
   float zz[4] = {0.f, 0.f, 0.f, 0.f};
   for (int a = t; a < mt.r; a += 256) {
+    // all trials of a split in one load, sixteen splits in flight: one value after the other, the splits were a chain of 256 loads
+    f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 16
+    for (int b = 0; b < FIRA_ORTHO_SPLITS; ++b) z += *reinterpret_cast<gptr<const f32x4>>(zp + ((long long)b * mt.r + a) * 4);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      float z = 0.0f;
-      for (int b = 0; b < FIRA_ORTHO_SPLITS; ++b) z += zp[((long long)b * mt.r + a) * 4 + k];
-      const float d = z - ortho_sign(a, k);
+      const float d = z[k] - ortho_sign(a, k);
       zz[k] += d * d;
     }
   }

@@ -301,6 +301,35 @@ __device__ __forceinline__ void sqrt_and_inverse(double x, double& root, double&
   inv = fma(inv, fma(-inv, root, 1.0), inv);
 }
 
+// Factor of a 32 x 32 diagonal block by one wavefront, lane i its row i (d[k], k <= i; lanes 32 .. 63 repeat them): pivot(j, 1 / L_jj) is
+// called by lane j.
+template <typename Pivot>
+__device__ __forceinline__ void chol_diagonal(double (&d)[FIRA_CHOL_NB], double floor_piv, Pivot pivot) {
+  const int lane = threadIdx.x & 63, row = lane & (FIRA_CHOL_NB - 1);
+#pragma unroll
+  for (int j = 0; j < FIRA_CHOL_NB; ++j) {
+    double piv, inv;
+    sqrt_and_inverse(fmax(lane_value(d[j], j), floor_piv), piv, inv);
+    const double lj = d[j] * inv;          // (rows above j hold what nobody reads)
+    d[j] = row == j ? piv : lj;
+    if (lane == j) pivot(j, inv);
+#pragma unroll
+    for (int k = j + 1; k < FIRA_CHOL_NB; ++k) d[k] = fma(-lj, lane_value(lj, k), d[k]);
+    __builtin_amdgcn_sched_barrier(0);     // (else the lane reads of many columns are gathered, and spill)
+  }
+}
+// One row of the panel below it, x D^T = x: DT holds the factor by columns, rinv the reciprocals of its diagonal.
+__device__ __forceinline__ void chol_panel_row(double (&x)[FIRA_CHOL_NB], const double* DT, const double* rinv) {
+#pragma unroll
+  for (int k = 0; k < FIRA_CHOL_NB; ++k) {
+    int col = k * (FIRA_CHOL_NB + 2);      // known only when x[k] is: the factor is read column by column (gathered at the top, it spills)
+    asm volatile("" : "+s"(col) : "v"(x[k]));
+    x[k] *= rinv[k];
+#pragma unroll
+    for (int j = k + 1; j < FIRA_CHOL_NB; ++j) x[j] = fma(-x[k], DT[col + j], x[j]);
+  }
+}
+
 __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(const FiraRefreshEnt* __restrict__ ents, int pan_rows) {
   constexpr int NB = FIRA_CHOL_NB, PP = NB + 1, DP = NB + 2;
   __shared__ __attribute__((aligned(16))) double DT[NB * DP];   // the diagonal block's factor, by columns: L[i][k] at k * DP + i
@@ -338,17 +367,7 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
       double d[NB];
 #pragma unroll
       for (int k = 0; k < NB; ++k) d[k] = DT[k * DP + row];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        double piv, inv;
-        sqrt_and_inverse(fmax(lane_value(d[j], j), floor_piv), piv, inv);
-        const double lj = d[j] * inv;          // (rows above j hold what nobody reads)
-        d[j] = row == j ? piv : lj;
-        if (lane == j) rinv_s[j] = inv;
-#pragma unroll
-        for (int k = j + 1; k < NB; ++k) d[k] = fma(-lj, lane_value(lj, k), d[k]);
-        __builtin_amdgcn_sched_barrier(0);     // (else the lane reads of many columns are gathered, and spill)
-      }
+      chol_diagonal(d, floor_piv, [&](int j, double inv) { rinv_s[j] = inv; });
       if (lane < NB) {
 #pragma unroll
         for (int k = 0; k < NB; ++k) DT[k * DP + row] = k <= row ? d[k] : 0.0;
@@ -374,14 +393,7 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
       double x[NB];
 #pragma unroll
       for (int k = 0; k < NB; ++k) x[k] = in_lds ? chol_pan[i * PP + k] : grow[k];
-#pragma unroll
-      for (int k = 0; k < NB; ++k) {
-        int col = k * DP;      // known only when x[k] is: the factor is read column by column (gathered at the top, it spills)
-        asm volatile("" : "+s"(col) : "v"(x[k]));
-        x[k] *= rinv_s[k];
-#pragma unroll
-        for (int j = k + 1; j < NB; ++j) x[j] = fma(-x[k], DT[col + j], x[j]);
-      }
+      chol_panel_row(x, DT, rinv_s);
 #pragma unroll
       for (int k = 0; k < NB; ++k) {
         if (in_lds) chol_pan[i * PP + k] = x[k];
@@ -466,6 +478,161 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
     }
     }
     __syncthreads();
+  }
+}
+
+// Factorisation and the inverses of its diagonal blocks in one launch for ranks up to 128 (lists of nothing larger), whose whole matrix fits
+// in LDS: the kernels above and below go through memory between their steps.  The same operations in the same order, and the chain
+// of those is what is left: 56 matrices of r = 128 98 us, 88 and 16 in two launches (a refresh of 8 blocks of 512 x 1376 729 -> 693 us, where
+// the estimate's last kernel, whose loads run side by side now, has 11 of it; 24 of 1024 x 2736 at r = 128 2672 -> 2600).
+// LDS: the factor in rows of FIRA_CHOL_SMALL_PITCH (an odd number of doubles), identity past r.  Of the half above the diagonal, rows 0 .. 63
+// of columns 64 .. 127 take the inverses of the 32 x 32 triangles; when the factor has left, the quarter below takes the products.
+#define FIRA_CHOL_SMALL_R 128
+#define FIRA_CHOL_SMALL_PITCH (FIRA_CHOL_SMALL_R + 1)
+#define FIRA_CHOL_SMALL_LDS (FIRA_CHOL_SMALL_R * FIRA_CHOL_SMALL_PITCH * 8)
+__global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_small_kernel(const FiraRefreshEnt* __restrict__ ents) {
+  constexpr int NB = FIRA_CHOL_NB, DP = NB + 2, P = FIRA_CHOL_SMALL_PITCH, N = FIRA_CHOL_SMALL_R, WAVES = FIRA_CHOL_THREADS / 64;
+  __shared__ __attribute__((aligned(16))) double DT[NB * DP];   // the diagonal block's factor, by columns: L[i][k] at k * DP + i
+  __shared__ double rinv_s[N];
+  __shared__ double dmax_s[WAVES];
+  extern __shared__ __attribute__((aligned(16))) double chol_a[];
+  const FiraRefreshEnt e = ents[blockIdx.x];
+  if (refresh_pass_done(e)) return;
+  const int r = e.r, r32 = (r + NB - 1) / NB * NB, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  gptr<double> C = as_global(e.C);
+  {
+    constexpr int PASSES = N * N / FIRA_CHOL_THREADS;
+    double mx = 0.0;
+#pragma unroll
+    for (int g = 0; g < PASSES; g += 8) {
+      double v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int x = t + FIRA_CHOL_THREADS * (g + q), i = x / N, k = x % N;
+        v[q] = k <= i && i < r ? C[(unsigned)(i * r + k)] : (i == k ? 1.0 : 0.0);
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int x = t + FIRA_CHOL_THREADS * (g + q), i = x / N, k = x % N;
+        chol_a[i * P + k] = v[q];
+        if (i == k && i < r) mx = fmax(mx, v[q]);
+      }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) dmax_s[wave] = mx;
+  }
+  __syncthreads();
+  double dmax = 0.0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) dmax = fmax(dmax, dmax_s[w]);
+  const double floor_piv = dmax * 1e-24 + 1e-300;
+  for (int jb = 0; jb < r; jb += NB) {
+    double* D = chol_a + jb * P + jb;
+    if (wave == 0) {
+      const int row = lane & (NB - 1);
+      double d[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) d[k] = k <= row ? D[row * P + k] : 0.0;
+      chol_diagonal(d, floor_piv, [&](int j, double inv) { rinv_s[j] = inv; });
+      if (lane < NB) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+          const double v = k <= row ? d[k] : 0.0;
+          DT[k * DP + row] = v;
+          if (k <= row) D[row * P + k] = v;
+        }
+      }
+    }
+    __syncthreads();
+    const int below = r32 - jb - NB;
+    double* pan = chol_a + (jb + NB) * P + jb;
+    if (t < below) {
+      double x[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) x[k] = pan[t * P + k];
+      chol_panel_row(x, DT, rinv_s);
+#pragma unroll
+      for (int k = 0; k < NB; ++k) pan[t * P + k] = x[k];
+    }
+    __syncthreads();
+    // trailing triangle: blocks of 32 x 32 (what lies above the diagonal in the diagonal ones is never read)
+    int cnt = 0;
+    for (int bi = 0; bi < below; bi += NB)
+      for (int bk = 0; bk <= bi; bk += NB, ++cnt) {
+        if (cnt % WAVES != wave) continue;
+        const int m0 = bi + (lane & 15), n0 = bk + (lane & 15);
+        RefreshAcc acc;
+        refresh_acc_zero(acc);
+#pragma unroll
+        for (int k4 = 0; k4 < NB; k4 += 4) {
+          const int k = k4 + (lane >> 4);
+          refresh_acc_step(acc, pan[m0 * P + k], pan[(m0 + 16) * P + k], pan[n0 * P + k], pan[(n0 + 16) * P + k]);
+        }
+        double* T = chol_a + (jb + NB + bi) * P + jb + NB + bk;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const int ri = 16 * i + (lane >> 4) + 4 * v, ck = 16 * j + (lane & 15);
+              if (bk < bi || ck <= ri) T[ri * P + ck] -= acc.v[i][j][v];
+            }
+      }
+    __syncthreads();
+  }
+  for (int x = t; x < r * N; x += FIRA_CHOL_THREADS) {
+    const int i = x / N, k = x % N;
+    if (k <= i) C[(unsigned)(i * r + k)] = chol_a[i * P + k];
+  }
+  if (t < N) rinv_s[t] = 1.0 / chol_a[t * P + t];
+  __syncthreads();
+  // fira_refresh_diaginv_kernel's steps, wave w < 4 the triangle at 32 w
+  const int blocks = (r + 63) / 64;
+  double* X = chol_a + 64;                            // triangle w: X[(32 (w >> 1) + i) P + 32 (w & 1) + c]
+  if (wave < 2 * blocks && lane < NB) {
+    const double* L = chol_a + NB * wave * (P + 1);
+    double x[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) x[i] = i == lane ? 1.0 : 0.0;
+#pragma unroll
+    for (int p = 0; p < NB; ++p) {
+      x[p] *= rinv_s[NB * wave + p];
+#pragma unroll
+      for (int i = p + 1; i < NB; ++i) x[i] = fma(-L[i * P + p], x[p], x[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) X[(NB * (wave >> 1) + i) * P + NB * (wave & 1) + lane] = x[i];
+  }
+  __syncthreads();
+  const int J = t >> 8, row = (t & 255) >> 3, c4 = (t & 7) * 4;      // 256 threads to a block, four of a row's values each
+  const double* XA = X + NB * J * P;
+  const double* XB = XA + NB;
+  double* W = chol_a + 64 * P + NB * J * P;           // (the factor's lower left quarter has left)
+  double q[4] = {0.0, 0.0, 0.0, 0.0};
+  if (J < blocks) {
+    const double* Cq = chol_a + (64 * J + NB) * P + 64 * J;
+    for (int k = 0; k < NB; ++k)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) q[c] = fma(Cq[row * P + k], XA[k * P + c4 + c], q[c]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) W[row * P + c4 + c] = q[c];
+  }
+  __syncthreads();
+  if (J >= blocks) return;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) q[c] = 0.0;
+  for (int k = 0; k < NB; ++k)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) q[c] = fma(XB[row * P + k], W[k * P + c4 + c], q[c]);
+  gptr<double> inv = reinterpret_cast<gptr<double>>(as_global(e.inst)) + (size_t)J * 64 * 64;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    inv[row * 64 + c4 + c] = XA[row * P + c4 + c];
+    inv[row * 64 + NB + c4 + c] = 0.0;
+    inv[(NB + row) * 64 + c4 + c] = -q[c];
+    inv[(NB + row) * 64 + NB + c4 + c] = XB[row * P + c4 + c];
   }
 }
 
