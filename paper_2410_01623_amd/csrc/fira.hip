@@ -111,10 +111,9 @@ struct fira_ctx {
   ListSlot slots[kSlots];
   char* h_stage_all = nullptr;
   // Host copy of every matrix's two gate values of the Gram route (FiraScal::ortho_err, FiraScal::gram_err;
-  // pinned; +inf until known), so that a step knows which listed matrices take which route and can leave out
+  // pinned, written by the kernels; +inf until known), so that a step knows which listed matrices take which route and can leave out
   // the launches that nobody needs.
-  struct Gate { float ortho_err, gram_err; };
-  Gate* h_gate = nullptr;
+  FiraGate* h_gate = nullptr;
   hipEvent_t ortho_event = nullptr;
   bool ortho_pending = false;
   // fira_set_projectors: host image (pinned) of the table of installations of one call, and the event after
@@ -192,11 +191,8 @@ bool valid_hp(const fira_hparams* hp) {
          hp->eps >= 0 && std::isfinite(hp->eps) && std::isfinite(hp->alpha) && hp->gamma > 0;
 }
 
-// Every matrix's gate values of the Gram route in one strided copy (stream-ordered; fira_step waits for it).
-fira_status read_back_gates(fira_ctx* ctx) {
-  const size_t nmat = ctx->plan.mats.size();
-  FIRA_HIP(ctx, hipMemcpy2DAsync(ctx->h_gate, sizeof(fira_ctx::Gate), reinterpret_cast<char*>(ctx->d_scal) + offsetof(FiraScal, ortho_err),
-                                 sizeof(FiraScal), sizeof(fira_ctx::Gate), nmat, hipMemcpyDeviceToHost, ctx->stream));
+// After kernels that write gate values have been enqueued: a later fira_step waits for them before it reads h_gate.
+fira_status gates_on_their_way(fira_ctx* ctx) {
   FIRA_HIP(ctx, hipEventRecord(ctx->ortho_event, ctx->stream));
   ctx->ortho_pending = true;
   return FIRA_OK;
@@ -361,8 +357,8 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(1)));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(2)));
   FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_stage_all, p.slot_bytes * kSlots, hipHostMallocDefault));
-  FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_gate, sizeof(fira_ctx::Gate) * count, hipHostMallocDefault));
-  for (int i = 0; i < count; ++i) ctx->h_gate[i] = fira_ctx::Gate{INFINITY, INFINITY};
+  FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_gate, sizeof(FiraGate) * count, hipHostMallocDefault));
+  for (int i = 0; i < count; ++i) ctx->h_gate[i] = FiraGate{INFINITY, INFINITY};
   FIRA_INIT_HIP(hipEventCreateWithFlags(&ctx->ortho_event, hipEventDisableTiming));
   FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_install, sizeof(FiraRefreshEnt) * count, hipHostMallocDefault));
   FIRA_INIT_HIP(hipEventCreateWithFlags(&ctx->install_event, hipEventDisableTiming));
@@ -443,6 +439,7 @@ fira_status fira_set_projector(fira_ctx* ctx, int idx, const void* dev_P, fira_d
   if (p_dtype != FIRA_F32 && p_dtype != FIRA_BF16) return fail(ctx, FIRA_ERR_DTYPE, "p_dtype must be FIRA_F32 or FIRA_BF16");
   HostMat& h = ctx->plan.mats[idx];
   const int grid = prep_tiles(h.dev.S, h.dev.r);
+  ctx->h_gate[idx] = FiraGate{INFINITY, INFINITY};   // (before the kernel that writes it can run)
   if (p_dtype == FIRA_F32)
     hipLaunchKernelGGL(fira_prep_projector_kernel<float>, dim3(grid), dim3(256), 0, ctx->stream, h.dev, (const float*)dev_P);
   else
@@ -452,17 +449,11 @@ fira_status fira_set_projector(fira_ctx* ctx, int idx, const void* dev_P, fira_d
   hipLaunchKernelGGL(fira_ortho_y_kernel, dim3((h.dev.S + 3) / 4), dim3(256), 0, ctx->stream, h.dev, ybuf);
   float* zbuf = reinterpret_cast<float*>(ctx->slab + ctx->plan.off_ortho + ctx->plan.ortho_z);
   hipLaunchKernelGGL(fira_ortho_z_kernel, dim3(FIRA_ORTHO_SPLITS), dim3(256), 0, ctx->stream, h.dev, (const float*)ybuf, zbuf);
-  hipLaunchKernelGGL(fira_ortho_final_kernel, dim3(1), dim3(256), 0, ctx->stream, h.dev, (const float*)zbuf, ctx->d_scal, idx);
+  hipLaunchKernelGGL(fira_ortho_final_kernel, dim3(1), dim3(256), 0, ctx->stream, h.dev, (const float*)zbuf, ctx->d_scal, ctx->h_gate, idx);
   FIRA_HIP(ctx, hipGetLastError());
-  static_assert(offsetof(FiraScal, gram_err) == offsetof(FiraScal, ortho_err) + sizeof(float), "the two gate values are read back as one piece");
-  ctx->h_gate[idx] = fira_ctx::Gate{INFINITY, INFINITY};
-  FIRA_HIP(ctx, hipMemcpyAsync(&ctx->h_gate[idx], reinterpret_cast<char*>(&ctx->d_scal[idx]) + offsetof(FiraScal, ortho_err),
-                               sizeof(fira_ctx::Gate), hipMemcpyDeviceToHost, ctx->stream));
-  FIRA_HIP(ctx, hipEventRecord(ctx->ortho_event, ctx->stream));
-  ctx->ortho_pending = true;
   h.has_projector = true;
   ctx->unmeasured[idx] = 1;
-  return FIRA_OK;
+  return gates_on_their_way(ctx);
 }
 
 fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* idx, const void* const* dev_P, fira_dtype p_dtype) {
@@ -486,6 +477,7 @@ fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* idx, const 
     ctx->install_pending = false;
   }
   char* scratch = ctx->slab + ctx->plan.off_ortho;
+  for (int e = 0; e < count; ++e) ctx->h_gate[idx[e]] = FiraGate{INFINITY, INFINITY};   // (before the kernels that write them can run)
   for (int e = 0; e < count; ++e) {
     const FiraMat& m = ctx->plan.mats[idx[e]].dev;
     FiraRefreshEnt& re = ctx->h_install[e];
@@ -511,24 +503,23 @@ fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* idx, const 
     hipLaunchKernelGGL(fira_refresh_prep_kernel, dim3(prep_blocks, nb), dim3(256), 0, q, ctx->d_mats, d_table + e0);
     hipLaunchKernelGGL(fira_refresh_ortho_y_kernel, dim3((max_S + 3) / 4, nb), dim3(256), 0, q, ctx->d_mats, d_table + e0);
     hipLaunchKernelGGL(fira_refresh_ortho_z_kernel, dim3(FIRA_ORTHO_SPLITS, nb), dim3(256), 0, q, ctx->d_mats, d_table + e0);
-    hipLaunchKernelGGL(fira_refresh_ortho_final_kernel, dim3(nb), dim3(256), 0, q, ctx->d_mats, d_table + e0, ctx->d_scal);
+    hipLaunchKernelGGL(fira_refresh_ortho_final_kernel, dim3(nb), dim3(256), 0, q, ctx->d_mats, d_table + e0, ctx->d_scal, ctx->h_gate);
   }
   {
     const hipError_t e_ = hipGetLastError();
     if (e_ != hipSuccess) {   // some of the listed matrices' operand copies may be half written
       for (int e = 0; e < count; ++e) {
         ctx->plan.mats[idx[e]].has_projector = false;
-        ctx->h_gate[idx[e]] = fira_ctx::Gate{INFINITY, INFINITY};
+        ctx->h_gate[idx[e]] = FiraGate{INFINITY, INFINITY};
       }
       return fail(ctx, FIRA_ERR_HIP, std::string("projector installation: ") + hipGetErrorString(e_));
     }
   }
   for (int e = 0; e < count; ++e) {
-    ctx->h_gate[idx[e]] = fira_ctx::Gate{INFINITY, INFINITY};
     ctx->plan.mats[idx[e]].has_projector = true;
     ctx->unmeasured[idx[e]] = 1;
   }
-  return read_back_gates(ctx);
+  return gates_on_their_way(ctx);
 }
 
 fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev_W, const void* const* dev_G) {
@@ -599,7 +590,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     }
     need_residual = false;
     for (int e = 0; e < count; ++e) {
-      const fira_ctx::Gate gt = ctx->h_gate[idx[e]];
+      const FiraGate gt = ctx->h_gate[idx[e]];
       const bool gram = gt.ortho_err <= hp.ortho_tol && gt.gram_err <= hp.gram_tol;
       any_gram = any_gram || gram;
       need_residual = need_residual || !gram;
@@ -616,7 +607,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   bool fused = ctx->fusion && !ctx->zsplit && !only_scaling && ctx->scaling == FIRA_SCALE_COLUMN && ctx->norm_mode == FIRA_NORM_GRAM && any_gram;
   bool keep_r = false, drop_r = false, any_fused = false;
   for (int e = 0; e < count && fused; ++e) {
-    const fira_ctx::Gate gt = ctx->h_gate[idx[e]];
+    const FiraGate gt = ctx->h_gate[idx[e]];
     if (!(gt.ortho_err <= hp.ortho_tol && gt.gram_err <= hp.gram_tol)) continue;
     const HostMat& h = ctx->plan.mats[idx[e]];
     any_fused = any_fused || h.fuse_list >= 0;
@@ -680,7 +671,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
                        ctx->d_partial, hp);
   mark(3);
   // 4. limiter factor, state advance
-  hipLaunchKernelGGL(fira_limiter_kernel, dim3(count), dim3(FIRA_LIMITER_THREADS), 0, q, ctx->d_mats, ctx->d_scal, s->d_ents, ctx->d_partial, hp);
+  hipLaunchKernelGGL(fira_limiter_kernel, dim3(count), dim3(FIRA_LIMITER_THREADS), 0, q, ctx->d_mats, ctx->d_scal, s->d_ents, ctx->d_partial, ctx->h_gate, hp);
   mark(4);
   // 5. Z = N - c k R (after the fused kernel, which keeps no R: Z = c Z_1 + (1 - c) N for the matrices with c < 1)
   if (!only_scaling)
@@ -702,7 +693,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   FIRA_HIP(ctx, hipGetLastError());
   if (!only_scaling && ctx->norm_mode == FIRA_NORM_GRAM)
     for (int e = 0; e < count; ++e) ctx->unmeasured[idx[e]] = 0;
-  if (measures) return read_back_gates(ctx);   // the limiter has measured a second gate value: the next step needs it
+  if (measures) return gates_on_their_way(ctx);   // the limiter has measured a second gate value: the next step needs it
   return FIRA_OK;
 }
 
@@ -835,7 +826,8 @@ fira_status fira_set_gate(fira_ctx* ctx, int idx, float ortho_err, float gram_er
   if (!ctx->plan.mats[idx].has_projector) return fail(ctx, FIRA_ERR_NO_PROJECTOR, "install the projector first: fira_set_projector resets the gate");
   if (!(ortho_err >= 0.0f) || !(gram_err >= 0.0f)) return fail(ctx, FIRA_ERR_INVALID_ARG, "gate values must be >= 0 (+inf = not measured)");
   FIRA_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  const fira_ctx::Gate gt{ortho_err, gram_err};
+  static_assert(offsetof(FiraScal, gram_err) == offsetof(FiraScal, ortho_err) + sizeof(float) && sizeof(FiraGate) == 2 * sizeof(float), "the two gate values go over as one piece");
+  const FiraGate gt{ortho_err, gram_err};
   FIRA_HIP(ctx, hipMemcpy(reinterpret_cast<char*>(ctx->d_scal + idx) + offsetof(FiraScal, ortho_err), &gt, sizeof(gt), hipMemcpyHostToDevice));
   ctx->h_gate[idx] = gt;
   ctx->unmeasured[idx] = 0;
@@ -1086,7 +1078,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   auto invalidate = [&]() {
     for (int e = 0; e < count; ++e) {
       ctx->plan.mats[idx[e]].has_projector = false;
-      ctx->h_gate[idx[e]] = fira_ctx::Gate{INFINITY, INFINITY};
+      ctx->h_gate[idx[e]] = FiraGate{INFINITY, INFINITY};
     }
   };
   {
@@ -1094,20 +1086,20 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     if (e_ != hipSuccess) { invalidate(); return fail(ctx, FIRA_ERR_HIP, std::string("projector refresh: ") + hipGetErrorString(e_)); }
   }
   // install the result (what fira_set_projector does per matrix, here one launch per phase for the whole list)
+  for (int e = 0; e < count; ++e) ctx->h_gate[idx[e]] = FiraGate{INFINITY, INFINITY};   // (before the kernel that writes them can run)
   hipLaunchKernelGGL(fira_refresh_prep_kernel, dim3(prep_blocks, count), dim3(256), 0, q, ctx->d_mats, d_ents2);
   hipLaunchKernelGGL(fira_refresh_ortho_y_kernel, dim3((max_S + 3) / 4, count), dim3(256), 0, q, ctx->d_mats, d_ents2);
   hipLaunchKernelGGL(fira_refresh_ortho_z_kernel, dim3(FIRA_ORTHO_SPLITS, count), dim3(256), 0, q, ctx->d_mats, d_ents2);
-  hipLaunchKernelGGL(fira_refresh_ortho_final_kernel, dim3(count), dim3(256), 0, q, ctx->d_mats, d_ents2, ctx->d_scal);
+  hipLaunchKernelGGL(fira_refresh_ortho_final_kernel, dim3(count), dim3(256), 0, q, ctx->d_mats, d_ents2, ctx->d_scal, ctx->h_gate);
   {
     const hipError_t e_ = hipGetLastError();
     if (e_ != hipSuccess) { invalidate(); return fail(ctx, FIRA_ERR_HIP, std::string("projector refresh: ") + hipGetErrorString(e_)); }
   }
   for (int e = 0; e < count; ++e) {
-    ctx->h_gate[idx[e]] = fira_ctx::Gate{INFINITY, INFINITY};
     ctx->plan.mats[idx[e]].has_projector = true;
     ctx->unmeasured[idx[e]] = 1;
   }
-  return read_back_gates(ctx);
+  return gates_on_their_way(ctx);
 }
 
 }  // namespace

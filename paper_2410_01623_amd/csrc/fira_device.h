@@ -87,6 +87,12 @@ struct FiraScal {
   int pad;
 };
 
+// The two gate values of a matrix as the host keeps them (pinned memory): the kernels that work them out (the orthonormality estimate's last
+// one, the limiter) write them there as well as into FiraScal, so that no copy has to bring them back (one after every
+// installation and one after the step that measures, which the stream stood still for: a refresh and its step over 4 blocks of 256 x 688 at
+// r = 16 453 us with them and 251 without, 8 of 512 x 1376 at r = 128 693 and 678).
+struct FiraGate { float ortho_err, gram_err; };
+
 // One entry of a step's work list.
 struct FiraEnt {
   int mat;          // index into FiraMat / FiraScal

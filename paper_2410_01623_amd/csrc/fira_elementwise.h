@@ -457,7 +457,7 @@ __device__ __forceinline__ double limiter_block_sum(double x, double* red) {
 __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limiter_kernel(const FiraMat* __restrict__ mats,
                                                                             FiraScal* __restrict__ scal,
                                                                             const FiraEnt* __restrict__ ents,
-                                                                            const float* __restrict__ partial, FiraHp hp) {
+                                                                            const float* __restrict__ partial, FiraGate* __restrict__ gate, FiraHp hp) {
   __shared__ double red[4];
   const FiraEnt ent = ents[blockIdx.x];
   const int tid = threadIdx.x;
@@ -511,7 +511,10 @@ __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limiter_kernel(cons
       const double ratio = den > 0.0 ? sn / den : INFINITY;
       c = hp.gamma / fmax(ratio, hp.gamma);
     }
-    if (calibrate) s.gram_err = (acc == accg) ? 0.0f : (float)fmin(fabs(accg - acc) / fmax(acc, 1e-300), 3.0e38);
+    if (calibrate) {
+      s.gram_err = (acc == accg) ? 0.0f : (float)fmin(fabs(accg - acc) / fmax(acc, 1e-300), 3.0e38);
+      as_global(gate)[ent.mat].gram_err = s.gram_err;
+    }
     s.gram_now = gram ? (hp.fused ? 2 : 1) : 0;
     s.s_pre = sn;
     s.s_post = c * sn;
@@ -897,7 +900,7 @@ __global__ __launch_bounds__(256) void fira_ortho_z_kernel(FiraMat mt, const flo
 }
 
 __device__ __forceinline__ void ortho_final_body(const FiraMat& mt, const float* __restrict__ zpart,
-                                                 FiraScal* __restrict__ scal, int mat, float (&red)[4][4]) {
+                                                 FiraScal* __restrict__ scal, FiraGate* __restrict__ gate, int mat, float (&red)[4][4]) {
   gptr<const float> zp = as_global(zpart);
   const int t = threadIdx.x;
   float zz[4] = {0.f, 0.f, 0.f, 0.f};
@@ -925,10 +928,12 @@ __device__ __forceinline__ void ortho_final_body(const FiraMat& mt, const float*
       worst = fmaxf(worst, sqrtf(((red[0][k] + red[1][k]) + (red[2][k] + red[3][k])) / (float)mt.r));
     as_global(scal)[mat].ortho_err = worst;
     as_global(scal)[mat].gram_err = INFINITY;   // to be measured on the next step
+    as_global(gate)[mat].ortho_err = worst;
+    as_global(gate)[mat].gram_err = INFINITY;
   }
 }
 __global__ __launch_bounds__(256) void fira_ortho_final_kernel(FiraMat mt, const float* __restrict__ zpart,
-                                                               FiraScal* __restrict__ scal, int mat) {
+                                                               FiraScal* __restrict__ scal, FiraGate* __restrict__ gate, int mat) {
   __shared__ float red[4][4];
-  ortho_final_body(mt, zpart, scal, mat, red);
+  ortho_final_body(mt, zpart, scal, gate, mat, red);
 }

@@ -842,8 +842,8 @@ __global__ __launch_bounds__(256) void fira_refresh_ortho_z_kernel(const FiraMat
   ortho_z_body(mats[e.mat], e.inst, e.inst + (size_t)e.S * 4);
 }
 __global__ __launch_bounds__(256) void fira_refresh_ortho_final_kernel(const FiraMat* __restrict__ mats, const FiraRefreshEnt* __restrict__ ents,
-                                                                       FiraScal* __restrict__ scal) {
+                                                                       FiraScal* __restrict__ scal, FiraGate* __restrict__ gate) {
   __shared__ float red[4][4];
   const FiraRefreshEnt e = ents[blockIdx.x];
-  ortho_final_body(mats[e.mat], e.inst + (size_t)e.S * 4, scal, e.mat, red);
+  ortho_final_body(mats[e.mat], e.inst + (size_t)e.S * 4, scal, gate, e.mat, red);
 }
