@@ -65,6 +65,8 @@ constexpr int kComputeUnits = 256, kLdsPerCu = 160 * 1024;
 // twice as often for nothing by smaller tiles, not quite one (fira_backproject_kernel has both sides of each measured).
 constexpr int kForwardsMaxR = 64;
 constexpr int kQuarterTiles = 1536, kQuarterTilesLongRank = 384;
+// Listed matrices up to which the limiter and Z are one launch (fira_limit_and_makez_kernel has both sides measured).
+constexpr int kLimitAndZ = 64;
 // Tiles of a list from which on the fused projection/Adam kernel serves ranks that leave R in memory (fira_step has both sides).
 constexpr int kFuseMinTiles = 100;
 
@@ -573,7 +575,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
     if (nl + nr)
       hipLaunchKernelGGL(fira_project_small_kernel, dim3(bl + br), blk, FIRA_PROJ_SMALL_LDS, q, ctx->d_mats, s->d_ents,
-                         s->d_tiles[kTilesProjSmallLeft], nl, bl, s->d_tiles[kTilesProjSmallRight], nr, norm_arg, (const FiraScal*)ctx->d_scal, hp);
+                         s->d_tiles[kTilesProjSmallLeft], nl, bl, s->d_tiles[kTilesProjSmallRight], nr, norm_arg, ctx->d_scal, ctx->d_scal, hp);
   };
   const int want_g2 = (ctx->norm_mode == FIRA_NORM_GRAM || only_scaling) ? 1 : 0;   // ||G_i||^2 per factor
   // Which listed matrices take the Gram route to ||S|| (the kernels apply the same test per matrix: both
@@ -629,10 +631,10 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       if (nl + nr == 0) continue;
       const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
       if (rt == 1)
-        hipLaunchKernelGGL(fira_project_adam_kernel<1>, dim3(bl + br), dim3(256), FIRA_FUSE_LDS(1), q, ctx->d_mats, ctx->d_scal, s->d_ents,
+        hipLaunchKernelGGL(fira_project_adam_kernel<1>, dim3(bl + br), dim3(256), FIRA_FUSE_LDS(1), q, ctx->d_mats, ctx->d_scal, ctx->d_scal, s->d_ents,
                            s->d_tiles[ll], nl, bl, s->d_tiles[lr], nr, hp);
       else
-        hipLaunchKernelGGL(fira_project_adam_kernel<2>, dim3(bl + br), dim3(512), FIRA_FUSE_LDS(2), q, ctx->d_mats, ctx->d_scal, s->d_ents,
+        hipLaunchKernelGGL(fira_project_adam_kernel<2>, dim3(bl + br), dim3(512), FIRA_FUSE_LDS(2), q, ctx->d_mats, ctx->d_scal, ctx->d_scal, s->d_ents,
                            s->d_tiles[ll], nl, bl, s->d_tiles[lr], nr, hp);
     }
   }
@@ -646,14 +648,14 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       const int planes = ctx->zsplit ? 2 : 1;
       if (need_residual)
         hipLaunchKernelGGL((fira_adam_kernel<1, true>), dim3(s->rowblocks), dim3(256),
-                           std::max(ctx->plan.adam_lds * planes, ctx->plan.adam_lds_staged * (planes + 1)), q, ctx->d_mats, ctx->d_scal,
+                           std::max(ctx->plan.adam_lds * planes, ctx->plan.adam_lds_staged * (planes + 1)), q, ctx->d_mats, ctx->d_scal, ctx->d_scal,
                            s->d_ents, count, s->rowblocks, backwards, hp);
       else
-        hipLaunchKernelGGL((fira_adam_kernel<1, false>), dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds * planes, q, ctx->d_mats, ctx->d_scal,
+        hipLaunchKernelGGL((fira_adam_kernel<1, false>), dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds * planes, q, ctx->d_mats, ctx->d_scal, ctx->d_scal,
                            s->d_ents, count, s->rowblocks, backwards, hp);
     }
     if (s->ntiles[kTilesBackF32])
-      hipLaunchKernelGGL((fira_adam_kernel<FIRA_KX_SPLIT, false>), dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds_f32, q, ctx->d_mats, ctx->d_scal,
+      hipLaunchKernelGGL((fira_adam_kernel<FIRA_KX_SPLIT, false>), dim3(s->rowblocks), dim3(256), ctx->plan.adam_lds_f32, q, ctx->d_mats, ctx->d_scal, ctx->d_scal,
                          s->d_ents, count, s->rowblocks, backwards, hp);
     mark(2);
   } else {
@@ -671,11 +673,17 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
                        ctx->d_partial, hp);
   mark(3);
   // 4. limiter factor, state advance
-  hipLaunchKernelGGL(fira_limiter_kernel, dim3(count), dim3(FIRA_LIMITER_THREADS), 0, q, ctx->d_mats, ctx->d_scal, s->d_ents, ctx->d_partial, ctx->h_gate, hp);
-  mark(4);
-  // 5. Z = N - c k R (after the fused kernel, which keeps no R: Z = c Z_1 + (1 - c) N for the matrices with c < 1)
-  if (!only_scaling)
-    hipLaunchKernelGGL(fira_makez_kernel, dim3(count * FIRA_MAKEZ_PARTS), dim3(256), 0, q, ctx->d_mats, ctx->d_scal, s->d_ents, hp);
+  // 5. Z = N - c k R where the limiter acts or the Adam kernel left N (after the fused kernel, which keeps no R: Z = c Z_1 + (1 - c) N)
+  if (only_scaling || ctx->scaling == FIRA_SCALE_MATRIX || count > kLimitAndZ) {
+    hipLaunchKernelGGL(fira_limiter_kernel, dim3(count), dim3(FIRA_LIMITER_THREADS), 0, q, ctx->d_mats, ctx->d_scal, s->d_ents, ctx->d_partial, ctx->h_gate, hp);
+    mark(4);
+    if (!only_scaling)
+      hipLaunchKernelGGL(fira_makez_kernel, dim3(count * FIRA_MAKEZ_PARTS), dim3(256), 0, q, ctx->d_mats, ctx->d_scal, s->d_ents, hp);
+  } else {
+    hipLaunchKernelGGL(fira_limit_and_makez_kernel, dim3(count * FIRA_MAKEZ_PARTS), dim3(FIRA_LIMITER_THREADS), 0, q, ctx->d_mats, ctx->d_scal, s->d_ents,
+                       ctx->d_partial, ctx->h_gate, hp);
+    mark(4);
+  }
   mark(5);
   // 6. W -= lr alpha (P Z + c k G)    (only-scaling variant: W -= lr alpha c k G, a plain stream)
   if (only_scaling) {

@@ -84,8 +84,20 @@ struct FiraScal {
   // subspace, and what is left is then the orthonormality defect of the rounded P and fp32 rounding.
   float gram_err;
   int gram_now;    // route of the last step for this matrix: 0 residual, 1 Gram with two kernels, 2 Gram with the fused kernel
-  int pad;
+  // What the limiter of a step goes by, as it was before the step: set aside by the kernel that runs Adam on the matrix, since of the
+  // workgroups that work out the factor, each for itself, one writes the new values over the old while others may not have read them.
+  int has_prev_in, t_in;
+  float ortho_err_in, gram_err_in;
+  double s_prev_in;
 };
+// (to: the same element of the table; two pointers, so that what is only read stays a scalar load)
+__device__ __forceinline__ void set_limiter_inputs(FiraScal* __restrict__ to, const FiraScal& s) {
+  to->s_prev_in = s.s_prev;
+  to->has_prev_in = s.has_prev;
+  to->t_in = s.t;
+  to->ortho_err_in = s.ortho_err;
+  to->gram_err_in = s.gram_err;
+}
 
 // The two gate values of a matrix as the host keeps them (pinned memory): the kernels that work them out (the orthonormality estimate's last
 // one, the limiter) write them there as well as into FiraScal, so that no copy has to bring them back (one after every

@@ -371,7 +371,7 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
 // (One kernel for both took ten registers too many for four wavefronts per SIMD, and 2 % of the bf16 time.)
 template <int KX, bool STAGE_R>
 __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __restrict__ mats,
-                                                        const FiraScal* __restrict__ scal,
+                                                        const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out,
                                                         const FiraEnt* __restrict__ ents, int count,
                                                         int total_rowblocks, int backwards, FiraHp hp) {
   extern __shared__ __attribute__((aligned(16))) char adam_lds[];   // zready matrices: 16 rows x planes x rp bf16 (and R's)
@@ -387,6 +387,7 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const FiraScal sc = scal[ent.mat];
   const bool gram = use_gram(hp, sc);
   if (hp.mixed && gram) return;                // the fused kernel has served this matrix
+  if (rb == ent.row0 && threadIdx.x == 0) set_limiter_inputs(scal_out + ent.mat, sc);
   const float bias = bias_correction(hp, sc.t + 1);   // (the step count is 1-based)
   const int wave = threadIdx.x >> 6;
   const long long row_base = (long long)(rb - ent.row0) * FIRA_ROWS_PER_WG + wave * 4;
@@ -454,6 +455,46 @@ __device__ __forceinline__ double limiter_block_sum(double x, double* red) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// This thread's share of a sum of n values, in a fixed order; eight loads in flight.
+__device__ __forceinline__ double limiter_thread_sum(gptr<const float> x, int n) {
+  double a = 0.0;
+  for (int i = threadIdx.x; i < n; i += 8 * FIRA_LIMITER_THREADS) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = x[min(i + k * FIRA_LIMITER_THREADS, n - 1)];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a += i + k * FIRA_LIMITER_THREADS < n ? (double)v[k] : 0.0;
+  }
+  return a;
+}
+// ||S||^2 (acc) of a matrix with a factor per row or none, and where both routes' data are at hand the Gram route's value of it (accg).
+__device__ __forceinline__ void limiter_sums(const FiraMat& mt, const FiraEnt& ent, const float* __restrict__ partial, bool gram, bool calibrate,
+                                             double* red, double& acc, double& accg) {
+  const double a = gram || calibrate ? limiter_thread_sum(as_global<const float>(mt.q), mt.L) : 0.0;
+  acc = limiter_block_sum(gram ? a : limiter_thread_sum(as_global<const float>(partial) + ent.part0, ent.npart), red);
+  accg = calibrate ? limiter_block_sum(a, red) : 0.0;     // (uniform over the workgroup)
+}
+// The limiter's factor for ||S|| = sn (Eq. 12).
+__device__ __forceinline__ double limiter_factor(const FiraHp& hp, double sn, int has_prev, double s_prev) {
+  if (!has_prev || isinf(hp.gamma) || sn == 0.0) return 1.0;
+  const double den = s_prev + hp.eps;
+  const double ratio = den > 0.0 ? sn / den : INFINITY;
+  return hp.gamma / fmax(ratio, hp.gamma);
+}
+// The state after the step (one thread).
+__device__ __forceinline__ void limiter_advance(FiraScal& s, FiraGate& gate, const FiraHp& hp, bool gram, bool calibrate, double acc, double accg, double sn,
+                                                double c, int t) {
+  if (calibrate) gate.gram_err = s.gram_err = (acc == accg) ? 0.0f : (float)fmin(fabs(accg - acc) / fmax(acc, 1e-300), 3.0e38);
+  s.gram_now = gram ? (hp.fused ? 2 : 1) : 0;
+  s.s_pre = sn;
+  s.s_post = c * sn;
+  s.s_prev = c * sn;        // the remembered norm is the limited one
+  s.has_prev = 1;
+  s.c = (float)c;
+  s.t = t + 1;
+}
+
+// The limiter by itself: one factor per matrix (Eq. 9), which is worked out here and written over phi, a step without Z, or a long list.
 __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limiter_kernel(const FiraMat* __restrict__ mats,
                                                                             FiraScal* __restrict__ scal,
                                                                             const FiraEnt* __restrict__ ents,
@@ -462,6 +503,7 @@ __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limiter_kernel(cons
   const FiraEnt ent = ents[blockIdx.x];
   const int tid = threadIdx.x;
   const FiraScal sc0 = scal[ent.mat];
+  const FiraMat mt = mats[ent.mat];
   const bool gram = use_gram(hp, sc0);
   // On the residual route with the Gram data at hand (the first step after an install), also form the
   // Gram route's value and record how far it is from the exact one: the second gate of that route.
@@ -470,7 +512,6 @@ __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limiter_kernel(cons
   if (hp.scaling == 1) {
     // Matrix-level factor (Eq. 9): k = ||N|| / (||R|| + eps) from the row sums the Adam kernel left in
     // phi and q; ||S||^2 = k^2 * (sum_i ||G_i - P R_i||^2), the sum taken with unit factors by either route.
-    const FiraMat mt = mats[ent.mat];
     gptr<float> phi = as_global(mt.phi);
     gptr<const float> q = as_global<const float>(mt.q);
     gptr<const float> g2 = as_global<const float>(mt.g2);
@@ -489,40 +530,14 @@ __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limiter_kernel(cons
     acc *= (double)k * (double)k;
     accg *= (double)k * (double)k;
     for (int i = tid; i < mt.L; i += FIRA_LIMITER_THREADS) phi[i] = k;
+    acc = limiter_block_sum(acc, red);
+    if (calibrate) accg = limiter_block_sum(accg, red);
   } else {
-    if (gram || calibrate) {
-      const FiraMat mt = mats[ent.mat];
-      gptr<const float> q = as_global<const float>(mt.q);
-      double a = 0.0;
-      for (int i = tid; i < mt.L; i += FIRA_LIMITER_THREADS) a += (double)q[i];
-      if (gram) acc = a; else accg = a;
-    }
-    if (!gram)
-      for (int i = tid; i < ent.npart; i += FIRA_LIMITER_THREADS) acc += (double)partial[ent.part0 + i];
+    limiter_sums(mt, ent, partial, gram, calibrate, red, acc, accg);
   }
-  acc = limiter_block_sum(acc, red);
-  if (calibrate) accg = limiter_block_sum(accg, red);   // (uniform over the workgroup)
   if (tid == 0) {
-    FiraScal s = scal[ent.mat];
-    const double sn = sqrt(acc);
-    double c = 1.0;
-    if (s.has_prev && !isinf(hp.gamma) && sn != 0.0) {
-      const double den = s.s_prev + hp.eps;
-      const double ratio = den > 0.0 ? sn / den : INFINITY;
-      c = hp.gamma / fmax(ratio, hp.gamma);
-    }
-    if (calibrate) {
-      s.gram_err = (acc == accg) ? 0.0f : (float)fmin(fabs(accg - acc) / fmax(acc, 1e-300), 3.0e38);
-      as_global(gate)[ent.mat].gram_err = s.gram_err;
-    }
-    s.gram_now = gram ? (hp.fused ? 2 : 1) : 0;
-    s.s_pre = sn;
-    s.s_post = c * sn;
-    s.s_prev = s.s_post;      // the remembered norm is the limited one
-    s.has_prev = 1;
-    s.c = (float)c;
-    s.t += 1;
-    scal[ent.mat] = s;
+    const double sn = sqrt(acc), c = limiter_factor(hp, sn, sc0.has_prev, sc0.s_prev);
+    limiter_advance(scal[ent.mat], gate[ent.mat], hp, gram, calibrate, acc, accg, sn, c, sc0.t);
   }
 }
 
@@ -562,27 +577,58 @@ __device__ __forceinline__ void makez_row(const FiraMat& mt, float f, long long 
   }
 }
 
-// Rows that already hold Z for c = 1 (N_i - k_i R_i): add back (1 - c) k_i R_i, with R in fp32.
-__device__ __forceinline__ void fixz_row(const FiraMat& mt, float f, long long row, bool zsplit) {
-  const int lane = threadIdx.x & 63;
-  gptr<bf16_raw> Nb = as_global(mt.Nb);
-  gptr<const float> R = as_global<const float>(mt.Rt) + row * mt.r;
-  for (int a = lane * 4; a < mt.r; a += 256) {
-    const long long o = kblk_index(mt.Lq, row, a), ol = kblk_index(mt.Lq, row, mt.rp + a);
-    const u32x2 zv = *reinterpret_cast<gptr<const u32x2>>(Nb + o);
-    const f32x4 rv = load_row4(R + a, mt.r - a);
-    const u32x2 mask = row4_mask(mt.r - a);
-    f32x4 z = f32x4{__uint_as_float(zv.x << 16), __uint_as_float(zv.x & 0xffff0000u), __uint_as_float(zv.y << 16),
-                    __uint_as_float(zv.y & 0xffff0000u)};
-    if (zsplit) {
-      const u32x2 lv = *reinterpret_cast<gptr<const u32x2>>(Nb + ol);
-      z += f32x4{__uint_as_float(lv.x << 16), __uint_as_float(lv.x & 0xffff0000u), __uint_as_float(lv.y << 16),
-                 __uint_as_float(lv.y & 0xffff0000u)};
+// Sixteen rows of a bf16 matrix that already hold Z for c = 1 (N_i - k_i R_i): add back (1 - c) k_i R_i, with R in fp32.  Memory bound, by one
+// wavefront: a lane takes eight values of a row, the sixteen rows of a K block are 1 KB of Z in one piece, and two K blocks, `first` and every
+// step-th from there, are in flight.  Limited steps over the 350M shapes at r = 256, residual route and two planes: 1364 and 1286 us row by
+// row with Z in scattered 8-byte pieces, 1334 and 1239 this way.
+__device__ __forceinline__ void fixz_block(const FiraMat& mt, float n, long long row0, int first, int step, bool zsplit) {
+  const int lane = threadIdx.x & 63, a8 = (lane & 3) * 8;
+  const long long row = row0 + (lane >> 2);
+  const int kblocks = (mt.r + 31) >> 5;
+  if (row >= mt.L) return;
+  gptr<char> Nb = reinterpret_cast<gptr<char>>(as_global(mt.Nb)) + row0 * 64 + lane * 16;
+  gptr<const float> R = as_global<const float>(mt.Rt) + row * mt.r + a8;
+  const long long plane = (long long)(mt.rp >> 5) * mt.Lq * 64;
+  const float f = n * as_global<const float>(mt.phi)[row];
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kb0 = first; kb0 < kblocks; kb0 += 2 * step) {
+    u32x4 zv[2], lv[2];
+    f32x4 rv[2][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int kb = kb0 + step * u;
+      if (kb < kblocks) {
+        zv[u] = *reinterpret_cast<gptr<const u32x4>>(Nb + (long long)kb * mt.Lq * 64);
+        if (zsplit) lv[u] = *reinterpret_cast<gptr<const u32x4>>(Nb + (long long)kb * mt.Lq * 64 + plane);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int mine = mt.r - 32 * kb - a8 - 4 * q;
+          rv[u][q] = mine > 0 ? load_row4(R + 32 * kb + 4 * q, mine) : zero;
+        }
+      }
     }
-    z += f * rv;
-    const u32x2 hi = u32x2{pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3])};
-    *reinterpret_cast<gptr<u32x2>>(Nb + o) = hi & mask;
-    if (zsplit) *reinterpret_cast<gptr<u32x2>>(Nb + ol) = split_remainder(z, hi) & mask;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int kb = kb0 + step * u;
+      if (kb < kblocks) {
+        const unsigned w[4] = {zv[u].x, zv[u].y, zv[u].z, zv[u].w}, l[4] = {lv[u].x, lv[u].y, lv[u].z, lv[u].w};
+        u32x2 h[2], lo[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          f32x4 z = f32x4{__uint_as_float(w[2 * q] << 16), __uint_as_float(w[2 * q] & 0xffff0000u), __uint_as_float(w[2 * q + 1] << 16),
+                          __uint_as_float(w[2 * q + 1] & 0xffff0000u)};
+          if (zsplit)
+            z += f32x4{__uint_as_float(l[2 * q] << 16), __uint_as_float(l[2 * q] & 0xffff0000u), __uint_as_float(l[2 * q + 1] << 16),
+                       __uint_as_float(l[2 * q + 1] & 0xffff0000u)};
+          z += f * rv[u][q];
+          const u32x2 mask = row4_mask(mt.r - 32 * kb - a8 - 4 * q), hi = pack_bf16x4(z);
+          h[q] = hi & mask;
+          lo[q] = split_remainder(z, hi) & mask;
+        }
+        *reinterpret_cast<gptr<u32x4>>(Nb + (long long)kb * mt.Lq * 64) = u32x4{h[0].x, h[0].y, h[1].x, h[1].y};
+        if (zsplit) *reinterpret_cast<gptr<u32x4>>(Nb + (long long)kb * mt.Lq * 64 + plane) = u32x4{lo[0].x, lo[0].y, lo[1].x, lo[1].y};
+      }
+    }
   }
 }
 
@@ -663,24 +709,21 @@ __device__ __forceinline__ void fixz_row_split(const FiraMat& mt, const FiraHp& 
 
 static_assert(FIRA_ZREADY_MAX_R_F32 == 512, "fira_adam_kernel's forms end there");
 #define FIRA_MAKEZ_PARTS 32   // workgroups per listed matrix
-// One workgroup per (listed matrix, part): it reads the matrix's c once and, in the common case, exits;
-// otherwise it takes every FIRA_MAKEZ_PARTS-th block of 16 rows.
-__global__ __launch_bounds__(256) void fira_makez_kernel(const FiraMat* __restrict__ mats,
-                                                         const FiraScal* __restrict__ scal,
-                                                         const FiraEnt* __restrict__ ents, FiraHp hp) {
-  const FiraEnt ent = ents[blockIdx.x / FIRA_MAKEZ_PARTS];
-  const int part = blockIdx.x % FIRA_MAKEZ_PARTS;
-  const float c = scal[ent.mat].c;
-  const FiraMat mt = mats[ent.mat];
+// A matrix's Z for a limiter factor of c, by one of FIRA_MAKEZ_PARTS workgroups, which takes every FIRA_MAKEZ_PARTS-th block of 16 rows.
+// t: the step count with this step in it; fused_here: the fused kernel served the matrix and left no copy of R.
+__device__ __forceinline__ void make_z(const FiraMat& mt, const FiraHp& hp, int part, float c, int t, bool fused_here) {
   const bool zready = mt.zready && hp.scaling != 1;
   if (zready && c == 1.0f) return;             // the Adam kernel already wrote Z for c = 1
-  // whether the fused kernel served this matrix (then no copy of R exists)
-  const bool fused_here = scal[ent.mat].gram_now == 2;
   const int wave = threadIdx.x >> 6;
   const int rowblocks = (mt.L + FIRA_ROWS_PER_WG - 1) / FIRA_ROWS_PER_WG;
-  // the limiter has already advanced t: the bias correction of this step uses the count as it stands now
-  const int t = scal[ent.mat].t;
   const float bias = fused_here || mt.kx != 1 ? bias_correction(hp, t) : 0.0f;
+  if (zready && mt.kx == 1 && !fused_here) {
+    // a row of one or two K blocks: each wavefront has sixteen rows of its own
+    const bool small = mt.r <= FIRA_PS;
+    for (int rb = small ? 4 * part + wave : part; rb < rowblocks; rb += (small ? 4 : 1) * FIRA_MAKEZ_PARTS)
+      fixz_block(mt, 1.0f - c, (long long)rb * FIRA_ROWS_PER_WG, small ? 0 : wave, small ? 1 : 4, hp.zsplit != 0);
+    return;
+  }
   for (int rb = part; rb < rowblocks; rb += FIRA_MAKEZ_PARTS) {
     if (zready && fused_here) {
       fixz_block_from_moments(mt, hp, c, bias, (long long)rb * FIRA_ROWS_PER_WG);
@@ -692,11 +735,46 @@ __global__ __launch_bounds__(256) void fira_makez_kernel(const FiraMat* __restri
       if (row >= mt.L) break;
       const float k = as_global<const float>(mt.phi)[row];
       if (zready && mt.kx != 1) fixz_row_split(mt, hp, c * k, bias, row);
-      else if (zready) fixz_row(mt, (1.0f - c) * k, row, hp.zsplit != 0);
       else if (mt.kx == 1) makez_row<1>(mt, c * k, row);
       else makez_row<FIRA_KX_SPLIT>(mt, c * k, row);
     }
   }
+}
+// One workgroup per (listed matrix, part): it reads the matrix's c once and, in the common case, exits.
+__global__ __launch_bounds__(256) void fira_makez_kernel(const FiraMat* __restrict__ mats,
+                                                         const FiraScal* __restrict__ scal,
+                                                         const FiraEnt* __restrict__ ents, FiraHp hp) {
+  const FiraEnt ent = ents[blockIdx.x / FIRA_MAKEZ_PARTS];
+  const FiraMat mt = mats[ent.mat];
+  make_z(mt, hp, blockIdx.x % FIRA_MAKEZ_PARTS, scal[ent.mat].c, scal[ent.mat].t, scal[ent.mat].gram_now == 2);
+}
+// The limiter and Z in one launch, for factors per row or none: every workgroup works the factor out for itself, from the values that the kernel
+// with Adam set aside (set_limiter_inputs), and the first one of a matrix advances its state.  Two launches in turn are two latencies, and
+// the second nearly always only reads c = 1: a step of 256 x 688 in fp32 30.4 and 28.2 us, 8 blocks of 512 x 1376 at r = 128 90.6 and 87.4 (56
+// matrices), limited 87.1 and 83.8.  With more workgroups than run at once the sums cost more than the launch: 168 matrices of the 350M shapes on
+// the residual route, limited, 1388 and 1398; lists that long keep two.
+__global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limit_and_makez_kernel(const FiraMat* __restrict__ mats, FiraScal* __restrict__ scal,
+                                                                                    const FiraEnt* __restrict__ ents, const float* __restrict__ partial,
+                                                                                    FiraGate* __restrict__ gate, FiraHp hp) {
+  __shared__ double red[4];
+  const FiraEnt ent = ents[blockIdx.x / FIRA_MAKEZ_PARTS];
+  const int part = blockIdx.x % FIRA_MAKEZ_PARTS;
+  const FiraMat mt = mats[ent.mat];
+  FiraScal in;
+  in.s_prev = scal[ent.mat].s_prev_in;
+  in.has_prev = scal[ent.mat].has_prev_in;
+  in.t = scal[ent.mat].t_in;
+  in.ortho_err = scal[ent.mat].ortho_err_in;
+  in.gram_err = scal[ent.mat].gram_err_in;
+  const bool gram = use_gram(hp, in);
+  // On the residual route with the Gram data at hand (the first step after an install), also form the
+  // Gram route's value and record how far it is from the exact one: the second gate of that route.
+  const bool calibrate = part == 0 && !gram && calibrates_gram(hp, in);
+  double acc, accg;
+  limiter_sums(mt, ent, partial, gram, calibrate, red, acc, accg);
+  const double sn = sqrt(acc), c = limiter_factor(hp, sn, in.has_prev, in.s_prev);
+  if (part == 0 && threadIdx.x == 0) limiter_advance(scal[ent.mat], gate[ent.mat], hp, gram, calibrate, acc, accg, sn, c, in.t);
+  make_z(mt, hp, part, (float)c, in.t + 1, gram && hp.fused);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -314,10 +314,11 @@ __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& m
 // Ranks up to 128 fill half a rank tile; their tiles multiply 64 x 64 per wave and go through
 // Adam in four chunks instead of eight (56 matrices of 512 x 512 and 512 x 1376 at r = 128: 48 us instead of 65).
 template <bool LEFT, int RT>
-__device__ __forceinline__ void project_adam_tile(char* lds, const FiraMat* __restrict__ mats, const FiraScal* __restrict__ scal,
+__device__ __forceinline__ void project_adam_tile(char* lds, const FiraMat* __restrict__ mats, const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out,
                                                   const FiraEnt* __restrict__ ents, const FiraTile& tile, const FiraHp& hp) {
   const FiraEnt ent = ents[tile.ent];
   if (!use_gram(hp, scal[ent.mat])) return;    // this matrix takes the residual route: the two-kernel path serves it
+  if (tile.ta == 0 && threadIdx.x == 0) set_limiter_inputs(scal_out + ent.mat, scal[ent.mat]);
   const FiraMat mt = mats[ent.mat];
   if (RT == 1 && mt.r <= 128) project_adam_tile_as<LEFT, 1, 2>(lds, mt, scal, ent, tile, hp);
   else project_adam_tile_as<LEFT, RT, 4>(lds, mt, scal, ent, tile, hp);
@@ -329,7 +330,7 @@ __device__ __forceinline__ void project_adam_tile(char* lds, const FiraMat* __re
 // which keeps the XCD-aware mapping of each part.
 template <int RT>
 __global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_project_adam_kernel(const FiraMat* __restrict__ mats,
-                                                                                      const FiraScal* __restrict__ scal,
+                                                                                      const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out,
                                                                                       const FiraEnt* __restrict__ ents,
                                                                                       const FiraTile* __restrict__ tiles_left, int ntiles_left,
                                                                                       int blocks_left,
@@ -339,11 +340,11 @@ __global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_project_adam_k
   if ((int)blockIdx.x < blocks_left) {
     const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
     if (ti < 0) return;
-    project_adam_tile<true, RT>(lds, mats, scal, ents, tiles_left[ti], hp);
+    project_adam_tile<true, RT>(lds, mats, scal, scal_out, ents, tiles_left[ti], hp);
   } else {
     const int ti = xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
     if (ti < 0) return;
-    project_adam_tile<false, RT>(lds, mats, scal, ents, tiles_right[ti], hp);
+    project_adam_tile<false, RT>(lds, mats, scal, scal_out, ents, tiles_right[ti], hp);
   }
 }
 
@@ -562,7 +563,7 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 4) void fira_project_small_kerne
                                                                                   const FiraTile* __restrict__ tiles_left, int ntiles_left,
                                                                                   int blocks_left,
                                                                                   const FiraTile* __restrict__ tiles_right, int ntiles_right,
-                                                                                  int norm_mode, const FiraScal* __restrict__ scal, FiraHp hp) {
+                                                                                  int norm_mode, const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out, FiraHp hp) {
   extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_PROJ_SMALL_LDS bytes
   const bool left = (int)blockIdx.x < blocks_left;
   const int ti = left ? xcd_chunked_index(blockIdx.x, ntiles_left) : xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
@@ -577,6 +578,7 @@ __global__ __launch_bounds__(FIRA_PROJ_THREADS, 4) void fira_project_small_kerne
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[tn][v] = 0.0f;
   const bool sumsq = norm_mode == 1;           // every wave owns its own 32 factors
+  if (tile.ta == 0 && threadIdx.x == 0) set_limiter_inputs(scal_out + ent.mat, scal[ent.mat]);
   const int t = scal[ent.mat].t + 1;           // 1-based
   float bias;
   auto prologue = [&] {
