@@ -194,7 +194,7 @@ FIRA_API int fira_last_step_fused(const fira_ctx* ctx);
  * for as long as that lasts.  planes = 2: Z is kept as two bf16 planes, its rounding and the rounding of the
  * remainder (16 mantissa bits), the contraction runs over both, and W follows exact arithmetic over long
  * runs; the back-projection does twice the multiplies and the fused projection/Adam kernel is not used.
- * Applies to bf16 matrices with r <= 1024 and column or no factors; others keep one plane. */
+ * Applies to bf16 matrices with r % 4 == 0, r <= 1024 and column or no factors; others keep one plane. */
 FIRA_API fira_status fira_set_z_planes(fira_ctx* ctx, int planes);
 
 /* Copy the state of matrix idx to host memory.  Synchronises the stream.

@@ -89,6 +89,8 @@ struct FiraScal {
   int has_prev_in, t_in;
   float ortho_err_in, gram_err_in;
   double s_prev_in;
+  float c_in;      // the factor of the step before (leaves_n_and_r)
+  int pad;
 };
 // (to: the same element of the table; two pointers, so that what is only read stays a scalar load)
 __device__ __forceinline__ void set_limiter_inputs(FiraScal* __restrict__ to, const FiraScal& s) {
@@ -97,6 +99,7 @@ __device__ __forceinline__ void set_limiter_inputs(FiraScal* __restrict__ to, co
   to->t_in = s.t;
   to->ortho_err_in = s.ortho_err;
   to->gram_err_in = s.gram_err;
+  to->c_in = s.c;
 }
 
 // The two gate values of a matrix as the host keeps them (pinned memory): the kernels that work them out (the orthonormality estimate's last
@@ -144,6 +147,18 @@ struct FiraHp {     // hyper-parameters as the kernels take them
 // without any condition on P.)
 __device__ __forceinline__ bool use_gram(const FiraHp& hp, const FiraScal& sc) {
   return hp.variant == 1 || (hp.norm_mode == 1 && sc.ortho_err <= hp.ortho_tol && sc.gram_err <= hp.gram_tol);
+}
+// bf16 matrices whose rank is no multiple of four form Z from N and R rounded to bf16, as they always have: Z would differ from that
+// by as much as its own rounding, and a run by one in the last place of many weights.
+__device__ __forceinline__ bool rounds_n_and_r(const FiraMat& mt) { return mt.kx == 1 && (mt.r & 3) != 0; }
+// Whether the kernel with Adam leaves them as they are, for the Z kernel to work on whatever this step's factor: limited steps follow limited
+// steps, and from Z for c = 1 that rounding can only be had from M, V and R again (14 bytes a value for 6).  c_prev: the factor of the step
+// before.  Steps, limited, over 8 blocks of 2048 x 5461 at r = 511 and 770 and 24 of 1024 x 2736 at r = 255 on the residual route: 1854, 2820 and
+// 1340 us, 2080, 3163 and 1552 with Z for c = 1 written first on every step.
+__device__ __forceinline__ bool leaves_n_and_r(const FiraMat& mt, float c_prev) { return rounds_n_and_r(mt) && c_prev != 1.0f; }
+// Whether Z of a bf16 matrix is kept in two planes.
+__device__ __forceinline__ bool two_planes(const FiraHp& hp, const FiraMat& mt) {
+  return hp.zsplit && mt.zready && mt.kx == 1 && (mt.r & 3) == 0 && hp.scaling != 1;
 }
 // Whether ||G_i||^2 is computed in this step (every listed matrix, whatever its route: the step that
 // measures FiraScal::gram_err needs both routes' data).
@@ -206,6 +221,10 @@ __device__ __forceinline__ void split3(float x, bf16_raw& h, bf16_raw& m, bf16_r
   m = f32_to_bf16(r1);
   float r2 = r1 - bf16_to_f32(m);
   l = f32_to_bf16(r2);
+}
+
+__device__ __forceinline__ f32x4 bf16_rounded(const f32x4& x) {
+  return f32x4{bf16_to_f32(f32_to_bf16(x[0])), bf16_to_f32(f32_to_bf16(x[1])), bf16_to_f32(f32_to_bf16(x[2])), bf16_to_f32(f32_to_bf16(x[3]))};
 }
 
 // XCD-aware mapping of a linear workgroup id onto a logical work index: consecutive workgroup

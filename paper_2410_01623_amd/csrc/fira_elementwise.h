@@ -211,7 +211,7 @@ __device__ __forceinline__ u32x2 row4_mask(int mine) {
 
 // Planes of an operand row element: 1, 2 (Z of a bf16 matrix with hp.zsplit) or 3 (fp32 matrices).
 template <int KX>
-__device__ __forceinline__ int z_planes(const FiraHp& hp) { return KX == 1 ? (hp.zsplit ? 2 : 1) : 3; }
+__device__ __forceinline__ int z_planes(const FiraHp& hp, const FiraMat& mt) { return KX == 1 ? (two_planes(hp, mt) ? 2 : 1) : 3; }
 // Four consecutive values as that many planes (each the rounding of what the ones before leave).
 template <int KX>
 __device__ __forceinline__ void bf16_planes(const f32x4& z, int planes, u32x2 (&pl)[3]) {
@@ -233,7 +233,7 @@ __device__ __forceinline__ void bf16_planes(const f32x4& z, int planes, u32x2 (&
 // rl: the same image of R for bf16 matrices on the residual route (null: R goes out from here, in 64-byte pieces).
 template <int KX, int NIT, bool ODD>   // 256 * NIT >= r; ODD: r is no multiple of four
 __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp& hp, float bias, long long row, bool gram,
-                                                bf16_raw* zl, bf16_raw* rl, int rowlocal) {
+                                                bf16_raw* zl, bf16_raw* rl, int rowlocal, bool leave) {
   const int lane = threadIdx.x & 63;
   const int r = mt.r;
   gptr<const float> R = as_global<const float>(mt.Rt) + row * r;
@@ -264,7 +264,7 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
   nn = wave_sum(nn);
   rr = wave_sum(rr);
   const float k = (hp.scaling == 2) ? 1.0f : sqrtf(nn) / (sqrtf(rr) + hp.epsf);
-  const int planes = z_planes<KX>(hp), plane_off = (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32);   // planes of the LDS image
+  const int planes = z_planes<KX>(hp, mt), plane_off = (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32);   // planes of the LDS image
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int a = lane * 4 + 256 * it;
@@ -272,13 +272,14 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
       u32x2 zp[3];
       zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};
       if (a < r) {
-        bf16_planes<KX>(nv[it] - k * rv[it], planes, zp);
+        if (ODD && KX == 1) bf16_planes<KX>(leave ? nv[it] : bf16_rounded(nv[it]) - k * bf16_rounded(rv[it]), planes, zp);
+        else bf16_planes<KX>(nv[it] - k * rv[it], planes, zp);
         if (ODD) {
           const u32x2 mask = row4_mask(r - a);
 #pragma unroll
           for (int p = 0; p < 3; ++p) zp[p] &= mask;
         }
-        if (!gram && !rl) {
+        if ((!gram || (ODD && leave)) && !rl) {
           u32x2 rb[3];
           bf16_planes<KX>(rv[it], KX == 1 ? 1 : 3, rb);
 #pragma unroll
@@ -333,7 +334,7 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
   rr = row_sum<16>(rr);
   const float k = (hp.scaling == 2) ? 1.0f : sqrtf(nn) / (sqrtf(rr) + hp.epsf);
   if (a < mt.rp) {
-    const int planes = z_planes<KX>(hp);
+    const int planes = z_planes<KX>(hp, mt);
     u32x2 zp[3];
     zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};   // rows beyond L and columns beyond r: the operand's zero padding
     if (live) {
@@ -391,7 +392,8 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const float bias = bias_correction(hp, sc.t + 1);   // (the step count is 1-based)
   const int wave = threadIdx.x >> 6;
   const long long row_base = (long long)(rb - ent.row0) * FIRA_ROWS_PER_WG + wave * 4;
-  const int planes = z_planes<KX>(hp);
+  const int planes = z_planes<KX>(hp, mt);
+  const bool leave = leaves_n_and_r(mt, sc.c);
   const bool staged = STAGE_R && zready && !gram && mt.r > 64 && mt.r <= FIRA_RSTAGE_MAX_R;
   bf16_raw* rl = staged ? zl + planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32) : nullptr;
   if (KX != 1 && zready && mt.r <= 64) {
@@ -401,7 +403,7 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
       for (int i = 0; i < 4; ++i) {
         const long long row = row_base + i;
         if (row < mt.L) {
-          adam_row_zready<KX, decltype(nit)::value, decltype(odd)::value>(mt, hp, bias, row, gram, zl, rl, wave * 4 + i);
+          adam_row_zready<KX, decltype(nit)::value, decltype(odd)::value>(mt, hp, bias, row, gram, zl, rl, wave * 4 + i, leave);
         } else {   // rows of the padding: zeros
           for (int a = (threadIdx.x & 63) * 4; a < (planes + (staged ? 1 : 0)) * mt.rp; a += 256)
             *reinterpret_cast<u32x2*>(zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + i) * 32 + (a & 31)) = u32x2{0u, 0u};
@@ -545,35 +547,49 @@ __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limiter_kernel(cons
 // Back-projection operand: Z_i = N_i - c k_i R_i, so that P N + c k (G - P R) = P Z + c k G.
 // Overwrites N in place.  Matrices flagged zready skip this unless their limiter factor is below 1.
 // ------------------------------------------------------------------------------------------------
-template <int KX>
-__device__ __forceinline__ void makez_row(const FiraMat& mt, float f, long long row) {
+// bf16 matrices: a wavefront takes sixteen rows, whose part of a K block is 1 KB of either operand, K blocks `first` and every step-th from there, two
+// in flight.  f: c, or c k_i where there is a factor per row.
+__device__ __forceinline__ void makez_block(const FiraMat& mt, float c, long long row0, int first, int step) {
+  const int lane = threadIdx.x & 63, a8 = (lane & 3) * 8;
+  const long long row = row0 + (lane >> 2);
+  const int kblocks = (mt.r + 31) >> 5;
+  if (row >= mt.L) return;
+  gptr<char> Nb = reinterpret_cast<gptr<char>>(as_global(mt.Nb)) + row0 * 64 + lane * 16;
+  gptr<const char> Rb = reinterpret_cast<gptr<const char>>(as_global<const bf16_raw>(mt.Rb)) + row0 * 64 + lane * 16;
+  const float f = c * as_global<const float>(mt.phi)[row];
+  for (int kb0 = first; kb0 < kblocks; kb0 += 2 * step) {
+    u32x4 nv[2], rv[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (kb0 + step * u < kblocks) {
+        const long long at = (long long)(kb0 + step * u) * mt.Lq * 64;
+        nv[u] = *reinterpret_cast<gptr<const u32x4>>(Nb + at);
+        rv[u] = *reinterpret_cast<gptr<const u32x4>>(Rb + at);
+      }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (kb0 + step * u < kblocks) {
+        const int left = mt.r - 32 * (kb0 + step * u) - a8;      // padding stays zero even for a non-finite factor
+        const unsigned nw[4] = {nv[u].x, nv[u].y, nv[u].z, nv[u].w}, rw[4] = {rv[u].x, rv[u].y, rv[u].z, rv[u].w};
+        unsigned zw[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          const float z0 = __uint_as_float(nw[d] << 16) - f * __uint_as_float(rw[d] << 16);
+          const float z1 = __uint_as_float(nw[d] & 0xffff0000u) - f * __uint_as_float(rw[d] & 0xffff0000u);
+          zw[d] = pack_bf16x2(2 * d < left ? z0 : 0.0f, 2 * d + 1 < left ? z1 : 0.0f);
+        }
+        *reinterpret_cast<gptr<u32x4>>(Nb + (long long)(kb0 + step * u) * mt.Lq * 64) = u32x4{zw[0], zw[1], zw[2], zw[3]};
+      }
+  }
+}
+__device__ __forceinline__ void makez_row_split(const FiraMat& mt, float f, long long row) {
   const int lane = threadIdx.x & 63;
   gptr<bf16_raw> Nb = as_global(mt.Nb);
   gptr<const bf16_raw> Rb = as_global<const bf16_raw>(mt.Rb);
-  if (KX == 1) {
-    // rp is a multiple of 64 and padded entries are zero: whole 16-byte groups
-    for (int a = lane * 8; a < mt.rp; a += 512) {
-      const long long o = kblk_index(mt.Lq, row, a);
-      const u32x4 nv = *reinterpret_cast<gptr<const u32x4>>(Nb + o);
-      const u32x4 rv = *reinterpret_cast<gptr<const u32x4>>(Rb + o);
-      const unsigned nw[4] = {nv.x, nv.y, nv.z, nv.w}, rw[4] = {rv.x, rv.y, rv.z, rv.w};
-      unsigned zw[4];
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        float z0 = __uint_as_float(nw[d] << 16) - f * __uint_as_float(rw[d] << 16);
-        float z1 = __uint_as_float(nw[d] & 0xffff0000u) - f * __uint_as_float(rw[d] & 0xffff0000u);
-        if (a + 2 * d >= mt.r) z0 = 0.0f;       // padding stays zero even for a non-finite factor
-        if (a + 2 * d + 1 >= mt.r) z1 = 0.0f;
-        zw[d] = pack_bf16x2(z0, z1);
-      }
-      *reinterpret_cast<gptr<u32x4>>(Nb + o) = u32x4{zw[0], zw[1], zw[2], zw[3]};
-    }
-  } else {
-    for (int a = lane; a < mt.r; a += 64) {
-      const float z = load_operand<KX>((gptr<const bf16_raw>)Nb, mt.Lq, row, mt.rp, a) -
-                      f * load_operand<KX>(Rb, mt.Lq, row, mt.rp, a);
-      store_operand<KX>(Nb, mt.Lq, row, mt.rp, a, z);
-    }
+  for (int a = lane; a < mt.r; a += 64) {
+    const float z = load_operand<FIRA_KX_SPLIT>((gptr<const bf16_raw>)Nb, mt.Lq, row, mt.rp, a) -
+                    f * load_operand<FIRA_KX_SPLIT>(Rb, mt.Lq, row, mt.rp, a);
+    store_operand<FIRA_KX_SPLIT>(Nb, mt.Lq, row, mt.rp, a, z);
   }
 }
 
@@ -602,8 +618,7 @@ __device__ __forceinline__ void fixz_block(const FiraMat& mt, float n, long long
         if (zsplit) lv[u] = *reinterpret_cast<gptr<const u32x4>>(Nb + (long long)kb * mt.Lq * 64 + plane);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-          const int mine = mt.r - 32 * kb - a8 - 4 * q;
-          rv[u][q] = mine > 0 ? load_row4(R + 32 * kb + 4 * q, mine) : zero;
+          rv[u][q] = 32 * kb + a8 + 4 * q < mt.r ? *reinterpret_cast<gptr<const f32x4>>(R + 32 * kb + 4 * q) : zero;   // r is a multiple of four
         }
       }
     }
@@ -621,9 +636,9 @@ __device__ __forceinline__ void fixz_block(const FiraMat& mt, float n, long long
             z += f32x4{__uint_as_float(l[2 * q] << 16), __uint_as_float(l[2 * q] & 0xffff0000u), __uint_as_float(l[2 * q + 1] << 16),
                        __uint_as_float(l[2 * q + 1] & 0xffff0000u)};
           z += f * rv[u][q];
-          const u32x2 mask = row4_mask(mt.r - 32 * kb - a8 - 4 * q), hi = pack_bf16x4(z);
-          h[q] = hi & mask;
-          lo[q] = split_remainder(z, hi) & mask;
+          if (32 * kb + a8 + 4 * q >= mt.r) z = zero;      // padding stays zero even for a non-finite factor
+          h[q] = pack_bf16x4(z);
+          lo[q] = split_remainder(z, h[q]);
         }
         *reinterpret_cast<gptr<u32x4>>(Nb + (long long)kb * mt.Lq * 64) = u32x4{h[0].x, h[0].y, h[1].x, h[1].y};
         if (zsplit) *reinterpret_cast<gptr<u32x4>>(Nb + (long long)kb * mt.Lq * 64 + plane) = u32x4{lo[0].x, lo[0].y, lo[1].x, lo[1].y};
@@ -687,6 +702,38 @@ __device__ __forceinline__ void fixz_block_from_moments(const FiraMat& mt, const
   }
 }
 
+// The same for ranks that are no multiple of four (rounds_n_and_r): Z = N - c k R formed again from the updated M and V and from R, both rounded
+// to bf16 first.  By one wavefront, K blocks `first` and every step-th from there (see fixz_block).
+__device__ __forceinline__ void fixz_block_rounded(const FiraMat& mt, const FiraHp& hp, float c, float bias, long long row0, int first, int step) {
+  const int lane = threadIdx.x & 63, a8 = (lane & 3) * 8;
+  const long long row = row0 + (lane >> 2);
+  const int kblocks = (mt.r + 31) >> 5;
+  if (row >= mt.L) return;
+  gptr<char> Nb = reinterpret_cast<gptr<char>>(as_global(mt.Nb)) + row0 * 64 + lane * 16;
+  gptr<const float> M = as_global<const float>(mt.M) + row * mt.r + a8, V = as_global<const float>(mt.V) + row * mt.r + a8;
+  gptr<const float> R = as_global<const float>(mt.Rt) + row * mt.r + a8;
+  const float f = c * as_global<const float>(mt.phi)[row];
+  for (int kb = first; kb < kblocks; kb += step) {
+    f32x4 mv[2], vv[2], rv[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int at = 32 * kb + 4 * q, mine = max(mt.r - a8 - at, 0);
+      mv[q] = load_row4(M + at, mine);
+      vv[q] = load_row4(V + at, mine);
+      rv[q] = load_row4(R + at, mine);
+    }
+    u32x2 h[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      f32x4 n;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) n[e] = adam_direction(mv[q][e], vv[q][e], bias, hp.epsf);
+      h[q] = pack_bf16x4(bf16_rounded(n) - f * bf16_rounded(rv[q])) & row4_mask(mt.r - a8 - 32 * kb - 4 * q);
+    }
+    *reinterpret_cast<gptr<u32x4>>(Nb + (long long)kb * mt.Lq * 64) = u32x4{h[0].x, h[0].y, h[1].x, h[1].y};
+  }
+}
+
 // fp32 rows that hold Z for c = 1: Z = N - c k R formed again from the updated M and V and from R.
 __device__ __forceinline__ void fixz_row_split(const FiraMat& mt, const FiraHp& hp, float f, float bias, long long row) {
   const int lane = threadIdx.x & 63;
@@ -710,33 +757,34 @@ __device__ __forceinline__ void fixz_row_split(const FiraMat& mt, const FiraHp& 
 static_assert(FIRA_ZREADY_MAX_R_F32 == 512, "fira_adam_kernel's forms end there");
 #define FIRA_MAKEZ_PARTS 32   // workgroups per listed matrix
 // A matrix's Z for a limiter factor of c, by one of FIRA_MAKEZ_PARTS workgroups, which takes every FIRA_MAKEZ_PARTS-th block of 16 rows.
-// t: the step count with this step in it; fused_here: the fused kernel served the matrix and left no copy of R.
-__device__ __forceinline__ void make_z(const FiraMat& mt, const FiraHp& hp, int part, float c, int t, bool fused_here) {
-  const bool zready = mt.zready && hp.scaling != 1;
-  if (zready && c == 1.0f) return;             // the Adam kernel already wrote Z for c = 1
+// t: the step count with this step in it; c_prev: the factor of the step before; fused_here: the fused kernel served the matrix and left no copy of R.
+__device__ __forceinline__ void make_z(const FiraMat& mt, const FiraHp& hp, int part, float c, float c_prev, int t, bool fused_here) {
+  const bool ready = mt.zready && hp.scaling != 1 && !leaves_n_and_r(mt, c_prev);
+  if (ready && c == 1.0f) return;              // the Adam kernel already wrote Z for c = 1
   const int wave = threadIdx.x >> 6;
   const int rowblocks = (mt.L + FIRA_ROWS_PER_WG - 1) / FIRA_ROWS_PER_WG;
-  const float bias = fused_here || mt.kx != 1 ? bias_correction(hp, t) : 0.0f;
-  if (zready && mt.kx == 1 && !fused_here) {
-    // a row of one or two K blocks: each wavefront has sixteen rows of its own
-    const bool small = mt.r <= FIRA_PS;
-    for (int rb = small ? 4 * part + wave : part; rb < rowblocks; rb += (small ? 4 : 1) * FIRA_MAKEZ_PARTS)
-      fixz_block(mt, 1.0f - c, (long long)rb * FIRA_ROWS_PER_WG, small ? 0 : wave, small ? 1 : 4, hp.zsplit != 0);
+  const float bias = ready && (fused_here || mt.kx != 1 || rounds_n_and_r(mt)) ? bias_correction(hp, t) : 0.0f;
+  if (mt.kx == 1) {
+    // where a row is one or two K blocks, each wavefront has sixteen rows of its own
+    const bool own = mt.r <= FIRA_PS;
+    const int first = own ? 0 : wave, step = own ? 1 : 4;
+    for (int rb = own ? 4 * part + wave : part; rb < rowblocks; rb += (own ? 4 : 1) * FIRA_MAKEZ_PARTS) {
+      const long long row0 = (long long)rb * FIRA_ROWS_PER_WG;
+      if (!ready) makez_block(mt, c, row0, first, step);
+      else if (fused_here) fixz_block_from_moments(mt, hp, c, bias, row0);
+      else if (rounds_n_and_r(mt)) fixz_block_rounded(mt, hp, c, bias, row0, first, step);
+      else fixz_block(mt, 1.0f - c, row0, first, step, two_planes(hp, mt));
+    }
     return;
   }
   for (int rb = part; rb < rowblocks; rb += FIRA_MAKEZ_PARTS) {
-    if (zready && fused_here) {
-      fixz_block_from_moments(mt, hp, c, bias, (long long)rb * FIRA_ROWS_PER_WG);
-      continue;
-    }
     const long long row_base = (long long)rb * FIRA_ROWS_PER_WG + wave * 4;
     for (int i = 0; i < 4; ++i) {
       const long long row = row_base + i;
       if (row >= mt.L) break;
       const float k = as_global<const float>(mt.phi)[row];
-      if (zready && mt.kx != 1) fixz_row_split(mt, hp, c * k, bias, row);
-      else if (mt.kx == 1) makez_row<1>(mt, c * k, row);
-      else makez_row<FIRA_KX_SPLIT>(mt, c * k, row);
+      if (ready) fixz_row_split(mt, hp, c * k, bias, row);
+      else makez_row_split(mt, c * k, row);
     }
   }
 }
@@ -746,7 +794,7 @@ __global__ __launch_bounds__(256) void fira_makez_kernel(const FiraMat* __restri
                                                          const FiraEnt* __restrict__ ents, FiraHp hp) {
   const FiraEnt ent = ents[blockIdx.x / FIRA_MAKEZ_PARTS];
   const FiraMat mt = mats[ent.mat];
-  make_z(mt, hp, blockIdx.x % FIRA_MAKEZ_PARTS, scal[ent.mat].c, scal[ent.mat].t, scal[ent.mat].gram_now == 2);
+  make_z(mt, hp, blockIdx.x % FIRA_MAKEZ_PARTS, scal[ent.mat].c, scal[ent.mat].c_in, scal[ent.mat].t, scal[ent.mat].gram_now == 2);
 }
 // The limiter and Z in one launch, for factors per row or none: every workgroup works the factor out for itself, from the values that the kernel
 // with Adam set aside (set_limiter_inputs), and the first one of a matrix advances its state.  Two launches in turn are two latencies, and
@@ -774,7 +822,7 @@ __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limit_and_makez_ker
   limiter_sums(mt, ent, partial, gram, calibrate, red, acc, accg);
   const double sn = sqrt(acc), c = limiter_factor(hp, sn, in.has_prev, in.s_prev);
   if (part == 0 && threadIdx.x == 0) limiter_advance(scal[ent.mat], gate[ent.mat], hp, gram, calibrate, acc, accg, sn, c, in.t);
-  make_z(mt, hp, part, (float)c, in.t + 1, gram && hp.fused);
+  make_z(mt, hp, part, (float)c, scal[ent.mat].c_in, in.t + 1, gram && hp.fused);
 }
 
 // ------------------------------------------------------------------------------------------------

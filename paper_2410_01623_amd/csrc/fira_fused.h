@@ -442,7 +442,8 @@ __device__ __forceinline__ void small_adam_rows(const f32x16_t (&acc)[2], float*
   const int lane = threadIdx.x & 63, a = 4 * (lane % LPR), lrow = lane / LPR, r = mt.r;
   constexpr int ROWS = 64 / LPR, PASSES = 32 / ROWS;
   const bool matrix = hp.scaling == 1;              // one factor per matrix: the limiter kernel forms it from the rows' sums
-  const bool operand_r = matrix || !use_gram(hp, sc), two_planes = hp.zsplit && !matrix;
+  const bool leave = matrix || leaves_n_and_r(mt, sc.c), operand_r = leave || !use_gram(hp, sc);
+  const bool planes = two_planes(hp, mt), rounded = rounds_n_and_r(mt);
   const int mine = min(max(r - a, 0), 4);           // this lane's values of a row
   const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
   auto load4 = [&](gptr<char> base, unsigned off) { return load_row4(reinterpret_cast<gptr<const float>>(base + off), mine); };
@@ -510,13 +511,14 @@ __device__ __forceinline__ void small_adam_rows(const f32x16_t (&acc)[2], float*
       const float root = sqrtf((lane & 1) ? srr : snn), other = lane_xor<1>(root);
       const float k = hp.scaling == 2 ? 1.0f : ((lane & 1) ? other : root) / (((lane & 1) ? root : other) + hp.epsf);
       if (a == 0) *reinterpret_cast<float2*>(here + p * ROWS * FIRA_PROJ_SMALL_PITCH + 64) = float2{matrix ? snn : k, srr};
-      const f32x4 z = matrix ? m[p] : m[p] - k * x[p];
+      f32x4 z = m[p];
+      if (!leave) z = rounded ? bf16_rounded(m[p]) - k * bf16_rounded(x[p]) : m[p] - k * x[p];
       const bool live = left > ROWS * p;
       // rows past L are zero; the rows of a K block follow each other, 64 bytes each (a second block that is all padding holds the zeros
       // it was initialised with)
       const u32x2 h = pack_bf16x4(z), mask = live ? keep : u32x2{0u, 0u};
       *reinterpret_cast<gptr<u32x2>>(Nb + (op + p * ROWS * 64)) = h & mask;
-      if (two_planes) *reinterpret_cast<gptr<u32x2>>(Nb + (op + p * ROWS * 64 + plane)) = split_remainder(z, h) & mask;
+      if (planes) *reinterpret_cast<gptr<u32x2>>(Nb + (op + p * ROWS * 64 + plane)) = split_remainder(z, h) & mask;
       if (operand_r) *reinterpret_cast<gptr<u32x2>>(Rb + (op + p * ROWS * 64)) = pack_bf16x4(x[p]);
     }
     off += 2 * step;

@@ -1534,7 +1534,7 @@ __global__ __launch_bounds__(FIRA_BACK_THREADS, TM == 4 ? 2 : sizeof(T) == 4 ? 3
   g.b_row0 = tile.tb * FIRA_BB + 64 * TN * (sub >> 1);
   g.b_rows = mt.m;
   // Z in two planes (hi + lo): the contraction runs over 2 rp, and the projector's K blocks are used twice
-  const bool split = MODE == 1 && hp.zsplit && mt.zready && mt.kx == 1 && hp.scaling != 1;
+  const bool split = MODE == 1 && two_planes(hp, mt);
   g.KA = g.KB = split ? 2 * mt.rp : (mt.r + 31) / 32 * 32;   // (fp32 matrices: split_mainloop counts for itself)
   g.wrapA = (split && !mt.left) ? mt.rp / FIRA_RK : 0;
   g.wrapB = (split && mt.left) ? mt.rp / FIRA_RK : 0;
