@@ -290,6 +290,10 @@ def main():
     limited = sum(1 for i in range(len(shapes)) if ctx.fira_get_diag(i)[2] < 1.0)   # limiter active in the last step
 
     model = kernel_models(shapes, wl.rank, args.norm_mode)
+    if not fused and wl.rank <= 64 and wl.dtype == "bf16":   # one kernel did their work, and left R in memory
+        ms_sum = dict([("project_adam", ms_sum["project"] + ms_sum["adam_norms"])] +
+                      [(k, v) for k, v in ms_sum.items() if k not in ("project", "adam_norms")])
+        model["project_adam"]["bytes"] += 4 * sum(max(m, n) * wl.rank for m, n in shapes)
     traffic = read_traffic(name, args.norm_mode)
     kernels = {}
     for k, tot in ms_sum.items():
