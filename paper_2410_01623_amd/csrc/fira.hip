@@ -359,9 +359,10 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(1)));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(2)));
   FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_stage_all, p.slot_bytes * kSlots, hipHostMallocDefault));
-  FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_gate, sizeof(FiraGate) * count, hipHostMallocDefault));
+  // (kernels write it and the host waits for an event only: coherent and released to the system whatever HIP_HOST_COHERENT says)
+  FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_gate, sizeof(FiraGate) * count, hipHostMallocCoherent | hipHostMallocMapped));
   for (int i = 0; i < count; ++i) ctx->h_gate[i] = FiraGate{INFINITY, INFINITY};
-  FIRA_INIT_HIP(hipEventCreateWithFlags(&ctx->ortho_event, hipEventDisableTiming));
+  FIRA_INIT_HIP(hipEventCreateWithFlags(&ctx->ortho_event, hipEventDisableTiming | hipEventReleaseToSystem));
   FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_install, sizeof(FiraRefreshEnt) * count, hipHostMallocDefault));
   FIRA_INIT_HIP(hipEventCreateWithFlags(&ctx->install_event, hipEventDisableTiming));
   {

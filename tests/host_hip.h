@@ -1,8 +1,10 @@
 // A stand-in for the HIP runtime below the library's host code (csrc/fira.hip, included by the programs before this file): device
 // memory is host memory, copies happen at once, kernels do nothing, everything that would be enqueued is counted, the stream
-// is "captured" while `capturing` is set, and every launch is handed to `on_launch`.
+// is "captured" while `capturing` is set, every launch is handed to `on_launch`, and the flags that events and host memory are made
+// with are kept.
 #pragma once
 #include <cstdlib>
+#include <map>
 
 namespace {
 bool capturing = false;
@@ -14,6 +16,7 @@ int failures = 0;
     if (!(cond)) { ++failures; std::printf("FAIL line %d: %s\n", __LINE__, #cond); }      \
   } while (0)
 alignas(256) char static_area[256];
+std::map<const void*, unsigned> made_with;      // flags of an event or of host memory
 }  // namespace
 
 extern "C" {
@@ -24,8 +27,12 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
 hipError_t hipStreamSynchronize(hipStream_t) { return capturing ? hipErrorStreamCaptureUnsupported : hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { *e = nullptr; return hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; return hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned flags) {
+  *e = (hipEvent_t)std::malloc(1);
+  made_with[*e] = flags;
+  return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t e) { std::free((void*)e); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { ++enqueued; return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.0f; return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
@@ -33,7 +40,11 @@ hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "stand-in"; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void*) { *p = static_area; return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) {
+  *p = std::malloc(n);
+  made_with[*p] = flags;
+  return *p ? hipSuccess : hipErrorOutOfMemory;
+}
 hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t) {
   ++enqueued;
