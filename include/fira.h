@@ -119,7 +119,8 @@ FIRA_API fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, 
 /* Install the projector of matrix idx (Eq. 7; built by the caller, e.g. every T steps).
  * dev_P: min(m,n) x r row-major, dtype p_dtype; it is copied/converted into the slab, so the
  * caller may free it after the stream has run the call.  For bf16 matrices an fp32 P is rounded
- * to bf16 (nearest even).  M, V, t and ||S_prev|| are kept (Sec. 4.2, loss-spike analysis). */
+ * to bf16 (nearest even).  M, V, t and ||S_prev|| are kept (Sec. 4.2, loss-spike analysis).  A launch failure
+ * (FIRA_ERR_HIP) leaves the matrix without a projector. */
 FIRA_API fira_status fira_set_projector(fira_ctx* ctx, int idx, const void* dev_P, fira_dtype p_dtype);
 
 /* fira_set_projector for `count` distinct matrices idx[0..count) at once (Eq. 7: a training loop

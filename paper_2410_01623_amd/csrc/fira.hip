@@ -200,6 +200,23 @@ fira_status gates_on_their_way(fira_ctx* ctx) {
   return FIRA_OK;
 }
 
+// Gates of matrices that an installation is about to be launched for (before its kernels, which write them, can run).
+void forget_gates(fira_ctx* ctx, int count, const int* idx) {
+  for (int e = 0; e < count; ++e) ctx->h_gate[idx[e]] = FiraGate{INFINITY, INFINITY};
+}
+
+// The end of an installation whose launches ended with `launched`.  If anything failed, the listed matrices' operand copies may be half
+// written, and the host would not know the gates that the device goes by: they have no projector then.
+fira_status finish_installation(fira_ctx* ctx, int count, const int* idx, hipError_t launched, const char* what) {
+  const fira_status st = launched != hipSuccess ? fail(ctx, FIRA_ERR_HIP, std::string(what) + ": " + hipGetErrorString(launched)) : gates_on_their_way(ctx);
+  if (st != FIRA_OK) forget_gates(ctx, count, idx);
+  for (int e = 0; e < count; ++e) {
+    ctx->plan.mats[idx[e]].has_projector = st == FIRA_OK;
+    if (st == FIRA_OK) ctx->unmeasured[idx[e]] = 1;
+  }
+  return st;
+}
+
 // The projection of the listed fp32 matrices over the tile lists tl (left) and tr.
 void launch_fp32_project(hipStream_t q, const ListSlot* s, const FiraMat* mats, const FiraTile* tl, int nl, const FiraTile* tr, int nr, int norm_mode, int pack) {
   const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
@@ -442,7 +459,7 @@ fira_status fira_set_projector(fira_ctx* ctx, int idx, const void* dev_P, fira_d
   if (p_dtype != FIRA_F32 && p_dtype != FIRA_BF16) return fail(ctx, FIRA_ERR_DTYPE, "p_dtype must be FIRA_F32 or FIRA_BF16");
   HostMat& h = ctx->plan.mats[idx];
   const int grid = prep_tiles(h.dev.S, h.dev.r);
-  ctx->h_gate[idx] = FiraGate{INFINITY, INFINITY};   // (before the kernel that writes it can run)
+  forget_gates(ctx, 1, &idx);
   if (p_dtype == FIRA_F32)
     hipLaunchKernelGGL(fira_prep_projector_kernel<float>, dim3(grid), dim3(256), 0, ctx->stream, h.dev, (const float*)dev_P);
   else
@@ -453,10 +470,7 @@ fira_status fira_set_projector(fira_ctx* ctx, int idx, const void* dev_P, fira_d
   float* zbuf = reinterpret_cast<float*>(ctx->slab + ctx->plan.off_ortho + ctx->plan.ortho_z);
   hipLaunchKernelGGL(fira_ortho_z_kernel, dim3(FIRA_ORTHO_SPLITS), dim3(256), 0, ctx->stream, h.dev, (const float*)ybuf, zbuf);
   hipLaunchKernelGGL(fira_ortho_final_kernel, dim3(1), dim3(256), 0, ctx->stream, h.dev, (const float*)zbuf, ctx->d_scal, ctx->h_gate, idx);
-  FIRA_HIP(ctx, hipGetLastError());
-  h.has_projector = true;
-  ctx->unmeasured[idx] = 1;
-  return gates_on_their_way(ctx);
+  return finish_installation(ctx, 1, &idx, hipGetLastError(), "projector installation");
 }
 
 fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* idx, const void* const* dev_P, fira_dtype p_dtype) {
@@ -480,7 +494,6 @@ fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* idx, const 
     ctx->install_pending = false;
   }
   char* scratch = ctx->slab + ctx->plan.off_ortho;
-  for (int e = 0; e < count; ++e) ctx->h_gate[idx[e]] = FiraGate{INFINITY, INFINITY};   // (before the kernels that write them can run)
   for (int e = 0; e < count; ++e) {
     const FiraMat& m = ctx->plan.mats[idx[e]].dev;
     FiraRefreshEnt& re = ctx->h_install[e];
@@ -494,6 +507,7 @@ fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* idx, const 
   FIRA_HIP(ctx, hipMemcpyAsync(d_table, ctx->h_install, sizeof(FiraRefreshEnt) * count, hipMemcpyHostToDevice, q));
   FIRA_HIP(ctx, hipEventRecord(ctx->install_event, q));
   ctx->install_pending = true;
+  forget_gates(ctx, count, idx);
   // one launch per phase for kInstallBatch matrices at a time (they share the scratch pieces, in stream order)
   for (int e0 = 0; e0 < count; e0 += kInstallBatch) {
     const int nb = std::min(kInstallBatch, count - e0);
@@ -508,21 +522,7 @@ fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* idx, const 
     hipLaunchKernelGGL(fira_refresh_ortho_z_kernel, dim3(FIRA_ORTHO_SPLITS, nb), dim3(256), 0, q, ctx->d_mats, d_table + e0);
     hipLaunchKernelGGL(fira_refresh_ortho_final_kernel, dim3(nb), dim3(256), 0, q, ctx->d_mats, d_table + e0, ctx->d_scal, ctx->h_gate);
   }
-  {
-    const hipError_t e_ = hipGetLastError();
-    if (e_ != hipSuccess) {   // some of the listed matrices' operand copies may be half written
-      for (int e = 0; e < count; ++e) {
-        ctx->plan.mats[idx[e]].has_projector = false;
-        ctx->h_gate[idx[e]] = FiraGate{INFINITY, INFINITY};
-      }
-      return fail(ctx, FIRA_ERR_HIP, std::string("projector installation: ") + hipGetErrorString(e_));
-    }
-  }
-  for (int e = 0; e < count; ++e) {
-    ctx->plan.mats[idx[e]].has_projector = true;
-    ctx->unmeasured[idx[e]] = 1;
-  }
-  return gates_on_their_way(ctx);
+  return finish_installation(ctx, count, idx, hipGetLastError(), "projector installation");
 }
 
 fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev_W, const void* const* dev_G) {
@@ -1081,34 +1081,19 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     hipLaunchKernelGGL(fira_refresh_check_kernel, dim3(nt128 * (nt128 + 1) / 2, count), dim3(256), 0, q, d_ents2);
   }
   orthonormalise(d_ents2);
-  // The rounds above worked in the listed matrices' operand copies of P.  If anything failed to launch, what
-  // they hold now is not a projector: mark the matrices as having none rather than leave a half-made basis
-  // behind the old gate values.
-  auto invalidate = [&]() {
-    for (int e = 0; e < count; ++e) {
-      ctx->plan.mats[idx[e]].has_projector = false;
-      ctx->h_gate[idx[e]] = FiraGate{INFINITY, INFINITY};
-    }
-  };
+  // The rounds above worked in the listed matrices' operand copies of P: from here on a failure leaves them without a projector rather
+  // than with a half-made basis behind the old gate values.
   {
     const hipError_t e_ = hipGetLastError();
-    if (e_ != hipSuccess) { invalidate(); return fail(ctx, FIRA_ERR_HIP, std::string("projector refresh: ") + hipGetErrorString(e_)); }
+    if (e_ != hipSuccess) return finish_installation(ctx, count, idx, e_, "projector refresh");
   }
   // install the result (what fira_set_projector does per matrix, here one launch per phase for the whole list)
-  for (int e = 0; e < count; ++e) ctx->h_gate[idx[e]] = FiraGate{INFINITY, INFINITY};   // (before the kernel that writes them can run)
+  forget_gates(ctx, count, idx);
   hipLaunchKernelGGL(fira_refresh_prep_kernel, dim3(prep_blocks, count), dim3(256), 0, q, ctx->d_mats, d_ents2);
   hipLaunchKernelGGL(fira_refresh_ortho_y_kernel, dim3((max_S + 3) / 4, count), dim3(256), 0, q, ctx->d_mats, d_ents2);
   hipLaunchKernelGGL(fira_refresh_ortho_z_kernel, dim3(FIRA_ORTHO_SPLITS, count), dim3(256), 0, q, ctx->d_mats, d_ents2);
   hipLaunchKernelGGL(fira_refresh_ortho_final_kernel, dim3(count), dim3(256), 0, q, ctx->d_mats, d_ents2, ctx->d_scal, ctx->h_gate);
-  {
-    const hipError_t e_ = hipGetLastError();
-    if (e_ != hipSuccess) { invalidate(); return fail(ctx, FIRA_ERR_HIP, std::string("projector refresh: ") + hipGetErrorString(e_)); }
-  }
-  for (int e = 0; e < count; ++e) {
-    ctx->plan.mats[idx[e]].has_projector = true;
-    ctx->unmeasured[idx[e]] = 1;
-  }
-  return gates_on_their_way(ctx);
+  return finish_installation(ctx, count, idx, hipGetLastError(), "projector refresh");
 }
 
 }  // namespace
