@@ -182,7 +182,8 @@ FIRA_API fira_status fira_set_variant(fira_ctx* ctx, fira_variant variant);
  * installed) run them as two kernels with R in memory in the same step.  Any other step, and every
  * step with enable == 0, runs two kernels for all (bf16 matrices with r <= 64: one, which leaves R in memory as two do).
  * Lists of 64 < r < 128 run fused as well where they are long enough for it to pay, but have R written to memory besides and
- * count as two kernels here and in fira_get_gate.  Both compute the same quantities; sums are taken in
+ * count as two kernels here and in fira_get_gate: with the same sums in the same order, so that a matrix gets the same bits
+ * whatever is listed with it.  From r = 128 on both compute the same quantities with sums taken in
  * a different order, so results agree to rounding, not bit for bit.  fira_last_step_fused: 1 if the
  * last fira_step on ctx took the fused kernel for every listed matrix, 0 if not (or ctx is NULL).  A
  * fused step keeps no copy of R: fira_get_lowrank then returns what an earlier two-kernel step left

@@ -68,7 +68,7 @@ constexpr int kQuarterTiles = 1536, kQuarterTilesLongRank = 384;
 // Listed matrices up to which the limiter and Z are one launch (fira_limit_and_makez_kernel has both sides measured).
 constexpr int kLimitAndZ = 64;
 // Tiles of a list from which on the fused projection/Adam kernel serves ranks that leave R in memory (fira_step has both sides).
-constexpr int kFuseMinTiles = 100;
+constexpr int kFuseMinTiles = 200;
 
 struct ListSlot {
   std::vector<int> idx;
@@ -603,10 +603,11 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   // The fused projection/Adam kernel serves the listed matrices on the Gram route if each of them can take
   // it; those on the residual route then go through the two-kernel path in the same step (hp.mixed).  Either all of them leave
   // R in memory, as small ranks do whatever the path, or none does.  Two kernels and the fused one, a step of 8 blocks of 512 x 1376, 24 of
-  // 1024 x 2736 and 24 of 2048 x 5461: r = 68 105 and 83, 761 and 626, 2524 and 2277; r = 96 106 and 83, 776 and 648, 2556 and 2316;
-  // r = 124 105 and 86, 790 and 687, 2597 and 2403.  Where there are few tiles, a workgroup's passes over its factors one after the
-  // other take longer than a second launch that deals them out (r = 96, by tiles: 32.5 and 35.8 (26), 37.6 and 38.7 (52), 47.0 and 48.8 (49),
-  // 46.2 and 45.7 (78), 59.4 and 59.2 (98), 48.2 and 47.5 (104), 67.2 and 61.7 (147), 104 and 96 (196)).
+  // 1024 x 2736 and 24 of 2048 x 5461: r = 68 87.7 and 79.6, 677 and 620, 2333 and 2236; r = 96 88.6 and 80.5, 693 and 642, 2362 and 2281;
+  // r = 124 92.8 and 84.4, 732 and 685, 2458 and 2355.  Where there are few tiles, a workgroup's passes over its factors one after the
+  // other take longer than a second launch that deals them out (r = 96, by tiles: 25.8 and 32.6 (26), 35.5 and 42.2 (49), 49.3 and 53.5 (98),
+  // 57.4 and 58.3 (147), 167.5 and 165.9 (193), 91.1 and 92.2 (196), 68.8 and 66.5 (245), 110.5 and 106.2 (294); at r = 68 and 124 the
+  // fused kernel takes 1.02 and 1.00 of the two at 196 tiles, 0.96 and 0.95 at 245).
   bool fused = ctx->fusion && !ctx->zsplit && !only_scaling && ctx->scaling == FIRA_SCALE_COLUMN && ctx->norm_mode == FIRA_NORM_GRAM && any_gram;
   bool keep_r = false, drop_r = false, any_fused = false;
   for (int e = 0; e < count && fused; ++e) {

@@ -300,25 +300,43 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
   }
 }
 
-// Small ranks (r <= 64) of fp32 matrices: a factor's row is at most 256 bytes, so
-// a wavefront takes its four rows at once, 16 lanes per row, instead of one after the other.
-template <int KX>
-__device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp& hp, float bias, long long row_base,
-                                                 bool gram, bf16_raw* zl, int wave) {
+// Sum of the squares of a row of up to 128 values, four to a lane of a half wave and zeros past the end, in the order in which the fused
+// projection/Adam kernel takes it: columns 32 apart (lanes 8 apart) in one lane, then by 16, 8 and 4 (lanes), 2 and 1 (a lane's four), then the
+// halves of 64.  At every step across lanes but the last ones each lane goes on with half of its values.
+__device__ __forceinline__ float square_sum_as_fused(const f32x4& x) {
+  const bool upper = (threadIdx.x & 8) != 0, odd = (threadIdx.x & 4) != 0;
+  float s[2];                                   // of values e, or 2 + e in the upper lanes
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const float keep = upper ? x[2 + e] : x[e], got = lane_xor<8>(upper ? x[e] : x[2 + e]);
+    const float lo = upper ? got : keep, hi = upper ? keep : got;
+    s[e] = __builtin_fmaf(lo, lo, hi * hi);
+  }
+  const float t = add_xor<1>(add_xor<2>((odd ? s[1] : s[0]) + lane_xor<4>(odd ? s[0] : s[1])));
+  return add_xor<16>(add_xor<4>(add_xor<8>(t)));
+}
+
+// Rows of few values: LPR lanes to a row, so that a wavefront takes 64 / LPR rows at once.  16 for fp32 matrices with r <= 64; 32 for bf16 ones with
+// 64 < r < FIRA_FUSE_DROP_R, r a multiple of four, whose lists take the fused kernel or this one by their length: what a matrix
+// gets must not depend on what else is listed, so the two norms are summed as that kernel sums them.
+template <int KX, int LPR>   // 4 LPR >= r
+__device__ __forceinline__ void adam_rows_short(const FiraMat& mt, const FiraHp& hp, float bias, long long row_base,
+                                                bool gram, bf16_raw* zl, bf16_raw* rl, int rowlocal) {
   const int lane = threadIdx.x & 63;
-  const int g = lane >> 4, a = (lane & 15) * 4;
+  const int g = lane / LPR, a = (lane % LPR) * 4;
   const int r = mt.r;
   const long long row = row_base + g;
   const bool live = row < mt.L && a < r;
+  const int mine = KX == 1 ? 4 : r - a;
   gptr<const float> R = as_global<const float>(mt.Rt) + row * r;
   gptr<float> M = as_global(mt.M) + row * r;
   gptr<float> V = as_global(mt.V) + row * r;
   f32x4 nv = f32x4{0.f, 0.f, 0.f, 0.f}, rv = nv;
   float nn = 0.0f, rr = 0.0f;
   if (live) {
-    rv = load_row4(R + a, r - a);
-    f32x4 mv = load_row4(M + a, r - a);
-    f32x4 vv = load_row4(V + a, r - a);
+    rv = load_row4(R + a, mine);
+    f32x4 mv = load_row4(M + a, mine);
+    f32x4 vv = load_row4(V + a, mine);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       mv[e] = hp.b1 * mv[e] + hp.omb1 * rv[e];
@@ -327,11 +345,16 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
       nn += nv[e] * nv[e];
       rr += rv[e] * rv[e];
     }
-    store_row4(M + a, mv, r - a);
-    store_row4(V + a, vv, r - a);
+    store_row4(M + a, mv, mine);
+    store_row4(V + a, vv, mine);
   }
-  nn = row_sum<16>(nn);
-  rr = row_sum<16>(rr);
+  if constexpr (KX == 1) {
+    nn = square_sum_as_fused(nv);
+    rr = square_sum_as_fused(rv);
+  } else {
+    nn = row_sum<16>(nn);
+    rr = row_sum<16>(rr);
+  }
   const float k = (hp.scaling == 2) ? 1.0f : sqrtf(nn) / (sqrtf(rr) + hp.epsf);
   if (a < mt.rp) {
     const int planes = z_planes<KX>(hp, mt);
@@ -339,10 +362,10 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
     zp[0] = zp[1] = zp[2] = u32x2{0u, 0u};   // rows beyond L and columns beyond r: the operand's zero padding
     if (live) {
       bf16_planes<KX>(nv - k * rv, planes, zp);
-      const u32x2 mask = row4_mask(r - a);
+      const u32x2 mask = row4_mask(mine);
 #pragma unroll
       for (int p = 0; p < 3; ++p) zp[p] &= mask;
-      if (!gram) {
+      if (!gram && !rl) {
         u32x2 rb[3];
         bf16_planes<KX>(rv, KX == 1 ? 1 : 3, rb);
 #pragma unroll
@@ -350,12 +373,13 @@ __device__ __forceinline__ void adam_rows4_small(const FiraMat& mt, const FiraHp
           *reinterpret_cast<gptr<u32x2>>(as_global(mt.Rb) + kblk_index(mt.Lq, row, p * mt.rp + a)) = rb[p];
       }
     }
-    bf16_raw* dst = zl + (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + g) * 32 + (a & 31);
+    const int at = (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (rowlocal + g) * 32 + (a & 31);
 #pragma unroll
     for (int p = 0; p < (KX == 1 ? 2 : 3); ++p)
-      if (p < planes) *reinterpret_cast<u32x2*>(dst + p * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32)) = zp[p];
+      if (p < planes) *reinterpret_cast<u32x2*>(zl + at + p * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32)) = zp[p];
+    if (KX == 1 && rl) *reinterpret_cast<u32x2*>(rl + at) = live ? pack_bf16x4(rv) : u32x2{0u, 0u};
   }
-  if ((lane & 15) == 0 && row < mt.L) {
+  if (a == 0 && row < mt.L) {
     as_global(mt.phi)[row] = k;
     if (have_g2(hp)) as_global(mt.q)[row] = k * k * residual_sq(hp, as_global<const float>(mt.g2)[row], rr);
   }
@@ -396,8 +420,9 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const bool leave = leaves_n_and_r(mt, sc.c);
   const bool staged = STAGE_R && zready && !gram && mt.r > 64 && mt.r <= FIRA_RSTAGE_MAX_R;
   bf16_raw* rl = staged ? zl + planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32) : nullptr;
-  if (KX != 1 && zready && mt.r <= 64) {
-    adam_rows4_small<KX>(mt, hp, bias, row_base, gram, zl, wave);
+  constexpr int LPR = KX == 1 ? 32 : 16;
+  if (zready && (KX == 1 ? mt.r < FIRA_FUSE_DROP_R && (mt.r & 3) == 0 : mt.r <= 64)) {
+    for (int i = 0; i < 4; i += 64 / LPR) adam_rows_short<KX, LPR>(mt, hp, bias, row_base + i, gram, zl, rl, wave * 4 + i);
   } else if (zready) {
     auto rows = [&](auto nit, auto odd) __attribute__((always_inline)) {
       for (int i = 0; i < 4; ++i) {

@@ -186,8 +186,13 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
         landM[idx] = m1;
         landV[idx] = v1;
         nv[tn][v] = n;
-        nn[v] += n * n;
-        rr[v] += x * x;
+        if (TM == 2 && !INTERIOR) {      // (r < 128 among them: spelled out, for square_sum_as_fused to take the same sums)
+          nn[v] = tn == 0 ? n : __builtin_fmaf(nn[v], nn[v], n * n);
+          rr[v] = tn == 0 ? x : __builtin_fmaf(rr[v], rr[v], x * x);
+        } else {
+          nn[v] += n * n;
+          rr[v] += x * x;
+        }
       }
     }
     {

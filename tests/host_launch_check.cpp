@@ -57,6 +57,15 @@ int main() {
     c.step({0, 2});
     CHECK(times(quarter) == 0 && times(whole) == 1);
   }
+  {   // ranks whose R stays in memory: the fused kernel from 200 tiles of 128 factors on, two kernels below and beside ranks whose R does not
+    Case c({desc(128, 128 * 199, 96, FIRA_BF16), desc(128, 128 * 200, 96, FIRA_BF16), desc(200, 128, 68, FIRA_BF16), desc(160, 256, 160, FIRA_BF16),
+            desc(300, 200, 40, FIRA_BF16), desc(128, 128 * 200, 97, FIRA_BF16)});
+    struct { std::vector<int> idx; int fused; } lists[] = {{{0}, 0}, {{1}, 1}, {{0, 2}, 1}, {{4, 1}, 1}, {{1, 3}, 0}, {{3}, 1}, {{3, 4}, 0}, {{1, 5}, 0}};
+    for (auto& l : lists) {
+      c.step(l.idx);
+      CHECK(times(fira_project_adam_kernel<1>) == l.fused && times(fira_adam_kernel<1, false>) == 1 - l.fused);
+    }
+  }
   {   // fp32 projection: whole panels where all of the list's run at once, tiles otherwise and for wider matrices
     Case c({desc(128, 256, 64, FIRA_F32), desc(2, 64 * 2600, 1, FIRA_F32), desc(417, 500, 64, FIRA_F32)});
     c.step({0});

@@ -11,7 +11,7 @@ import fira_harness as H
 
 pytestmark = pytest.mark.gpu
 
-FILL = 100      # tiles of 128 factors from which on a list takes the fused kernel at these ranks
+FILL = 200      # tiles of 128 factors from which on a list takes the fused kernel at these ranks
 
 
 def run(shapes, ranks, dtype, seed, check, **kw):
@@ -43,7 +43,7 @@ def test_fused_kernel_leaves_r_behind(m, n, r):
     assert max(res.w_err) <= 2e-2 and res.c_min < 1.0
     assert res.worst["R"] <= 1e-5 and res.worst["M"] <= 1e-5 and res.worst["V"] <= 1e-5 and res.worst["k"] <= 1e-4
     assert res.worst["s_pre"] <= 2e-3 and res.worst["c"] <= 2e-3      # a bf16 P's orthonormality defect
-    # the same list in two kernels: other sums of the norms, the same R
+    # the same list in two kernels: the same R
     two = run(shapes, [r] * count + [40], fira.FIRA_BF16, m + n, [0, count], norm_mode=fira.FIRA_NORM_GRAM, fusion=False)
     assert np.array_equal(res.ctx.fira_get_lowrank(0).numpy(), two.ctx.fira_get_lowrank(0).numpy())
 
@@ -66,3 +66,18 @@ def test_fp32_rows_of_any_length(m, n, r, norm):
     assert max(res.w_err) <= 1e-4 and res.c_min < 1.0
     assert res.worst["R"] <= 1e-5 and res.worst["M"] <= 1e-5 and res.worst["V"] <= 1e-5 and res.worst["k"] <= 1e-4
     assert res.worst["s_pre"] <= 1e-3 and res.worst["c"] <= 1e-3
+
+
+@pytest.mark.parametrize("m,n,r", [(130, 1700, 68), (1665, 129, 124), (161, 1600, 96), (200, 1537, 100), (1540, 300, 72), (128, 1664, 112)])
+def test_what_else_is_listed_does_not_show(m, n, r):
+    """The same matrix in a list long enough for the fused kernel, in the same list in two kernels, and by itself: sums in one order, so the same
+    bits in everything that a step leaves."""
+    count = -(-FILL // -(-max(m, n) // 128))
+    left = []
+    for shapes, kw in [([(m, n)] * count, {}), ([(m, n)] * count, dict(fusion=False)), ([(m, n)], {})]:
+        ctx, W = (lambda res: (res.ctx, res.W_dev[0]))(run(shapes, [r] * len(shapes), fira.FIRA_BF16, m + n, [0], norm_mode=fira.FIRA_NORM_GRAM, **kw))
+        M, V, s_prev, _ = ctx.fira_get_state(0)
+        left.append(dict(W=H.to_host(W), M=M.numpy(), V=V.numpy(), R=ctx.fira_get_lowrank(0).numpy(), k=ctx.fira_get_factors(0).numpy(),
+                         s=np.array([s_prev, *ctx.fira_get_diag(0)])))
+    for other in left[1:]:
+        assert {name: int(np.sum(left[0][name] != other[name])) for name in left[0]} == {name: 0 for name in left[0]}
