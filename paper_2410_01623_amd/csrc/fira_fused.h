@@ -285,10 +285,12 @@ __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& m
   g.lda = mt.ld;
   g.KA = mt.S;
   const int t = scal[ent.mat].t + 1;             // 1-based
-  float bias;
+  // RT = 2 has no register to spare while loads are in flight (one value went to memory and back there)
+  float bias = RT == 2 ? bias_correction(hp, t) : 0.0f;
   auto prologue = [&] {
+    if (RT == 2) return;
     bias = bias_correction(hp, t);
-    if (RT == 1) asm volatile("" : "+v"(bias));    // (here, not where it is used; RT = 2 has no register to spare)
+    asm volatile("" : "+v"(bias));                 // (here, not where it is used)
   };
   f32x16_t acc[TM][2];
   float sq[TM];
