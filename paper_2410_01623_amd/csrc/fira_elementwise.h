@@ -95,9 +95,8 @@ __device__ __forceinline__ void store_operand(gptr<bf16_raw> op, int rows, long 
     op[kblk_index(rows, row, 2 * rp + a)] = l;
   }
 }
-template <int KX>
-__device__ __forceinline__ float load_operand(gptr<const bf16_raw> op, int rows, long long row, int rp, int a) {
-  if (KX == 1) return bf16_to_f32(op[kblk_index(rows, row, a)]);
+// Such an element of a fp32 matrix.
+__device__ __forceinline__ float load_split_operand(gptr<const bf16_raw> op, int rows, long long row, int rp, int a) {
   return (bf16_to_f32(op[kblk_index(rows, row, a)]) + bf16_to_f32(op[kblk_index(rows, row, rp + a)])) +
          bf16_to_f32(op[kblk_index(rows, row, 2 * rp + a)]);
 }
@@ -418,7 +417,7 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const long long row_base = (long long)(rb - ent.row0) * FIRA_ROWS_PER_WG + wave * 4;
   const int planes = z_planes<KX>(hp, mt);
   const bool leave = leaves_n_and_r(mt, sc.c);
-  const bool staged = STAGE_R && zready && !gram && mt.r > 64 && mt.r <= FIRA_RSTAGE_MAX_R;
+  const bool staged = STAGE_R && zready && !gram && mt.r <= FIRA_RSTAGE_MAX_R;
   bf16_raw* rl = staged ? zl + planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32) : nullptr;
   constexpr int LPR = KX == 1 ? 32 : 16;
   if (zready && (KX == 1 ? mt.r < FIRA_FUSE_DROP_R && (mt.r & 3) == 0 : mt.r <= 64)) {
@@ -612,8 +611,7 @@ __device__ __forceinline__ void makez_row_split(const FiraMat& mt, float f, long
   gptr<bf16_raw> Nb = as_global(mt.Nb);
   gptr<const bf16_raw> Rb = as_global<const bf16_raw>(mt.Rb);
   for (int a = lane; a < mt.r; a += 64) {
-    const float z = load_operand<FIRA_KX_SPLIT>((gptr<const bf16_raw>)Nb, mt.Lq, row, mt.rp, a) -
-                    f * load_operand<FIRA_KX_SPLIT>(Rb, mt.Lq, row, mt.rp, a);
+    const float z = load_split_operand((gptr<const bf16_raw>)Nb, mt.Lq, row, mt.rp, a) - f * load_split_operand(Rb, mt.Lq, row, mt.rp, a);
     store_operand<FIRA_KX_SPLIT>(Nb, mt.Lq, row, mt.rp, a, z);
   }
 }

@@ -87,8 +87,9 @@ bool make_plan(const fira_matrix_desc* d, int count, Plan* plan, fira_status* st
     h.small_proj = m.kx == 1 && m.r <= FIRA_PS;
     m.zready = m.r <= (m.kx == 1 ? FIRA_ZREADY_MAX_R : FIRA_ZREADY_MAX_R_F32) ? 1 : 0;
     if (m.zready && m.kx != 1) plan->adam_lds_f32 = std::max(plan->adam_lds_f32, FIRA_ROWS_PER_WG * m.rp * 6);
-    if (m.zready && m.kx == 1) plan->adam_lds = std::max(plan->adam_lds, FIRA_ROWS_PER_WG * m.rp * 2);   // (twice that with Z in two planes)
-    if (m.zready && m.kx == 1 && m.r <= FIRA_RSTAGE_MAX_R) plan->adam_lds_staged = std::max(plan->adam_lds_staged, FIRA_ROWS_PER_WG * m.rp * 2);
+    const bool in_adam = m.zready && m.kx == 1 && !h.small_proj;
+    if (in_adam) plan->adam_lds = std::max(plan->adam_lds, FIRA_ROWS_PER_WG * m.rp * 2);   // (twice that with Z in two planes)
+    if (in_adam && m.r <= FIRA_RSTAGE_MAX_R) plan->adam_lds_staged = std::max(plan->adam_lds_staged, FIRA_ROWS_PER_WG * m.rp * 2);
     const size_t Lr = (size_t)m.L * m.r;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     m.M = (float*)take(Lr * 4);
