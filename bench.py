@@ -283,16 +283,16 @@ def main():
         dt = time.perf_counter() - t0
     ms_sum, rec = ctx.fira_profile_end()
     fused = ctx.fira_last_step_fused()
-    if fused:   # one kernel did the work of the first two slots
+    # one kernel did the work of the first two slots: its time is in the first, and the second holds what lies between two events (5 us)
+    merged = fused or (wl.dtype == "bf16" and ms_sum["adam_norms"] < 7e-3 * rec)
+    if merged:
         ms_sum = dict([("project_adam", ms_sum["project"] + ms_sum["adam_norms"])] +
                       [(k, v) for k, v in ms_sum.items() if k not in ("project", "adam_norms")])
     finite = all(bool(torch.isfinite(w).all()) for w in W[:7])
     limited = sum(1 for i in range(len(shapes)) if ctx.fira_get_diag(i)[2] < 1.0)   # limiter active in the last step
 
     model = kernel_models(shapes, wl.rank, args.norm_mode)
-    if not fused and wl.rank <= 64 and wl.dtype == "bf16":   # one kernel did their work, and left R in memory
-        ms_sum = dict([("project_adam", ms_sum["project"] + ms_sum["adam_norms"])] +
-                      [(k, v) for k, v in ms_sum.items() if k not in ("project", "adam_norms")])
+    if merged and not fused:   # (ranks below 128: it left R in memory)
         model["project_adam"]["bytes"] += 4 * sum(max(m, n) * wl.rank for m, n in shapes)
     traffic = read_traffic(name, args.norm_mode)
     kernels = {}

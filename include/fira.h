@@ -127,8 +127,8 @@ FIRA_API fira_status fira_set_projector(fira_ctx* ctx, int idx, const void* dev_
  * installs every matrix's projector at the same step, every T steps): dev_P[i] is the projector of
  * matrix idx[i], all of dtype p_dtype; idx and dev_P are host arrays of length count.  The same
  * copies, the same estimate behind the Gram route's first gate and the same result as `count` single
- * calls, bit for bit, in one launch per phase for every 16 matrices and one read-back of the gate values
- * instead of four launches and a copy per matrix.  A call may wait on the host for the previous call's
+ * calls, bit for bit, in one launch per phase for every 16 matrices instead of four launches per matrix
+ * (the kernels write the gate values to pinned host memory themselves).  A call may wait on the host for the previous call's
  * table of pointers to have reached the device.  Errors found on the host (a bad index, a matrix
  * listed twice, a null pointer, an unknown dtype) leave every projector as it was; a launch failure
  * (FIRA_ERR_HIP) leaves the listed matrices without a projector (fira_step then reports
@@ -151,7 +151,7 @@ FIRA_API fira_status fira_set_projectors(fira_ctx* ctx, int count, const int* id
  * fira_set_options, fira_set_variant, fira_set_fusion, and fira_set_projector(s) or
  * fira_refresh_projectors calls (which may change a matrix's route) do not reach it, and it must be
  * captured again after any of them.  Capture only from the second step after a projector was
- * installed on: in the FIRA_NORM_GRAM mode the first one measures the Gram route's gate and reads it back, and
+ * installed on: in the FIRA_NORM_GRAM mode the first one measures the Gram route's gate, for the next one to go by, and
  * is refused while the stream is being captured (FIRA_ERR_HIP, nothing enqueued).  While a captured
  * step may still be replayed, do not step more than three other distinct (idx, W, G) lists on the
  * same context: the fifth distinct list reuses the oldest slot and would rewrite the captured one's
@@ -289,7 +289,13 @@ FIRA_API fira_status fira_refresh_projectors_static(fira_ctx* ctx, int count, co
  * and one after each kernel.  fira_profile_end synchronises, adds up the elapsed time of each of
  * the FIRA_NUM_KERNELS kernels over the recorded steps into ms_sum[0..FIRA_NUM_KERNELS) (host
  * array, milliseconds), stores the number of recorded steps in *steps, and destroys the events.
- * Kernel order: fira_kernel_name(k). */
+ * Kernel order: fira_kernel_name(k).  Where one launch does the work of two slots, the first of them holds its
+ * time and the second one nothing but what lies between two event records (about five microseconds):
+ *   project + adam_norms  steps that run fused for every listed matrix (fira_last_step_fused, or 64 < r < 128 in
+ *                         a long list), and lists of bf16 matrices with r <= 64; where only some of the listed
+ *                         matrices do, project holds both of theirs and the others' projection
+ *   limiter + make_z      lists of up to 64 matrices with a factor per row or none
+ * The slots together cover the step in every case. */
 #define FIRA_NUM_KERNELS 6
 FIRA_API fira_status fira_profile_begin(fira_ctx* ctx, int max_steps);
 FIRA_API fira_status fira_profile_end(fira_ctx* ctx, double* ms_sum, int* steps);

@@ -129,7 +129,7 @@ struct fira_ctx {
   hipEvent_t refresh_event = nullptr;
   bool refresh_pending = false;
   // Matrices whose projector was installed after the last step that could measure their second gate value: that value
-  // is +inf, which is all a step has to know to take the residual route for them, so it need not wait for the read-back.
+  // is +inf, which is all a step has to know to take the residual route for them, so it need not wait for the gate values.
   std::vector<char> unmeasured;
   uint64_t use_counter = 0;
   int device = -1;               // HIP device that was current at fira_init_state
@@ -540,7 +540,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       if (!ctx->plan.mats[idx[e]].has_projector) return fail(ctx, FIRA_ERR_NO_PROJECTOR, "fira_set_projector was never called for a listed matrix");
     }
   }
-  // Listed matrices whose second gate value this step will measure and read back (FiraScal::gram_err is +inf).
+  // Listed matrices whose second gate value this step will measure (FiraScal::gram_err is +inf).
   const bool only_scaling = ctx->variant == FIRA_VARIANT_ONLY_SCALING;
   bool any_unmeasured = false, all_unmeasured = true;
   for (int e = 0; e < count; ++e) {
@@ -587,7 +587,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   if (need_residual && ctx->norm_mode == FIRA_NORM_GRAM && all_unmeasured) {
     measures = true;            // (whatever the first gate value will turn out to be)
   } else if (need_residual && ctx->norm_mode == FIRA_NORM_GRAM) {
-    if (ctx->ortho_pending) {   // gate values are on their way back (a projector was installed, or a step measured one)
+    if (ctx->ortho_pending) {   // kernels that write gate values are on their way (a projector was installed, or a step measured one)
       FIRA_HIP(ctx, hipEventSynchronize(ctx->ortho_event));
       ctx->ortho_pending = false;
     }

@@ -318,6 +318,8 @@ __device__ __forceinline__ float square_sum_as_fused(const f32x4& x) {
 // Rows of few values: LPR lanes to a row, so that a wavefront takes 64 / LPR rows at once.  16 for fp32 matrices with r <= 64; 32 for bf16 ones with
 // 64 < r < FIRA_FUSE_DROP_R, r a multiple of four, whose lists take the fused kernel or this one by their length: what a matrix
 // gets must not depend on what else is listed, so the two norms are summed as that kernel sums them.
+// Bound by instructions in short lists and by memory in long ones.  A row at a time, half the lanes idle, and two at a time, a step at r = 96 of one block of
+// 256 x 688 28.9 and 26.4 us, two of 512 x 1376 53.3 and 49.7, 24 of 1024 x 2736 on the residual route 903 and 854 and in two planes 802 and 743.
 template <int KX, int LPR>   // 4 LPR >= r
 __device__ __forceinline__ void adam_rows_short(const FiraMat& mt, const FiraHp& hp, float bias, long long row_base,
                                                 bool gram, bf16_raw* zl, bf16_raw* rl, int rowlocal) {
@@ -569,10 +571,11 @@ __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limiter_kernel(cons
 
 // ------------------------------------------------------------------------------------------------
 // Back-projection operand: Z_i = N_i - c k_i R_i, so that P N + c k (G - P R) = P Z + c k G.
-// Overwrites N in place.  Matrices flagged zready skip this unless their limiter factor is below 1.
+// Overwrites N in place.  Matrices flagged zready hold Z for c = 1 already and skip this unless their limiter factor is below 1,
+// but for those whose N and R were left as they are (leaves_n_and_r).
 // ------------------------------------------------------------------------------------------------
 // bf16 matrices: a wavefront takes sixteen rows, whose part of a K block is 1 KB of either operand, K blocks `first` and every step-th from there, two
-// in flight.  f: c, or c k_i where there is a factor per row.
+// in flight.  c: the limiter's factor; k_i is read from phi (one value in all rows where there is a factor per matrix).
 __device__ __forceinline__ void makez_block(const FiraMat& mt, float c, long long row0, int first, int step) {
   const int lane = threadIdx.x & 63, a8 = (lane & 3) * 8;
   const long long row = row0 + (lane >> 2);
@@ -821,9 +824,12 @@ __global__ __launch_bounds__(256) void fira_makez_kernel(const FiraMat* __restri
 }
 // The limiter and Z in one launch, for factors per row or none: every workgroup works the factor out for itself, from the values that the kernel
 // with Adam set aside (set_limiter_inputs), and the first one of a matrix advances its state.  Two launches in turn are two latencies, and
-// the second nearly always only reads c = 1: a step of 256 x 688 in fp32 30.4 and 28.2 us, 8 blocks of 512 x 1376 at r = 128 90.6 and 87.4 (56
-// matrices), limited 87.1 and 83.8.  With more workgroups than run at once the sums cost more than the launch: 168 matrices of the 350M shapes on
-// the residual route, limited, 1388 and 1398; lists that long keep two.
+// the second nearly always only reads c = 1.  What the repeated sums cost depends on how many workgroups there are, FIRA_MAKEZ_PARTS a matrix:
+// up to 64 matrices all of them run at once, eight a CU, and beyond that the sums cost more than the launch.  Two launches and one, by matrices (21,
+// 63, 84 and 168), a step of 256 x 688 at r = 64 29.8 and 28.2, 39.3 and 38.9, 45.8 and 46.1, 64.8 and 69.0 us; of 512 x 1376 at r = 128 61.5 and
+// 59.9, 92.2 and 92.2, 113.5 and 114.9, 213 and 218, residual 76.1 and 74.1, 130.9 and 130.2, 168.1 and 169.3, 333 and 337; of 1024 x 2736 at
+// r = 256, 63 matrices and 112, 351.5 and 351.6, 593.7 and 598.0, limited 352.8 and 352.6, 602.7 and 606.3; of 256 x 688 in fp32 47.2 and 45.2 (21),
+// 84.5 and 83.8 (63), 119.6 and 121.5 (112).
 __global__ __launch_bounds__(FIRA_LIMITER_THREADS) void fira_limit_and_makez_kernel(const FiraMat* __restrict__ mats, FiraScal* __restrict__ scal,
                                                                                     const FiraEnt* __restrict__ ents, const float* __restrict__ partial,
                                                                                     FiraGate* __restrict__ gate, FiraHp hp) {

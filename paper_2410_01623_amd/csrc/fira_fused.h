@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_project_adam_k
 // Projection and Adam for small ranks (r <= 64, the fine-tuning setting's r = 32), bf16 matrices on every route and with any
 // rank.  The tile is 128 (gradient side) x 64 (rank): with a 256-wide rank tile three quarters or more of the multiplies
 // would work on padding.  Wave w owns gradient rows 32 w .. 32 w + 31 and all 64 rank columns (two accumulator
-// blocks), so the kernel needs few registers and 28 KB of LDS, several workgroups share a CU, and the
+// blocks), so the kernel needs few registers and 34 KB of LDS (Adam's rows; the multiplies take 28), four workgroups share a CU, and the
 // gradient stream is what bounds it.  Same pipeline as proj_pipeline (single gradient tile, E and O halves);
 // a ring stage is 64 rows x 32 k = 4 KB, one request instruction per wavefront, so the E-half wait is
 // vmcnt(1) and the O-half wait vmcnt(5) (one ring request and the four of A(S+1) are younger).
@@ -371,7 +371,8 @@ __global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_project_adam_k
 // (the projection alone 1745, Adam 334, this kernel 1958); 350M shapes at r = 16, 32 and 64 602, 612, 644 and 525, 540, 590, on the residual
 // route at r = 32 790 and 701; 8 blocks of 512 x 512 and 512 x 1376 at r = 64 87 and 74; one block of 256 x 256 and 256 x 688
 // 26.8 and 24.4 at r = 16, 26.0 and 26.1 at r = 64.  Ranks that are no multiple of four, whose N and R went out as operands
-// for a pass of their own to form Z from: 350M shapes at r = 50 791 and 577, the 1B shapes 2595 and 2165.
+// for a pass of their own to form Z from: 350M shapes at r = 50 791 and 577, the 1B shapes 2595 and 2165.  (The four workgroups' 128
+// registers leave five values of an edge tile in memory during its multiplies, outside the loop over K.)
 // ------------------------------------------------------------------------------------------------
 #define FIRA_PROJ_SMALL_STAGE (FIRA_PS * 64)
 #define FIRA_PROJ_SMALL_PITCH 68   // floats of a factor's row in LDS: 16-byte alignment, banks shifted from row to row
