@@ -322,7 +322,7 @@ __device__ __forceinline__ float square_sum_as_fused(const f32x4& x) {
 // 256 x 688 28.9 and 26.4 us, two of 512 x 1376 53.3 and 49.7, 24 of 1024 x 2736 on the residual route 903 and 854 and in two planes 802 and 743.
 template <int KX, int LPR>   // 4 LPR >= r
 __device__ __forceinline__ void adam_rows_short(const FiraMat& mt, const FiraHp& hp, float bias, long long row_base,
-                                                bool gram, bf16_raw* zl, bf16_raw* rl, int rowlocal) {
+                                                bool gram, bf16_raw* zl, bf16_raw* rl, int wave, int i) {
   const int lane = threadIdx.x & 63;
   const int g = lane / LPR, a = (lane % LPR) * 4;
   const int r = mt.r;
@@ -374,7 +374,7 @@ __device__ __forceinline__ void adam_rows_short(const FiraMat& mt, const FiraHp&
           *reinterpret_cast<gptr<u32x2>>(as_global(mt.Rb) + kblk_index(mt.Lq, row, p * mt.rp + a)) = rb[p];
       }
     }
-    const int at = (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (rowlocal + g) * 32 + (a & 31);
+    const int at = (a >> 5) * (FIRA_ROWS_PER_WG * 32) + (wave * 4 + i + g) * 32 + (a & 31);
 #pragma unroll
     for (int p = 0; p < (KX == 1 ? 2 : 3); ++p)
       if (p < planes) *reinterpret_cast<u32x2*>(zl + at + p * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32)) = zp[p];
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   bf16_raw* rl = staged ? zl + planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32) : nullptr;
   constexpr int LPR = KX == 1 ? 32 : 16;
   if (zready && (KX == 1 ? mt.r < FIRA_FUSE_DROP_R && (mt.r & 3) == 0 : mt.r <= 64)) {
-    for (int i = 0; i < 4; i += 64 / LPR) adam_rows_short<KX, LPR>(mt, hp, bias, row_base + i, gram, zl, rl, wave * 4 + i);
+    for (int i = 0; i < 4; i += 64 / LPR) adam_rows_short<KX, LPR>(mt, hp, bias, row_base + i, gram, zl, rl, wave, i);
   } else if (zready) {
     auto rows = [&](auto nit, auto odd) __attribute__((always_inline)) {
       for (int i = 0; i < 4; ++i) {
