@@ -369,7 +369,7 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<1, bf16_raw>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<0, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_backproject_kernel<1, float>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_BACK_LDS));
-  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_chol_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_CHOL_PAN_ROWS * (FIRA_CHOL_NB + 1) * 8));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_chol_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_CHOL_ROWS * FIRA_CHOL_PITCH * 8));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_refresh_chol_small_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_CHOL_SMALL_LDS));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
@@ -1044,8 +1044,8 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     if (max_r <= FIRA_CHOL_SMALL_R) {
       hipLaunchKernelGGL(fira_refresh_chol_small_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), FIRA_CHOL_SMALL_LDS, q, de);
     } else {
-      const int pan_rows = std::min(FIRA_CHOL_PAN_ROWS, std::max(max_r - FIRA_CHOL_NB, 0));
-      hipLaunchKernelGGL(fira_refresh_chol_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), (size_t)pan_rows * (FIRA_CHOL_NB + 1) * 8, q, de, pan_rows);
+      const int rows = std::min(FIRA_CHOL_ROWS, round_up_int(max_r, FIRA_CHOL_NB));
+      hipLaunchKernelGGL(fira_refresh_chol_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), (size_t)rows * FIRA_CHOL_PITCH * 8, q, de);
       const int nj = (max_r + FIRA_SOLVE_JB - 1) / FIRA_SOLVE_JB;
       hipLaunchKernelGGL(fira_refresh_diaginv_kernel, dim3(nj, count), dim3(256), 0, q, de);
     }

@@ -98,6 +98,23 @@ __device__ __forceinline__ f32x4 refresh_load4(gptr<const float> A, int row, int
   return f32x4{p[0], col + 1 < cols ? p[1] : 0.f, col + 2 < cols ? p[2] : 0.f, col + 3 < cols ? p[3] : 0.f};
 }
 
+// Place of element (row, col), col <= row, of the Gram matrix and its factor.  Above the ranks of fira_refresh_chol_small_kernel they are kept as 32 x 32
+// tiles, block row after block row of the lower triangle (r^2 / 2 + 16 r doubles of the r^2 there are).  A quarter of a tile, 16 x 16, holds its
+// columns two by two, those with (column % 4) / 2 = 0 first: the 16 rows x 8 columns that one instruction reads as an operand of the factorisation are
+// 1 KB of contiguous memory in lane order (fira_refresh_chol_kernel over 168 matrices of r = 512: 667 us; 920 with a tile's rows one after the
+// other, of which sixteen bytes each make an operand's instruction, and the same with rows of r).
+#define FIRA_CHOL_SMALL_R 128
+__device__ __forceinline__ bool chol_tiled(int r) { return r > FIRA_CHOL_SMALL_R; }
+__device__ __forceinline__ unsigned chol_row(int r, int row) {      // element (row, 0)
+  const unsigned i = (unsigned)row, b = i >> 5;
+  return chol_tiled(r) ? (b * (b + 1) / 2) * 1024u + ((i >> 4) & 1u) * 512u + (i & 15u) * 2u : i * (unsigned)r;
+}
+__device__ __forceinline__ unsigned chol_col(int r, int col) {      // ... from there to (row, col)
+  const unsigned k = (unsigned)col;
+  return chol_tiled(r) ? (k >> 5) * 1024u + ((k >> 4) & 1u) * 256u + ((k >> 1) & 1u) * 128u + ((k >> 2) & 3u) * 32u + (k & 1u) : k;
+}
+__device__ __forceinline__ unsigned chol_at(int r, int row, int col) { return chol_row(r, row) + chol_col(r, col); }
+
 // The second orthonormalisation pass asks of the basis it is given whether max |Y^T Y - I| is within done_tol, and for
 // bf16 matrices (1e-4) three bf16 plane products h h + h m + m h answer that: a matrix whose products come out within
 // refresh_check_tolerance, done_tol less all that they can be off by, is within done_tol, so it needs no fp64 Gram matrix; any
@@ -258,7 +275,7 @@ __global__ __launch_bounds__(256, 5) void fira_refresh_gram_kernel(const FiraRef
   refresh_acc_foreach(acc, [&](int row, int col, double v) {
     const int ra_ = ta * 64 + row, cb = tb * 64 + col;
     if (ra_ < e.r && cb < e.r && cb <= ra_) {
-      C[(long long)ra_ * e.r + cb] = v;
+      C[chol_at(e.r, ra_, cb)] = v;
       off = off || !(fabs(v - (ra_ == cb ? 1.0 : 0.0)) <= (double)e.done_tol);   // (true for a NaN)
     }
   });
@@ -270,20 +287,23 @@ __global__ __launch_bounds__(256, 5) void fira_refresh_gram_kernel(const FiraRef
 // (FIRA_PASS_NEEDED counts against the pass: unset until a tile of the Gram matrix shows that the basis is not orthonormal yet)
 __device__ __forceinline__ bool refresh_pass_done(const FiraRefreshEnt& e) { return e.done && !(*as_global<const int>(e.done) & FIRA_PASS_NEEDED); }
 
-// In-place Cholesky factorisation of the lower triangle of C (fp64), one workgroup per matrix, blocked by 32
-// columns: factor the diagonal block, solve the panel below it one row per thread, update the trailing triangle from
-// the panel.  A pivot that is not safely positive is replaced by a small multiple of the largest diagonal entry.  That
+// In-place Cholesky factorisation of the lower triangle of C (fp64), one workgroup per matrix, 32 columns (a panel) at a time, each panel brought
+// up to date with all the columns before it when its turn comes (left-looking: the triangle is read, never rewritten).  A pivot that is not
+// safely positive is replaced by a small multiple of the largest diagonal entry.  That
 // carries a Y that is deficient by rounding, not one whose gradient has a numerical rank below r: the rounding left of
 // the missing directions, divided by such pivots, grows from panel to panel and can end in a basis of NaNs.
 //
-// What bounds it is the chain of dependent steps of one panel, not its arithmetic, so both triangular parts work in
-// registers: the diagonal block with one row per lane and the column's entries handed round by lane reads, the panel
-// with one row per thread and independent multiply-adds per column; the triangle's old values are requested before
-// the products that are taken off them.  168 matrices of r = 512: 870 us; 56 of r = 128: 88 us (1890 and 255 us
-// while both parts went through LDS element by element and the largest diagonal entry was looked for by one thread).
+// What bounds it is the chain of dependent steps of one panel, not its arithmetic.  chol_eliminate therefore does the diagonal block and the rows
+// below it in one pass: every wavefront repeats the block's elimination in its lanes 0 .. 31 and carries 32 rows of the panel along in the
+// others, whose multiply-adds are the same instructions (and 64 more in a second set of registers where there are many rows; the lane
+// reads, two for each multiply-add, are shared).  Rows of the identity carried along become the block's inverse, which the solve needs.
+// A column is scaled by 1 / pivot as it is eliminated, and by the square roots when all are known, side by side.
+// 168 matrices of r = 512, the inverses of the diagonal blocks included: 690 us, of which 150 are the elimination's chains and 420 the updates, whose
+// multiplies alone take 200; 930 with the panel solved after its block by one row per thread and a trailing triangle rewritten for every panel.
 #define FIRA_CHOL_THREADS 512
 #define FIRA_CHOL_NB 32
-#define FIRA_CHOL_PAN_ROWS 544   // panel rows kept in LDS: 544 x 33 doubles = 140 KB (every panel of a matrix with r <= 576)
+#define FIRA_CHOL_ROWS 512        // rows of a panel that are in LDS at a time, the diagonal block's among them
+#define FIRA_CHOL_PITCH (FIRA_CHOL_NB + 1)
 
 // sqrt(x) and 1 / sqrt(x) for a normal x > 0: two rounds of Goldschmidt's coupled iteration from the hardware's estimate
 // and a last Newton correction of each (within one ulp), a third of the instructions of a square root and a division.
@@ -301,339 +321,366 @@ __device__ __forceinline__ void sqrt_and_inverse(double x, double& root, double&
   inv = fma(inv, fma(-inv, root, 1.0), inv);
 }
 
-// Factor of a 32 x 32 diagonal block by one wavefront, lane i its row i (d[k], k <= i; lanes 32 .. 63 repeat them): pivot(j, 1 / L_jj) is
-// called by lane j.
-template <typename Pivot>
-__device__ __forceinline__ void chol_diagonal(double (&d)[FIRA_CHOL_NB], double floor_piv, Pivot pivot) {
-  const int lane = threadIdx.x & 63, row = lane & (FIRA_CHOL_NB - 1);
+// Lane i < 32: row i of a 32 x 32 diagonal block (d[k], k <= i; what stands above is never handed on), lanes 32 .. 63 and x, where EXTRA,
+// a row each of what lies below it.  Afterwards the block's factor D, and X D^T = what was there.
+// (Lane reads in groups of eight: one right before the multiply-add that takes it costs twice as much, 22 cycles against 14.  The next pivot's
+// reciprocal is formed beside a column's later groups.)
+template <bool EXTRA>
+__device__ __forceinline__ void chol_eliminate(double (&d)[FIRA_CHOL_NB], double (&x)[EXTRA ? FIRA_CHOL_NB : 1], double floor_piv) {
+  constexpr int NB = FIRA_CHOL_NB, GROUP = 8;
+  const int lane = threadIdx.x & 63;
+  double own = 1.0;                        // lane j: pivot j
+  double piv, inv;
+  auto pivot = [&](int j) {
+    piv = fmax(lane_value(d[j], j), floor_piv);
+    inv = __builtin_amdgcn_rcp(piv);
+    inv = fma(inv, fma(-piv, inv, 1.0), inv);
+    inv = fma(inv, fma(-piv, inv, 1.0), inv);
+  };
+  pivot(0);
 #pragma unroll
-  for (int j = 0; j < FIRA_CHOL_NB; ++j) {
-    double piv, inv;
-    sqrt_and_inverse(fmax(lane_value(d[j], j), floor_piv), piv, inv);
-    const double lj = d[j] * inv;          // (rows above j hold what nobody reads)
-    d[j] = row == j ? piv : lj;
-    if (lane == j) pivot(j, inv);
+  for (int j = 0; j < NB; ++j) {
+    const double t = -d[j] * inv;          // (rows above j hold what nobody reads)
+    double tx = 0.0;
+    if (EXTRA) tx = -x[j] * inv;
+    const double p = piv;
 #pragma unroll
-    for (int k = j + 1; k < FIRA_CHOL_NB; ++k) d[k] = fma(-lj, lane_value(lj, k), d[k]);
+    for (int k0 = j + 1; k0 < NB; k0 += GROUP) {
+      double b[GROUP];
+#pragma unroll
+      for (int k = k0; k < NB && k < k0 + GROUP; ++k) b[k - k0] = lane_value(d[j], k);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = k0; k < NB && k < k0 + GROUP; ++k) {
+        d[k] = fma(t, b[k - k0], d[k]);
+        if (EXTRA) x[k] = fma(tx, b[k - k0], x[k]);
+      }
+      if (k0 == j + 1) pivot(j + 1);
+    }
+    d[j] = lane == j ? p : d[j];
+    own = lane == j ? p : own;
     __builtin_amdgcn_sched_barrier(0);     // (else the lane reads of many columns are gathered, and spill)
   }
-}
-// One row of the panel below it, x D^T = x: DT holds the factor by columns, rinv the reciprocals of its diagonal.
-__device__ __forceinline__ void chol_panel_row(double (&x)[FIRA_CHOL_NB], const double* DT, const double* rinv) {
+  double root, scale;
+  sqrt_and_inverse(own, root, scale);
 #pragma unroll
-  for (int k = 0; k < FIRA_CHOL_NB; ++k) {
-    int col = k * (FIRA_CHOL_NB + 2);      // known only when x[k] is: the factor is read column by column (gathered at the top, it spills)
-    asm volatile("" : "+s"(col) : "v"(x[k]));
-    x[k] *= rinv[k];
+  for (int j0 = 0; j0 < NB; j0 += GROUP) {
+    double b[GROUP];
 #pragma unroll
-    for (int j = k + 1; j < FIRA_CHOL_NB; ++j) x[j] = fma(-x[k], DT[col + j], x[j]);
+    for (int j = 0; j < GROUP; ++j) b[j] = lane_value(scale, j0 + j);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < GROUP; ++j) {
+      d[j0 + j] *= b[j];
+      if (EXTRA) x[j0 + j] *= b[j];
+    }
   }
 }
 
-__global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(const FiraRefreshEnt* __restrict__ ents, int pan_rows) {
-  constexpr int NB = FIRA_CHOL_NB, PP = NB + 1, DP = NB + 2;
-  __shared__ __attribute__((aligned(16))) double DT[NB * DP];   // the diagonal block's factor, by columns: L[i][k] at k * DP + i
-  __shared__ double rinv_s[NB];
-  __shared__ double dmax_s[FIRA_CHOL_THREADS / 64];
-  // the panel below the diagonal block, [rows][PP], while it fits (pan_rows rows of dynamic LDS):
-  // the panel solve and the trailing update then read it from LDS instead of walking through memory
-  extern __shared__ __attribute__((aligned(16))) double chol_pan[];
-  const FiraRefreshEnt e = ents[blockIdx.x];
-  if (refresh_pass_done(e)) return;
-  const int r = e.r, t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  gptr<double> C = as_global(e.C);
-  {
-    double mx = 0.0;
-    for (int i = t; i < r; i += FIRA_CHOL_THREADS) mx = fmax(mx, C[(long long)i * r + i]);
+// Floor of the pivots: from the largest diagonal entry that a thread has seen.  red: a value per wavefront.
+__device__ __forceinline__ double chol_floor(double mx, double* red) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-    if (lane == 0) dmax_s[wave] = mx;
-  }
+  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
   __syncthreads();
   double dmax = 0.0;
 #pragma unroll
-  for (int w = 0; w < FIRA_CHOL_THREADS / 64; ++w) dmax = fmax(dmax, dmax_s[w]);
-  const double floor_piv = dmax * 1e-24 + 1e-300;
-  for (int jb = 0; jb < r; jb += NB) {
-    const int nb = min(NB, r - jb);
-    // (1) diagonal block -> LDS -> registers of the first wavefront (lane i: row i; identity past the end)
-    for (int x = t; x < NB * NB; x += FIRA_CHOL_THREADS) {
-      const int i = x / NB, k = x % NB;
-      DT[k * DP + i] = (i < nb && k <= i) ? C[(long long)(jb + i) * r + jb + k] : (i == k ? 1.0 : 0.0);
-    }
-    __syncthreads();
-    if (wave == 0) {
-      const int row = lane & (NB - 1);
-      double d[NB];
+  for (int w = 0; w < FIRA_CHOL_THREADS / 64; ++w) dmax = fmax(dmax, red[w]);
+  return dmax * 1e-24 + 1e-300;
+}
+
+// acc[i][j] += the products of four k of 16 rows and 16 columns.
+template <int RB, int CB>
+__device__ __forceinline__ void chol_products(f64x4_t (&acc)[RB][CB], const double (&a)[RB], const double (&b)[CB]) {
 #pragma unroll
-      for (int k = 0; k < NB; ++k) d[k] = DT[k * DP + row];
-      chol_diagonal(d, floor_piv, [&](int j, double inv) { rinv_s[j] = inv; });
-      if (lane < NB) {
+  for (int i = 0; i < RB; ++i)
 #pragma unroll
-        for (int k = 0; k < NB; ++k) DT[k * DP + row] = k <= row ? d[k] : 0.0;
+    for (int j = 0; j < CB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+}
+// Puts f(row, col, value) in the place of each value that this lane holds.
+template <int RB, int CB, typename F>
+__device__ __forceinline__ void chol_foreach(f64x4_t (&acc)[RB][CB], F f) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int j = 0; j < CB; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[i][j][v] = f(16 * i + (lane >> 4) + 4 * v, 16 * j + (lane & 15), acc[i][j][v]);
+}
+
+// Rows row0 .. row0 + 16 RB - 1 of the panel of columns jb .. jb + 31, C - L[rows][<jb] L[jb ..][<jb]^T, into LDS; row x of pan is the
+// matrix's row at(x).  The sums start from -C, which is on its way meanwhile; operands are requested four stages of 16 k ahead.  Of these, lane l
+// takes four from 4 (l / 16), and an instruction those with the same place among the four.
+template <int RB, typename At>
+__device__ __forceinline__ void chol_update(double* pan, gptr<const double> C, int r, int jb, int row0, At at) {
+  typedef double __attribute__((ext_vector_type(2), aligned(8))) f64x2_a8;
+  const int lane = threadIdx.x & 63;
+  f64x4_t acc[RB][2];
+  chol_foreach(acc, [&](int row, int col, double) {
+    const int g = at(row0 + row), c = jb + col;
+    return g < r && c <= g ? -C[chol_at(r, g, c)] : 0.0;
+  });
+  gptr<const double> pa[RB], pb[2];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) pa[i] = C + (chol_row(r, min(at(row0 + 16 * i + (lane & 15)), r - 1)) + chol_col(r, 4 * (lane >> 4)));
+#pragma unroll
+  for (int i = 0; i < 2; ++i) pb[i] = C + (chol_row(r, min(jb + 16 * i + (lane & 15), r - 1)) + chol_col(r, 4 * (lane >> 4)));
+  struct Operands { double a[4][RB], b[4][2]; };
+  const int pair = (int)chol_col(r, 2);
+  auto load = [&](Operands& o, int k) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        const f64x2_a8 u = *reinterpret_cast<gptr<const f64x2_a8>>(pa[i] + (k + h * pair));
+        o.a[2 * h][i] = u.x;
+        o.a[2 * h + 1][i] = u.y;
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const f64x2_a8 u = *reinterpret_cast<gptr<const f64x2_a8>>(pb[i] + (k + h * pair));
+        o.b[2 * h][i] = u.x;
+        o.b[2 * h + 1][i] = u.y;
       }
     }
-    __syncthreads();
-    for (int x = t; x < NB * NB; x += FIRA_CHOL_THREADS) {
-      const int i = x / NB, k = x % NB;
-      if (i < nb && k <= i) C[(long long)(jb + i) * r + jb + k] = DT[k * DP + i];
+  };
+  auto multiply = [&](const Operands& o) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) chol_products(acc, o.a[s], o.b[s]);
+  };
+  if (jb > 0) {                            // (a multiple of 32: an even number of stages; what is requested past the end is not used)
+    Operands o[4];
+    auto stage = [&](int s) { return (int)chol_col(r, 16 * min(s, jb / 16 - 1)); };
+#pragma unroll
+    for (int s = 0; s < 4; ++s) load(o[s], stage(s));
+    int s0 = 0;
+    for (; s0 + 4 <= jb / 16; s0 += 4) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        multiply(o[s]);
+        load(o[s], stage(s0 + s + 4));
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-    // (2) panel: rows below the block (which is then a whole one), X D^T = C_panel, forward substitution along its columns
-    const int below = r - (jb + nb);
-    const bool in_lds = below <= pan_rows;
-    if (in_lds) {
-      for (int x = t; x < below * NB; x += FIRA_CHOL_THREADS) {
-        const int i = x / NB, k = x % NB;
-        chol_pan[i * PP + k] = C[(long long)(jb + NB + i) * r + jb + k];
+    if (s0 < jb / 16) {
+      multiply(o[0]);
+      multiply(o[1]);
+    }
+  }
+  chol_foreach(acc, [&](int row, int col, double v) {
+    const int x = row0 + row;
+    return pan[x * FIRA_CHOL_PITCH + col] = at(x) < r ? -v : (x == col ? 1.0 : 0.0);      // (identity past the end)
+  });
+}
+
+// Lower left quarter -B C A of a 64 x 64 inverse, from the inverses A and B of the 32 x 32 triangles and what lies below the first, C, by four wavefronts:
+// a wavefront's 16 x 16 of C A goes to W, and then, when all are there, of -B W to store(row, col, value).  Arrays in LDS, P doubles a row.
+template <int P>
+__device__ __forceinline__ void chol_quarter(f64x4_t& acc, const double* left, const double* right) {
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
+  const double *pa = left + (16 * (wave >> 1) + (lane & 15)) * P + (lane >> 4), *pb = right + (lane >> 4) * P + 16 * (wave & 1) + (lane & 15);
+  acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < FIRA_CHOL_NB; k += 4) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(pa[k], pb[k * P], acc, 0, 0, 0);
+}
+template <typename F>
+__device__ __forceinline__ void chol_quarter_foreach(const f64x4_t& acc, F f) {
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) f(16 * (wave >> 1) + (lane >> 4) + 4 * v, 16 * (wave & 1) + (lane & 15), acc[v]);
+}
+
+__global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(const FiraRefreshEnt* __restrict__ ents) {
+  constexpr int NB = FIRA_CHOL_NB, PP = FIRA_CHOL_PITCH, WAVES = FIRA_CHOL_THREADS / 64, PANEL = FIRA_CHOL_ROWS - NB;
+  static_assert(FIRA_CHOL_ROWS <= 3 * NB * (WAVES - 1) + NB, "the wavefronts hold a panel's rows and the identity's");
+  __shared__ double red[WAVES];
+  // the diagonal block's 32 rows and, below them, up to PANEL of the others: [rows][PP]
+  extern __shared__ __attribute__((aligned(16))) double chol_pan[];
+  const FiraRefreshEnt e = ents[blockIdx.x];
+  if (refresh_pass_done(e)) return;
+  const int r = e.r, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int t = threadIdx.x;
+  gptr<double> C = as_global(e.C);
+  double mx = 0.0;
+  for (int i = t; i < r; i += FIRA_CHOL_THREADS) mx = fmax(mx, C[chol_at(r, i, i)]);
+  const double floor_piv = chol_floor(mx, red);
+  for (int jb = 0; jb < r; jb += NB) {
+    // (each part of the rows repeats the diagonal block, which is stored with the last)
+    for (int base = jb + NB;; base += PANEL) {
+      asm volatile("" : "+v"(t));          // (else the offsets of all that follows are formed out here, and spill)
+      const int lane = t & 63;
+      const int rows = max(min(PANEL, r - base), 0), blocks = 1 + (rows + NB - 1) / NB;
+      const bool last = base + PANEL >= r;
+      auto at = [&](int x) { return x < NB ? jb + x : base + x - NB; };
+      // 32 rows to a wavefront at a time, or 16 where that keeps more of them busy
+      if (blocks > WAVES)
+        for (int b = wave; b < blocks; b += WAVES) chol_update<2>(chol_pan, C, r, jb, NB * b, at);
+      else
+        for (int b = wave; b < 2 * blocks; b += WAVES) chol_update<1>(chol_pan, C, r, jb, NB / 2 * b, at);
+      __syncthreads();
+      // the panel's rows, 96 to a wavefront, and the identity's 32 to the last one
+      const bool identity = wave == WAVES - 1;
+      const int end = NB * blocks, row0 = 3 * NB * wave + lane;
+      const bool works = identity ? base == jb + NB : wave == 0 || NB * (3 * wave + 1) < end;
+      double d[NB], x[NB];
+      if (works) {
+        const double* from = chol_pan + (lane < NB ? lane : min(row0, end - 1)) * PP;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) d[k] = identity && lane >= NB ? (k == lane - NB ? 1.0 : 0.0) : from[k];
+        from = chol_pan + min(row0 + 2 * NB, end - 1) * PP;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) x[k] = from[k];
+      }
+      __syncthreads();                     // (the block's rows have been read by everybody)
+      if (works) {
+        chol_eliminate<true>(d, x, floor_piv);
+        if (identity) {                    // D^-T, a row per lane
+          if (lane >= NB) {
+            gptr<double> inv = reinterpret_cast<gptr<double>>(as_global(e.inst)) + (size_t)(jb / 64) * 64 * 64 + (jb & 32) * 65 + lane - NB;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) inv[k * 64] = k >= lane - NB ? d[k] : 0.0;
+          }
+        } else {
+          if (lane < NB ? wave == 0 : row0 < end) {
+            double* to = chol_pan + (lane < NB ? lane : row0) * PP;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) to[k] = d[k];
+          }
+          if (row0 + 2 * NB < end) {
+            double* to = chol_pan + (row0 + 2 * NB) * PP;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) to[k] = x[k];
+          }
+        }
       }
       __syncthreads();
-    }
-    for (int i = t; i < below; i += FIRA_CHOL_THREADS) {
-      gptr<double> grow = C + (long long)(jb + NB + i) * r + jb;
-      double x[NB];
-#pragma unroll
-      for (int k = 0; k < NB; ++k) x[k] = in_lds ? chol_pan[i * PP + k] : grow[k];
-      chol_panel_row(x, DT, rinv_s);
-#pragma unroll
-      for (int k = 0; k < NB; ++k) {
-        if (in_lds) chol_pan[i * PP + k] = x[k];
-        else grow[k] = x[k];
-      }
-    }
-    __syncthreads();   // (HIP's barrier also waits for this wave's global stores)
-    if (in_lds) {
-      for (int x = t; x < below * NB; x += FIRA_CHOL_THREADS) {
-        const int i = x / NB, k = x % NB;
-        C[(long long)(jb + NB + i) * r + jb + k] = chol_pan[i * PP + k];
-      }
-      // (3) trailing triangle: C[i][k] -= sum_p P[i][p] P[k][p],  jb+NB <= k <= i < r,  P = the panel, on the matrix
-      // pipe: 32 x 32 blocks of the triangle dealt out to the wavefronts, operands from the panel in
-      // LDS (rows past the end are clamped to the last row; what they produce is not stored)
-      const int nb32 = (below + 31) / 32;
-      int cnt = 0;
-      for (int bi = 0; bi < nb32; ++bi)
-        for (int bk = 0; bk <= bi; ++bk, ++cnt) {
-          if (cnt % (FIRA_CHOL_THREADS / 64) != wave) continue;
-          double old[2][2][4];
-          gptr<double> Cb = C + (long long)(jb + NB + 32 * bi) * r + jb + NB + 32 * bk;
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int v = 0; v < 4; ++v) {
-                const int ri = 16 * i + (lane >> 4) + 4 * v, ck = 16 * j + (lane & 15);
-                const bool in = 32 * bi + ri < below && 32 * bk + ck <= 32 * bi + ri;
-                old[i][j][v] = in ? Cb[(long long)ri * r + ck] : 0.0;
-              }
-          const int m0 = min(32 * bi + (lane & 15), below - 1), m1 = min(32 * bi + 16 + (lane & 15), below - 1);
-          const int n0 = min(32 * bk + (lane & 15), below - 1), n1 = min(32 * bk + 16 + (lane & 15), below - 1);
-          RefreshAcc acc;
-          refresh_acc_zero(acc);
-#pragma unroll
-          for (int k4 = 0; k4 < NB; k4 += 4) {
-            const int k = k4 + (lane >> 4);
-            const double a0 = chol_pan[m0 * PP + k], a1 = chol_pan[m1 * PP + k];
-            const double b0 = chol_pan[n0 * PP + k], b1 = chol_pan[n1 * PP + k];
-            refresh_acc_step(acc, a0, a1, b0, b1);
-          }
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int v = 0; v < 4; ++v) {
-                const int ri = 16 * i + (lane >> 4) + 4 * v, ck = 16 * j + (lane & 15);
-                if (32 * bi + ri < below && 32 * bk + ck <= 32 * bi + ri) Cb[(long long)ri * r + ck] = old[i][j][v] - acc.v[i][j][v];
-              }
+      if (chol_tiled(r)) {                 // a tile is 16 bytes a thread (what stands above the diagonal and past the end is nobody's)
+        typedef double f64x2_t __attribute__((ext_vector_type(2)));
+        const int i = 16 * (t >> 8) + (t & 15), k = 16 * ((t >> 7) & 1) + 4 * ((t >> 4) & 3) + 2 * ((t >> 6) & 1);
+#pragma unroll 4
+        for (int b = last ? 0 : 1; b < blocks; ++b) {
+          const double* from = chol_pan + (NB * b + i) * PP + k;
+          *reinterpret_cast<gptr<f64x2_t>>(C + (chol_at(r, b ? base + NB * (b - 1) : jb, jb) + 2 * t)) = f64x2_t{from[0], from[1]};
         }
-    } else {
-    const int nt4 = (below + 3) / 4;
-    for (int x = t; x < nt4 * nt4; x += FIRA_CHOL_THREADS) {
-      const int bi = x / nt4, bk = x % nt4;
-      if (bk > bi) continue;
-      const int i0 = jb + nb + 4 * bi, k0 = jb + nb + 4 * bk;
-      double acc[4][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[i][k] = 0.0;
-      for (int p = 0; p < nb; ++p) {
-        double a[4], b[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          a[i] = (i0 + i < r) ? C[(long long)(i0 + i) * r + jb + p] : 0.0;
-          b[i] = (k0 + i < r) ? C[(long long)(k0 + i) * r + jb + p] : 0.0;
+      } else {
+        for (int y = t + (last ? 0 : NB * NB); y < (NB + rows) * NB; y += FIRA_CHOL_THREADS) {
+          const int i = y / NB, k = y % NB, g = at(i);
+          if (g < r && jb + k <= g) C[chol_at(r, g, jb + k)] = chol_pan[i * PP + k];
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int k = 0; k < 4; ++k) acc[i][k] += a[i] * b[k];
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (i0 + i < r && k0 + k <= i0 + i) C[(long long)(i0 + i) * r + k0 + k] -= acc[i][k];
+      __syncthreads();                     // (HIP's barrier also waits for this wave's global stores)
+      if (last) break;
     }
-    }
-    __syncthreads();
   }
 }
 
 // Factorisation and the inverses of its diagonal blocks in one launch for ranks up to 128 (lists of nothing larger), whose whole matrix fits
-// in LDS: the kernels above and below go through memory between their steps.  The same operations in the same order, and the chain
-// of those is what is left: 56 matrices of r = 128 98 us, 88 and 16 in two launches (a refresh of 8 blocks of 512 x 1376 729 -> 693 us, where
-// the estimate's last kernel, whose loads run side by side now, has 11 of it; 24 of 1024 x 2736 at r = 128 2672 -> 2600).
+// in LDS: the kernels above and below go through memory between their steps.  The same operations in the same order.  56 matrices of r = 128: 38 us;
+// 98 with one row per thread below a block and the inverses formed afterwards, a step each for every column (a refresh of 8 blocks of 512 x 1376
+// 683 -> 559 us).
 // LDS: the factor in rows of FIRA_CHOL_SMALL_PITCH (an odd number of doubles), identity past r.  Of the half above the diagonal, rows 0 .. 63
 // of columns 64 .. 127 take the inverses of the 32 x 32 triangles; when the factor has left, the quarter below takes the products.
-#define FIRA_CHOL_SMALL_R 128
 #define FIRA_CHOL_SMALL_PITCH (FIRA_CHOL_SMALL_R + 1)
 #define FIRA_CHOL_SMALL_LDS (FIRA_CHOL_SMALL_R * FIRA_CHOL_SMALL_PITCH * 8)
 __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_small_kernel(const FiraRefreshEnt* __restrict__ ents) {
-  constexpr int NB = FIRA_CHOL_NB, DP = NB + 2, P = FIRA_CHOL_SMALL_PITCH, N = FIRA_CHOL_SMALL_R, WAVES = FIRA_CHOL_THREADS / 64;
-  __shared__ __attribute__((aligned(16))) double DT[NB * DP];   // the diagonal block's factor, by columns: L[i][k] at k * DP + i
-  __shared__ double rinv_s[N];
-  __shared__ double dmax_s[WAVES];
+  constexpr int NB = FIRA_CHOL_NB, P = FIRA_CHOL_SMALL_PITCH, N = FIRA_CHOL_SMALL_R, WAVES = FIRA_CHOL_THREADS / 64;
+  __shared__ double red[WAVES];
   extern __shared__ __attribute__((aligned(16))) double chol_a[];
   const FiraRefreshEnt e = ents[blockIdx.x];
   if (refresh_pass_done(e)) return;
-  const int r = e.r, r32 = (r + NB - 1) / NB * NB, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int r = e.r, t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int blocks = (r + 63) / 64, r32 = (r + NB - 1) / NB * NB;
   gptr<double> C = as_global(e.C);
+  double* X = chol_a + 64;                            // the inverse of triangle w: X[(32 (w >> 1) + i) P + 32 (w & 1) + c]
+  double mx = 0.0;
   {
-    constexpr int PASSES = N * N / FIRA_CHOL_THREADS;
-    double mx = 0.0;
+    constexpr int PASSES = N * N / FIRA_CHOL_THREADS, AT_ONCE = 16;
 #pragma unroll
-    for (int g = 0; g < PASSES; g += 8) {
-      double v[8];
+    for (int g = 0; g < PASSES; g += AT_ONCE) {
+      double v[AT_ONCE];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
+      for (int q = 0; q < AT_ONCE; ++q) {
         const int x = t + FIRA_CHOL_THREADS * (g + q), i = x / N, k = x % N;
         v[q] = k <= i && i < r ? C[(unsigned)(i * r + k)] : (i == k ? 1.0 : 0.0);
       }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
+      for (int q = 0; q < AT_ONCE; ++q) {
         const int x = t + FIRA_CHOL_THREADS * (g + q), i = x / N, k = x % N;
         chol_a[i * P + k] = v[q];
         if (i == k && i < r) mx = fmax(mx, v[q]);
       }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-    if (lane == 0) dmax_s[wave] = mx;
   }
-  __syncthreads();
-  double dmax = 0.0;
-#pragma unroll
-  for (int w = 0; w < WAVES; ++w) dmax = fmax(dmax, dmax_s[w]);
-  const double floor_piv = dmax * 1e-24 + 1e-300;
+  const double floor_piv = chol_floor(mx, red);
+  if (r32 < 64 * blocks)                              // the last 64 columns' second triangle is past the end
+    for (int x = t; x < NB * NB; x += FIRA_CHOL_THREADS) X[(r32 / 64 * NB + x / NB) * P + NB + x % NB] = x / NB == x % NB ? 1.0 : 0.0;
   for (int jb = 0; jb < r; jb += NB) {
-    double* D = chol_a + jb * P + jb;
-    if (wave == 0) {
-      const int row = lane & (NB - 1);
-      double d[NB];
-#pragma unroll
-      for (int k = 0; k < NB; ++k) d[k] = k <= row ? D[row * P + k] : 0.0;
-      chol_diagonal(d, floor_piv, [&](int j, double inv) { rinv_s[j] = inv; });
-      if (lane < NB) {
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-          const double v = k <= row ? d[k] : 0.0;
-          DT[k * DP + row] = v;
-          if (k <= row) D[row * P + k] = v;
-        }
-      }
-    }
-    __syncthreads();
     const int below = r32 - jb - NB;
-    double* pan = chol_a + (jb + NB) * P + jb;
-    if (t < below) {
-      double x[NB];
+    if (jb > 0) {                                     // (rows past r take zeros off an identity)
+      for (int u = wave; u < 4 * (below / NB + 1); u += WAVES) {      // 16 x 16 at a time
+        const int row0 = jb + 16 * (u >> 1), col0 = jb + 16 * (u & 1);
+        f64x4_t acc[1][1];
+        chol_foreach(acc, [&](int row, int col, double) { return -chol_a[(row0 + row) * P + col0 + col]; });
+        const double *pa = chol_a + (row0 + (lane & 15)) * P + 4 * (lane >> 4), *pb = chol_a + (col0 + (lane & 15)) * P + 4 * (lane >> 4);
+        for (int k = 0; k < jb; k += NB) {
+          double a[8], b[8];
 #pragma unroll
-      for (int k = 0; k < NB; ++k) x[k] = pan[t * P + k];
-      chol_panel_row(x, DT, rinv_s);
+          for (int s = 0; s < 8; ++s) {
+            a[s] = pa[k + 16 * (s >> 2) + (s & 3)];
+            b[s] = pb[k + 16 * (s >> 2) + (s & 3)];
+          }
 #pragma unroll
-      for (int k = 0; k < NB; ++k) pan[t * P + k] = x[k];
+          for (int s = 0; s < 8; ++s) acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc[0][0], 0, 0, 0);
+        }
+        chol_foreach(acc, [&](int row, int col, double v) { return chol_a[(row0 + row) * P + col0 + col] = -v; });
+      }
+      __syncthreads();
+    }
+    // wavefront w carries the panel's rows 32 w ..; the one after them, the identity's
+    const bool identity = NB * wave == below;
+    double d[NB], none[1];
+    double* at = chol_a + (jb + (lane < NB ? 0 : NB * wave) + lane) * P + jb;
+    if (NB * wave <= below) {
+#pragma unroll
+      for (int k = 0; k < NB; ++k) d[k] = identity && lane >= NB ? (k == lane - NB ? 1.0 : 0.0) : at[k];
     }
     __syncthreads();
-    // trailing triangle: blocks of 32 x 32 (what lies above the diagonal in the diagonal ones is never read)
-    int cnt = 0;
-    for (int bi = 0; bi < below; bi += NB)
-      for (int bk = 0; bk <= bi; bk += NB, ++cnt) {
-        if (cnt % WAVES != wave) continue;
-        const int m0 = bi + (lane & 15), n0 = bk + (lane & 15);
-        RefreshAcc acc;
-        refresh_acc_zero(acc);
+    if (NB * wave <= below) {
+      chol_eliminate<false>(d, none, floor_piv);
+      if (lane >= NB && identity) {
 #pragma unroll
-        for (int k4 = 0; k4 < NB; k4 += 4) {
-          const int k = k4 + (lane >> 4);
-          refresh_acc_step(acc, pan[m0 * P + k], pan[(m0 + 16) * P + k], pan[n0 * P + k], pan[(n0 + 16) * P + k]);
-        }
-        double* T = chol_a + (jb + NB + bi) * P + jb + NB + bk;
+        for (int k = 0; k < NB; ++k) X[(jb / 64 * NB + k) * P + (jb & 32) + lane - NB] = k >= lane - NB ? d[k] : 0.0;
+      } else if (lane >= NB || wave == 0) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const int ri = 16 * i + (lane >> 4) + 4 * v, ck = 16 * j + (lane & 15);
-              if (bk < bi || ck <= ri) T[ri * P + ck] -= acc.v[i][j][v];
-            }
+        for (int k = 0; k < NB; ++k) at[k] = d[k];     // (nobody reads what stands above the diagonal)
       }
+    }
     __syncthreads();
   }
   for (int x = t; x < r * N; x += FIRA_CHOL_THREADS) {
     const int i = x / N, k = x % N;
     if (k <= i) C[(unsigned)(i * r + k)] = chol_a[i * P + k];
   }
-  if (t < N) rinv_s[t] = 1.0 / chol_a[t * P + t];
-  __syncthreads();
-  // fira_refresh_diaginv_kernel's steps, wave w < 4 the triangle at 32 w
-  const int blocks = (r + 63) / 64;
-  double* X = chol_a + 64;                            // triangle w: X[(32 (w >> 1) + i) P + 32 (w & 1) + c]
-  if (wave < 2 * blocks && lane < NB) {
-    const double* L = chol_a + NB * wave * (P + 1);
-    double x[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) x[i] = i == lane ? 1.0 : 0.0;
-#pragma unroll
-    for (int p = 0; p < NB; ++p) {
-      x[p] *= rinv_s[NB * wave + p];
-#pragma unroll
-      for (int i = p + 1; i < NB; ++i) x[i] = fma(-L[i * P + p], x[p], x[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) X[(NB * (wave >> 1) + i) * P + NB * (wave & 1) + lane] = x[i];
-  }
-  __syncthreads();
-  const int J = t >> 8, row = (t & 255) >> 3, c4 = (t & 7) * 4;      // 256 threads to a block, four of a row's values each
+  // fira_refresh_diaginv_kernel's steps, four wavefronts to a block
+  const int J = t >> 8;
   const double* XA = X + NB * J * P;
   const double* XB = XA + NB;
-  double* W = chol_a + 64 * P + NB * J * P;           // (the factor's lower left quarter has left)
-  double q[4] = {0.0, 0.0, 0.0, 0.0};
-  if (J < blocks) {
-    const double* Cq = chol_a + (64 * J + NB) * P + 64 * J;
-    for (int k = 0; k < NB; ++k)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) q[c] = fma(Cq[row * P + k], XA[k * P + c4 + c], q[c]);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) W[row * P + c4 + c] = q[c];
-  }
+  double* W = chol_a + 64 * P + NB * J * P;           // (the factor's lower left quarter)
+  f64x4_t q;
+  chol_quarter<P>(q, chol_a + (64 * J + NB) * P + 64 * J, XA);
+  __syncthreads();                                    // (which has left)
+  chol_quarter_foreach(q, [&](int row, int col, double v) { W[row * P + col] = v; });
   __syncthreads();
   if (J >= blocks) return;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) q[c] = 0.0;
-  for (int k = 0; k < NB; ++k)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) q[c] = fma(XB[row * P + k], W[k * P + c4 + c], q[c]);
+  chol_quarter<P>(q, XB, W);
   gptr<double> inv = reinterpret_cast<gptr<double>>(as_global(e.inst)) + (size_t)J * 64 * 64;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    inv[row * 64 + c4 + c] = XA[row * P + c4 + c];
-    inv[row * 64 + NB + c4 + c] = 0.0;
-    inv[(NB + row) * 64 + c4 + c] = -q[c];
-    inv[(NB + row) * 64 + NB + c4 + c] = XB[row * P + c4 + c];
-  }
+  chol_quarter_foreach(q, [&](int row, int col, double v) {
+    inv[row * 64 + col] = XA[row * P + col];
+    inv[row * 64 + NB + col] = 0.0;
+    inv[(NB + row) * 64 + col] = -v;
+    inv[(NB + row) * 64 + NB + col] = XB[row * P + col];
+  });
 }
 
 // Q = Y L^-T, i.e. every row solves  q L^T = y  by forward substitution, done in column blocks of 64:
@@ -657,65 +704,35 @@ __device__ __forceinline__ int solve_swz_q(int k) { return 16 * ((k >> 2) & 3); 
 __device__ __forceinline__ int solve_swz_l(int k) { return 8 * ((k >> 2) & 3); }
 
 // inv(L_JJ) for every diagonal block J of a matrix: inv[J][k][c], k >= c (zero above the diagonal).
-// Rows and columns beyond r act as an identity.  By halves: the inverses of the two 32 x 32 triangles A and B, one
-// column per lane in registers (independent multiply-adds per row of the substitution), then the lower left quarter
-// -inv(B) C inv(A).  (48 us for 168 matrices of r = 512; 390 us as one chain of 64 dependent rows per lane.)
+// Rows and columns beyond r act as an identity.  The inverses A and B of the two 32 x 32 triangles are there already (fira_refresh_chol_kernel);
+// this adds the lower left quarter -B C A and the zeros.
 __global__ __launch_bounds__(256) void fira_refresh_diaginv_kernel(const FiraRefreshEnt* __restrict__ ents) {
-  constexpr int H = 32, DP = H + 2;
-  __shared__ __attribute__((aligned(16))) double LT[2][H * DP];   // the triangles by columns: L[i][k] at k * DP + i
-  __shared__ double Cq[H][H + 1], W[H][H + 1], rinv[2][H];
-  __shared__ double X[2][H][H + 1];
+  constexpr int H = 32;
+  __shared__ double Cq[H][H + 1], W[H][H + 1], X[2][H][H + 1];
   const FiraRefreshEnt e = ents[blockIdx.y];
   const int r = e.r, j0 = blockIdx.x * FIRA_SOLVE_JB, t = threadIdx.x;
   if (j0 >= r || refresh_pass_done(e)) return;
   gptr<const double> Lm = as_global<const double>(e.C);
-#pragma unroll
-  for (int p = 0; p < 16; ++p) {
-    const int x = t + 256 * p, i = x >> 6, k = x & 63;
-    const bool in = j0 + i < r && k <= i;
-    const double v = in ? Lm[(long long)(j0 + i) * r + j0 + k] : (i == k ? 1.0 : 0.0);
-    if (i >= H && k < H) Cq[i - H][k] = v;
-    else if (i < H && k < H) LT[0][k * DP + i] = v;
-    else if (i >= H) LT[1][(k - H) * DP + i - H] = v;
-    if (i == k) rinv[i / H][i % H] = 1.0 / v;
-  }
-  __syncthreads();
-  if (t < 2 * H) {
-    const int half = t / H, c = t % H;      // column c of the inverse of a triangle: L x = e_c
-    double x[H];
-#pragma unroll
-    for (int i = 0; i < H; ++i) x[i] = i == c ? 1.0 : 0.0;
-#pragma unroll
-    for (int p = 0; p < H; ++p) {
-      x[p] *= rinv[half][p];
-#pragma unroll
-      for (int i = p + 1; i < H; ++i) x[i] = fma(-LT[half][p * DP + i], x[p], x[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < H; ++i) X[half][i][c] = x[i];
-  }
-  __syncthreads();
-  const int row = t >> 3, c4 = (t & 7) * 4;
-  double q[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int k = 0; k < H; ++k)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) q[c] = fma(Cq[row][k], X[0][k][c4 + c], q[c]);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) W[row][c4 + c] = q[c];
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < 4; ++c) q[c] = 0.0;
-  for (int k = 0; k < H; ++k)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) q[c] = fma(X[1][row][k], W[k][c4 + c], q[c]);
   gptr<double> inv = reinterpret_cast<gptr<double>>(as_global(e.inst)) + (size_t)blockIdx.x * 64 * 64;
+  const bool second = j0 + H < r;          // (the second triangle is past the end otherwise)
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    inv[row * 64 + c4 + c] = X[0][row][c4 + c];
-    inv[row * 64 + H + c4 + c] = 0.0;
-    inv[(H + row) * 64 + c4 + c] = -q[c];
-    inv[(H + row) * 64 + H + c4 + c] = X[1][row][c4 + c];
+  for (int p = 0; p < 4; ++p) {
+    const int x = t + 256 * p, i = x >> 5, k = x & 31;
+    X[0][i][k] = inv[i * 64 + k];
+    X[1][i][k] = second ? inv[(H + i) * 64 + H + k] : (i == k ? 1.0 : 0.0);
+    Cq[i][k] = j0 + H + i < r ? Lm[chol_at(r, j0 + H + i, j0 + k)] : 0.0;
   }
+  __syncthreads();
+  f64x4_t q;
+  chol_quarter<H + 1>(q, &Cq[0][0], &X[0][0][0]);
+  chol_quarter_foreach(q, [&](int row, int col, double v) { W[row][col] = v; });
+  __syncthreads();
+  chol_quarter<H + 1>(q, &X[1][0][0], &W[0][0]);
+  chol_quarter_foreach(q, [&](int row, int col, double v) {
+    inv[row * 64 + H + col] = 0.0;
+    inv[(H + row) * 64 + col] = -v;
+    if (!second) inv[(H + row) * 64 + H + col] = X[1][row][col];
+  });
 }
 
 // All of Q for 64 rows.
@@ -740,13 +757,14 @@ __global__ __launch_bounds__(256, 4) void fira_refresh_solve_kernel(const FiraRe
     // into registers before the current one is multiplied.
     f32x4 rq;
     double rl[4];
+    const unsigned lrow = chol_row(r, j0 + lr);
     auto fetch = [&](int k0) {
       rq = refresh_load4(Q + (long long)s0 * r + k0, lr, lk, e.S - s0, r, r);
       if (j0 + lr < r) {
-        gptr<const double> pl = Lm + (long long)j0 * r + k0 + (unsigned)(lr * r + lk);
-        if ((r & 1) == 0) {
+        gptr<const double> pl = Lm + (lrow + chol_col(r, k0 + lk));
+        if (chol_tiled(r) || (r & 1) == 0) {
           typedef double f64x2_t __attribute__((ext_vector_type(2)));
-          const f64x2_t u = *reinterpret_cast<gptr<const f64x2_t>>(pl), w = *reinterpret_cast<gptr<const f64x2_t>>(pl + 2);
+          const f64x2_t u = *reinterpret_cast<gptr<const f64x2_t>>(pl), w = *reinterpret_cast<gptr<const f64x2_t>>(pl + chol_col(r, 2));
           rl[0] = u.x; rl[1] = u.y; rl[2] = w.x; rl[3] = w.y;
         } else {
 #pragma unroll

@@ -1,0 +1,33 @@
+"""Refresh at ranks whose factor is kept in tiles and whose panels are worked through in parts of 512 rows: the smallest of them, both sides
+of a tile's 32 rows, and both sides of one part.  The basis is orthonormal to what its storage holds and keeps what the SVD's keeps."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fira_oracle as orc
+from paper_2410_01623_amd import fira
+
+import fira_harness as H
+from test_gpu_refresh import _gapped_gradient
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [fira.FIRA_BF16, fira.FIRA_F32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("r", [129, 159, 161, 224, 385, 511, 512, 513, 545, 577])
+def test_factor_in_tiles(r, dtype):
+    rng = np.random.default_rng(r)
+    m, n = (2 * r + 37, r + 60) if r % 2 else (r + 60, 2 * r + 37)
+    G = _gapped_gradient(rng, m, n, r)
+    ctx = fira.FiraContext([(m, n)], r, dtype, device=H.DEV)
+    Gd = torch.from_numpy(G.astype(np.float32)).to(H.DEV).to(torch.bfloat16 if dtype == fira.FIRA_BF16 else torch.float32)
+    ws = torch.full((ctx.fira_refresh_workspace_bytes([0]),), 0xFF, dtype=torch.uint8, device=H.DEV)   # (NaNs: only what was written is read)
+    ctx.fira_refresh_projectors([0], [Gd], iters=3, seed=7, workspace=ws)
+    torch.cuda.synchronize()
+    P = ctx.fira_get_projector(0).numpy().astype(np.float64)
+    Pref = orc.top_r_projector(G, r)
+    sines = orc.subspace_sines(Pref, P)
+    defect = np.max(np.abs(P.T @ P - np.eye(r)))
+    # (bounds as in test_gpu_refresh_edges.py)
+    assert sines.max() < 1e-2 and orc.captured_energy(G, P) > orc.captured_energy(G, Pref) - 1e-4
+    assert defect < (3e-3 if dtype == fira.FIRA_BF16 else 1e-5)
