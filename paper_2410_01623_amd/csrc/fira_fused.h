@@ -304,16 +304,14 @@ __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& m
   }
   const int wave = threadIdx.x >> 6;
   const bool sumsq = TM == 2 ? (wave & 1) == 0 : wave == 0;      // the waves of the first 64 rank columns
-  const bool interior = g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB;
-  if (interior) {
-    if (sumsq) proj_pipeline<LEFT, true, true, RT, true, TM>(acc, lds, g, sq, prologue);
-    else if (RT == 1 || wave < 4) proj_pipeline<LEFT, true, false, RT, true, TM>(acc, lds, g, sq, prologue);
-    else if constexpr (RT == 2) proj_pipeline<LEFT, true, false, 2, false, TM>(acc, lds, g, sq, prologue);
-  } else {
-    if (sumsq) proj_pipeline<LEFT, false, true, RT, true, TM>(acc, lds, g, sq, prologue);
-    else if (RT == 1 || wave < 4) proj_pipeline<LEFT, false, false, RT, true, TM>(acc, lds, g, sq, prologue);
-    else if constexpr (RT == 2) proj_pipeline<LEFT, false, false, 2, false, TM>(acc, lds, g, sq, prologue);
-  }
+  auto run = [&](auto mode) {
+    constexpr ProjLoads MODE = decltype(mode)::value;
+    if (sumsq) proj_pipeline<LEFT, MODE, true, RT, true, TM>(acc, lds, g, sq, prologue);
+    else if (RT == 1 || wave < 4) proj_pipeline<LEFT, MODE, false, RT, true, TM>(acc, lds, g, sq, prologue);
+    else if constexpr (RT == 2) proj_pipeline<LEFT, MODE, false, 2, false, TM>(acc, lds, g, sq, prologue);
+  };
+  if (proj_interior(g)) run(std::integral_constant<ProjLoads, PROJ_FAST>{});
+  else run(std::integral_constant<ProjLoads, PROJ_EDGE>{});        // (both sides are at least r >= FIRA_FUSE_MIN_R)
   if (g.a_row0 + FIRA_PA <= mt.L && mt.r == 64 * TM * RT) project_adam_epilogue<RT, TM, true>(acc, lds, mt, hp, bias, g.a_row0, sq);
   else project_adam_epilogue<RT, TM, false>(acc, lds, mt, hp, bias, g.a_row0, sq);
 }
@@ -398,7 +396,7 @@ __device__ __forceinline__ void proj_compute_small(f32x16_t (&acc)[2], const cha
   }
 }
 
-template <bool LEFT, bool FAST, bool SUMSQ, typename Prologue>
+template <bool LEFT, ProjLoads MODE, bool SUMSQ, typename Prologue>
 __device__ __forceinline__ void proj_pipeline_small(f32x16_t (&acc)[2], char* lds, const GemmOperands& g, float& sq, Prologue prologue) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   char* la = lds;
@@ -412,7 +410,7 @@ __device__ __forceinline__ void proj_pipeline_small(f32x16_t (&acc)[2], char* ld
   auto request_b = [&](int s) {   // this wave's 16 of the stage's 64 rows
     lds_dma16(pb + (long long)s * g.ldb * 64, offb, ring0 + (unsigned)((s % FIRA_RING_STAGES) * FIRA_PROJ_SMALL_STAGE + wave * 1024));
   };
-  ProjALoader<LEFT, FAST> al(g);
+  ProjALoader<LEFT, MODE> al(g);
   u32x4 ra[4];
   al.load(ra);                                 // A(0)
   request_b(0);
@@ -422,16 +420,18 @@ __device__ __forceinline__ void proj_pipeline_small(f32x16_t (&acc)[2], char* ld
     constexpr bool LAST = decltype(last)::value;
     wait_loads<1>(ra);                         // A(S) and D(2S) have landed; D(2S+1) may be in flight
     asm volatile("s_barrier" ::: "memory");
+    if (MODE == PROJ_EDGE) al.template settle<LAST>(ra);
     proj_store_a<LEFT>(la, ra);
     if (!LAST) {
       request_b(2 * S + 2);
+      if (MODE == PROJ_EDGE && S + 2 == SS) al.last();
       al.load(ra);                             // A(S+1)
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     proj_compute_small<SUMSQ>(acc, la, ring + ((2 * S) % FIRA_RING_STAGES) * FIRA_PROJ_SMALL_STAGE, 0, sq);
-    // D(2S+1) has landed (guarded A loads may be fewer than 4 instructions: the edge path lets one stay)
+    // D(2S+1) has landed (guarded A loads may be fewer than 4 instructions: that path lets one stay)
     if (LAST) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    else if (FAST) asm volatile("s_waitcnt vmcnt(5)\n\ts_barrier" ::: "memory");
+    else if (MODE != PROJ_GUARDED) asm volatile("s_waitcnt vmcnt(5)\n\ts_barrier" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(1)\n\ts_barrier" ::: "memory");
     if (!LAST) request_b(2 * S + 3);
     proj_compute_small<SUMSQ>(acc, la, ring + ((2 * S + 1) % FIRA_RING_STAGES) * FIRA_PROJ_SMALL_STAGE, 2, sq);
@@ -557,14 +557,13 @@ __device__ __forceinline__ void project_small_tile(f32x16_t (&acc)[2], char* lds
   g.A = as_global(reinterpret_cast<const bf16_raw*>(ent.G));
   g.lda = mt.ld;
   g.KA = mt.S;
-  const bool interior = g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB;
-  if (interior) {
-    if (sumsq) proj_pipeline_small<LEFT, true, true>(acc, lds, g, sq, prologue);
-    else proj_pipeline_small<LEFT, true, false>(acc, lds, g, sq, prologue);
-  } else {
-    if (sumsq) proj_pipeline_small<LEFT, false, true>(acc, lds, g, sq, prologue);
-    else proj_pipeline_small<LEFT, false, false>(acc, lds, g, sq, prologue);
-  }
+  auto run = [&](auto mode) {
+    if (sumsq) proj_pipeline_small<LEFT, decltype(mode)::value, true>(acc, lds, g, sq, prologue);
+    else proj_pipeline_small<LEFT, decltype(mode)::value, false>(acc, lds, g, sq, prologue);
+  };
+  if (proj_interior(g)) run(std::integral_constant<ProjLoads, PROJ_FAST>{});
+  else if (!proj_guarded(LEFT, g)) run(std::integral_constant<ProjLoads, PROJ_EDGE>{});
+  else run(std::integral_constant<ProjLoads, PROJ_GUARDED>{});
 }
 
 // Both orientations in one grid, as in fira_project_kernel.

@@ -243,7 +243,7 @@ __device__ __forceinline__ void ring_mainloop(f32x16_t (&acc)[TM][TN], char* lds
 // All requests of the interior path are inline assembly, so the waits can be exact: loads retire in
 // order, each request group is 4 instructions per thread, and the queue order is
 // A(0) D(0) D(1) | D(2) A(1) | D(3) | D(4) A(2) | D(5) ...; E waits with vmcnt(4) (only the newest
-// D may be in flight), O with vmcnt(8).  Edge tiles load A with ordinary guarded loads at the same
+// D may be in flight), O with vmcnt(8).  Matrices with a side of less than eight load A with ordinary guarded loads at the same
 // points of the sequence; the compiler's own waits for those only wait longer.
 // ------------------------------------------------------------------------------------------------
 #define FIRA_PROJ_THREADS 256
@@ -272,34 +272,87 @@ __device__ __forceinline__ void wait_loads(u32x4 (&r)[4]) {
 __device__ __forceinline__ int proj_kslow_ib(int t) { return (t & 7) | ((t >> 1) & 8); }
 __device__ __forceinline__ int proj_kslow_kq(int t) { return ((t >> 3) & 1) | ((t >> 4) & ~1); }
 
-template <bool LEFT, bool FAST>
+// How a tile's gradient is read: all of it there; up to the matrix's edge or the end of the contraction (EDGE): pieces that would leave it are moved back,
+// stay in flight like any other, and are moved into place in registers when they are stored; or, for matrices with a side of less than
+// eight, value by value (GUARDED).  A launch of few tiles waits for its edge tiles: 56 matrices of 512 x 512 and 512 x 1376, fused
+// kernel at r = 128, multiply phase of an edge tile 29 us where pieces were realigned as they were loaded, of any other 12.
+enum ProjLoads { PROJ_FAST, PROJ_EDGE, PROJ_GUARDED };
+template <bool LEFT, ProjLoads MODE>
 struct ProjALoader {
   const GemmOperands& g;
   const char* base;       // wave-uniform, advances along K
   unsigned off[4];        // byte offsets of this thread's four 16-byte loads
   long long step;         // bytes per K stage of 64
   int k0;
-  __device__ __forceinline__ ProjALoader(const GemmOperands& g_) : g(g_), k0(0) {
+  int down;               // EDGE: elements by which a loaded piece is moved down (LEFT: in every stage, RIGHT: in the last)
+  __device__ __forceinline__ ProjALoader(const GemmOperands& g_) : g(g_), k0(0), down(0) {
     const int t = threadIdx.x;
     if (LEFT) {
       const int ib = proj_kslow_ib(t), kq = proj_kslow_kq(t);
-      base = reinterpret_cast<const char*>((const bf16_raw*)g.A + g.a_row0);
+      int a0 = g.a_row0, a = 8 * ib;
+      if (MODE == PROJ_EDGE) {
+        a0 = min(a0, g.a_rows - 8);
+        const int at = min(g.a_row0 + 8 * ib, g.a_rows - 8);
+        down = min(g.a_row0 + 8 * ib - at, 8);
+        a = at - a0;
+      }
+      base = reinterpret_cast<const char*>((const bf16_raw*)g.A + a0);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) off[j] = (unsigned)(((4 * kq + j) * g.lda + 8 * ib) * 2);
+      for (int j = 0; j < 4; ++j) off[j] = (unsigned)(((4 * kq + j) * g.lda + a) * 2);
       step = 64 * g.lda * 2;
     } else {
       const int cc = t & 7, rr = t >> 3;
       base = reinterpret_cast<const char*>((const bf16_raw*)g.A + (long long)g.a_row0 * g.lda);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) off[q] = (unsigned)(((rr + 32 * q) * g.lda + 8 * cc) * 2);
+      for (int q = 0; q < 4; ++q) {
+        int row = rr + 32 * q;
+        if (MODE == PROJ_EDGE) row = min(row, g.a_rows - 1 - g.a_row0);     // (rows past the end are nobody's)
+        off[q] = (unsigned)((row * g.lda + 8 * cc) * 2);
+      }
       step = 64 * 2;
     }
+    if (MODE == PROJ_EDGE && g.KB == 64) last();
   }
-  // FAST only: request j of the four of a stage (the caller issues all four, in order, then advance())
+  // All but GUARDED: request j of the four of a stage (the caller issues all four, in order, then advance())
   __device__ __forceinline__ void load_one(u32x4 (&ra)[4], int j) { gload16_async(ra[j], base, off[j]); }
   __device__ __forceinline__ void advance() { base += step; }
+  // EDGE, before the requests of the last stage: those past the end of the contraction go to where it ends
+  __device__ __forceinline__ void last() {
+    const int t = threadIdx.x, left = g.KA - (g.KB - 64);      // k of the stage that there are
+    if (left >= 64) return;
+    if (LEFT) {
+      const int kq = proj_kslow_kq(t);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) off[j] -= (unsigned)(max(4 * kq + j - (left - 1), 0) * g.lda * 2);
+    } else {
+      const int k = 8 * (t & 7), back = min(left - 8, 0);      // (the stage may hold less than a piece)
+      down = min(max(k - (left - 8), 0), 8);
+      base += 2 * back;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) off[q] = (unsigned)((int)off[q] + 2 * (min(k, left - 8) - k - back));
+    }
+  }
+  // EDGE, after the wait for a stage: everything in its place, zeros past the ends
+  template <bool LAST>
+  __device__ __forceinline__ void settle(u32x4 (&ra)[4]) {
+    const int left = g.KA - (g.KB - 64);
+    if (LEFT) {
+      if (g.a_row0 + FIRA_PA > g.a_rows) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ra[j] = shift8_bf16(ra[j], down);
+      }
+      if (LAST && left < 64) {
+        const int kq = proj_kslow_kq(threadIdx.x);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) ra[j] = 4 * kq + j < left ? ra[j] : u32x4{0u, 0u, 0u, 0u};
+      }
+    } else if (LAST && left < 64) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ra[q] = shift8_bf16(ra[q], down);
+    }
+  }
   __device__ __forceinline__ void load(u32x4 (&ra)[4]) {
-    if (FAST) {
+    if (MODE != PROJ_GUARDED) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) gload16_async(ra[j], base, off[j]);
       base += step;
@@ -329,6 +382,9 @@ struct ProjALoader {
     }
   }
 };
+// The loads that a tile takes.
+__device__ __forceinline__ bool proj_interior(const GemmOperands& g) { return g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB; }
+__device__ __forceinline__ bool proj_guarded(bool left, const GemmOperands& g) { return (left ? g.a_rows : g.KA) < 8; }
 
 // Registers -> LDS tile of one K stage (128 rows x 64 k, lds_tile_off layout), written as eight parts.  t = the thread's place among the 256 loaders.
 //   K-slow (LEFT): ra[j] holds row k = 4*kq + j of a 4(k) x 8(a) block, dword d of it the elements
@@ -422,7 +478,7 @@ __device__ __forceinline__ void proj_compute(f32x16_t (&acc)[TM][2], const char*
 // TM = 2: half a rank tile (r <= 128), two wavefronts along the factors (64 each) and two along the rank; a ring
 // stage is 128 rows, two requests per wave, and the queue depths are TM where four requests make them 4 above.
 // prologue(): called when the first operands have been requested, for work that would otherwise stand before or after the contraction.
-template <bool LEFT, bool FAST, bool SUMSQ, int RT = 1, bool LOADER = true, int TM = 4, typename Prologue>
+template <bool LEFT, ProjLoads MODE, bool SUMSQ, int RT = 1, bool LOADER = true, int TM = 4, typename Prologue>
 __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds, const GemmOperands& g, float (&sq)[TM], Prologue prologue) {
   static_assert(LOADER || RT == 2, "only the second rank tile's wavefronts go without the gradient");
   static_assert(TM == 4 || RT == 1, "half a rank tile, or whole ones");
@@ -448,7 +504,7 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
 #pragma unroll
     for (int q = 0; q < TM; ++q) request_b1(s, q);
   };
-  ProjALoader<LEFT, FAST> al(g);
+  ProjALoader<LEFT, MODE> al(g);
   u32x4 ra[4];
   if (loader) al.load(ra);                     // A(0)
   request_b(0);
@@ -462,7 +518,10 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
     if (loader) wait_loads<TM>(ra);            // A(S) and D(2S) have landed; D(2S+1) may be in flight
     else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");    // everybody is done with the previous stage's A tile and ring slot
-    if (loader) proj_store_a<LEFT>(la, ra);
+    if (loader) {
+      if (MODE == PROJ_EDGE) al.template settle<LAST>(ra);
+      proj_store_a<LEFT>(la, ra);
+    }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     // the requests of D(2S+2) (into the slot of D(2S-1), free since the first barrier) and of A(S+1)
     // (whose registers proj_store_a has just released) go out between the multiplies
@@ -470,7 +529,8 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
       if (LAST) return;
       if (j < TM) request_b1(2 * S + 2, j);
       else if (j >= 4 && loader) {
-        if (FAST) {
+        if (MODE != PROJ_GUARDED) {
+          if (MODE == PROJ_EDGE && j == 4 && S + 2 == SS) al.last();
           al.load_one(ra, j - 4);
           if (j == 7) al.advance();
         } else if (j == 4) {
@@ -480,9 +540,9 @@ __device__ __forceinline__ void proj_pipeline(f32x16_t (&acc)[TM][2], char* lds,
     });
     // O half
     // D(2S+1) has landed.  Guarded A loads are the compiler's and may be fewer than 4 instructions,
-    // so the edge path only lets D(2S+2)'s stay in flight.
+    // so that path only lets D(2S+2)'s stay in flight.
     if (LAST) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    else if (FAST && loader) {
+    else if (MODE != PROJ_GUARDED && loader) {
       if (TM == 4) asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
       else asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");
     } else {
@@ -864,14 +924,13 @@ __device__ __forceinline__ void project_tile_as(char* lds, const FiraMat& mt, co
   // first 64 columns of each panel's first rank tile.
   const bool sumsq = norm_mode == 1 && tile.tb == 0 && b0 == 0;
   // LEFT: the k rows of G are whole rows of the matrix (any ld); RIGHT: a row of G holds KA values
-  const bool interior = g.a_row0 + FIRA_PA <= g.a_rows && g.KA == g.KB;
-  if (interior) {
-    if (sumsq) proj_pipeline<LEFT, true, true, 1, true, TM>(acc, lds, g, sq, [] {});
-    else proj_pipeline<LEFT, true, false, 1, true, TM>(acc, lds, g, sq, [] {});
-  } else {
-    if (sumsq) proj_pipeline<LEFT, false, true, 1, true, TM>(acc, lds, g, sq, [] {});
-    else proj_pipeline<LEFT, false, false, 1, true, TM>(acc, lds, g, sq, [] {});
-  }
+  auto run = [&](auto mode) {
+    if (sumsq) proj_pipeline<LEFT, decltype(mode)::value, true, 1, true, TM>(acc, lds, g, sq, [] {});
+    else proj_pipeline<LEFT, decltype(mode)::value, false, 1, true, TM>(acc, lds, g, sq, [] {});
+  };
+  if (proj_interior(g)) run(std::integral_constant<ProjLoads, PROJ_FAST>{});
+  else if (TM == 4 || !proj_guarded(LEFT, g)) run(std::integral_constant<ProjLoads, PROJ_EDGE>{});
+  else if constexpr (TM == 2) run(std::integral_constant<ProjLoads, PROJ_GUARDED>{});      // (r <= min(m, n) < 8)
   if (sumsq) {
     gptr<float> g2 = as_global(mt.g2);
 #pragma unroll
