@@ -12,7 +12,7 @@ import fira_harness as H
 pytestmark = pytest.mark.gpu
 
 SHORT = [193, 199, 200, 201, 255, 256, 257]      # 64 k + 1, 7, 8, 9, 63, 64 and one more
-LONG = [257, 263, 264, 265, 320, 383, 384]
+LONG = [259, 263, 264, 265, 320, 383, 385]
 SIZES = [(s, l) for i, s in enumerate(SHORT) for j, l in enumerate(LONG) if (i + j) % 2 == 0 or j == 6]
 
 
