@@ -183,7 +183,8 @@ FIRA_API fira_status fira_set_variant(fira_ctx* ctx, fira_variant variant);
  * step with enable == 0, runs two kernels for all (bf16 matrices with r <= 64: one, which leaves R in memory as two do).
  * Lists of 64 < r < 128 run fused as well where they are long enough for it to pay, but have R written to memory besides and
  * count as two kernels here and in fira_get_gate: with the same sums in the same order, so that a matrix gets the same bits
- * whatever is listed with it.  From r = 128 on both compute the same quantities with sums taken in
+ * whatever is listed with it.  So do long lists of such matrices, of any rank up to 512, none of which takes the Gram route, and with Z
+ * in two planes.  From r = 128 on both compute the same quantities with sums taken in
  * a different order, so results agree to rounding, not bit for bit.  fira_last_step_fused: 1 if the
  * last fira_step on ctx took the fused kernel for every listed matrix, 0 if not (or ctx is NULL).  A
  * fused step keeps no copy of R: fira_get_lowrank then returns what an earlier two-kernel step left
@@ -197,7 +198,7 @@ FIRA_API int fira_last_step_fused(const fira_ctx* ctx);
  * update sits next to half an ulp then moves or stays differently from exact arithmetic, one ulp per step
  * for as long as that lasts.  planes = 2: Z is kept as two bf16 planes, its rounding and the rounding of the
  * remainder (16 mantissa bits), the contraction runs over both, and W follows exact arithmetic over long
- * runs; the back-projection does twice the multiplies and the fused projection/Adam kernel is not used.
+ * runs; the back-projection does twice the multiplies, and R is left in memory (fira_set_fusion).
  * Applies to bf16 matrices with r % 4 == 0, r <= 1024 and column or no factors; others keep one plane. */
 FIRA_API fira_status fira_set_z_planes(fira_ctx* ctx, int planes);
 
@@ -291,8 +292,8 @@ FIRA_API fira_status fira_refresh_projectors_static(fira_ctx* ctx, int count, co
  * array, milliseconds), stores the number of recorded steps in *steps, and destroys the events.
  * Kernel order: fira_kernel_name(k).  Where one launch does the work of two slots, the first of them holds its
  * time and the second one nothing but what lies between two event records (about five microseconds):
- *   project + adam_norms  steps that run fused for every listed matrix (fira_last_step_fused, or 64 < r < 128 in
- *                         a long list), and lists of bf16 matrices with r <= 64; where only some of the listed
+ *   project + adam_norms  steps that run fused for every listed matrix (fira_last_step_fused, or a long
+ *                         list that leaves R, see fira_set_fusion), and lists of bf16 matrices with r <= 64; where only some of the listed
  *                         matrices do, project holds both of theirs and the others' projection
  *   limiter + make_z      lists of up to 64 matrices with a factor per row or none
  * The slots together cover the step in every case. */

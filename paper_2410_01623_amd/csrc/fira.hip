@@ -81,6 +81,7 @@ struct ListSlot {
   int panel_lds = 0;           // LDS of the panel projection's widest listed matrix, 0 if none is listed
   bool split_proj = false;     // fp32 matrices that it does not serve are listed
   bool general_bf16 = false;   // bf16 matrices that the small-rank kernel does not serve are listed
+  bool fuse_any = false, fuse_all = false;   // matrices for the fused projection/Adam kernel are listed; and none but those and the small-rank kernel's
   // device views (inside the slab)
   FiraEnt* d_ents = nullptr;
   FiraTile* d_tiles[kNumTileLists] = {};
@@ -180,7 +181,7 @@ FiraHp make_hp(const fira_ctx* ctx) {
   h.scaling = ctx->scaling;
   h.norm_mode = ctx->norm_mode;
   h.variant = ctx->variant;
-  h.fused = h.keep_r = 0;
+  h.fused = 0;
   h.ortho_tol = 0.02f;   // bf16-rounded orthonormal projectors measure ~1e-3; a projector beyond 0.02 is not meant to be orthonormal
   h.gram_tol = 2e-3f;    // measured relative error of ||S||^2 by the Gram route: 1e-3 of ||S||
   h.mixed = 0;
@@ -267,13 +268,16 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
   long long panel_groups = 0;
   s->max_r = s->max_r_bf16 = 0;
   s->panel_lds = 0;
-  s->split_proj = s->general_bf16 = false;
+  s->split_proj = s->general_bf16 = s->fuse_any = false;
+  s->fuse_all = true;
   for (int e = 0; e < count; ++e) {
     const HostMat& h = p.mats[idx[e]];
     const FiraMat& m = h.dev;
     s->max_r = std::max(s->max_r, m.r);
     if (m.kx == 1) s->max_r_bf16 = std::max(s->max_r_bf16, m.r);
     s->general_bf16 = s->general_bf16 || (m.kx == 1 && !h.small_proj);
+    s->fuse_any = s->fuse_any || h.fuse_list >= 0;
+    s->fuse_all = s->fuse_all && (h.small_proj || h.fuse_list >= 0);
     if (panel_projection(m)) {
       panel_groups += 2 * h.ta_project;
       s->panel_lds = std::max(s->panel_lds, panel_lds(m.S));
@@ -374,7 +378,9 @@ fira_status fira_init_state(fira_ctx** out, const fira_matrix_desc* d, int count
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_adam_kernel<1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FIRA_ROWS_PER_WG * FIRA_ZREADY_MAX_R * 2));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(1)));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_fused_leave_r_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(1)));
   FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_project_adam_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(2)));
+  FIRA_INIT_HIP(hipFuncSetAttribute((const void*)fira_fused_leave_r_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, FIRA_FUSE_LDS(2)));
   FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_stage_all, p.slot_bytes * kSlots, hipHostMallocDefault));
   // (kernels write it and the host waits for an event only: coherent and released to the system whatever HIP_HOST_COHERENT says)
   FIRA_INIT_HIP(hipHostMalloc((void**)&ctx->h_gate, sizeof(FiraGate) * count, hipHostMallocCoherent | hipHostMallocMapped));
@@ -600,7 +606,12 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       measures = measures || (gt.ortho_err <= hp.ortho_tol && !(gt.gram_err < INFINITY));
     }
   }
-  // The fused projection/Adam kernel serves the listed matrices on the Gram route if each of them can take
+  // The fused projection/Adam kernel serves a list of matrices that can all take it where all of them leave R in memory: on the residual route, with
+  // Z in two planes.  Two kernels and this one, residual route and two planes: 24 of 1024 x 2736 at r = 256 1245 and 1192 us, 1098 and 1046; 4 of
+  // 2048 x 5461 at r = 512 1063 and 1047, 971 and 958.  By tiles: r = 128 46.5 and 57.8, 37.4 and 49.1 (49), 71.1 and 75.4, 61.6 and
+  // 64.4 (196), 114.1 and 108.2, 97.0 and 90.8 (392); r = 256 132 and 138, 113 and 120 (196), 232 and 228, 199 and 195 (392); r = 512 304 and
+  // 296, 274 and 263 (193), 553 and 557, 500 and 502 (386).
+  // On the Gram route it serves the listed matrices if each of them can take
   // it; those on the residual route then go through the two-kernel path in the same step (hp.mixed).  Either all of them leave
   // R in memory, as small ranks do whatever the path, or none does.  Two kernels and the fused one, a step of 8 blocks of 512 x 1376, 24 of
   // 1024 x 2736 and 24 of 2048 x 5461: r = 68 87.7 and 79.6, 677 and 620, 2333 and 2236; r = 96 88.6 and 80.5, 693 and 642, 2362 and 2281;
@@ -608,8 +619,10 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   // other take longer than a second launch that deals them out (r = 96, by tiles: 25.8 and 32.6 (26), 35.5 and 42.2 (49), 49.3 and 53.5 (98),
   // 57.4 and 58.3 (147), 167.5 and 165.9 (193), 91.1 and 92.2 (196), 68.8 and 66.5 (245), 110.5 and 106.2 (294); at r = 68 and 124 the
   // fused kernel takes 1.02 and 1.00 of the two at 196 tiles, 0.96 and 0.95 at 245).
-  bool fused = ctx->fusion && !ctx->zsplit && !only_scaling && ctx->scaling == FIRA_SCALE_COLUMN && ctx->norm_mode == FIRA_NORM_GRAM && any_gram;
-  bool keep_r = false, drop_r = false, any_fused = false;
+  const bool may_fuse = ctx->fusion && !only_scaling && ctx->scaling == FIRA_SCALE_COLUMN && s->fuse_any;
+  const int fuse_tiles = s->ntiles[kTilesFuse] + s->ntiles[kTilesFuse + 1] + s->ntiles[kTilesFuse + 2] + s->ntiles[kTilesFuse + 3];
+  const bool every = may_fuse && s->fuse_all && (ctx->zsplit || !any_gram) && fuse_tiles >= kFuseMinTiles;
+  bool fused = may_fuse && !ctx->zsplit && any_gram, keep_r = every, drop_r = false, any_fused = false;
   for (int e = 0; e < count && fused; ++e) {
     const FiraGate gt = ctx->h_gate[idx[e]];
     if (!(gt.ortho_err <= hp.ortho_tol && gt.gram_err <= hp.gram_tol)) continue;
@@ -618,11 +631,10 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     (h.dev.r < FIRA_FUSE_DROP_R ? keep_r : drop_r) = true;
     fused = (h.small_proj || h.fuse_list >= 0) && !(keep_r && drop_r);
   }
-  fused = fused && any_fused && !(keep_r && s->ntiles[kTilesFuse] + s->ntiles[kTilesFuse + 1] < kFuseMinTiles);
-  const bool mixed = fused && need_residual;
+  fused = every || (fused && any_fused && !(keep_r && fuse_tiles < kFuseMinTiles));
+  const bool mixed = fused && !every && need_residual;
   ctx->last_step_fused = fused && !keep_r && !mixed;
   hp.fused = fused && !keep_r ? 1 : 0;
-  hp.keep_r = fused && keep_r ? 1 : 0;
   hp.mixed = mixed ? 1 : 0;
   launch_small(want_g2);
   if (fused) {
@@ -632,12 +644,12 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       const int nl = s->ntiles[ll], nr = s->ntiles[lr];
       if (nl + nr == 0) continue;
       const int bl = (nl + 7) / 8 * 8, br = (nr + 7) / 8 * 8;
-      if (rt == 1)
-        hipLaunchKernelGGL(fira_project_adam_kernel<1>, dim3(bl + br), dim3(256), FIRA_FUSE_LDS(1), q, ctx->d_mats, ctx->d_scal, ctx->d_scal, s->d_ents,
-                           s->d_tiles[ll], nl, bl, s->d_tiles[lr], nr, hp);
-      else
-        hipLaunchKernelGGL(fira_project_adam_kernel<2>, dim3(bl + br), dim3(512), FIRA_FUSE_LDS(2), q, ctx->d_mats, ctx->d_scal, ctx->d_scal, s->d_ents,
-                           s->d_tiles[ll], nl, bl, s->d_tiles[lr], nr, hp);
+      auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(bl + br), dim3(256 * rt), rt == 1 ? FIRA_FUSE_LDS(1) : FIRA_FUSE_LDS(2), q, ctx->d_mats, ctx->d_scal, ctx->d_scal,
+                           s->d_ents, s->d_tiles[ll], nl, bl, s->d_tiles[lr], nr, hp);
+      };
+      if (rt == 1) launch(every ? fira_fused_leave_r_kernel<1> : fira_project_adam_kernel<1>);
+      else launch(every ? fira_fused_leave_r_kernel<2> : fira_project_adam_kernel<2>);
     }
   }
   const int backwards = s->max_r > kForwardsMaxR ? 1 : 0;

@@ -139,7 +139,6 @@ struct FiraHp {     // hyper-parameters as the kernels take them
   int zsplit;       // 1: Z of the register-resident Adam rows is stored as two bf16 planes, hi + lo (K = 2 rp)
   int variant;      // 0: Algorithm 1; 1: factors on the full gradient, no Adam term ("Fira-only-scaling")
   int fused;        // 1: this step's projection and Adam ran as one kernel and no copy of R exists
-  int keep_r;       // 1: ... as one kernel that leaves a copy of R
 };
 
 // Whether matrix `sc` takes the Gram route to ||S||^2 in this step.

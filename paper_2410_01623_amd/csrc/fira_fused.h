@@ -27,8 +27,8 @@
 // assumption about the order in which loads and stores retire relative to each other, is involved.
 //
 // A step takes this kernel only if every listed matrix is bf16 with r % 4 == 0, 64 < r <= 512, column
-// factors, Algorithm 1 proper, and the Gram route to ||S|| (no operand copy of R is made here).  Lists of ranks below
-// FIRA_FUSE_DROP_R have R written to memory besides, as two kernels leave it (FiraHp::keep_r).
+// factors, Algorithm 1 proper.  On the Gram route to ||S|| R is written below FIRA_FUSE_DROP_R only.  On the residual route (with the operand
+// copy of R that it contracts) and with Z in two planes a form of its own leaves R in memory whatever the rank, as two kernels do (fira_fused_leave_r_kernel).
 // The limiter runs after it; for a matrix whose factor c came out below 1, fira_makez_kernel turns the Z
 // written here (for c = 1) into c Z + (1 - c) N, with N formed again from the updated M and V.
 #pragma once
@@ -70,9 +70,11 @@ __device__ __forceinline__ const char* scalar_pointer(const char* p) {
 
 // TM = 4: a wave's factors of a chunk are the chunk's 16.  TM = 2 (r <= 128): a chunk is 16 factors of either half of
 // the tile, 32 rows of 128 in the same LDS, and half as many chunks.
-template <int RT, int TM, bool INTERIOR>
+// KEEP: R is left in memory, and as an operand too where operand_r is set (its image has Z's place in LDS before Z has); Z has a second plane where
+// the step asks for one, whose image has it afterwards.
+template <int RT, int TM, bool INTERIOR, bool KEEP>
 __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], char* lds, const FiraMat& mt, const FiraHp& hp,
-                                                      float bias, int a_row0, const float (&sq)[TM]) {
+                                                      float bias, int a_row0, const float (&sq)[TM], bool operand_r) {
   constexpr int HALVES = 4 / TM, NW = 4 * RT / HALVES, THREADS = 256 * RT, C = 64 * NW, F = FIRA_FUSE_F * HALVES, NCHUNK = 128 / F;
   constexpr int ARR = F * C * 4;                                   // bytes of one array (M or V) of a chunk
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hi = lane >> 5;
@@ -143,6 +145,27 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
   // this lane's element (v', tn) of a chunk sits at float index (16*half + 8*(v'>>2) + 4*hi + (v'&3)) * C + 64*wcol + 32*tn + l32
   const int row_lane = 16 * half + 4 * hi, lane_idx = row_lane * C + 64 * wcol + l32;
 
+  // an operand's pieces of a chunk from their image: C/32 K blocks x F rows of 64 bytes, 2 pieces of 16 per thread
+  // (KEEP: offsets formed anew for every chunk; held over all of them, some would not fit the registers)
+  auto thread = [&] {
+    int t = threadIdx.x;
+    if (KEEP) asm volatile("" : "+v"(t));
+    return t;
+  };
+  auto store_operand_rows = [&](bf16_raw* to, int c, int kb0) {
+    const int t = thread();
+    gptr<char> out = reinterpret_cast<gptr<char>>(as_global(to));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int p = t + THREADS * i;                               // K block, quarter p % 4 of a row
+      const int kb = p / (4 * F);
+      if (INTERIOR || kb < kblocks)
+        *reinterpret_cast<gptr<u32x4>>(out + ((long long)(kb0 + kb) * mt.Lq + factor(c, (p % (4 * F)) >> 2)) * 64 + (p & 3) * 16) =
+            *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(zl) + p * 16);
+    }
+  };
+  const bool planes = KEEP && two_planes(hp, mt);
+
   // One body for all chunks, with the chunk's sixteen accumulators moved to a place of their own first (they can only be indexed
   // statically): written out per chunk the epilogue was 6 KB of code eight times over, which a workgroup of a launch of one round
   // fetched as it went; the kernels are half as long now (427 -> 422 us over the 350M shapes, 2104 -> 2094 over the 1B shapes).
@@ -176,8 +199,7 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
         const int idx = lane_idx + dr * C + 32 * tn;
         const bool ok = INTERIOR || (col < r && row_w + 4 * hi + dr < L);
         const float x = cur[tn][v];
-        // (128 bytes of a factor's row per half wave)
-        if (TM == 2 && hp.keep_r && ok) as_global(mt.Rt)[(unsigned)((row_w + 4 * hi + dr) * r + col)] = x;
+        if (KEEP && operand_r) zl[((2 * wcol + tn) * F + row_lane + dr) * 32 + l32] = f32_to_bf16(ok ? x : 0.0f);
         const float m0 = ok ? landM[idx] : 0.0f, v0 = ok ? landV[idx] : 0.0f;
         const float m1 = hp.b1 * m0 + hp.omb1 * x;
         const float v1 = hp.b2 * v0 + hp.omb2 * (x * x);
@@ -200,6 +222,7 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
       if ((lane & 3) == 0) *reinterpret_cast<float2*>(part + (wcol * F + rl_own) * 2) = float2{tn_, tr_};
     }
     __syncthreads();
+    if (KEEP && operand_r) store_operand_rows(mt.Rb, c, 0);
     if (threadIdx.x < F) {
       float snn = 0.0f, srr = 0.0f;
 #pragma unroll
@@ -219,21 +242,25 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
       ks[threadIdx.x] = k;
     }
     __syncthreads();
+    auto z_image = [&](auto plane) {                               // Z, or what its rounding leaves
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const f32x4 kq = *reinterpret_cast<const f32x4*>(ks + 8 * g + row_lane);
+      for (int g = 0; g < 2; ++g) {
+        const f32x4 kq = *reinterpret_cast<const f32x4*>(ks + 8 * g + row_lane);
 #pragma unroll
-      for (int tn = 0; tn < 2; ++tn) {
-        const int kb = 2 * wcol + tn;
+        for (int tn = 0; tn < 2; ++tn) {
+          const int kb = 2 * wcol + tn;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int v = 4 * g + e;
-          const bool ok = INTERIOR || (64 * wcol + 32 * tn + l32 < r && row_w + 8 * g + 4 * hi + e < L);
-          const float z = ok ? nv[tn][v] - kq[e] * cur[tn][v] : 0.0f;
-          zl[(kb * F + 8 * g + row_lane + e) * 32 + l32] = f32_to_bf16(z);
+          for (int e = 0; e < 4; ++e) {
+            const int v = 4 * g + e;
+            const bool ok = INTERIOR || (64 * wcol + 32 * tn + l32 < r && row_w + 8 * g + 4 * hi + e < L);
+            float z = ok ? nv[tn][v] - kq[e] * cur[tn][v] : 0.0f;
+            if (decltype(plane)::value == 1) z -= bf16_to_f32(f32_to_bf16(z));
+            zl[(kb * F + 8 * g + row_lane + e) * 32 + l32] = f32_to_bf16(z);
+          }
         }
       }
-    }
+    };
+    z_image(std::integral_constant<int, 0>{});
     __syncthreads();
     // The next chunk has landed (this wave's share of it).  The wait stands before this chunk's stores are
     // issued, so that it can be "everything": the only other operations in flight are the previous chunk's
@@ -241,10 +268,11 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
     // to let exactly their number stay in flight, which is right only if stores never retire before older
     // loads and the compiler emits exactly the instructions counted.)
     if (c + 1 < NCHUNK) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    // M and V: 2 x F rows x C/4 pieces of 16 bytes, 8 per thread; Z: C/32 K blocks x F rows of 64 bytes, 2 pieces per thread
+    // M and V: 2 x F rows x C/4 pieces of 16 bytes, 8 per thread
+    const int tx = thread();
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int arr = i >> 2, rem = threadIdx.x + THREADS * (i & 3);
+      const int arr = i >> 2, rem = tx + THREADS * (i & 3);
       const int row = rem / (C / 4), c4 = rem % (C / 4);
       const long long grow = factor(c, row);
       if (INTERIOR || (grow < L && 4 * c4 < r)) {
@@ -253,15 +281,22 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
         *reinterpret_cast<gptr<u32x4>>(dst) = val;
       }
     }
-    {
-      gptr<char> nb = reinterpret_cast<gptr<char>>(as_global(mt.Nb));
+    store_operand_rows(mt.Nb, c, 0);
+    if (KEEP || (TM == 2 && r < FIRA_FUSE_DROP_R)) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int p = threadIdx.x + THREADS * i;                   // 16-byte piece: K block, quarter p % 4 of a row
-        const int kb = p / (4 * F);
-        if (INTERIOR || kb < kblocks)
-          *reinterpret_cast<gptr<u32x4>>(nb + ((long long)kb * mt.Lq + factor(c, (p % (4 * F)) >> 2)) * 64 + (p & 3) * 16) =
-              *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(zl) + p * 16);
+      for (int tn = 0; tn < 2; ++tn) {                             // (128 bytes of a factor's row per half wave)
+        const int col = 64 * wcol + 32 * tn + l32;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+          const int row = row_w + 4 * hi + 8 * (v >> 2) + (v & 3);
+          if (INTERIOR || (col < r && row < L)) as_global(mt.Rt)[(unsigned)(row * r + col)] = cur[tn][v];
+        }
+      }
+      if (planes) {
+        __syncthreads();
+        z_image(std::integral_constant<int, 1>{});
+        __syncthreads();
+        store_operand_rows(mt.Nb, c, kblocks);
       }
     }
     // everybody's share of the next chunk has landed, and all are done reading this chunk's LDS (the stores
@@ -270,9 +305,9 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
   }
 }
 
-template <bool LEFT, int RT, int TM>
+template <bool LEFT, int RT, int TM, bool KEEP>
 __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& mt, const FiraScal* __restrict__ scal,
-                                                     const FiraEnt& ent, const FiraTile& tile, const FiraHp& hp) {
+                                                     const FiraEnt& ent, const FiraTile& tile, const FiraHp& hp, bool gram) {
   GemmOperands g;
   g.a_row0 = tile.ta * FIRA_PA;
   g.a_rows = mt.L;
@@ -312,27 +347,42 @@ __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& m
   };
   if (proj_interior(g)) run(std::integral_constant<ProjLoads, PROJ_FAST>{});
   else run(std::integral_constant<ProjLoads, PROJ_EDGE>{});        // (both sides are at least r >= FIRA_FUSE_MIN_R)
-  if (g.a_row0 + FIRA_PA <= mt.L && mt.r == 64 * TM * RT) project_adam_epilogue<RT, TM, true>(acc, lds, mt, hp, bias, g.a_row0, sq);
-  else project_adam_epilogue<RT, TM, false>(acc, lds, mt, hp, bias, g.a_row0, sq);
+  if (g.a_row0 + FIRA_PA <= mt.L && mt.r == 64 * TM * RT) project_adam_epilogue<RT, TM, true, KEEP>(acc, lds, mt, hp, bias, g.a_row0, sq, !gram);
+  else project_adam_epilogue<RT, TM, false, KEEP>(acc, lds, mt, hp, bias, g.a_row0, sq, !gram);
 }
 
 // Ranks up to 128 fill half a rank tile; their tiles multiply 64 x 64 per wave and go through
 // Adam in four chunks instead of eight (56 matrices of 512 x 512 and 512 x 1376 at r = 128: 48 us instead of 65).
-template <bool LEFT, int RT>
+template <bool LEFT, int RT, bool KEEP>
 __device__ __forceinline__ void project_adam_tile(char* lds, const FiraMat* __restrict__ mats, const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out,
                                                   const FiraEnt* __restrict__ ents, const FiraTile& tile, const FiraHp& hp) {
   const FiraEnt ent = ents[tile.ent];
-  if (!use_gram(hp, scal[ent.mat])) return;    // this matrix takes the residual route: the two-kernel path serves it
+  const bool gram = use_gram(hp, scal[ent.mat]);
+  if (!gram && !KEEP) return;    // this matrix takes the residual route: the two-kernel path serves it
   if (tile.ta == 0 && threadIdx.x == 0) set_limiter_inputs(scal_out + ent.mat, scal[ent.mat]);
   const FiraMat mt = mats[ent.mat];
-  if (RT == 1 && mt.r <= 128) project_adam_tile_as<LEFT, 1, 2>(lds, mt, scal, ent, tile, hp);
-  else project_adam_tile_as<LEFT, RT, 4>(lds, mt, scal, ent, tile, hp);
+  if (RT == 1 && mt.r <= 128) project_adam_tile_as<LEFT, 1, 2, KEEP>(lds, mt, scal, ent, tile, hp, gram);
+  else project_adam_tile_as<LEFT, RT, 4, KEEP>(lds, mt, scal, ent, tile, hp, gram);
 }
 
 // One grid for both orientations: workgroups [0, blocks_left) take the tiles of the matrices with
 // m <= n, the rest those with m > n.  With one workgroup per CU (RT = 2) a launch ends in a round that is
 // only partly filled; one launch instead of two has one such round.  blocks_left is a multiple of 8,
 // which keeps the XCD-aware mapping of each part.
+template <int RT, bool KEEP>
+__device__ __forceinline__ void project_adam_block(char* lds, const FiraMat* __restrict__ mats, const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out,
+                                                   const FiraEnt* __restrict__ ents, const FiraTile* __restrict__ tiles_left, int ntiles_left, int blocks_left,
+                                                   const FiraTile* __restrict__ tiles_right, int ntiles_right, const FiraHp& hp) {
+  if ((int)blockIdx.x < blocks_left) {
+    const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
+    if (ti < 0) return;
+    project_adam_tile<true, RT, KEEP>(lds, mats, scal, scal_out, ents, tiles_left[ti], hp);
+  } else {
+    const int ti = xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
+    if (ti < 0) return;
+    project_adam_tile<false, RT, KEEP>(lds, mats, scal, scal_out, ents, tiles_right[ti], hp);
+  }
+}
 template <int RT>
 __global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_project_adam_kernel(const FiraMat* __restrict__ mats,
                                                                                       const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out,
@@ -342,15 +392,19 @@ __global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_project_adam_k
                                                                                       const FiraTile* __restrict__ tiles_right, int ntiles_right,
                                                                                       FiraHp hp) {
   extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_FUSE_LDS(RT) bytes
-  if ((int)blockIdx.x < blocks_left) {
-    const int ti = xcd_chunked_index(blockIdx.x, ntiles_left);
-    if (ti < 0) return;
-    project_adam_tile<true, RT>(lds, mats, scal, scal_out, ents, tiles_left[ti], hp);
-  } else {
-    const int ti = xcd_chunked_index((int)blockIdx.x - blocks_left, ntiles_right);
-    if (ti < 0) return;
-    project_adam_tile<false, RT>(lds, mats, scal, scal_out, ents, tiles_right[ti], hp);
-  }
+  project_adam_block<RT, false>(lds, mats, scal, scal_out, ents, tiles_left, ntiles_left, blocks_left, tiles_right, ntiles_right, hp);
+}
+// The same with R left behind (KEEP), on every route, for lists whose matrices all do that.
+template <int RT>
+__global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_fused_leave_r_kernel(const FiraMat* __restrict__ mats,
+                                                                                       const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out,
+                                                                                       const FiraEnt* __restrict__ ents,
+                                                                                       const FiraTile* __restrict__ tiles_left, int ntiles_left,
+                                                                                       int blocks_left,
+                                                                                       const FiraTile* __restrict__ tiles_right, int ntiles_right,
+                                                                                       FiraHp hp) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_FUSE_LDS(RT) bytes
+  project_adam_block<RT, true>(lds, mats, scal, scal_out, ents, tiles_left, ntiles_left, blocks_left, tiles_right, ntiles_right, hp);
 }
 
 // ------------------------------------------------------------------------------------------------
