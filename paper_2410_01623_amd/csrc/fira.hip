@@ -69,6 +69,8 @@ constexpr int kQuarterTiles = 1536, kQuarterTilesLongRank = 384;
 constexpr int kLimitAndZ = 64;
 // Tiles of a list from which on the fused projection/Adam kernel serves ranks that leave R in memory (fira_step has both sides).
 constexpr int kFuseMinTiles = 200;
+// Tiles of a list's Gram matrices, all of small ranks, up to which they are summed in parts side by side (fira_refresh_gram_kernel).
+constexpr int kGramTilesInParts = 256;
 
 struct ListSlot {
   std::vector<int> idx;
@@ -989,7 +991,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   FiraMat* vmats = (FiraMat*)(ctx->h_refresh + rp.off_vmats);
   FiraEnt* vents = (FiraEnt*)(ctx->h_refresh + rp.off_vents);
   FiraTile* vtiles[2] = {(FiraTile*)(ctx->h_refresh + rp.off_vtiles[0]), (FiraTile*)(ctx->h_refresh + rp.off_vtiles[1])};
-  int max_S = 0, max_r = 0;
+  int max_S = 0, max_r = 0, min_r = INT32_MAX;
   for (int e = 0; e < count; ++e) {
     const FiraMat& m = ctx->plan.mats[idx[e]].dev;
     FiraRefreshEnt& re = ents[e];
@@ -1005,7 +1007,7 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
     // ... which is left out for a matrix whose basis is orthonormal already, to the accuracy its storage can hold
     ents2[e].done = (int*)(ws + rp.off_done) + e;
     ents2[e].done_tol = m.kx == 1 ? 1e-4f : 1e-6f;
-    max_S = std::max(max_S, m.S); max_r = std::max(max_r, m.r);
+    max_S = std::max(max_S, m.S); max_r = std::max(max_r, m.r); min_r = std::min(min_r, m.r);
     // The way back, Y[s][a] = sum_i G(s, i) T[i][a], is the projection kernel on the other orientation
     // of the same gradient: long side L' = S, contraction over S' = L, operand "PT" = Top, output "Rt" = Y.
     FiraMat& v = vmats[e];
@@ -1052,9 +1054,14 @@ fira_status refresh_run(fira_ctx* ctx, int count, const int* idx, const void* co
   const int nt64 = (max_r + 63) / 64;
   const int prep_blocks = prep_tiles(max_S, max_r);
   auto orthonormalise = [&](const FiraRefreshEnt* de) {
-    hipLaunchKernelGGL(fira_refresh_gram_kernel, dim3(nt64 * (nt64 + 1) / 2, count), dim3(256), 0, q, de);
+    // (a first pass over a list of few tiles sums in parts that run side by side)
+    const int nt_small = (std::min(max_r, FIRA_CHOL_SMALL_R) + 63) / 64;
+    const int parts = max_r <= FIRA_CHOL_SMALL_R && de == d_ents && count * nt_small * (nt_small + 1) / 2 <= kGramTilesInParts ? FIRA_GRAM_PARTS : 1;
+    if (min_r <= FIRA_CHOL_SMALL_R)
+      hipLaunchKernelGGL(fira_refresh_gram_kernel<true>, dim3(nt_small * (nt_small + 1) / 2, count, parts), dim3(256), 0, q, de, parts);
+    if (max_r > FIRA_CHOL_SMALL_R) hipLaunchKernelGGL(fira_refresh_gram_kernel<false>, dim3(nt64 * (nt64 + 1) / 2, count), dim3(256), 0, q, de, 1);
     if (max_r <= FIRA_CHOL_SMALL_R) {
-      hipLaunchKernelGGL(fira_refresh_chol_small_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), FIRA_CHOL_SMALL_LDS, q, de);
+      hipLaunchKernelGGL(fira_refresh_chol_small_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), FIRA_CHOL_SMALL_LDS, q, de, parts);
     } else {
       const int rows = std::min(FIRA_CHOL_ROWS, round_up_int(max_r, FIRA_CHOL_NB));
       hipLaunchKernelGGL(fira_refresh_chol_kernel, dim3(count), dim3(FIRA_CHOL_THREADS), (size_t)rows * FIRA_CHOL_PITCH * 8, q, de);

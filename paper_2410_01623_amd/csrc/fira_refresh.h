@@ -232,10 +232,26 @@ __global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRe
 // registers before the current one is multiplied.  What is not a multiply on the matrix pipe costs here: with the
 // register count left to the compiler it kept the sums in the other half of the register file between stages and moved all
 // of them there and back per stage (168 matrices of 2048 rows at r = 512: 1.82 ms, 2.04 before; five workgroups per CU).
+// SMALL: the matrices with r <= FIRA_CHOL_SMALL_R, whose rows are summed in four parts, one after the other or, in lists of few tiles (parts = 4), by a workgroup
+// each: a multiply of a wavefront that has its SIMD to itself takes 136 cycles, of two that share it 99 each, so that tiles which leave the chip
+// idle wait for their own chain.  The parts lie in C, in Q, which the solve has yet to write, and in Top, which the way back has read; the factorisation adds
+// them up in the same order.  (56 matrices of 512 rows at r = 128: 32 us for a workgroup per
+// tile, 23 for four.  A refresh step in one part and in four: 28 matrices of 256 x 688 at r = 64 233 and 220 us; r = 128, 14 of 512 x 1376 362 and 333, 56
+// 495 and 485, 84 of 1024 x 2736 1361 and 1344, 168 of 512 x 1376 1005 and 1021.)
 #define FIRA_GRAM_KS 32
-__global__ __launch_bounds__(256, 5) void fira_refresh_gram_kernel(const FiraRefreshEnt* __restrict__ ents) {
+#define FIRA_GRAM_PARTS 4
+// Whether a matrix's Gram matrix lies in parts (where there is room for them), and where part 1 .. 3 does.
+__device__ __forceinline__ bool gram_in_parts(const FiraRefreshEnt& e, int parts) {
+  return parts == FIRA_GRAM_PARTS && !e.done && e.r <= FIRA_CHOL_SMALL_R && e.S >= 2 * e.r && (long long)e.Lp * e.rq >= 8 * e.r * e.r;
+}
+__device__ __forceinline__ gptr<double> gram_part(const FiraRefreshEnt& e, int part) {
+  return part == 1 ? reinterpret_cast<gptr<double>>(as_global(e.Q)) : reinterpret_cast<gptr<double>>(as_global(e.Top)) + (part - 2) * e.r * e.r;
+}
+template <bool SMALL>
+__global__ __launch_bounds__(256, SMALL ? 4 : 5) void fira_refresh_gram_kernel(const FiraRefreshEnt* __restrict__ ents, int parts) {
   __shared__ __attribute__((aligned(16))) float sa[FIRA_GRAM_KS * FIRA_STAGE_LD], sb[FIRA_GRAM_KS * FIRA_STAGE_LD];
   const FiraRefreshEnt e = ents[blockIdx.y];
+  if ((e.r <= FIRA_CHOL_SMALL_R) != SMALL) return;
   if (e.done && !(*as_global<const int>(e.done) & FIRA_PASS_UNSURE)) return;
   const int nt = (e.r + 63) / 64;
   // linear index -> (ta >= tb)
@@ -243,9 +259,12 @@ __global__ __launch_bounds__(256, 5) void fira_refresh_gram_kernel(const FiraRef
   while (ta < nt && rem > ta) { rem -= ta + 1; ++ta; }
   if (ta >= nt) return;
   const int tb = rem;
+  const bool own = SMALL && gram_in_parts(e, parts);        // this workgroup has a part of its own
+  const int part = own ? (int)blockIdx.z : 0;
+  if (SMALL && !own && blockIdx.z > 0) return;
   gptr<const float> Y = as_global<const float>(e.Y);
   const int t = threadIdx.x;
-  RefreshAcc acc;
+  RefreshAcc acc, sum;
   refresh_acc_zero(acc);
   const bool upper = ta == tb && (t >> 6) == 1;      // the wave above the diagonal: nobody stores its block
   f32x4 ra[2], rb[2];
@@ -257,8 +276,21 @@ __global__ __launch_bounds__(256, 5) void fira_refresh_gram_kernel(const FiraRef
       rb[p] = refresh_load4(Y, s0 + sl, tb * 64 + c4, e.S, e.r, e.r);
     }
   };
-  fetch(0);
-  for (int s0 = 0; s0 < e.S; s0 += FIRA_GRAM_KS) {
+  // rows of a part: a quarter of them in whole stages
+  const int rows = ((e.S + FIRA_GRAM_PARTS - 1) / FIRA_GRAM_PARTS + FIRA_GRAM_KS - 1) / FIRA_GRAM_KS * FIRA_GRAM_KS;
+  const int begin = own ? part * rows : 0, end = own ? min(begin + rows, e.S) : e.S;
+  if (SMALL) refresh_acc_zero(sum);
+  fetch(begin);
+  int until = begin + rows;
+  for (int s0 = begin; s0 < end; s0 += FIRA_GRAM_KS) {
+    if (SMALL && s0 == until) {                      // one part after the other: the parts' sums are added up as the factorisation adds them
+      until += rows;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) sum.v[i][j] += acc.v[i][j];
+      refresh_acc_zero(acc);
+    }
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       const int x = t + 256 * p, sl = x >> 4, c4 = (x & 15) * 4;
@@ -266,11 +298,17 @@ __global__ __launch_bounds__(256, 5) void fira_refresh_gram_kernel(const FiraRef
       *reinterpret_cast<f32x4*>(&sb[sl * FIRA_STAGE_LD + c4]) = rb[p];
     }
     __syncthreads();
-    if (s0 + FIRA_GRAM_KS < e.S) fetch(s0 + FIRA_GRAM_KS);
+    if (s0 + FIRA_GRAM_KS < end) fetch(s0 + FIRA_GRAM_KS);
     if (!upper) refresh_acc_steps<FIRA_GRAM_KS>(acc, sa, FIRA_STAGE_LD, 1, sb, FIRA_STAGE_LD, 1);
     __syncthreads();
   }
-  gptr<double> C = as_global(e.C);
+  if (SMALL) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc.v[i][j] = sum.v[i][j] + acc.v[i][j];
+  }
+  gptr<double> C = part == 0 ? as_global(e.C) : gram_part(e, part);
   bool off = false;
   refresh_acc_foreach(acc, [&](int row, int col, double v) {
     const int ra_ = ta * 64 + row, cb = tb * 64 + col;
@@ -583,7 +621,7 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
 // of columns 64 .. 127 take the inverses of the 32 x 32 triangles; when the factor has left, the quarter below takes the products.
 #define FIRA_CHOL_SMALL_PITCH (FIRA_CHOL_SMALL_R + 1)
 #define FIRA_CHOL_SMALL_LDS (FIRA_CHOL_SMALL_R * FIRA_CHOL_SMALL_PITCH * 8)
-__global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_small_kernel(const FiraRefreshEnt* __restrict__ ents) {
+__global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_small_kernel(const FiraRefreshEnt* __restrict__ ents, int parts) {
   constexpr int NB = FIRA_CHOL_NB, P = FIRA_CHOL_SMALL_PITCH, N = FIRA_CHOL_SMALL_R, WAVES = FIRA_CHOL_THREADS / 64;
   __shared__ double red[WAVES];
   extern __shared__ __attribute__((aligned(16))) double chol_a[];
@@ -595,22 +633,33 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_small_ker
   double* X = chol_a + 64;                            // the inverse of triangle w: X[(32 (w >> 1) + i) P + 32 (w & 1) + c]
   double mx = 0.0;
   {
-    constexpr int PASSES = N * N / FIRA_CHOL_THREADS, AT_ONCE = 16;
+    constexpr int PASSES = N * N / FIRA_CHOL_THREADS;
+    auto load = [&](auto at_once, auto in_parts) {       // AT values of a thread at a time, and the other parts', in flight
+      constexpr int AT = decltype(at_once)::value, MORE = decltype(in_parts)::value ? FIRA_GRAM_PARTS - 1 : 0;
 #pragma unroll
-    for (int g = 0; g < PASSES; g += AT_ONCE) {
-      double v[AT_ONCE];
+      for (int g = 0; g < PASSES; g += AT) {
+        double v[MORE + 1][AT];
 #pragma unroll
-      for (int q = 0; q < AT_ONCE; ++q) {
-        const int x = t + FIRA_CHOL_THREADS * (g + q), i = x / N, k = x % N;
-        v[q] = k <= i && i < r ? C[(unsigned)(i * r + k)] : (i == k ? 1.0 : 0.0);
+        for (int p = 0; p <= MORE; ++p) {
+          gptr<const double> from = p == 0 ? (gptr<const double>)C : (gptr<const double>)gram_part(e, p);
+#pragma unroll
+          for (int q = 0; q < AT; ++q) {
+            const int x = t + FIRA_CHOL_THREADS * (g + q), i = x / N, k = x % N;
+            v[p][q] = k <= i && i < r ? from[(unsigned)(i * r + k)] : (i == k && p == 0 ? 1.0 : 0.0);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < AT; ++q) {
+          const int x = t + FIRA_CHOL_THREADS * (g + q), i = x / N, k = x % N;
+#pragma unroll
+          for (int p = 1; p <= MORE; ++p) v[0][q] += v[p][q];
+          chol_a[i * P + k] = v[0][q];
+          if (i == k && i < r) mx = fmax(mx, v[0][q]);
+        }
       }
-#pragma unroll
-      for (int q = 0; q < AT_ONCE; ++q) {
-        const int x = t + FIRA_CHOL_THREADS * (g + q), i = x / N, k = x % N;
-        chol_a[i * P + k] = v[q];
-        if (i == k && i < r) mx = fmax(mx, v[q]);
-      }
-    }
+    };
+    if (gram_in_parts(e, parts)) load(std::integral_constant<int, 8>{}, std::true_type{});
+    else load(std::integral_constant<int, 16>{}, std::false_type{});
   }
   const double floor_piv = chol_floor(mx, red);
   if (r32 < 64 * blocks)                              // the last 64 columns' second triangle is past the end
