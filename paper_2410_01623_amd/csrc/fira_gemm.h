@@ -894,7 +894,8 @@ __device__ __forceinline__ void project_split_tile(char* lds, const FiraMat& mt,
 }
 
 // bf16 matrices: TM = 2 where the rank fits half a rank tile (64 < r <= 128 in a step; a refresh also brings smaller
-// ones), else 4.  (Both orientations of 56 matrices of 512 x 512 and 512 x 1376 at r = 128: 31 us; 38 us with TM = 4.)
+// ones), else 4.  (Both orientations of 56 matrices of 512 x 512 and 512 x 1376 at r = 128: 31 us; 38 us with TM = 4; 22 since edge tiles keep
+// their loads in flight.)
 template <bool LEFT, int TM>
 __device__ __forceinline__ void project_tile_as(char* lds, const FiraMat& mt, const FiraEnt& ent, const FiraTile& tile, int norm_mode, int pack) {
   GemmOperands g;
