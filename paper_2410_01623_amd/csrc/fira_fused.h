@@ -352,7 +352,7 @@ __device__ __forceinline__ void project_adam_tile_as(char* lds, const FiraMat& m
 }
 
 // Ranks up to 128 fill half a rank tile; their tiles multiply 64 x 64 per wave and go through
-// Adam in four chunks instead of eight (56 matrices of 512 x 512 and 512 x 1376 at r = 128: 48 us instead of 65; 33 since edge tiles keep their loads
+// Adam in four chunks instead of eight (56 matrices of 512 x 512 and 512 x 1376 at r = 128: 48 us instead of 65; 40 since edge tiles keep their loads
 // in flight).
 template <bool LEFT, int RT, bool KEEP>
 __device__ __forceinline__ void project_adam_tile(char* lds, const FiraMat* __restrict__ mats, const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out,

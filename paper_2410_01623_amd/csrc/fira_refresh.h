@@ -614,8 +614,8 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
 }
 
 // Factorisation and the inverses of its diagonal blocks in one launch for ranks up to 128 (lists of nothing larger), whose whole matrix fits
-// in LDS: the kernels above and below go through memory between their steps.  The same operations in the same order.  56 matrices of r = 128: 38 us;
-// 98 with one row per thread below a block and the inverses formed afterwards, a step each for every column (a refresh of 8 blocks of 512 x 1376
+// in LDS: the kernels above and below go through memory between their steps.  The same operations in the same order.  56 matrices of r = 128: 38 us, 42
+// with the parts of the Gram matrices to add up; 98 with one row per thread below a block and the inverses formed afterwards, a step each for every column (a refresh of 8 blocks of 512 x 1376
 // 683 -> 559 us).
 // LDS: the factor in rows of FIRA_CHOL_SMALL_PITCH (an odd number of doubles), identity past r.  Of the half above the diagonal, rows 0 .. 63
 // of columns 64 .. 127 take the inverses of the 32 x 32 triangles; when the factor has left, the quarter below takes the products.
