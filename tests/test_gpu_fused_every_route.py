@@ -38,6 +38,23 @@ def test_fused_kernel_on_every_route(m, n, r, option):
     assert np.abs(a - b).max() <= 4 * 2.0 ** -8 * np.abs(b).max() and np.linalg.norm(a - b) <= 5e-4 * np.linalg.norm(b)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("option", [dict(norm_mode=fira.FIRA_NORM_RESIDUAL), dict(norm_mode=fira.FIRA_NORM_GRAM, z_planes=2)], ids=["residual", "planes"])
+@pytest.mark.parametrize("m,n,r", [(130, 1700, 68), (1665, 129, 124), (161, 1600, 96)])
+def test_what_else_is_listed_does_not_show(m, n, r, option):
+    """Below r = 128 both kernels take the same sums in the same order: the same bits in everything that a step leaves, in a list long enough for the
+    fused kernel, in the same list in two kernels, and by itself."""
+    count = -(-FILL // -(-max(m, n) // 128))
+    left = []
+    for shapes, kw in [([(m, n)] * count, {}), ([(m, n)] * count, dict(fusion=False)), ([(m, n)], {})]:
+        res = run(shapes, [r] * len(shapes), fira.FIRA_BF16, m + n, [0], **option, **kw)
+        M, V, s_prev, _ = res.ctx.fira_get_state(0)
+        left.append(dict(W=H.to_host(res.W_dev[0]), M=M.numpy(), V=V.numpy(), R=res.ctx.fira_get_lowrank(0).numpy(), k=res.ctx.fira_get_factors(0).numpy(),
+                         s=np.array([s_prev, *res.ctx.fira_get_diag(0)])))
+    for other in left[1:]:
+        assert {name: int(np.sum(left[0][name] != other[name])) for name in left[0]} == {name: 0 for name in left[0]}
+
+
 def test_registers_of_asynchronous_loads(tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
