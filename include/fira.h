@@ -182,10 +182,10 @@ FIRA_API fira_status fira_set_variant(fira_ctx* ctx, fira_variant variant);
  * installed) run them as two kernels with R in memory in the same step.  Any other step, and every
  * step with enable == 0, runs two kernels for all (bf16 matrices with r <= 64: one, which leaves R in memory as two do).
  * Lists of 64 < r < 128 run fused as well where they are long enough for it to pay, but have R written to memory besides and
- * count as two kernels here and in fira_get_gate: with the same sums in the same order, so that a matrix gets the same bits
- * whatever is listed with it.  So do long lists of such matrices, of any rank up to 512, none of which takes the Gram route, and with Z
- * in two planes.  From r = 128 on both compute the same quantities with sums taken in
- * a different order, so results agree to rounding, not bit for bit.  fira_last_step_fused: 1 if the
+ * count as two kernels here and in fira_get_gate.  The same holds for long lists of ranks 64 < r <= 512, r % 4 == 0, with Z in two
+ * planes, or none of whose matrices takes the Gram route.  Both ways take the same sums in the same order, so a matrix gets the same bits
+ * whatever is listed with it, with one exception: where the limiter cuts a step (c < 1) that kept no R, Z is formed from what the fused kernel left
+ * of it, and results agree to its rounding.  fira_last_step_fused: 1 if the
  * last fira_step on ctx took the fused kernel for every listed matrix, 0 if not (or ctx is NULL).  A
  * fused step keeps no copy of R: fira_get_lowrank then returns what an earlier two-kernel step left
  * (zeros if there was none). */

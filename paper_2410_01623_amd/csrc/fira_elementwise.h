@@ -222,6 +222,35 @@ __device__ __forceinline__ void bf16_planes(const f32x4& z, int planes, u32x2 (&
   }
 }
 
+// Sums of the squares of 64 consecutive values of a row, four to a lane of a row of 16 lanes and zeros past the end, in the order in which the fused
+// projection/Adam kernel takes them: columns 32 apart (lanes 8 apart) in one lane, then by 16, 8 and 4 (lanes), 2 and 1 (a lane's four). At every
+// step across lanes but the last ones each lane goes on with half of its values.
+__device__ __forceinline__ float square_sum_of_64(const f32x4& x) {
+  const bool upper = (threadIdx.x & 8) != 0, odd = (threadIdx.x & 4) != 0;
+  float s[2];                                   // of values e, or 2 + e in the upper lanes
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const float keep = upper ? x[2 + e] : x[e], got = lane_xor<8>(upper ? x[e] : x[2 + e]);
+    const float lo = upper ? got : keep, hi = upper ? keep : got;
+    s[e] = __builtin_fmaf(lo, lo, hi * hi);
+  }
+  const float t = add_xor<1>(add_xor<2>((odd ? s[1] : s[0]) + lane_xor<4>(odd ? s[0] : s[1])));
+  return add_xor<4>(add_xor<8>(t));
+}
+// Such sums of a row of up to 128 values in a half wave, and of up to 256 NIT in a wavefront (one after the other, as that kernel adds its waves' up).
+__device__ __forceinline__ float square_sum_as_fused(const f32x4& x) { return add_xor<16>(square_sum_of_64(x)); }
+template <int NIT>
+__device__ __forceinline__ float square_sum_as_fused(const f32x4 (&x)[NIT]) {
+  float sum = 0.0f;
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int part = (int)__float_as_uint(square_sum_of_64(x[it]));
+#pragma unroll
+    for (int w = 0; w < 4; ++w) sum += __uint_as_float((unsigned)__builtin_amdgcn_readlane(part, 16 * w));
+  }
+  return sum;
+}
+
 // Same update for matrices with r <= FIRA_ZREADY_MAX_R (fp32: FIRA_ZREADY_MAX_R_F32): the factor's N
 // and R stay in registers until k_i is known, and the row is written once as the back-projection operand for
 // an inactive limiter, Z_i = N_i - k_i R_i, rounded from fp32 a single time.  R is written as an
@@ -230,6 +259,8 @@ __device__ __forceinline__ void bf16_planes(const f32x4& z, int planes, u32x2 (&
 // 1 KB contiguous pieces (fira_adam_kernel).  fp32 matrices move 26 bytes per element here; with N and R written
 // as planes and turned into Z by a pass of their own it was 92 (350M shapes at r = 256: 916 + 602 -> 364 us).
 // rl: the same image of R for bf16 matrices on the residual route (null: R goes out from here, in 64-byte pieces).
+// AS_FUSED: ranks whose lists take the fused projection/Adam kernel or this one by their length and by what else they hold.  What a matrix gets
+// must not depend on that, so the two norms are summed as that kernel sums them.
 template <int KX, int NIT, bool ODD>   // 256 * NIT >= r; ODD: r is no multiple of four
 __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp& hp, float bias, long long row, bool gram,
                                                 bf16_raw* zl, bf16_raw* rl, int rowlocal, bool leave) {
@@ -239,11 +270,13 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
   gptr<float> M = as_global(mt.M) + row * r;
   gptr<float> V = as_global(mt.V) + row * r;
   gptr<bf16_raw> Rb = as_global(mt.Rb);
+  constexpr bool AS_FUSED = KX == 1 && !ODD && 256 * NIT <= FIRA_FUSE_MAX_R;
   float nn = 0.0f, rr = 0.0f;
   f32x4 nv[NIT], rv[NIT];
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int a = lane * 4 + 256 * it;
+    if (AS_FUSED) nv[it] = rv[it] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (a < r) {
       auto load = [&](gptr<const float> p) { return ODD ? load_row4_inside(p, a, r) : (f32x4)*reinterpret_cast<gptr<const f32x4>>(p + a); };
       rv[it] = load(R);
@@ -253,15 +286,22 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
         mv[e] = hp.b1 * mv[e] + hp.omb1 * rv[it][e];
         vv[e] = hp.b2 * vv[e] + hp.omb2 * (rv[it][e] * rv[it][e]);
         nv[it][e] = adam_direction(mv[e], vv[e], bias, hp.epsf);
-        nn += nv[it][e] * nv[it][e];
-        rr += rv[it][e] * rv[it][e];
+        if (!AS_FUSED) {
+          nn += nv[it][e] * nv[it][e];
+          rr += rv[it][e] * rv[it][e];
+        }
       }
       store_row4(M + a, mv, ODD ? r - a : 4);
       store_row4(V + a, vv, ODD ? r - a : 4);
     }
   }
-  nn = wave_sum(nn);
-  rr = wave_sum(rr);
+  if constexpr (AS_FUSED) {
+    nn = square_sum_as_fused(nv);
+    rr = square_sum_as_fused(rv);
+  } else {
+    nn = wave_sum(nn);
+    rr = wave_sum(rr);
+  }
   const float k = (hp.scaling == 2) ? 1.0f : sqrtf(nn) / (sqrtf(rr) + hp.epsf);
   const int planes = z_planes<KX>(hp, mt), plane_off = (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32);   // planes of the LDS image
 #pragma unroll
@@ -299,25 +339,8 @@ __device__ __forceinline__ void adam_row_zready(const FiraMat& mt, const FiraHp&
   }
 }
 
-// Sum of the squares of a row of up to 128 values, four to a lane of a half wave and zeros past the end, in the order in which the fused
-// projection/Adam kernel takes it: columns 32 apart (lanes 8 apart) in one lane, then by 16, 8 and 4 (lanes), 2 and 1 (a lane's four), then the
-// halves of 64.  At every step across lanes but the last ones each lane goes on with half of its values.
-__device__ __forceinline__ float square_sum_as_fused(const f32x4& x) {
-  const bool upper = (threadIdx.x & 8) != 0, odd = (threadIdx.x & 4) != 0;
-  float s[2];                                   // of values e, or 2 + e in the upper lanes
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const float keep = upper ? x[2 + e] : x[e], got = lane_xor<8>(upper ? x[e] : x[2 + e]);
-    const float lo = upper ? got : keep, hi = upper ? keep : got;
-    s[e] = __builtin_fmaf(lo, lo, hi * hi);
-  }
-  const float t = add_xor<1>(add_xor<2>((odd ? s[1] : s[0]) + lane_xor<4>(odd ? s[0] : s[1])));
-  return add_xor<16>(add_xor<4>(add_xor<8>(t)));
-}
-
 // Rows of few values: LPR lanes to a row, so that a wavefront takes 64 / LPR rows at once.  16 for fp32 matrices with r <= 64; 32 for bf16 ones with
-// 64 < r < FIRA_FUSE_DROP_R, r a multiple of four, whose lists take the fused kernel or this one by their length: what a matrix
-// gets must not depend on what else is listed, so the two norms are summed as that kernel sums them.
+// 64 < r <= 128, r a multiple of four (whose norms are summed as the fused kernel sums them, see AS_FUSED above).
 // Bound by instructions in short lists and by memory in long ones.  A row at a time, half the lanes idle, and two at a time, a step at r = 96 of one block of
 // 256 x 688 28.9 and 26.4 us, two of 512 x 1376 53.3 and 49.7, 24 of 1024 x 2736 on the residual route 903 and 854 and in two planes 802 and 743.
 template <int KX, int LPR>   // 4 LPR >= r
@@ -422,7 +445,7 @@ __global__ __launch_bounds__(256, 4) void fira_adam_kernel(const FiraMat* __rest
   const bool staged = STAGE_R && zready && !gram && mt.r <= FIRA_RSTAGE_MAX_R;
   bf16_raw* rl = staged ? zl + planes * (mt.rp >> 5) * (FIRA_ROWS_PER_WG * 32) : nullptr;
   constexpr int LPR = KX == 1 ? 32 : 16;
-  if (zready && (KX == 1 ? mt.r < FIRA_FUSE_DROP_R && (mt.r & 3) == 0 : mt.r <= 64)) {
+  if (zready && mt.r <= 4 * LPR && (KX != 1 || (mt.r & 3) == 0)) {
     for (int i = 0; i < 4; i += 64 / LPR) adam_rows_short<KX, LPR>(mt, hp, bias, row_base + i, gram, zl, rl, wave, i);
   } else if (zready) {
     auto rows = [&](auto nit, auto odd) __attribute__((always_inline)) {

@@ -189,8 +189,6 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
     if (c + 1 < NCHUNK) request(c + 1);
     float nv[2][8], nn[8], rr[8];
 #pragma unroll
-    for (int v = 0; v < 8; ++v) nn[v] = rr[v] = 0.0f;
-#pragma unroll
     for (int tn = 0; tn < 2; ++tn) {
       const int col = 64 * wcol + 32 * tn + l32;
 #pragma unroll
@@ -208,13 +206,9 @@ __device__ __forceinline__ void project_adam_epilogue(f32x16_t (&acc)[TM][2], ch
         landM[idx] = m1;
         landV[idx] = v1;
         nv[tn][v] = n;
-        if (TM == 2 && !INTERIOR) {      // (r < 128 among them: spelled out, for square_sum_as_fused to take the same sums)
-          nn[v] = tn == 0 ? n : __builtin_fmaf(nn[v], nn[v], n * n);
-          rr[v] = tn == 0 ? x : __builtin_fmaf(rr[v], rr[v], x * x);
-        } else {
-          nn[v] += n * n;
-          rr[v] += x * x;
-        }
+        // (spelled out, for square_sum_as_fused to take the same sums)
+        nn[v] = tn == 0 ? n : __builtin_fmaf(nn[v], nn[v], n * n);
+        rr[v] = tn == 0 ? x : __builtin_fmaf(rr[v], rr[v], x * x);
       }
     }
     {
