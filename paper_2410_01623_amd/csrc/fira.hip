@@ -67,8 +67,37 @@ constexpr int kForwardsMaxR = 64;
 constexpr int kQuarterTiles = 1536, kQuarterTilesLongRank = 384;
 // Listed matrices up to which the limiter and Z are one launch (fira_limit_and_makez_kernel has both sides measured).
 constexpr int kLimitAndZ = 64;
-// Tiles of a list from which on the fused projection/Adam kernel serves ranks that leave R in memory (fira_step has both sides).
+// Tiles of a list from which on the fused projection/Adam kernel serves ranks below FIRA_FUSE_DROP_R on the Gram route (fira_step has both sides).
 constexpr int kFuseMinTiles = 200;
+
+// Share, in 32nds, of the workgroups that run at once which a launch of fira_fused_leave_r_kernel has to fill, on average over its rounds, for
+// a matrix of rank r to gain by it; more than 32: it never does.  Two kernels and this one, us a step on the residual route and in two planes:
+//   a rank of its tile's whole width, which the epilogue works through without bounds checks
+//     r = 128  512 x 1376: 105 and 106, 88 and 92 (22/32); 113 and 111, 94 and 94 (24/32); 125 and 120, 105 and 102 (28/32)
+//              1024 x 2736: 143 and 142, 120 and 121 (20/32); 165 and 161, 137 and 134 (24/32); 211 and 199, 173 and 159 (32/32); 273 and 269, 228 and 222 (20/32 of two rounds)
+//     r = 256  512 x 1376: 168 and 173, 152 and 153 (24/32); 187 and 183, 174 and 167 (28/32).  1024 x 2736: 219 and 219, 193 and 190 (22/32); 231 and 230, 207 and 201 (24/32);
+//              265 and 255, 231 and 217 (28/32)
+//              2048 x 5461: 390 and 383, 327 and 320 (24/32); two rounds: 556 and 554, 472 and 462 (18/32); 741 and 746, 632 and 621 (25/32)
+//     r = 512  1024 x 2736: 173 and 170, 155 and 156 (20/32); 197 and 186, 175 and 171 (24/32); 250 and 274, 227 and 250 (one more than a round); 360 and 357, 327 and 324 (24/32 of two)
+//              2048 x 5461: 252 and 258, 226 and 233 (19/32); 318 and 314, 285 and 283 (25/32); 478 and 498, 425 and 443 (20/32 of two)
+//   a narrower one, whose tiles take about as long as whole ones
+//     r = 68   512 x 1376: 112 and 114, 98 and 100 (28/32); 126 and 123, 109 and 107 (32/32)
+//     r = 112  512 x 1376: 118 and 118, 101 and 103 (27/32); 122 and 121, 105 and 104 (29/32)
+//     r = 240  512 x 1376: 188 and 189, 175 and 174 (29/32); 199 and 198, 187 and 183 (31/32).  1024 x 2736: 525 and 520, 465 and 452 (30/32 of two)
+//     r = 224  1024 x 2736: 522 and 522, 470 and 461 (32/32 of two).  2048 x 5461: 889 and 893, 768 and 763 (32/32 of two)
+//     r = 192  1024 x 2736: 260 and 263, 226 and 224 (32/32)
+//     r = 480  1024 x 2736: 411 and 415, 386 and 385 (29/32 of two); 426 and 424, 398 and 395 (31/32 of two)
+//     r = 448  1024 x 2736: 406 and 412, 373 and 379 (31/32 of two);  r = 320  356 and 377, 321 and 337 (32/32 of two)
+int leave_r_fill(int r) {
+  const int width = r <= 128 ? 128 : r <= 256 ? 256 : 512;
+  if (r == width) return 24;
+  return width == 128 || 16 * r >= 15 * width ? 30 : 33;
+}
+// Whether its launch over nl + nr tiles (their parts start anew on every XCD) fills as much; rt rank tiles leave room for 2 / rt workgroups on a CU.
+bool leave_r_fills(int nl, int nr, int rt, int share) {
+  const int each = (nl + 7) / 8 + (nr + 7) / 8, at_once = kComputeUnits / 8 * 2 / rt;
+  return each == 0 || 32LL * each >= (long long)share * ((each + at_once - 1) / at_once) * at_once;
+}
 // Tiles of a list's Gram matrices, all of small ranks, up to which they are summed in parts side by side (fira_refresh_gram_kernel).
 constexpr int kGramTilesInParts = 256;
 
@@ -83,7 +112,8 @@ struct ListSlot {
   int panel_lds = 0;           // LDS of the panel projection's widest listed matrix, 0 if none is listed
   bool split_proj = false;     // fp32 matrices that it does not serve are listed
   bool general_bf16 = false;   // bf16 matrices that the small-rank kernel does not serve are listed
-  bool fuse_any = false, fuse_all = false;   // matrices for the fused projection/Adam kernel are listed; and none but those and the small-rank kernel's
+  bool fuse_any = false;       // matrices for the fused projection/Adam kernel are listed
+  bool leave_r = false;        // ... none but those and the small-rank kernel's, and they gain by it where all of them leave R in memory
   // device views (inside the slab)
   FiraEnt* d_ents = nullptr;
   FiraTile* d_tiles[kNumTileLists] = {};
@@ -271,7 +301,8 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
   s->max_r = s->max_r_bf16 = 0;
   s->panel_lds = 0;
   s->split_proj = s->general_bf16 = s->fuse_any = false;
-  s->fuse_all = true;
+  s->leave_r = true;
+  int fill[2] = {0, 0};
   for (int e = 0; e < count; ++e) {
     const HostMat& h = p.mats[idx[e]];
     const FiraMat& m = h.dev;
@@ -279,7 +310,11 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
     if (m.kx == 1) s->max_r_bf16 = std::max(s->max_r_bf16, m.r);
     s->general_bf16 = s->general_bf16 || (m.kx == 1 && !h.small_proj);
     s->fuse_any = s->fuse_any || h.fuse_list >= 0;
-    s->fuse_all = s->fuse_all && (h.small_proj || h.fuse_list >= 0);
+    s->leave_r = s->leave_r && (h.small_proj || h.fuse_list >= 0);
+    if (h.fuse_list >= 0) {
+      int& f = fill[(h.fuse_list - kTilesFuse) / 2];
+      f = std::max(f, leave_r_fill(m.r));
+    }
     if (panel_projection(m)) {
       panel_groups += 2 * h.ta_project;
       s->panel_lds = std::max(s->panel_lds, panel_lds(m.S));
@@ -287,6 +322,8 @@ ListSlot* acquire_list(fira_ctx* ctx, int count, const int* idx, void* const* W,
       s->split_proj = true;
     }
   }
+  for (int rt = 1; rt <= 2; ++rt)
+    s->leave_r = s->leave_r && leave_r_fills(s->ntiles[kTilesFuse + 2 * (rt - 1)], s->ntiles[kTilesFuse + 2 * (rt - 1) + 1], rt, fill[rt - 1]);
   if (s->panel_lds && panel_groups > kComputeUnits * std::min(kLdsPerCu / s->panel_lds, FIRA_PANEL_WG_PER_CU)) {
     s->panel_lds = 0;
     s->split_proj = true;
@@ -608,11 +645,8 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
       measures = measures || (gt.ortho_err <= hp.ortho_tol && !(gt.gram_err < INFINITY));
     }
   }
-  // The fused projection/Adam kernel serves a list of matrices that can all take it where all of them leave R in memory: on the residual route, with
-  // Z in two planes.  Two kernels and this one, residual route and two planes: 24 of 1024 x 2736 at r = 256 1245 and 1192 us, 1098 and 1046; 4 of
-  // 2048 x 5461 at r = 512 1063 and 1047, 971 and 958.  By tiles: r = 128 46.5 and 57.8, 37.4 and 49.1 (49), 71.1 and 75.4, 61.6 and
-  // 64.4 (196), 114.1 and 108.2, 97.0 and 90.8 (392); r = 256 132 and 138, 113 and 120 (196), 232 and 228, 199 and 195 (392); r = 512 304 and
-  // 296, 274 and 263 (193), 553 and 557, 500 and 502 (386).
+  // The fused projection/Adam kernel serves a list of matrices that can all take it where all of them leave R in memory (on the residual route, with
+  // Z in two planes) and its last round is full enough for that to pay (leave_r_fill).
   // On the Gram route it serves the listed matrices if each of them can take
   // it; those on the residual route then go through the two-kernel path in the same step (hp.mixed).  Either all of them leave
   // R in memory, as small ranks do whatever the path, or none does.  Two kernels and the fused one, a step of 8 blocks of 512 x 1376, 24 of
@@ -622,8 +656,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
   // 57.4 and 58.3 (147), 167.5 and 165.9 (193), 91.1 and 92.2 (196), 68.8 and 66.5 (245), 110.5 and 106.2 (294); at r = 68 and 124 the
   // fused kernel takes 1.02 and 1.00 of the two at 196 tiles, 0.96 and 0.95 at 245).
   const bool may_fuse = ctx->fusion && !only_scaling && ctx->scaling == FIRA_SCALE_COLUMN && s->fuse_any;
-  const int fuse_tiles = s->ntiles[kTilesFuse] + s->ntiles[kTilesFuse + 1] + s->ntiles[kTilesFuse + 2] + s->ntiles[kTilesFuse + 3];
-  const bool every = may_fuse && s->fuse_all && (ctx->zsplit || !any_gram) && fuse_tiles >= kFuseMinTiles;
+  const bool every = may_fuse && s->leave_r && (ctx->zsplit || !any_gram);
   bool fused = may_fuse && !ctx->zsplit && any_gram, keep_r = every, drop_r = false, any_fused = false;
   for (int e = 0; e < count && fused; ++e) {
     const FiraGate gt = ctx->h_gate[idx[e]];
@@ -633,7 +666,7 @@ fira_status fira_step(fira_ctx* ctx, int count, const int* idx, void* const* dev
     (h.dev.r < FIRA_FUSE_DROP_R ? keep_r : drop_r) = true;
     fused = (h.small_proj || h.fuse_list >= 0) && !(keep_r && drop_r);
   }
-  fused = every || (fused && any_fused && !(keep_r && fuse_tiles < kFuseMinTiles));
+  fused = every || (fused && any_fused && !(keep_r && s->ntiles[kTilesFuse] + s->ntiles[kTilesFuse + 1] < kFuseMinTiles));
   const bool mixed = fused && !every && need_residual;
   ctx->last_step_fused = fused && !keep_r && !mixed;
   hp.fused = fused && !keep_r ? 1 : 0;

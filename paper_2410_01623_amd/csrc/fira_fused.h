@@ -389,7 +389,7 @@ __global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_project_adam_k
   extern __shared__ __attribute__((aligned(16))) char lds[];   // FIRA_FUSE_LDS(RT) bytes
   project_adam_block<RT, false>(lds, mats, scal, scal_out, ents, tiles_left, ntiles_left, blocks_left, tiles_right, ntiles_right, hp);
 }
-// The same with R left behind (KEEP), on every route, for lists whose matrices all do that.
+// The same with R left behind (KEEP), on every route, for lists whose matrices all do that (and which leave_r_fill finds long enough).
 template <int RT>
 __global__ __launch_bounds__(256 * RT, RT == 1 ? 2 : 1) void fira_fused_leave_r_kernel(const FiraMat* __restrict__ mats,
                                                                                        const FiraScal* __restrict__ scal, FiraScal* __restrict__ scal_out,

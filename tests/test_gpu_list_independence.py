@@ -7,10 +7,10 @@ import torch
 from paper_2410_01623_amd import fira
 
 import fira_harness as H
+from test_gpu_fused_every_route import filled
 
 pytestmark = pytest.mark.gpu
 
-TILES = 600      # of 128 factors: enough for the fused kernel on every route and at every rank
 OPTIONS = {"residual": dict(norm_mode=fira.FIRA_NORM_RESIDUAL), "planes": dict(z_planes=2), "residual-planes": dict(norm_mode=fira.FIRA_NORM_RESIDUAL, z_planes=2),
            "gram": {}}
 
@@ -47,10 +47,10 @@ def _left_after(shapes, ranks, option, fusion, limited):
 
 
 @pytest.mark.parametrize("option", OPTIONS)
-@pytest.mark.parametrize("m,n,r", [(200, 1537, 128), (1665, 256, 128), (259, 1700, 132), (1665, 300, 200), (320, 1536, 256), (1665, 300, 260), (400, 1700, 388),
-                                   (520, 1536, 512)])
+@pytest.mark.parametrize("m,n,r", [(200, 1537, 128), (1665, 256, 128), (259, 1700, 132), (1665, 300, 240), (320, 1536, 256), (1665, 300, 260), (520, 1700, 484),
+                                   (620, 1536, 512)])
 def test_same_bits_whatever_is_listed(m, n, r, option):
-    count = -(-TILES // -(-max(m, n) // 128))
+    count = filled(m, n, r)                      # (at r = 132 and 260 the fused kernel serves the Gram route only)
     limited = option != "gram"                   # (a limited step of the Gram route forms Z from what its kernels have left: N alone, or N and R)
     lists = [([(m, n)] * count, [r] * count, True), ([(m, n)] * count, [r] * count, False), ([(m, n)], [r], True),
              ([(m, n)] * count + [(300, 260)], [r] * count + [97], True)]
