@@ -101,7 +101,7 @@ __device__ __forceinline__ f32x4 refresh_load4(gptr<const float> A, int row, int
 // Place of element (row, col), col <= row, of the Gram matrix and its factor.  Above the ranks of fira_refresh_chol_small_kernel they are kept as 32 x 32
 // tiles, block row after block row of the lower triangle (r^2 / 2 + 16 r doubles of the r^2 there are).  A quarter of a tile, 16 x 16, holds its
 // columns two by two, those with (column % 4) / 2 = 0 first: the 16 rows x 8 columns that one instruction reads as an operand of the factorisation are
-// 1 KB of contiguous memory in lane order (fira_refresh_chol_kernel over 168 matrices of r = 512: 667 us; 920 with a tile's rows one after the
+// 1 KB of contiguous memory in lane order (fira_refresh_chol_kernel over 168 matrices of r = 512, as it was then: 667 us; 920 with a tile's rows one after the
 // other, of which sixteen bytes each make an operand's instruction, and the same with rows of r).
 #define FIRA_CHOL_SMALL_R 128
 __device__ __forceinline__ bool chol_tiled(int r) { return r > FIRA_CHOL_SMALL_R; }
@@ -336,8 +336,8 @@ __device__ __forceinline__ bool refresh_pass_done(const FiraRefreshEnt& e) { ret
 // others, whose multiply-adds are the same instructions (and 64 more in a second set of registers where there are many rows; the lane
 // reads, two for each multiply-add, are shared).  Rows of the identity carried along become the block's inverse, which the solve needs.
 // A column is scaled by 1 / pivot as it is eliminated, and by the square roots when all are known, side by side.
-// 168 matrices of r = 512, the inverses of the diagonal blocks included: 690 us, of which 150 are the elimination's chains and 420 the updates, whose
-// multiplies alone take 200; 930 with the panel solved after its block by one row per thread and a trailing triangle rewritten for every panel.
+// 168 matrices of r = 512, the inverses of the diagonal blocks included: 560 us (680 while offsets, masks and rows of one panel after the other were held
+// across them and 132 registers went to memory); 930 with the panel solved after its block by one row per thread and a trailing triangle rewritten for every panel.
 #define FIRA_CHOL_THREADS 512
 #define FIRA_CHOL_NB 32
 #define FIRA_CHOL_ROWS 512        // rows of a panel that are in LDS at a time, the diagonal block's among them
@@ -364,9 +364,8 @@ __device__ __forceinline__ void sqrt_and_inverse(double x, double& root, double&
 // (Lane reads in groups of eight: one right before the multiply-add that takes it costs twice as much, 22 cycles against 14.  The next pivot's
 // reciprocal is formed beside a column's later groups.)
 template <bool EXTRA>
-__device__ __forceinline__ void chol_eliminate(double (&d)[FIRA_CHOL_NB], double (&x)[EXTRA ? FIRA_CHOL_NB : 1], double floor_piv) {
+__device__ __forceinline__ void chol_eliminate(double (&d)[FIRA_CHOL_NB], double (&x)[EXTRA ? FIRA_CHOL_NB : 1], int lane, double floor_piv) {
   constexpr int NB = FIRA_CHOL_NB, GROUP = 8;
-  const int lane = threadIdx.x & 63;
   double own = 1.0;                        // lane j: pivot j
   double piv, inv;
   auto pivot = [&](int j) {
@@ -437,8 +436,7 @@ __device__ __forceinline__ void chol_products(f64x4_t (&acc)[RB][CB], const doub
 }
 // Puts f(row, col, value) in the place of each value that this lane holds.
 template <int RB, int CB, typename F>
-__device__ __forceinline__ void chol_foreach(f64x4_t (&acc)[RB][CB], F f) {
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ void chol_foreach(f64x4_t (&acc)[RB][CB], int lane, F f) {
 #pragma unroll
   for (int i = 0; i < RB; ++i)
 #pragma unroll
@@ -451,11 +449,10 @@ __device__ __forceinline__ void chol_foreach(f64x4_t (&acc)[RB][CB], F f) {
 // matrix's row at(x).  The sums start from -C, which is on its way meanwhile; operands are requested four stages of 16 k ahead.  Of these, lane l
 // takes four from 4 (l / 16), and an instruction those with the same place among the four.
 template <int RB, typename At>
-__device__ __forceinline__ void chol_update(double* pan, gptr<const double> C, int r, int jb, int row0, At at) {
+__device__ __forceinline__ void chol_update(double* pan, gptr<const double> C, int r, int jb, int row0, int lane, At at) {
   typedef double __attribute__((ext_vector_type(2), aligned(8))) f64x2_a8;
-  const int lane = threadIdx.x & 63;
   f64x4_t acc[RB][2];
-  chol_foreach(acc, [&](int row, int col, double) {
+  chol_foreach(acc, lane, [&](int row, int col, double) {
     const int g = at(row0 + row), c = jb + col;
     return g < r && c <= g ? -C[chol_at(r, g, c)] : 0.0;
   });
@@ -506,7 +503,7 @@ __device__ __forceinline__ void chol_update(double* pan, gptr<const double> C, i
       multiply(o[1]);
     }
   }
-  chol_foreach(acc, [&](int row, int col, double v) {
+  chol_foreach(acc, lane, [&](int row, int col, double v) {
     const int x = row0 + row;
     return pan[x * FIRA_CHOL_PITCH + col] = at(x) < r ? -v : (x == col ? 1.0 : 0.0);      // (identity past the end)
   });
@@ -546,22 +543,26 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
   for (int jb = 0; jb < r; jb += NB) {
     // (each part of the rows repeats the diagonal block, which is stored with the last)
     for (int base = jb + NB;; base += PANEL) {
-      asm volatile("" : "+v"(t));          // (else the offsets of all that follows are formed out here, and spill)
+      asm volatile("" : "+v"(t));          // (else the offsets, and 32 masks, of all that follows are formed out here, and spill)
       const int lane = t & 63;
       const int rows = max(min(PANEL, r - base), 0), blocks = 1 + (rows + NB - 1) / NB;
       const bool last = base + PANEL >= r;
       auto at = [&](int x) { return x < NB ? jb + x : base + x - NB; };
       // 32 rows to a wavefront at a time, or 16 where that keeps more of them busy
       if (blocks > WAVES)
-        for (int b = wave; b < blocks; b += WAVES) chol_update<2>(chol_pan, C, r, jb, NB * b, at);
+        for (int b = wave; b < blocks; b += WAVES) chol_update<2>(chol_pan, C, r, jb, NB * b, lane, at);
       else
-        for (int b = wave; b < 2 * blocks; b += WAVES) chol_update<1>(chol_pan, C, r, jb, NB / 2 * b, at);
+        for (int b = wave; b < 2 * blocks; b += WAVES) chol_update<1>(chol_pan, C, r, jb, NB / 2 * b, lane, at);
       __syncthreads();
       // the panel's rows, 96 to a wavefront, and the identity's 32 to the last one
       const bool identity = wave == WAVES - 1;
       const int end = NB * blocks, row0 = 3 * NB * wave + lane;
       const bool works = identity ? base == jb + NB : wave == 0 || NB * (3 * wave + 1) < end;
+      // (Registers, which this kernel is short of: rows that are set wherever they are used do not live from panel to panel, and x stays one register a
+      // value only if its elimination cannot move into the store below. 132 spilled without these two and with lanes formed per function.)
       double d[NB], x[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) d[k] = x[k] = 0.0;
       if (works) {
         const double* from = chol_pan + (lane < NB ? lane : min(row0, end - 1)) * PP;
 #pragma unroll
@@ -572,7 +573,9 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_kernel(co
       }
       __syncthreads();                     // (the block's rows have been read by everybody)
       if (works) {
-        chol_eliminate<true>(d, x, floor_piv);
+        chol_eliminate<true>(d, x, lane, floor_piv);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) asm volatile("" : "+v"(x[k]));
         if (identity) {                    // D^-T, a row per lane
           if (lane >= NB) {
             gptr<double> inv = reinterpret_cast<gptr<double>>(as_global(e.inst)) + (size_t)(jb / 64) * 64 * 64 + (jb & 32) * 65 + lane - NB;
@@ -670,7 +673,7 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_small_ker
       for (int u = wave; u < 4 * (below / NB + 1); u += WAVES) {      // 16 x 16 at a time
         const int row0 = jb + 16 * (u >> 1), col0 = jb + 16 * (u & 1);
         f64x4_t acc[1][1];
-        chol_foreach(acc, [&](int row, int col, double) { return -chol_a[(row0 + row) * P + col0 + col]; });
+        chol_foreach(acc, lane, [&](int row, int col, double) { return -chol_a[(row0 + row) * P + col0 + col]; });
         const double *pa = chol_a + (row0 + (lane & 15)) * P + 4 * (lane >> 4), *pb = chol_a + (col0 + (lane & 15)) * P + 4 * (lane >> 4);
         for (int k = 0; k < jb; k += NB) {
           double a[8], b[8];
@@ -682,7 +685,7 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_small_ker
 #pragma unroll
           for (int s = 0; s < 8; ++s) acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc[0][0], 0, 0, 0);
         }
-        chol_foreach(acc, [&](int row, int col, double v) { return chol_a[(row0 + row) * P + col0 + col] = -v; });
+        chol_foreach(acc, lane, [&](int row, int col, double v) { return chol_a[(row0 + row) * P + col0 + col] = -v; });
       }
       __syncthreads();
     }
@@ -696,7 +699,7 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_small_ker
     }
     __syncthreads();
     if (NB * wave <= below) {
-      chol_eliminate<false>(d, none, floor_piv);
+      chol_eliminate<false>(d, none, lane, floor_piv);
       if (lane >= NB && identity) {
 #pragma unroll
         for (int k = 0; k < NB; ++k) X[(jb / 64 * NB + k) * P + (jb & 32) + lane - NB] = k >= lane - NB ? d[k] : 0.0;
