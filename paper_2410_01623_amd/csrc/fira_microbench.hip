@@ -4,6 +4,8 @@
 //                         workgroups striding through the buffer, non-temporal accesses)
 //   mfma                : v_mfma_f32_32x32x16_bf16 on register operands, 8 independent accumulator blocks
 //                         per wavefront (the shape of the step's contractions), 1 or 2 wavefronts per SIMD
+//   fp64                : v_mfma_f64_16x16x4_f64 and v_fma_f64 on register operands (the refresh's Gram matrices and
+//                         solves), each by itself, in turn in every wavefront, and side by side in different wavefronts
 //   lds                 : ds_read_b128 fragment reads, all wavefronts of a CU at once
 //   power               : socket power (amdgpu hwmon file) while the copy and the mfma loop run for two seconds each,
 //                         the latter with constant and with pseudo-random operands: what a byte moved and a
@@ -18,11 +20,13 @@
 #include <cstdio>
 #include <cstdlib>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
 #define CHECK(call)                                                                         \
   do {                                                                                      \
@@ -146,6 +150,56 @@ __global__ __launch_bounds__(256) void mfma_kernel(int iters, float* __restrict_
 #pragma unroll
     for (int b = 0; b < 2; ++b) s += acc[a][b][0];
   if (s == 12345.678f) sink[0] = s;
+}
+
+// fp64 on pseudo-random operands in [-1, 1), two sets in turn.  Per iteration and wavefront, where asked for: 8 multiplies of the matrix pipe on SUMS
+// sums in turn (2048 flop each), and 64 vector multiply-adds on 32 sums of their own (128 flop each).
+// MODE 0: matrix pipe, 1: vector unit, 2: both, one multiply and eight multiply-adds in turn, 3: the first four wavefronts of a workgroup of eight the one, the others the other
+// (512 threads: the compiler then keeps the sums where the multiplies leave them.  At 256 it moved all of them to the accumulation registers and back
+// once per iteration, and the same loop gave 48 TFLOP/s.)
+template <int MODE, int SUMS = 8>
+__global__ __launch_bounds__(512) void fp64_kernel(int iters, double* __restrict__ sink) {
+  f64x4_t acc[SUMS];
+  double own[32], a[2][4], b[2][4];
+  unsigned h = (blockIdx.x * 512u + threadIdx.x) * 2654435761u + 12345u;
+  auto next = [&]() { h = h * 1664525u + 1013904223u; return (double)(int)h * (1.0 / 2147483648.0); };
+#pragma unroll
+  for (int i = 0; i < SUMS; ++i) acc[i] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < 32; ++i) own[i] = 0.0;
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      a[s][i] = next();
+      b[s][i] = next();
+    }
+  const bool matrix = MODE == 0 || MODE == 2 || (MODE == 3 && threadIdx.x < 256);
+  const bool vector = MODE == 1 || MODE == 2 || (MODE == 3 && threadIdx.x >= 256);
+  auto rounds = [&](auto m, auto v) {
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (decltype(m)::value) acc[i % SUMS] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i & 1][i >> 1], b[i & 1][(i + 1) & 3], acc[i % SUMS], 0, 0, 0);
+        if (decltype(v)::value) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            double& x = own[(8 * i + j) & 31];
+            asm volatile("v_fma_f64 %0, %1, %2, %0" : "+v"(x) : "v"(a[j & 1][j >> 1]), "v"(b[i & 1][j & 3]));
+          }
+        }
+      }
+    }
+  };
+  if (matrix && vector) rounds(std::true_type{}, std::true_type{});
+  else if (matrix) rounds(std::true_type{}, std::false_type{});
+  else if (vector) rounds(std::false_type{}, std::true_type{});
+  double sum = 0.0;
+#pragma unroll
+  for (int i = 0; i < SUMS; ++i) sum += acc[i][0] + acc[i][1] + acc[i][2] + acc[i][3];
+#pragma unroll
+  for (int i = 0; i < 32; ++i) sum += own[i];
+  if (sum == 12345.678) sink[0] = sum;
 }
 
 // every lane reads 16 bytes per instruction from a 64 KB LDS array, consecutive lanes consecutive pieces
@@ -329,6 +383,25 @@ int main() {
     const double t = time_ms([&] { hipLaunchKernelGGL(mfma_kernel, grid, blk, 0, 0, iters, (float*)sink); }, 5);
     const double flop = (double)grid.x * 4 * iters * 8 * (2.0 * 32 * 32 * 16);
     std::printf("mfma 32x32x16 bf16, %d wavefront(s) per SIMD: %.0f TFLOP/s\n", waves_per_simd, flop / t / 1e9);
+  }
+  for (int waves_per_simd : {1, 2, 4}) {
+    const int iters = 4000;
+    const dim3 grid(cus * waves_per_simd), blk(256);
+    const double per = (double)grid.x * 4 * iters, mflop = per * 8 * 2048, vflop = per * 64 * 128;
+    const double t0 = time_ms([&] { hipLaunchKernelGGL(fp64_kernel<0>, grid, blk, 0, 0, iters, (double*)sink); }, 5);
+    const double t1 = time_ms([&] { hipLaunchKernelGGL(fp64_kernel<1>, grid, blk, 0, 0, iters, (double*)sink); }, 5);
+    const double t2 = time_ms([&] { hipLaunchKernelGGL(fp64_kernel<2>, grid, blk, 0, 0, iters, (double*)sink); }, 5);
+    std::printf("fp64, %d wavefront(s) per SIMD: v_mfma_f64_16x16x4_f64 %.1f TFLOP/s, v_fma_f64 %.1f, one multiply and eight multiply-adds in turn %.1f + %.1f", waves_per_simd,
+                mflop / t0 / 1e9, vflop / t1 / 1e9, mflop / t2 / 1e9, vflop / t2 / 1e9);
+    if (waves_per_simd == 1) {
+      const double t4 = time_ms([&] { hipLaunchKernelGGL((fp64_kernel<0, 4>), grid, blk, 0, 0, iters, (double*)sink); }, 5);
+      const double t5 = time_ms([&] { hipLaunchKernelGGL((fp64_kernel<0, 1>), grid, blk, 0, 0, iters, (double*)sink); }, 5);
+      std::printf(", multiplies on four sums in turn %.1f, on one %.1f", mflop / t4 / 1e9, mflop / t5 / 1e9);
+    } else {
+      const double t3 = time_ms([&] { hipLaunchKernelGGL(fp64_kernel<3>, dim3(grid.x / 2), dim3(512), 0, 0, iters, (double*)sink); }, 5);
+      std::printf(", in wavefronts of their own %.1f + %.1f", mflop / 2 / t3 / 1e9, vflop / 2 / t3 / 1e9);
+    }
+    std::printf("\n");
   }
   {
     const int iters = 4000;

@@ -45,8 +45,8 @@ __global__ __launch_bounds__(256) void fira_refresh_start_kernel(const FiraMat* 
 // owns the 32 x 32 block at rows 32 (w >> 1), columns 32 (w & 1), as 2 x 2 blocks of 16 x 16.  Operand layout of
 // the instruction: lane l supplies A[m = l % 16][k = l / 16] and B[k = l / 16][n = l % 16]; of its four result
 // values, number v is D[m = l / 16 + 4 v][n = l % 16] (checked on the device against a plain product).  The products are fp64 multiply-adds like the vector
-// unit's; the matrix pipe has the same peak on this chip but takes one instruction for 2048 of them, which
-// frees the issue slots that the vector form spends on conversions and LDS reads.
+// unit's.  Both have the same peak, of which the matrix pipe sustains 77 TFLOP/s, on one sum in turn as on eight, and the vector unit 55 to 60; together they give
+// 72 (fira_microbench).  One instruction does 1024 of them, which frees the issue slots that the vector form spends on conversions and LDS reads.
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 struct RefreshAcc { f64x4_t v[2][2]; };
 __device__ __forceinline__ void refresh_acc_zero(RefreshAcc& acc) {
@@ -233,8 +233,8 @@ __global__ __launch_bounds__(256, 2) void fira_refresh_check_kernel(const FiraRe
 // register count left to the compiler it kept the sums in the other half of the register file between stages and moved all
 // of them there and back per stage (168 matrices of 2048 rows at r = 512: 1.82 ms, 2.04 before; five workgroups per CU).
 // SMALL: the matrices with r <= FIRA_CHOL_SMALL_R, whose rows are summed in four parts, one after the other or, in lists of few tiles (parts = 4), by a workgroup
-// each: a multiply of a wavefront that has its SIMD to itself takes 136 cycles, of two that share it 99 each, so that tiles which leave the chip
-// idle wait for their own chain.  The parts lie in C, in Q, which the solve has yet to write, and in Top, which the way back has read; the factorisation adds
+// each: a wavefront that has its SIMD to itself waits for its LDS reads, conversions and barriers between multiplies (512 rows are 512 multiplies of 64 cycles, 14 us, and took 32), and
+// tiles which leave the chip idle have nothing beside them.  The parts lie in C, in Q, which the solve has yet to write, and in Top, which the way back has read; the factorisation adds
 // them up in the same order.  (56 matrices of 512 rows at r = 128: 32 us for a workgroup per
 // tile, 23 for four.  A refresh step in one part and in four: 28 matrices of 256 x 688 at r = 64 233 and 220 us; r = 128, 14 of 512 x 1376 362 and 333, 56
 // 495 and 485, 84 of 1024 x 2736 1361 and 1344, 168 of 512 x 1376 1005 and 1021.)
