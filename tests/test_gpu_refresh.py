@@ -31,8 +31,8 @@ def _gapped_gradient(rng, m, n, r, tail=0.05):
                               "2048x5461r512", "5461x2048r512", "330x650r131", "650x331r131", "700x900r610", "900x700r610"])
 def test_refreshed_projector_spans_the_leading_singular_subspace(m, n, r):
     """(2048 x 5461 at r = 512 are the headline workload's rectangular shapes at its rank, the configuration whose
-    refresh bench.py times; an odd rank above 64 takes the solve's element-wise loads; at r = 610 the first panels of
-    the Cholesky factorisation do not fit in LDS, the later ones do, and the last block is a partial one.)"""
+    refresh bench.py times; an odd rank from 65 to 127 takes the solve's element-wise loads, 131 its factor from tiles; at r = 610
+    the first panels of the Cholesky factorisation are worked through in two parts, the later ones in one, and the last block is a partial one.)"""
     rng = np.random.default_rng(1000 + m + n)
     G = _gapped_gradient(rng, m, n, r)
     ctx = fira.FiraContext([(m, n)], r, fira.FIRA_BF16, device=H.DEV)

@@ -31,3 +31,21 @@ def test_factor_in_tiles(r, dtype):
     # (bounds as in test_gpu_refresh_edges.py)
     assert sines.max() < 1e-2 and orc.captured_energy(G, P) > orc.captured_energy(G, Pref) - 1e-4
     assert defect < (3e-3 if dtype == fira.FIRA_BF16 else 1e-5)
+
+
+@pytest.mark.parametrize("r", [992, 993, 1024])
+def test_panels_of_two_and_three_parts(r):
+    """A panel is worked through in parts of 480 rows: the first one of r = 992 has two, of the largest rank listed anywhere, 1024, three."""
+    rng = np.random.default_rng(r)
+    m, n = (1500, r + 60) if r % 2 else (r + 60, 1500)
+    G = _gapped_gradient(rng, m, n, r)
+    ctx = fira.FiraContext([(m, n)], r, fira.FIRA_BF16, device=H.DEV)
+    Gd = torch.from_numpy(G.astype(np.float32)).to(H.DEV).to(torch.bfloat16)
+    ws = torch.full((ctx.fira_refresh_workspace_bytes([0]),), 0xFF, dtype=torch.uint8, device=H.DEV)
+    ctx.fira_refresh_projectors([0], [Gd], iters=3, seed=7, workspace=ws)
+    torch.cuda.synchronize()
+    P = ctx.fira_get_projector(0).numpy().astype(np.float64)
+    Pref = orc.top_r_projector(G, r)
+    # (bounds as above)
+    assert orc.subspace_sines(Pref, P).max() < 1e-2 and orc.captured_energy(G, P) > orc.captured_energy(G, Pref) - 1e-4
+    assert np.max(np.abs(P.T @ P - np.eye(r))) < 3e-3
