@@ -740,9 +740,9 @@ __global__ __launch_bounds__(FIRA_CHOL_THREADS) void fira_refresh_chol_small_ker
 // Rows do not depend on each other, so a workgroup takes 64 of them through all column blocks, reading back the blocks of Q
 // that it wrote before (fp32, as the result is stored).  Everything but the 64 x 64 inverses of the diagonal blocks is a dense
 // product, tiled like the Gram kernel (64 x 64 output tile, fp64 on the matrix pipe, operands staged through LDS
-// with the next stage's values requested into registers meanwhile).  The inverses of the diagonal blocks come from a small
-// kernel of their own (one thread per column of an inverse) and live in the scratch of the installation,
-// which is idle until the solves are done.  (Forms that kept a workgroup's rows in LDS and walked along
+// with the next stage's values requested into registers meanwhile).  The inverses of the diagonal blocks are there
+// already (their 32 x 32 triangles from the factorisation, which carries rows of an identity along, the quarters below from fira_refresh_diaginv_kernel)
+// and live in the scratch of the installation, which is idle until the solves are done.  (Forms that kept a workgroup's rows in LDS and walked along
 // the columns, one row per lane with L read from memory or staged in LDS, ran at a tenth of the fp64
 // rate: bound by the latency, or the LDS bandwidth, of the operand every lane shares.)
 // The staged operands and, after them, Y_J - update share the LDS (33 KB, four workgroups per CU: the stages of 16 k
