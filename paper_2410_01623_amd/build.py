@@ -37,7 +37,7 @@ MICROBENCH_PATH = os.path.join(PKG_DIR, "fira_microbench")
 
 
 def build_microbench(verbose: bool = True) -> str:
-    """The machine-calibration program (HBM streams, MFMA rate, LDS read rate); not part of the library."""
+    """The machine-calibration program (HBM streams, bf16 and fp64 MFMA rates, LDS read rate); not part of the library."""
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC", "-fvisibility=hidden")]
     cmd = [hipcc, *flags, os.path.join(CSRC, "fira_microbench.hip"), "-o", MICROBENCH_PATH]

@@ -28,7 +28,8 @@
 //
 // A step takes this kernel only if every listed matrix is bf16 with r % 4 == 0, 64 < r <= 512, column
 // factors, Algorithm 1 proper.  On the Gram route to ||S|| R is written below FIRA_FUSE_DROP_R only.  On the residual route (with the operand
-// copy of R that it contracts) and with Z in two planes a form of its own leaves R in memory whatever the rank, as two kernels do (fira_fused_leave_r_kernel).
+// copy of R that it contracts) and with Z in two planes a form of its own leaves R in memory whatever the rank, as two kernels do (fira_fused_leave_r_kernel, for lists that fill
+// its rounds of workgroups).
 // The limiter runs after it; for a matrix whose factor c came out below 1, fira_makez_kernel turns the Z
 // written here (for c = 1) into c Z + (1 - c) N, with N formed again from the updated M and V.
 #pragma once
